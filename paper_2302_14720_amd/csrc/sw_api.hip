@@ -129,6 +129,7 @@ Layout layout_of(const sw_config &c) {
     o.ring = take(ring * sizeof(sw_obs));
     o.labels = (le || (c.flags & SW_FLAG_LABELS)) ? take(N * 4) : 0;
     o.dense = (c.flags & SW_FLAG_DENSE_HIST) ? take((N + 1) * 8) : 0;
+    o.tdense = (c.flags & SW_FLAG_DENSE_HIST) ? take(ntiles * swmi::kDenseBins * 2) : 0;
     o.le_mask = le ? take(N) : 0;
     o.le_cnt = le ? take(N * 4) : 0;
     o.le_rsp = le ? take(N) : 0;
@@ -178,6 +179,7 @@ Dev make_dev(const sw_config &c, char *base, const Layout &lo) {
     const bool le = (c.flags & SW_FLAG_LABEL_EQUIV) != 0u || c.dims == 3;
     d.labels = (le || (c.flags & SW_FLAG_LABELS)) ? (uint32_t *)(base + lo.labels) : nullptr;
     d.dense = (c.flags & SW_FLAG_DENSE_HIST) ? (uint64_t *)(base + lo.dense) : nullptr;
+    d.tdense = (c.flags & SW_FLAG_DENSE_HIST) ? (uint16_t *)(base + lo.tdense) : nullptr;
     if (le) {
         d.ntiles = 0;
         d.ntx = 0;

@@ -42,6 +42,7 @@ constexpr int kGroupPart = 48;        // uint64 words of a per-group partial
 constexpr int kMaxQ = 8;              // largest q of the Potts model
 constexpr int kAccWords = 64;         // record accumulator + completion counter
 constexpr int kGroupTiles = 16;       // tiles per workgroup in k_flatten / k_roots
+constexpr uint32_t kDenseBins = 256;  // sizes below this are counted per tile and group (dense histogram)
 constexpr uint32_t kUG = 4;           // side, in tiles, of a k_ulocal group
 
 // tile partial (int32 words)
@@ -68,6 +69,7 @@ struct Dev {
     sw_obs *ring;         // [ring_cap]
     uint32_t *labels;     // [N] or nullptr
     uint64_t *dense;      // [N + 1] or nullptr
+    uint16_t *tdense;     // [ntiles][kDenseBins] interior clusters by size (with dense, tile path)
     // label-equivalence path (SW_FLAG_LABEL_EQUIV); nullptr otherwise
     uint8_t *le_mask;     // [N] bonds of each site: bit 0 to E, bit 1 to N
     uint32_t *le_cnt;     // [N] cluster size at each root
