@@ -505,8 +505,10 @@ int sw_phi4_sync(sw_phi4 *sim);
 
 /* Measurement aid: n >= 1 updates exactly as sw_phi4_sweep, launched kernel
  * by kernel with HIP events on the sim's stream; ms[0..4] receive the mean
- * milliseconds of the five kernels (projections, bonds and unions,
- * flattening and sizes, reflections, measurement and record); nk >= 5. */
+ * milliseconds of the five stages (projections, bonds and unions,
+ * flattening and sizes, reflections, measurement and record); nk >= 5.  The
+ * projections are taken by the kernels that use them and the reflections
+ * done with the flattening, so ms[0] and ms[3] are the events' own cost. */
 int sw_phi4_profile(sw_phi4 *sim, int64_t n, double *ms, int32_t nk);
 
 /* Records first .. first+count-1 (Sec. 3 updates; measured after each) into

@@ -5,16 +5,18 @@
 // are not given in the paper; with |phi| = 1, the lambda -> infinity limit,
 // the cluster update alone samples exp(2 kappa sum_<xy> phi_x . phi_y)).
 // A sweep t:
-//   k_phi_proj    every site projects its field on the sweep's random
-//                 direction r (unnormalised, drawn by 4-ball rejection from
-//                 Philox({k, t, 5, 0})); parents and sizes are reset
-//   k_phi_bond    link (x, mu) is bonded (eq. 2) iff a = ((p_x p_y) 4 kappa)
-//                 / (r . r) > 0 and its word (word mu of Philox({x, t, 7, 0}))
-//                 times 2^-32 is below 1 - E(a); bonded sites are joined by
-//                 the lock-free union-find of sw_uf.h (smaller index is root)
+//   k_phi_bond    the sweep's random direction r (unnormalised, drawn by
+//                 4-ball rejection from Philox({k, t, 5, 0})); link (x, mu) is
+//                 bonded (eq. 2) iff a = ((p_x p_y) 4 kappa) / (r . r) > 0,
+//                 p the projections on r, and its word (word mu of
+//                 Philox({x, t, 7, 0})) times 2^-32 is below 1 - E(a); bonded
+//                 sites of one chunk of kPhiChunk consecutive sites are
+//                 joined in LDS
+//   k_phi_union   bonds between chunks join the chunks' local roots by the
+//                 lock-free union-find of sw_uf.h (smaller index is root)
 //   k_phi_flat    every site points at its root (the cluster's smallest
-//                 site); sizes are counted at the roots
-//   k_phi_flip    a cluster whose root's Philox bit ({root >> 7, t, 6, 0},
+//                 site); the local components' sizes are added at the roots;
+//                 a cluster whose root's Philox bit ({root >> 7, t, 6, 0},
 //                 bit root mod 128) is set is reflected (eq. 3):
 //                 phi -= ((2 p_x) / (r . r)) r
 //   k_phi_record  exact int64 sums of rint(2^32 phi_x . phi_y) over links and
@@ -42,19 +44,30 @@ namespace swmi {
 namespace {
 
 constexpr int kPhiBlock = 256;
+// Sites per workgroup (one per thread) whose bonds are joined in LDS.  A sweep
+// is bound by its chains of dependent loads and atomics, not by its 330 B per
+// site: joining every bond in global memory, counting sizes with an atomic
+// per wavefront and root, and summing the record with 42 atomics and two
+// cache fences per 256 sites took 28 + 20 + 42 us at 20^4, kappa = 0.304;
+// local components first leave about a third of the bonds and one size per
+// component to the global steps: bond 10, union 15, flat with reflection 7,
+// record 13 us; 117 -> 57 us an update with its launches.
+constexpr uint32_t kPhiChunk = 1024;
+constexpr uint32_t kPhiRecGroups = 512;  // most workgroups of k_phi_record (2 per CU)
 constexpr int kPhiMaxL = 64;
 constexpr double kPhiMaxKappa = 4.0;
 // accumulator words: e, m[4], n, max, sum_sq, hist[33], completion counter
-enum { PA_E = 0, PA_M = 1, PA_N = 5, PA_MAX = 6, PA_SQ = 7, PA_HIST = 8, PA_END = 41, PA_COUNT = 48 };
-constexpr int kPhiAccWords = 64;
+enum { PA_E = 0, PA_M = 1, PA_N = 5, PA_MAX = 6, PA_SQ = 7, PA_HIST = 8, PA_END = 41 };
+constexpr int kPhiPart = 48;  // words of a workgroup's partial
 
 struct PhiDev {
     double *phi;      // [N][4] fields
-    double *proj;     // [N] projection of phi_x on r (unnormalised)
     uint32_t *parent; // [N] union-find parents, then roots (labels)
-    uint32_t *csize;  // [N] cluster size at roots
+    uint32_t *csize;  // [N] size of the chunk's component at local roots, 0 elsewhere; then cluster sizes at roots
+    uint8_t *cross;   // [N] bit mu: the link to x + mu-hat is bonded and leaves the chunk
     double *dir;      // [8] r[4], r . r of the current sweep
-    uint64_t *acc;    // [kPhiAccWords]
+    uint64_t *part;   // [kPhiRecGroups][kPhiPart] partial records
+    uint64_t *acc;    // [0] workgroups of k_phi_record done
     uint64_t *tdev;   // [0] index of the next sweep
     sw_phi4_obs *ring;
     uint32_t L, N, ring_cap, seed_lo, seed_hi;
@@ -68,27 +81,19 @@ __device__ __forceinline__ double dot4(double a0, double a1, double a2, double a
     return ((a0 * b0 + a1 * b1) + a2 * b2) + a3 * b3;
 }
 
-// The sweep's random direction: the first of up to 64 candidates
+// The sweep's random direction: the first of 64 candidates
 // (Philox({k, t, 5, 0}) as four uniforms in (-1, 1)) inside the unit ball;
-// (1, 0, 0, 0) if none is.  Every thread draws the same sequence.
+// (1, 0, 0, 0) if none is.  Lane k of the wavefront draws candidate k.
 __device__ __forceinline__ void phi_direction(uint32_t t, uint32_t k0, uint32_t k1, double r[4], double &rr) {
-    for (uint32_t k = 0; k < 64u; ++k) {
-        uint32_t w0 = k, w1 = t, w2 = 5u, w3 = 0u;
-        philox10(w0, w1, w2, w3, k0, k1);
-        const double v0 = phi_uniform(w0), v1 = phi_uniform(w1), v2 = phi_uniform(w2), v3 = phi_uniform(w3);
-        const double vv = dot4(v0, v1, v2, v3, v0, v1, v2, v3);
-        if (vv < 1.0) {
-            r[0] = v0;
-            r[1] = v1;
-            r[2] = v2;
-            r[3] = v3;
-            rr = vv;
-            return;
-        }
-    }
-    r[0] = 1.0;
-    r[1] = r[2] = r[3] = 0.0;
-    rr = 1.0;
+    uint32_t w0 = threadIdx.x & 63u, w1 = t, w2 = 5u, w3 = 0u;
+    philox10(w0, w1, w2, w3, k0, k1);
+    const double v[4] = {phi_uniform(w0), phi_uniform(w1), phi_uniform(w2), phi_uniform(w3)};
+    const double vv = dot4(v[0], v[1], v[2], v[3], v[0], v[1], v[2], v[3]);
+    const uint64_t in = __ballot(vv < 1.0);
+    const int first = in ? __ffsll((unsigned long long)in) - 1 : 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) r[i] = in ? __shfl(v[i], first, 64) : i == 0 ? 1.0 : 0.0;
+    rr = in ? __shfl(vv, first, 64) : 1.0;
 }
 
 // exp(-a) for the bond test: halve a to at most 1/8 (k times), Taylor
@@ -107,12 +112,16 @@ __device__ __forceinline__ double phi_expm(double a) {
     return q;
 }
 
-// x + mu-hat on the periodic L^4 lattice (x_0 fastest)
-__device__ __forceinline__ uint32_t phi_step(uint32_t x, uint32_t L, uint32_t mu) {
-    uint32_t stride = 1u;
-    for (uint32_t d = 0; d < mu; ++d) stride *= L;
-    const uint32_t c = (x / stride) % L;
-    return c + 1u == L ? x - c * stride : x + stride;
+// x + mu-hat, mu = 0..3, on the periodic L^4 lattice (x_0 fastest)
+__device__ __forceinline__ void phi_neighbours(uint32_t x, uint32_t L, uint32_t nb[4]) {
+    uint32_t rest = x, stride = 1u;
+#pragma unroll
+    for (uint32_t mu = 0; mu < 4u; ++mu) {
+        const uint32_t q = rest / L, c = rest - q * L;
+        nb[mu] = c + 1u == L ? x - c * stride : x + stride;
+        rest = q;
+        stride *= L;
+    }
 }
 
 __global__ __launch_bounds__(kPhiBlock) void k_phi_init(PhiDev d, int cold) {
@@ -139,9 +148,22 @@ __global__ __launch_bounds__(kPhiBlock) void k_phi_init(PhiDev d, int cold) {
     p[x] = make_double4(f0, f1, f2, f3);
 }
 
-__global__ __launch_bounds__(kPhiBlock) void k_phi_proj(PhiDev d) {
-    const uint32_t x = blockIdx.x * kPhiBlock + threadIdx.x;
+__global__ __launch_bounds__(kPhiChunk) void k_phi_bond(PhiDev d) {
+    __shared__ uint32_t s_par[kPhiChunk];
+    __shared__ uint32_t s_cnt[kPhiChunk];
+    const uint32_t tid = threadIdx.x, base = blockIdx.x * kPhiChunk, x = base + tid;
+    const bool valid = x < d.N;
     const uint32_t t = (uint32_t)*d.tdev;
+    const uint32_t xs = valid ? x : 0u;  // past the lattice: site 0, bonds ignored
+    const double4 *p = reinterpret_cast<const double4 *>(d.phi);
+    uint32_t nb[4];
+    phi_neighbours(xs, d.L, nb);
+    const double4 f = p[xs];
+    double4 g[4];
+#pragma unroll
+    for (uint32_t mu = 0; mu < 4u; ++mu) g[mu] = p[nb[mu]];
+    s_par[tid] = tid;
+    s_cnt[tid] = 0u;
     double r[4], rr;
     phi_direction(t, d.seed_lo, d.seed_hi, r, rr);
     if (x == 0u) {
@@ -151,117 +173,159 @@ __global__ __launch_bounds__(kPhiBlock) void k_phi_proj(PhiDev d) {
         d.dir[3] = r[3];
         d.dir[4] = rr;
     }
-    if (x >= d.N) return;
-    const double4 f = reinterpret_cast<const double4 *>(d.phi)[x];
-    d.proj[x] = dot4(f.x, f.y, f.z, f.w, r[0], r[1], r[2], r[3]);
-    d.parent[x] = x;
-    d.csize[x] = 0u;
-}
-
-__global__ __launch_bounds__(kPhiBlock) void k_phi_bond(PhiDev d) {
-    const uint32_t x = blockIdx.x * kPhiBlock + threadIdx.x;
-    if (x >= d.N) return;
-    const uint32_t t = (uint32_t)*d.tdev;
-    const double rr = d.dir[4];
-    const double k4 = 4.0 * d.kappa;
-    const double px = d.proj[x];
     uint32_t w[4] = {x, t, 7u, 0u};
     philox10(w[0], w[1], w[2], w[3], d.seed_lo, d.seed_hi);
-    uint32_t nb[4];
-    bool bond[4];
+    const double k4 = 4.0 * d.kappa;
+    const double px = dot4(f.x, f.y, f.z, f.w, r[0], r[1], r[2], r[3]);
+    uint32_t bonds = 0u;
 #pragma unroll
     for (uint32_t mu = 0; mu < 4u; ++mu) {
-        nb[mu] = phi_step(x, d.L, mu);
-        const double a = ((px * d.proj[nb[mu]]) * k4) / rr;
-        bond[mu] = false;
+        const double py = dot4(g[mu].x, g[mu].y, g[mu].z, g[mu].w, r[0], r[1], r[2], r[3]);
+        const double a = ((px * py) * k4) / rr;
         if (a > 0.0) {
             const double u = (double)w[mu] * 0x1p-32;
-            bond[mu] = u < 1.0 - phi_expm(a);
+            if (u < 1.0 - phi_expm(a)) bonds |= 1u << mu;
         }
     }
+    if (!valid) bonds = 0u;
+    __syncthreads();
+    uint32_t cross = 0u;
 #pragma unroll
-    for (uint32_t mu = 0; mu < 4u; ++mu)
-        if (bond[mu]) g_union(d.parent, x, nb[mu]);
+    for (uint32_t mu = 0; mu < 4u; ++mu) {
+        if (!((bonds >> mu) & 1u)) continue;
+        const uint32_t y = nb[mu] - base;
+        if (y < kPhiChunk)
+            lds_union(s_par, tid, y);
+        else
+            cross |= 1u << mu;
+    }
+    __syncthreads();
+    const uint32_t root = lds_find(s_par, tid);
+    // sizes: one add per run of lanes with the same root
+    const uint32_t lane = tid & 63u;
+    const uint32_t prev = __shfl_up(root, 1, 64);
+    const uint64_t starts = __ballot(lane == 0u || prev != root);
+    if ((starts >> lane) & 1u) {
+        const uint64_t later = lane == 63u ? 0ull : starts >> (lane + 1u);
+        const uint32_t len = later ? (uint32_t)__ffsll((unsigned long long)later) : 64u - lane;
+        atomicAdd(&s_cnt[root], len);
+    }
+    __syncthreads();
+    if (!valid) return;
+    d.parent[x] = base + root;
+    d.csize[x] = s_cnt[tid];
+    d.cross[x] = (uint8_t)cross;
 }
 
-__global__ __launch_bounds__(kPhiBlock) void k_phi_flat(PhiDev d) {
-    const uint32_t x = blockIdx.x * kPhiBlock + threadIdx.x;
+// One thread per site and direction (blockIdx.y) with a bond that leaves its
+// chunk, so that a site's unions run beside each other instead of one after
+// the other (17.0 -> 14.6 us at 20^4, kappa = 0.304).  Every union starts
+// from the two sites' local roots; a bond that joins the same two as the bond
+// of the lane below is skipped.
+__global__ __launch_bounds__(kPhiBlock) void k_phi_union(PhiDev d) {
+    const uint32_t x = blockIdx.x * kPhiBlock + threadIdx.x, mu = blockIdx.y;
+    const bool has = x < d.N && ((d.cross[x] >> mu) & 1u);
+    if (__ballot(has) == 0ull) return;
+    uint32_t nb[4];
+    phi_neighbours(has ? x : 0u, d.L, nb);
+    const uint32_t y = mu == 0u ? nb[0] : mu == 1u ? nb[1] : mu == 2u ? nb[2] : nb[3];
+    const uint32_t ra = has ? g_load(&d.parent[x]) : 0u, rb = has ? g_load(&d.parent[y]) : 0u;
+    const uint32_t pa = __shfl_up(ra, 1, 64), pb = __shfl_up(rb, 1, 64);
+    const int ph = __shfl_up((int)has, 1, 64);
+    const bool dup = (threadIdx.x & 63u) != 0u && ph && pa == ra && pb == rb;
+    if (has && !dup) g_union(d.parent, ra, rb);
+}
+
+// The local components' sizes are gathered per workgroup in an LDS hash (at
+// most one entry per thread, so a free slot is always found) and added with
+// one atomic per workgroup and root.
+__global__ __launch_bounds__(kPhiChunk) void k_phi_flat(PhiDev d) {
+    constexpr uint32_t kNone = 0xFFFFFFFFu;
+    __shared__ uint32_t s_key[kPhiChunk];
+    __shared__ uint32_t s_val[kPhiChunk];
+    const uint32_t tid = threadIdx.x, x = blockIdx.x * kPhiChunk + tid;
     const bool valid = x < d.N;
-    uint32_t root = 0u;
-    if (valid) {
-        root = x;
-        while (true) {
-            const uint32_t p = g_load(&d.parent[root]);
-            if (p == root) break;
-            root = p;
-        }
-        if (root != x) g_store(&d.parent[x], root);
-    }
-    // one atomic per distinct root of the wavefront
-    const uint32_t lane = threadIdx.x & 63u;
-    bool pending = valid;
-    while (true) {
-        const uint64_t act = __ballot(pending);
-        if (act == 0ull) break;
-        const uint32_t leader = (uint32_t)__ffsll((unsigned long long)act) - 1u;
-        const uint32_t lr = __shfl(root, (int)leader, 64);
-        const bool mine = pending && root == lr;
-        const uint64_t same = __ballot(mine);
-        if (lane == leader) atomicAdd(&d.csize[lr], (uint32_t)__popcll(same));
-        if (mine) pending = false;
-    }
-}
-
-__global__ __launch_bounds__(kPhiBlock) void k_phi_flip(PhiDev d) {
-    const uint32_t x = blockIdx.x * kPhiBlock + threadIdx.x;
-    if (x >= d.N) return;
     const uint32_t t = (uint32_t)*d.tdev;
-    const uint32_t root = d.parent[x];
-    uint32_t w0 = root >> 7, w1 = t, w2 = 6u, w3 = 0u;
-    philox10(w0, w1, w2, w3, d.seed_lo, d.seed_hi);
-    const uint32_t q = (root >> 5) & 3u;
-    const uint32_t w = q == 0 ? w0 : q == 1 ? w1 : q == 2 ? w2 : w3;
-    if (((w >> (root & 31u)) & 1u) == 0u) return;
-    const double r0 = d.dir[0], r1 = d.dir[1], r2 = d.dir[2], r3 = d.dir[3], rr = d.dir[4];
+    s_key[tid] = kNone;
+    s_val[tid] = 0u;
+    const uint32_t p0 = valid ? g_load(&d.parent[x]) : 0u;
     double4 *p = reinterpret_cast<double4 *>(d.phi);
-    double4 f = p[x];
-    const double c = (2.0 * d.proj[x]) / rr;
-    f.x = f.x - c * r0;
-    f.y = f.y - c * r1;
-    f.z = f.z - c * r2;
-    f.w = f.w - c * r3;
-    p[x] = f;
+    const double4 f = p[valid ? x : 0u];
+    const double r0 = d.dir[0], r1 = d.dir[1], r2 = d.dir[2], r3 = d.dir[3], rr = d.dir[4];
+    uint32_t root = p0;
+    if (valid) {
+        while (true) {
+            const uint32_t q = g_load(&d.parent[root]);
+            if (q == root) break;
+            root = q;
+        }
+        if (root != p0) g_store(&d.parent[x], root);
+    }
+    __syncthreads();  // the hash is clear
+    // a component that is not its cluster's root holds its own size alone
+    const uint32_t size = valid && root != x ? d.csize[x] : 0u;
+    if (size) {
+        uint32_t h = (root * 2654435761u) >> 22;
+        static_assert(kPhiChunk == 1024u, "ten hash bits");
+        while (true) {
+            const uint32_t old = atomicCAS(&s_key[h], kNone, root);
+            if (old == kNone || old == root) break;
+            h = (h + 1u) & (kPhiChunk - 1u);
+        }
+        atomicAdd(&s_val[h], size);
+    }
+    if (valid) {
+        uint32_t w0 = root >> 7, w1 = t, w2 = 6u, w3 = 0u;
+        philox10(w0, w1, w2, w3, d.seed_lo, d.seed_hi);
+        const uint32_t q = (root >> 5) & 3u;
+        const uint32_t w = q == 0 ? w0 : q == 1 ? w1 : q == 2 ? w2 : w3;
+        if ((w >> (root & 31u)) & 1u) {
+            const double c = (2.0 * dot4(f.x, f.y, f.z, f.w, r0, r1, r2, r3)) / rr;
+            p[x] = make_double4(f.x - c * r0, f.y - c * r1, f.z - c * r2, f.w - c * r3);
+        }
+    }
+    __syncthreads();
+    if (s_key[tid] != kNone) atomicAdd(&d.csize[s_key[tid]], s_val[tid]);
 }
 
 __device__ __forceinline__ int64_t fix32(double v) { return (int64_t)rint(v * 0x1p32); }
 
-__global__ __launch_bounds__(kPhiBlock) void k_phi_record(PhiDev d) {
+// Workgroup partials go out as agent-scope stores, every wavefront waits for
+// its own to complete before its workgroup counts itself in, and the last
+// workgroup folds them with agent-scope loads (no cache fences).
+__global__ __launch_bounds__(kPhiChunk) void k_phi_record(PhiDev d) {
+    constexpr uint32_t NW = kPhiChunk / 64u;
     __shared__ uint32_t s_hist[33];
-    __shared__ int64_t s_red[kPhiBlock / 64][8];
+    __shared__ int64_t s_red[NW][8];
+    __shared__ unsigned long long s_tot[PA_END];
     __shared__ int s_last;
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wv = tid >> 6;
-    const uint32_t x = blockIdx.x * kPhiBlock + tid;
     if (tid < 33u) s_hist[tid] = 0u;
+    if (tid < (uint32_t)PA_END) s_tot[tid] = 0ull;
     __syncthreads();
     int64_t e = 0, m0 = 0, m1 = 0, m2 = 0, m3 = 0;
     uint64_t n = 0, mx = 0, sq = 0;
-    if (x < d.N) {
+    for (uint32_t x = blockIdx.x * kPhiChunk + tid; x < d.N; x += gridDim.x * kPhiChunk) {
         const double4 *p = reinterpret_cast<const double4 *>(d.phi);
+        uint32_t nb[4];
+        phi_neighbours(x, d.L, nb);
         const double4 f = p[x];
+        double4 g[4];
 #pragma unroll
-        for (uint32_t mu = 0; mu < 4u; ++mu) {
-            const double4 g = p[phi_step(x, d.L, mu)];
-            e += fix32(dot4(f.x, f.y, f.z, f.w, g.x, g.y, g.z, g.w));
-        }
-        m0 = fix32(f.x);
-        m1 = fix32(f.y);
-        m2 = fix32(f.z);
-        m3 = fix32(f.w);
-        if (d.parent[x] == x) {
-            const uint64_t S = d.csize[x];
-            n = 1u;
-            mx = S;
-            sq = S * S;
+        for (uint32_t mu = 0; mu < 4u; ++mu) g[mu] = p[nb[mu]];
+        const uint32_t par = d.parent[x];
+        const uint64_t S = d.csize[x];
+#pragma unroll
+        for (uint32_t mu = 0; mu < 4u; ++mu)
+            e += fix32(dot4(f.x, f.y, f.z, f.w, g[mu].x, g[mu].y, g[mu].z, g[mu].w));
+        m0 += fix32(f.x);
+        m1 += fix32(f.y);
+        m2 += fix32(f.z);
+        m3 += fix32(f.w);
+        if (par == x) {
+            n += 1u;
+            mx = max(mx, S);
+            sq += S * S;
             atomicAdd(&s_hist[63 - __clzll((long long)S)], 1u);
         }
     }
@@ -287,31 +351,44 @@ __global__ __launch_bounds__(kPhiBlock) void k_phi_record(PhiDev d) {
         s_red[wv][7] = (int64_t)sq;
     }
     __syncthreads();
-    unsigned long long *acc = reinterpret_cast<unsigned long long *>(d.acc);
-    if (tid < 8u) {
+    if (tid < (uint32_t)PA_END) {
         int64_t v = 0;
-        for (int w = 0; w < kPhiBlock / 64; ++w)
-            v = tid == 6u ? max(v, s_red[w][tid]) : v + s_red[w][tid];
-        const uint32_t slot = tid < 5u ? PA_E + tid : tid == 5u ? PA_N : tid == 6u ? PA_MAX : PA_SQ;
-        if (tid == 6u)
-            atomicMax(&acc[slot], (unsigned long long)v);
-        else if (v != 0)
-            atomicAdd(&acc[slot], (unsigned long long)v);
+        if (tid < 8u) {
+            for (uint32_t w = 0; w < NW; ++w) v = tid == (uint32_t)PA_MAX ? max(v, s_red[w][tid]) : v + s_red[w][tid];
+        } else {
+            v = s_hist[tid - (uint32_t)PA_HIST];
+        }
+        __hip_atomic_store(&d.part[(size_t)blockIdx.x * kPhiPart + tid], (uint64_t)v, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
     }
-    if (tid < 33u && s_hist[tid]) atomicAdd(&acc[PA_HIST + tid], (unsigned long long)s_hist[tid]);
-    __threadfence();
+    __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    if (tid == 0u) s_last = atomicAdd(&acc[PA_COUNT], 1ull) == (unsigned long long)gridDim.x - 1ull;
+    unsigned long long *count = reinterpret_cast<unsigned long long *>(d.acc);
+    if (tid == 0u) s_last = atomicAdd(count, 1ull) == (unsigned long long)gridDim.x - 1ull;
     __syncthreads();
     if (!s_last) return;
-    __threadfence();
-    // the last workgroup: the record of sweep t, then clear for the next
-    __shared__ uint64_t s_tot[PA_END];
-    if (tid < (uint32_t)PA_END) {
-        s_tot[tid] = __hip_atomic_load(&acc[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(&acc[tid], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // the last workgroup: fold the partials (thread t: field t % 64 of every
+    // NW-th one), then the record of sweep t
+    if (tid == 0u) __hip_atomic_store(count, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (lane < (uint32_t)PA_END) {
+        uint64_t v = 0;
+        for (uint32_t i = wv; i < gridDim.x; i += 4u * NW) {
+            uint64_t y[4];
+#pragma unroll
+            for (uint32_t u = 0; u < 4u; ++u) {
+                const uint32_t it = i + u * NW;
+                y[u] = it < gridDim.x ? __hip_atomic_load(&d.part[(size_t)it * kPhiPart + lane], __ATOMIC_RELAXED,
+                                                          __HIP_MEMORY_SCOPE_AGENT)
+                                      : 0u;
+            }
+#pragma unroll
+            for (uint32_t u = 0; u < 4u; ++u) v = lane == (uint32_t)PA_MAX ? max(v, y[u]) : v + y[u];
+        }
+        if (lane == (uint32_t)PA_MAX)
+            atomicMax(&s_tot[lane], (unsigned long long)v);
+        else if (v)
+            atomicAdd(&s_tot[lane], (unsigned long long)v);
     }
-    if (tid == (uint32_t)PA_END) __hip_atomic_store(&acc[PA_COUNT], 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     const uint64_t tsw = *d.tdev;
     sw_phi4_obs *rec = &d.ring[tsw % d.ring_cap];
@@ -334,22 +411,22 @@ __global__ __launch_bounds__(kPhiBlock) void k_phi_record(PhiDev d) {
         rec->sum_sq_sizes = s_tot[PA_SQ];
     }
     __syncthreads();
-    if (tid == 0u) {
-        *d.tdev = tsw + 1u;
-        __threadfence();
-    }
+    if (tid == 0u) *d.tdev = tsw + 1u;
 }
 
 constexpr int kPhiStages = 5;
 
 hipError_t phi_launch_stage(const PhiDev &d, int stage, hipStream_t s) {
-    const uint32_t g = (d.N + kPhiBlock - 1) / kPhiBlock;
+    const uint32_t g = (d.N + kPhiChunk - 1) / kPhiChunk;
     switch (stage) {
-    case 0: k_phi_proj<<<g, kPhiBlock, 0, s>>>(d); break;
-    case 1: k_phi_bond<<<g, kPhiBlock, 0, s>>>(d); break;
-    case 2: k_phi_flat<<<g, kPhiBlock, 0, s>>>(d); break;
-    case 3: k_phi_flip<<<g, kPhiBlock, 0, s>>>(d); break;
-    case 4: k_phi_record<<<g, kPhiBlock, 0, s>>>(d); break;
+    case 0: break;  // projections: taken in k_phi_bond and k_phi_flat
+    case 1:
+        k_phi_bond<<<g, kPhiChunk, 0, s>>>(d);
+        if (g > 1u) k_phi_union<<<dim3((d.N + kPhiBlock - 1) / kPhiBlock, 4), kPhiBlock, 0, s>>>(d);
+        break;
+    case 2: k_phi_flat<<<g, kPhiChunk, 0, s>>>(d); break;
+    case 3: break;  // reflections: done by k_phi_flat
+    case 4: k_phi_record<<<std::min(g, kPhiRecGroups), kPhiChunk, 0, s>>>(d); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -364,7 +441,7 @@ hipError_t phi_launch_sweep(const PhiDev &d, hipStream_t s) {
 }
 
 struct PhiLayout {
-    size_t phi, proj, parent, csize, dir, acc, tdev, ring, total;
+    size_t phi, parent, csize, cross, dir, part, acc, tdev, ring, total;
 };
 
 PhiLayout phi_layout(int32_t L, int64_t ring) {
@@ -377,11 +454,12 @@ PhiLayout phi_layout(int32_t L, int64_t ring) {
         return o;
     };
     lo.phi = take(N * 4 * sizeof(double));
-    lo.proj = take(N * sizeof(double));
     lo.parent = take(N * sizeof(uint32_t));
     lo.csize = take(N * sizeof(uint32_t));
+    lo.cross = take(N);
     lo.dir = take(8 * sizeof(double));
-    lo.acc = take(kPhiAccWords * sizeof(uint64_t));
+    lo.part = take(std::min<size_t>((N + kPhiChunk - 1) / kPhiChunk, kPhiRecGroups) * kPhiPart * sizeof(uint64_t));
+    lo.acc = take(sizeof(uint64_t));
     lo.tdev = take(sizeof(uint64_t));
     lo.ring = take((size_t)ring * sizeof(sw_phi4_obs));
     lo.total = off;
@@ -517,10 +595,11 @@ int sw_phi4_create(int32_t L, double kappa, uint64_t seed, int32_t init, int64_t
     char *base = (char *)p->ws;
     PhiDev &d = p->dev;
     d.phi = (double *)(base + lo.phi);
-    d.proj = (double *)(base + lo.proj);
     d.parent = (uint32_t *)(base + lo.parent);
     d.csize = (uint32_t *)(base + lo.csize);
     d.dir = (double *)(base + lo.dir);
+    d.cross = (uint8_t *)(base + lo.cross);
+    d.part = (uint64_t *)(base + lo.part);
     d.acc = (uint64_t *)(base + lo.acc);
     d.tdev = (uint64_t *)(base + lo.tdev);
     d.ring = (sw_phi4_obs *)(base + lo.ring);
