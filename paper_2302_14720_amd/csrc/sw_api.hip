@@ -94,15 +94,16 @@ int validate(const sw_config *c) {
 
 Layout layout_of(const sw_config &c) {
     const size_t L = (size_t)c.L, N = sites_of(c);
-    // the label-equivalence path and the cubic bricks keep labels in global
-    // memory and no tile structures; their group partials are one per
-    // kLeChunk sites
-    const bool le = (c.flags & SW_FLAG_LABEL_EQUIV) != 0u || c.dims == 3;
+    // the label-equivalence path keeps labels in global memory and no tile
+    // structures; its group partials are one per kLeChunk sites
+    const bool le = (c.flags & SW_FLAG_LABEL_EQUIV) != 0u;
+    const bool brick = c.dims == 3 && !le;
     const size_t tw = (size_t)resolve_tile(c);
-    const size_t ntiles = le ? 0 : (L / tw) * (L / tw);
+    // tiles, or bricks of the simple cubic lattice
+    const size_t ntiles = le ? 0 : brick ? N / (swmi::kBrick * swmi::kBrick * swmi::kBrick) : (L / tw) * (L / tw);
     const size_t ngroups = le ? (N + swmi::kLeChunk - 1) / swmi::kLeChunk
-                              : (ntiles + swmi::kGroupTiles - 1) / swmi::kGroupTiles;
-    const size_t nodes = ntiles * swmi::kNodeSlots;
+                              : brick ? ntiles : (ntiles + swmi::kGroupTiles - 1) / swmi::kGroupTiles;
+    const size_t nodes = ntiles * (brick ? swmi::kBrickNodes : swmi::kNodeSlots);
     const size_t ring = (size_t)(c.ring > 0 ? c.ring : kDefaultRing);
     Layout o{};
     size_t off = 0;
@@ -112,32 +113,31 @@ Layout layout_of(const sw_config &c) {
         return at;
     };
     o.spins[0] = take(N);
-    o.spins[1] = le ? o.spins[0] : take(N);  // final spins in place
+    o.spins[1] = le || brick ? o.spins[0] : take(N);  // final spins in place
     o.parent[0] = take(nodes * 4);
-    o.parent[1] = take(nodes * 4);
+    o.parent[1] = brick ? o.parent[0] : take(nodes * 4);
     o.nk[0] = take(ntiles * 4);
-    o.nk[1] = take(ntiles * 4);
+    o.nk[1] = brick ? o.nk[0] : take(ntiles * 4);
     o.key = take(nodes * 4);
     o.nsize = take(nodes * 4);
-    o.rspin = take(nodes);
-    o.edge = take(ntiles * 4 * tw);
-    o.xb = take(ntiles * 16);
+    o.rspin = brick ? 0 : take(nodes);
+    o.edge = brick ? 0 : take(ntiles * 4 * tw);
+    o.xb = brick ? 0 : take(ntiles * 16);
     o.tpart = take(ntiles * swmi::kTilePart * 4);
     o.gpart = take(ngroups * swmi::kGroupPart * 8);
     o.acc = take(swmi::kAccWords * 8);
     o.tdev = take(8);
     o.ring = take(ring * sizeof(sw_obs));
-    o.labels = (le || (c.flags & SW_FLAG_LABELS)) ? take(N * 4) : 0;
+    o.labels = (le || brick || (c.flags & SW_FLAG_LABELS)) ? take(N * 4) : 0;
     o.dense = (c.flags & SW_FLAG_DENSE_HIST) ? take((N + 1) * 8) : 0;
-    o.tdense = (c.flags & SW_FLAG_DENSE_HIST) ? take(ntiles * swmi::kDenseBins * 2) : 0;
+    o.tdense = (c.flags & SW_FLAG_DENSE_HIST) && !brick ? take(ntiles * swmi::kDenseBins * 2) : 0;
     o.le_mask = le ? take(N) : 0;
     o.le_cnt = le ? take(N * 4) : 0;
     o.le_rsp = le ? take(N) : 0;
     o.le_ctl = le ? take(64) : 0;
-    // cubic bricks: the x-face labels of every brick, so that the face
-    // unions read them contiguously
-    const bool brick = c.dims == 3 && !(c.flags & SW_FLAG_LABEL_EQUIV);
-    o.bface = brick ? take(N / 4096 * 512 * 4) : 0;
+    o.codes = brick ? take(N * 2) : 0;
+    o.faces = brick ? take(ntiles * 6 * 256 * 2) : 0;
+    o.nroot = brick ? take(nodes * 2) : 0;
     o.total = off;
     return o;
 }
@@ -176,23 +176,28 @@ Dev make_dev(const sw_config &c, char *base, const Layout &lo) {
     d.acc = (uint64_t *)(base + lo.acc);
     d.tdev = (uint64_t *)(base + lo.tdev);
     d.ring = (sw_obs *)(base + lo.ring);
-    const bool le = (c.flags & SW_FLAG_LABEL_EQUIV) != 0u || c.dims == 3;
-    d.labels = (le || (c.flags & SW_FLAG_LABELS)) ? (uint32_t *)(base + lo.labels) : nullptr;
+    const bool le = (c.flags & SW_FLAG_LABEL_EQUIV) != 0u, brick = c.dims == 3 && !le;
+    d.labels = (le || brick || (c.flags & SW_FLAG_LABELS)) ? (uint32_t *)(base + lo.labels) : nullptr;
     d.dense = (c.flags & SW_FLAG_DENSE_HIST) ? (uint64_t *)(base + lo.dense) : nullptr;
-    d.tdense = (c.flags & SW_FLAG_DENSE_HIST) ? (uint16_t *)(base + lo.tdense) : nullptr;
+    d.tdense = (c.flags & SW_FLAG_DENSE_HIST) && !brick ? (uint16_t *)(base + lo.tdense) : nullptr;
     if (le) {
         d.ntiles = 0;
         d.ntx = 0;
         d.ngroups = (uint32_t)((d.nsite + swmi::kLeChunk - 1) / swmi::kLeChunk);
-        if (c.dims == 3 && !(c.flags & SW_FLAG_LABEL_EQUIV)) {
-            d.brick = 1u;
-            d.tw = swmi::kBrick;
-            d.bface = (uint32_t *)(base + lo.bface);
-        }
         d.le_mask = (uint8_t *)(base + lo.le_mask);
         d.le_cnt = (uint32_t *)(base + lo.le_cnt);
         d.le_rsp = (int8_t *)(base + lo.le_rsp);
         d.le_ctl = (uint32_t *)(base + lo.le_ctl);
+    }
+    if (brick) {
+        d.brick = 1u;
+        d.tw = swmi::kBrick;
+        d.ntx = d.L / swmi::kBrick;
+        d.ntiles = d.ntx * d.ntx * d.ntx;
+        d.ngroups = d.ntiles;
+        d.codes = (uint16_t *)(base + lo.codes);
+        d.faces = (uint16_t *)(base + lo.faces);
+        d.nroot = (uint16_t *)(base + lo.nroot);
     }
     return d;
 }
@@ -552,6 +557,7 @@ int sw_get_labels(sw_sim *s, uint32_t *host, int64_t n) {
     if (s->next_sweep == s->first_valid) return fail(SW_ESTATE, "no sweep has run since the last reset / set_spins");
     int rc = ensure_device(s);
     if (rc != SW_OK) return rc;
+    if (s->dev.brick) HIP_TRY(swmi::launch_brick_labels(s->dev, s->stream));
     HIP_TRY(hipMemcpyAsync(host, s->dev.labels, (size_t)n * 4, hipMemcpyDeviceToHost, s->stream));
     HIP_TRY(hipStreamSynchronize(s->stream));
     return SW_OK;

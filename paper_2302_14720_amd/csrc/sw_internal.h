@@ -25,8 +25,9 @@
 // values 0..q-1 as final bytes and node codes from 4 (64-wide tiles, q <= 4)
 // or 8 (32-wide tiles).
 //
-// The simple cubic lattice, and the paper's label equivalence on either
-// lattice, keep 32-bit labels per site in global memory instead (sw_le.hip).
+// The simple cubic lattice has the same pipeline on 16^3 bricks
+// (sw_brick.hip).  The paper's label equivalence, on either lattice, keeps
+// 32-bit labels per site in global memory instead (sw_le.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -75,8 +76,12 @@ struct Dev {
     uint32_t *le_cnt;     // [N] cluster size at each root
     int8_t *le_rsp;       // [N] new spin, valid at roots
     uint32_t *le_ctl;     // [8] pass flags (3), passes of the last sweep, status
-    uint32_t *bface;      // cubic bricks: [nbricks][2][256] labels of the x = 15 sites
-                          // (kMapNone unless bonded to +x) and of the x = 0 sites
+    // simple cubic lattice on bricks (sw_brick.hip); parent[0], nk[0], key, nsize
+    // and tpart by brick, kBrickNodes node slots each; gpart one per brick
+    uint16_t *codes;      // [nbricks][4096] brick-local index of the site's component's smallest site
+    uint16_t *faces;      // [nbricks][6][256] nodes of the sites of the +x, +y, +z faces (0xFFFF unless
+                          // bonded through the face) and of the x = 0, y = 0, z = 0 faces
+    uint16_t *nroot;      // [nbricks][kBrickNodes] smallest brick-local site of every node
     uint32_t L, tw, ntx, ntiles, ngroups;
     uint32_t T, seed_lo, seed_hi;
     uint32_t ring_cap;
@@ -126,15 +131,20 @@ struct BatchDev {
 };
 
 
-// Paths with labels in global memory: stages 0..4 of a sweep (bonds and, for
-// cubic bricks, brick-local clusters; global labelling by iterated label
-// equivalence or by union-find across brick faces; new spins and sizes;
-// statistics; record), and the cooperative grid size of label equivalence.
+// Label equivalence: stages 0..3 of a sweep (bonds; labelling; new spins and
+// sizes; statistics) and the cooperative grid size.
 hipError_t launch_le_stage(const Dev &d, int stage, hipStream_t s);
 uint32_t le_grid_size(uint32_t dims);
 constexpr uint32_t kLeChunk = 4096;  // sites per workgroup in the per-site passes
 constexpr uint32_t kBrick = 16;      // side of a brick of the simple cubic lattice
+constexpr uint32_t kBrickNodes = 1352;  // node slots per brick: its surface sites
 enum { LE_PASSES = 3, LE_STATUS = 4 };
+
+// Cubic bricks: stages 0..3 of a sweep, the closing measurement (brick
+// partials), and the labels of the last sweep.
+hipError_t launch_brick_stage(const Dev &d, int stage, hipStream_t s);
+hipError_t launch_brick_measure(const Dev &d, hipStream_t s);
+hipError_t launch_brick_labels(const Dev &d, hipStream_t s);
 
 // Stage 0 is the tile kernel of every replica; stages 1..4 the global merge;
 // launch_batch_smerge the LDS merge of the small replicas, which may run

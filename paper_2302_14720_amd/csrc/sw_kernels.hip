@@ -3,6 +3,7 @@
 // row of 64 sites is one 64-bit mask, so row runs of horizontal bonds come
 // from bit arithmetic on ballot-sized masks, and only vertical bonds go
 // through the LDS union-find.
+#include "sw_device.h"
 #include "sw_internal.h"
 #include "sw_philox.h"
 #include "sw_uf.h"
@@ -44,73 +45,6 @@ __device__ __forceinline__ typename RowOf<TW>::T row_gather(uint32_t piece) {
         return row_piece<0, 2>(piece) | (row_piece<1, 2>(piece) << 16);
     }
 }
-
-// Workgroup b runs on XCD b % 8; give each XCD a contiguous band of tiles so
-// that neighbouring tiles (which share halo rows and cache lines) meet in
-// the same L2 (the last n mod 8 blocks keep their own index).
-__device__ __forceinline__ uint32_t tile_of_block(uint32_t b, uint32_t n) {
-    const uint32_t n8 = n & ~7u;
-    if (b < n8) return (b & 7u) * (n8 >> 3) + (b >> 3);
-    return b;
-}
-
-// ---------------------------------------------------------------- LDS union-find
-// (the plain-index helpers are in sw_uf.h)
-// The tile kernel's parent words hold byte offsets into the LDS array (so a
-// parent is directly a load address) and carry other data in their high
-// halves (a work list while the unions run).
-__device__ __forceinline__ uint32_t *word_at(uint32_t *base, uint32_t off) {
-    return reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(base) + off);
-}
-
-// Union of the sets of the words at byte offsets a and b: parents are the
-// low 16 bits, and the compare-and-swap that links the larger root under the
-// smaller keeps the high half it read.  A failed swap (another lane linked
-// the root, or the high half changed) resumes from what it found.
-__device__ __forceinline__ void lds_union_lo(uint32_t *par, uint32_t a, uint32_t b) {
-    while (true) {
-        uint32_t wa = lds_load(word_at(par, a)), wb = lds_load(word_at(par, b));
-        uint32_t pa = wa & 0xFFFFu, pb = wb & 0xFFFFu;
-        while (pa != a || pb != b) {
-            a = pa;
-            b = pb;
-            wa = lds_load(word_at(par, a));
-            wb = lds_load(word_at(par, b));
-            pa = wa & 0xFFFFu;
-            pb = wb & 0xFFFFu;
-        }
-        if (a == b) return;
-        const bool ahi = a > b;
-        const uint32_t hi = ahi ? a : b, lo = ahi ? b : a;
-        uint32_t expected = ahi ? wa : wb;
-        const uint32_t desired = (expected & 0xFFFF0000u) | lo;
-        if (__hip_atomic_compare_exchange_strong(word_at(par, hi), &expected, desired, __ATOMIC_RELAXED,
-                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
-            return;
-        a = lo;
-        b = expected & 0xFFFFu;
-    }
-}
-
-// Low half (the parent) and high half of the word at byte offset off, each
-// read on its own (16-bit loads; the halves are little-endian).
-__device__ __forceinline__ uint32_t lo16_at(uint32_t *base, uint32_t off) {
-    return *reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(base) + off);
-}
-__device__ __forceinline__ uint32_t hi16_at(uint32_t *base, uint32_t off) {
-    return *reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(base) + off + 2u);
-}
-
-// Root (byte offset) of the word at byte offset a once the unions are done.
-__device__ __forceinline__ uint32_t lds_root_b(uint32_t *par, uint32_t a) {
-    while (true) {
-        const uint32_t p = lds_load(word_at(par, a)) & 0xFFFFu;
-        if (p == a) return a;
-        a = p;
-    }
-}
-
-
 
 // Spin (+1/-1) encoded by a byte of the previous sweep's output that belongs
 // to tile `tile`: final spins are 0x01 / 0xFF, a code 2 + k refers to node k
@@ -205,24 +139,6 @@ __device__ __forceinline__ void decode16_potts_remote(const uint4 &v, uint32_t t
         pl[0] |= (x & 1u) << q;
         pl[1] |= ((x >> 1) & 1u) << q;
         pl[2] |= (x >> 2) << q;
-    }
-}
-
-// Equal-neighbour masks of 16 sites from their bit planes and those of the
-// E and N neighbours; equal pairs and the population of every value 0..7
-// (two 16-bit counts per word).
-__device__ __forceinline__ void potts_counts(const uint32_t pl[3], uint32_t cpk[4]) {
-#pragma unroll
-    for (int k = 0; k < 8; k += 2) {
-        uint32_t c[2];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int v = k + h;
-            const uint32_t m = ~((pl[0] ^ ((v & 1) ? 0xFFFFu : 0u)) | (pl[1] ^ ((v & 2) ? 0xFFFFu : 0u)) |
-                                 (pl[2] ^ ((v & 4) ? 0xFFFFu : 0u))) & 0xFFFFu;
-            c[h] = (uint32_t)__popc(m);
-        }
-        cpk[k >> 1] = c[0] | (c[1] << 16);
     }
 }
 
@@ -1795,13 +1711,13 @@ hipError_t launch_init(const Dev &d, int cold, hipStream_t s) {
 
 hipError_t launch_stage(const Dev &d, int stage, hipStream_t s) {
     const size_t n = d.nsite;
-    if (d.le_grid || d.brick) {  // labels in global memory (label equivalence, cubic bricks)
+    if (d.le_grid || d.brick) {  // label equivalence, cubic bricks
         if (stage == 0 && d.dense) k_zero_u64<<<grid_for(n + 1, 256, 65536), 256, 0, s>>>(d.dense, n + 1);
         if (stage != 4) {
             const hipError_t e = hipGetLastError();
-            return e != hipSuccess ? e : launch_le_stage(d, stage, s);
+            return e != hipSuccess ? e : d.brick ? launch_brick_stage(d, stage, s) : launch_le_stage(d, stage, s);
         }
-        k_record<<<(d.ngroups + kRecordGroups - 1) / kRecordGroups, 256, 0, s>>>(d, d.ngroups, 2);
+        k_record<<<(d.ngroups + kRecordGroups - 1) / kRecordGroups, 256, 0, s>>>(d, d.ngroups, d.brick ? 0 : 2);
         return hipGetLastError();
     }
     switch (stage) {
@@ -1872,7 +1788,13 @@ hipError_t launch_sweep(const Dev &d, hipStream_t s) {
 }
 
 hipError_t launch_resolve(const Dev &d, hipStream_t s) {
-    if (d.le_grid || d.brick) return hipSuccess;  // those paths write final spins and full records
+    if (d.le_grid) return hipSuccess;  // label equivalence writes final spins and full records
+    if (d.brick) {  // spins are final; their energy and magnetisation go into the last record
+        const hipError_t e = launch_brick_measure(d, s);
+        if (e != hipSuccess) return e;
+        k_record<<<(d.ntiles + kRecordTiles - 1) / kRecordTiles, 256, 0, s>>>(d, d.ntiles, 1);
+        return hipGetLastError();
+    }
     if (d.q && d.tw == 64)
         k_resolve<64, true><<<d.ntiles, 256, 0, s>>>(d);
     else if (d.q)

@@ -49,6 +49,60 @@ __device__ __forceinline__ void lds_union(uint32_t *par, uint32_t a, uint32_t b)
     }
 }
 
+// The tile and brick kernels' parent words hold byte offsets into the LDS array
+// (so a parent is directly a load address) and carry other data in their high
+// halves (a work list while the unions run).
+__device__ __forceinline__ uint32_t *word_at(uint32_t *base, uint32_t off) {
+    return reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(base) + off);
+}
+
+// Union of the sets of the words at byte offsets a and b: parents are the
+// low 16 bits, and the compare-and-swap that links the larger root under the
+// smaller keeps the high half it read.  A failed swap (another lane linked
+// the root, or the high half changed) resumes from what it found.
+__device__ __forceinline__ void lds_union_lo(uint32_t *par, uint32_t a, uint32_t b) {
+    while (true) {
+        uint32_t wa = lds_load(word_at(par, a)), wb = lds_load(word_at(par, b));
+        uint32_t pa = wa & 0xFFFFu, pb = wb & 0xFFFFu;
+        while (pa != a || pb != b) {
+            a = pa;
+            b = pb;
+            wa = lds_load(word_at(par, a));
+            wb = lds_load(word_at(par, b));
+            pa = wa & 0xFFFFu;
+            pb = wb & 0xFFFFu;
+        }
+        if (a == b) return;
+        const bool ahi = a > b;
+        const uint32_t hi = ahi ? a : b, lo = ahi ? b : a;
+        uint32_t expected = ahi ? wa : wb;
+        const uint32_t desired = (expected & 0xFFFF0000u) | lo;
+        if (__hip_atomic_compare_exchange_strong(word_at(par, hi), &expected, desired, __ATOMIC_RELAXED,
+                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP))
+            return;
+        a = lo;
+        b = expected & 0xFFFFu;
+    }
+}
+
+// Low half (the parent) and high half of the word at byte offset off, each
+// read on its own (16-bit loads; the halves are little-endian).
+__device__ __forceinline__ uint32_t lo16_at(uint32_t *base, uint32_t off) {
+    return *reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(base) + off);
+}
+__device__ __forceinline__ uint32_t hi16_at(uint32_t *base, uint32_t off) {
+    return *reinterpret_cast<const uint16_t *>(reinterpret_cast<const char *>(base) + off + 2u);
+}
+
+// Root (byte offset) of the word at byte offset a once the unions are done.
+__device__ __forceinline__ uint32_t lds_root_b(uint32_t *par, uint32_t a) {
+    while (true) {
+        const uint32_t p = lds_load(word_at(par, a)) & 0xFFFFu;
+        if (p == a) return a;
+        a = p;
+    }
+}
+
 __device__ __forceinline__ uint32_t g_load(uint32_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
