@@ -137,7 +137,7 @@ Layout layout_of(const sw_config &c) {
     o.le_ctl = le ? take(64) : 0;
     o.codes = brick ? take(N * 2) : 0;
     o.faces = brick ? take(ntiles * 6 * 256 * 2) : 0;
-    o.nroot = brick ? take(nodes * 2) : 0;
+    o.node = brick ? take(nodes * 4) : 0;
     o.total = off;
     return o;
 }
@@ -197,7 +197,7 @@ Dev make_dev(const sw_config &c, char *base, const Layout &lo) {
         d.ngroups = d.ntiles;
         d.codes = (uint16_t *)(base + lo.codes);
         d.faces = (uint16_t *)(base + lo.faces);
-        d.nroot = (uint16_t *)(base + lo.nroot);
+        d.node = (uint32_t *)(base + lo.node);
     }
     return d;
 }

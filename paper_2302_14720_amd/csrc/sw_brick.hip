@@ -2,8 +2,8 @@
 // dims = 3).  One sweep:
 //   k_brick3   bonds (Sec. 2.1) and the connected components of the bonds
 //              inside each brick, in LDS; energy and magnetisation of the
-//              incoming configuration (Sec. 2.5).  A component that touches
-//              the brick's surface becomes a node of a global graph.
+//              incoming configuration (Sec. 2.5).  A component with a bond
+//              through the brick's surface becomes a node of a global graph.
 //   k_blocal3  node unions across the faces inside each 2x2x2 group of
 //              bricks, in LDS
 //   k_bunion3  node unions across the faces between groups (lock-free
@@ -15,6 +15,12 @@
 // brick-local index of its component's smallest site, so the label of a site
 // (2 bytes, not 4) is written once and read once; 32-bit labels are made
 // from the codes only when they are asked for (k_blabels3).
+//
+// At 512^3, q = 3 at 0.5505 (times per sweep): k_brick3 0.59 ms, bound by VALU
+// issue (410 M wavefront instructions, 84 % of what independent integer chains
+// reach, a quarter of them Philox); k_bflat3 0.17, k_bunion3 0.17, k_blocal3
+// 0.10 and k_bspin3 0.13 ms, bound by their dependent loads and device-scope
+// atomics over 228 nodes a brick.  32-bit labels in global memory took 2.9 ms.
 #include "sw_device.h"
 #include "sw_internal.h"
 #include "sw_philox.h"
@@ -28,6 +34,9 @@ constexpr uint32_t kNoNode = 0xFFFFu;
 constexpr uint32_t kRows = kBrick * kBrick;   // x-rows of a brick: one thread each
 constexpr uint32_t kVol = kRows * kBrick;     // sites of a brick
 constexpr uint32_t kPS = kBrick + 1u;         // words of a row in LDS: lanes reading equal x fall in distinct banks
+// 64 VGPRs (the Philox calls unrolled by 4, not 16) and 19.9 KB of LDS: eight
+// workgroups per CU
+constexpr int kBrickWavesPerEU = 8;
 static_assert(kBrickNodes == kVol - 14u * 14u * 14u, "a node holds a site of the brick's surface");
 
 // Brick coordinates.
@@ -37,6 +46,10 @@ struct Brick {
 __device__ __forceinline__ Brick brick_of(uint32_t b, uint32_t nb) {
     const uint32_t q = b / nb, z = q / nb;
     return {b, b - q * nb, q - z * nb, z};
+}
+// Lattice site of brick-local site s.
+__device__ __forceinline__ uint32_t site_at(const Brick &B, uint32_t L, uint32_t s) {
+    return ((B.z * kBrick + (s >> 8)) * L + B.y * kBrick + ((s >> 4) & 15u)) * L + B.x * kBrick + (s & 15u);
 }
 
 // Bit `bit` of each of 16 bytes, as a 16-bit mask.
@@ -179,33 +192,71 @@ __device__ __forceinline__ void join_listed(uint32_t *s_par, uint32_t R, uint32_
 // component's smallest site.
 // =====================================================================
 template <bool POTTS, bool DENSE>
-__global__ __launch_bounds__(256) void k_brick3(Dev d) {
+__global__ __launch_bounds__(256, kBrickWavesPerEU) void k_brick3(Dev d) {
     constexpr uint32_t NPL = POTTS ? 3u : 1u;
     __shared__ uint32_t s_par[kRows * kPS];
-    __shared__ uint32_t s_node[kBrickNodes];  // site | size << 16
     __shared__ uint16_t s_pl[NPL][kRows];
     __shared__ uint16_t s_ex[kRows];
     __shared__ uint16_t s_hi[2][kBrick];  // bonds that leave through +y (by z) and +z (by y)
+    __shared__ uint16_t s_in[2][kBrick];  // bonds that come in through y = 0 (by z) and z = 0 (by y)
     __shared__ uint32_t s_bf[kVol / 32];
-    __shared__ uint32_t s_hist[12];
+    __shared__ uint32_t s_hist[kTileBins];
     __shared__ uint32_t s_dense[DENSE ? kDenseBins : 1];
     __shared__ int32_t s_red[kRows / 64][3];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, y = tid & 15u, z = tid >> 4;
     const Brick B = brick_of(tile_of_block(blockIdx.x, gridDim.x), d.L / kBrick);
     const uint32_t L = d.L;
-    const uint32_t s0 = ((B.z * kBrick + z) * L + B.y * kBrick + y) * L + B.x * kBrick;
+    const uint32_t s0 = site_at(B, L, tid * kBrick);
     const uint32_t t = (uint32_t)*d.tdev, T = d.T;
     if (tid < kVol / 32u) s_bf[tid] = 0u;
-    if (tid < 12u) s_hist[tid] = 0u;
+    if (tid < kTileBins) s_hist[tid] = 0u;
     if constexpr (DENSE) s_dense[tid] = 0u;
     uint32_t pl[3];
     const Equal eq = row_equal<POTTS>(d, B, s_pl, pl);
     brick_measure<POTTS>(d, B.b, eq, pl);
 
+    // bonds that come in through the x = 0, y = 0 and z = 0 faces, one site of
+    // each face per thread: the neighbours own them, so their words are drawn
+    // here a second time (3 calls beside a thread's 16), which leaves only
+    // components that do go on outside as nodes -- a third of those that touch
+    // the surface (228 of 640-700 per brick at the critical points)
+    uint32_t in_x;
+    {
+        const uint32_t a = tid & 15u, c = tid >> 4;
+        const uint32_t gx0 = B.x * kBrick, gy0 = B.y * kBrick, gz0 = B.z * kBrick;
+        const uint32_t nx = s0 - gx0 + (gx0 == 0u ? L - 1u : gx0 - 1u);
+        const uint32_t ny = ((gz0 + c) * L + (gy0 == 0u ? L - 1u : gy0 - 1u)) * L + gx0 + a;
+        const uint32_t nz = ((gz0 == 0u ? L - 1u : gz0 - 1u) * L + gy0 + c) * L + gx0 + a;
+        const int8_t *sp = d.spins[0];
+        const uint32_t vx = (uint8_t)sp[nx], vy = (uint8_t)sp[ny], vz = (uint8_t)sp[nz];
+        uint32_t dx = 0u, dy = 0u, dz = 0u;
+#pragma unroll
+        for (uint32_t b = 0; b < NPL; ++b) {
+            const uint32_t bit = spin_bit<POTTS>(b);
+            dx |= (vx >> bit) ^ pl[b];
+            dy |= (vy >> bit) ^ ((uint32_t)s_pl[b][c * 16u] >> a);
+            dz |= (vz >> bit) ^ ((uint32_t)s_pl[b][c] >> a);
+        }
+        uint32_t n[3] = {nx, ny, nz};
+        bool in[3];
+#pragma unroll
+        for (uint32_t f = 0; f < 3u; ++f) {
+            uint32_t w[4] = {n[f], t, 4u, 0u};
+            philox10(w[0], w[1], w[2], w[3], d.seed_lo, d.seed_hi);
+            in[f] = w[f] < T && !((f == 0u ? dx : f == 1u ? dy : dz) & 1u);
+        }
+        in_x = in[0] ? 1u : 0u;
+        const uint64_t by = __ballot(in[1]), bz = __ballot(in[2]);
+        if (a == 0u) {
+            s_in[0][c] = (uint16_t)(by >> (tid & 48u));
+            s_in[1][c] = (uint16_t)(bz >> (tid & 48u));
+        }
+    }
+
     // bonds (Sec. 2.1): one Philox call per site, words 0, 1, 2 of counter
     // {s, t, 4, 0} for +x, +y, +z
     uint32_t EX = 0u, EY = 0u, EZ = 0u;
-#pragma unroll
+#pragma unroll 4
     for (uint32_t j = 0; j < 16u; ++j) {
         uint32_t w0 = s0 + j, w1 = t, w2 = 4u, w3 = 0u;
         philox10(w0, w1, w2, w3, d.seed_lo, d.seed_hi);
@@ -247,11 +298,11 @@ __global__ __launch_bounds__(256) void k_brick3(Dev d) {
     }
     __syncthreads();
 
-    // sizes at the roots; components that touch the surface marked: every run
-    // of a row on a y or z face, else the row's first and last run
+    // sizes at the roots; components with a bond through the surface marked
     uint32_t rootmask = 0u;
     {
-        const bool edge_row = y == 0u || y == 15u || z == 0u || z == 15u;
+        const uint32_t linked = (EX & 0x8000u) | in_x | (y == 15u ? EY : 0u) | (z == 15u ? EZ : 0u) |
+                                (y == 0u ? s_in[0][z] : 0u) | (z == 0u ? s_in[1][y] : 0u);
         uint32_t acc_root = 0u, acc_len = 0u, m = st;
         while (m) {
             const uint32_t i = (uint32_t)__ffs((int)m) - 1u;
@@ -262,11 +313,11 @@ __global__ __launch_bounds__(256) void k_brick3(Dev d) {
                 __hip_atomic_store(word_at(s_par, n), root, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             else
                 rootmask |= 1u << i;
-            if (edge_row || i == 0u || m == 0u) {
+            const uint32_t len = (m ? (uint32_t)__ffs((int)m) - 1u : kBrick) - i;
+            if ((linked >> i) & ((1u << len) - 1u)) {
                 const uint32_t rs = site_of(root);
                 atomicOr(&s_bf[rs >> 5], 1u << (rs & 31u));
             }
-            const uint32_t len = (m ? (uint32_t)__ffs((int)m) - 1u : kBrick) - i;
             if (root != acc_root && acc_len != 0u)
                 __hip_atomic_fetch_add(word_at(s_par, acc_root), acc_len << 16, __ATOMIC_RELAXED,
                                        __HIP_MEMORY_SCOPE_WORKGROUP);
@@ -293,8 +344,9 @@ __global__ __launch_bounds__(256) void k_brick3(Dev d) {
         n_nodes = min((uint32_t)__shfl((int)incl, 63, 64), kBrickNodes);
     }
 
-    // roots: node into the root's word, node entries staged in LDS,
-    // interior-component statistics (size classes 0-2 packed, 10 bits each)
+    // roots: node into the root's word, node entries, interior-component
+    // statistics (size classes 0-2 packed in 11, 10 and 11 bits: a wavefront's
+    // 1024 sites may all be single)
     uint32_t max_int = 0u, sq_int = 0u, hpk = 0u;
     {
         const uint32_t sbase = tid * kBrick, word = sbase >> 5, bsh = sbase & 31u;
@@ -309,13 +361,13 @@ __global__ __launch_bounds__(256) void k_brick3(Dev d) {
             uint32_t k = kNoNode;
             if ((bmask >> i) & 1u) {
                 k = min(kbase + __popc(bmask & ((1u << i) - 1u)), kBrickNodes - 1u);
-                s_node[k] = (sbase + i) | (S << 16);
+                d.node[B.b * kBrickNodes + k] = (sbase + i) | (S << 16);
             } else {
                 max_int = max(max_int, S);
                 sq_int += S * S;
                 const uint32_t bin = 31u - (uint32_t)__clz((int)S);
                 if (bin < 3u)
-                    hpk += 1u << (10u * bin);
+                    hpk += 1u << (11u * bin - (bin >> 1));
                 else
                     atomicAdd(&s_hist[bin], 1u);
                 if constexpr (DENSE) {
@@ -331,12 +383,6 @@ __global__ __launch_bounds__(256) void k_brick3(Dev d) {
     __syncthreads();
     if constexpr (DENSE)
         if (s_dense[tid]) atomicAdd(reinterpret_cast<unsigned long long *>(&d.dense[tid]), (unsigned long long)s_dense[tid]);
-    for (uint32_t k = tid; k < n_nodes; k += kRows) {
-        const uint32_t e = s_node[k], s = e & 0xFFFFu, node = B.b * kBrickNodes + k;
-        d.key[node] = ((B.z * kBrick + (s >> 8)) * L + B.y * kBrick + ((s >> 4) & 15u)) * L + B.x * kBrick + (s & 15u);
-        d.nsize[node] = e >> 16;
-        d.nroot[node] = (uint16_t)s;
-    }
     // codes
     {
         uint32_t out[8], cur = rowoff;
@@ -351,7 +397,8 @@ __global__ __launch_bounds__(256) void k_brick3(Dev d) {
         cp[1] = make_uint4(out[4], out[5], out[6], out[7]);
     }
     // nodes of the face sites, one site of each face per thread (kNoNode on
-    // the +x, +y, +z faces unless the site's bond through the face is set)
+    // the +x, +y, +z faces unless the site's bond through the face is set; on
+    // the others the entry matters only where the neighbour's is set)
     {
         const uint32_t a = tid & 15u, c = tid >> 4;
         auto node_at = [&](uint32_t r, uint32_t x) {
@@ -385,16 +432,16 @@ __global__ __launch_bounds__(256) void k_brick3(Dev d) {
         int32_t mx = 0, sq = 0, h[3] = {0, 0, 0};
         for (uint32_t w = 0; w < kRows / 64u; ++w) {
             const uint32_t hw = (uint32_t)s_red[w][0];
-            h[0] += (int32_t)(hw & 0x3FFu);
-            h[1] += (int32_t)((hw >> 10) & 0x3FFu);
-            h[2] += (int32_t)(hw >> 20);
+            h[0] += (int32_t)(hw & 0x7FFu);
+            h[1] += (int32_t)((hw >> 11) & 0x3FFu);
+            h[2] += (int32_t)(hw >> 21);
             mx = max(mx, s_red[w][1]);
             sq += s_red[w][2];
         }
         int32_t n = h[0] + h[1] + h[2];
         int32_t *tp = d.tpart + (size_t)B.b * kTilePart;
         for (int k = 0; k < 3; ++k) tp[TP_HIST + k] = h[k];
-        for (int k = 3; k < 12; ++k) {
+        for (uint32_t k = 3; k < kTileBins; ++k) {
             n += (int32_t)s_hist[k];
             tp[TP_HIST + k] = (int32_t)s_hist[k];
         }
@@ -445,6 +492,10 @@ __global__ __launch_bounds__(kGroupThreads) void k_blocal3(Dev d) {
     const bool okw = group_brick(g, wv, nb, bw);
     const uint32_t nk = okw ? min(d.nk[0][bw], kBrickNodes) : 0u;
     for (uint32_t k = lane; k < nk; k += 64u) s_p[wv * kBrickNodes + k] = wv * kBrickNodes + k;
+    constexpr uint32_t kAhead = 5;  // node entries loaded before the unions (320 per brick)
+    uint32_t ahead[kAhead];
+#pragma unroll
+    for (uint32_t j = 0; j < kAhead; ++j) ahead[j] = lane + 64u * j < nk ? d.node[bw * kBrickNodes + lane + 64u * j] : 0u;
     __syncthreads();
 #pragma unroll
     for (uint32_t it = 0; it < NIT; ++it) {
@@ -454,13 +505,22 @@ __global__ __launch_bounds__(kGroupThreads) void k_blocal3(Dev d) {
         if (a != kEmpty && !dup) lds_union(s_p, a, b);
     }
     __syncthreads();
-    for (uint32_t k = lane; k < nk; k += 64u) {
-        const uint32_t li = wv * kBrickNodes + k;
+    const Brick B = brick_of(bw, nb);
+    auto settle = [&](uint32_t k, uint32_t e) {
+        const uint32_t li = wv * kBrickNodes + k, node = bw * kBrickNodes + k;
         const uint32_t r = lds_find(s_p, li), tr = r / kBrickNodes;
         uint32_t br;
         group_brick(g, tr, nb, br);
-        d.parent[0][bw * kBrickNodes + k] = br * kBrickNodes + (r - tr * kBrickNodes);
-    }
+        d.parent[0][node] = br * kBrickNodes + (r - tr * kBrickNodes);
+        if (r == li) {  // only a group root can be a cluster's root
+            d.nsize[node] = e >> 16;
+            d.key[node] = site_at(B, d.L, e & 0xFFFFu);
+        }
+    };
+#pragma unroll
+    for (uint32_t j = 0; j < kAhead; ++j)
+        if (lane + 64u * j < nk) settle(lane + 64u * j, ahead[j]);
+    for (uint32_t k = lane + 64u * kAhead; k < nk; k += 64u) settle(k, d.node[bw * kBrickNodes + k]);
 }
 
 // =====================================================================
@@ -519,14 +579,16 @@ __global__ __launch_bounds__(kGroupThreads) void k_bflat3(Dev d) {
     const bool ok = group_brick(tile_of_block(blockIdx.x, gridDim.x), wv, d.L / kBrick, b);
     const uint32_t nk = ok ? min(d.nk[0][b], kBrickNodes) : 0u;
     const uint32_t node0 = b * kBrickNodes;
-    constexpr uint32_t kChase = 8;
+    const Brick B = brick_of(b, d.L / kBrick);
+    constexpr uint32_t kChase = 4;
     for (uint32_t k0 = 0; k0 < nk; k0 += 64u * kChase) {
-        // up to eight nodes per lane, their chains followed together
-        uint32_t p0[kChase], r[kChase];
+        // up to four nodes per lane, their chains followed together
+        uint32_t p0[kChase], r[kChase], en[kChase];
 #pragma unroll
         for (uint32_t j = 0; j < kChase; ++j) {
             const uint32_t k = k0 + 64u * j + lane;
             p0[j] = k < nk ? g_load(&par[node0 + k]) : kEmpty;
+            en[j] = k < nk ? d.node[node0 + k] : 0u;
         }
 #pragma unroll
         for (uint32_t j = 0; j < kChase; ++j) r[j] = p0[j];
@@ -547,7 +609,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_bflat3(Dev d) {
             const uint32_t node = node0 + k0 + 64u * j + lane, root = r[j];
             if (root == kEmpty || root == node) continue;
             if (root != p0[j]) g_store(&par[node], root);
-            const uint32_t size = d.nsize[node], key = d.key[node];
+            const uint32_t e = en[j], size = e >> 16, key = site_at(B, d.L, e & 0xFFFFu);
             uint32_t h = (root * 2654435761u) >> 21;  // 11 bits
             bool placed = false;
             for (int probe = 0; probe < 64 && !placed; ++probe) {
@@ -601,13 +663,18 @@ __global__ __launch_bounds__(256) void k_bspin3(Dev d) {
     __shared__ uint32_t s_hist[33];
     __shared__ uint64_t s_red[kRows / 64][3];
     __shared__ uint32_t s_dense[DENSE ? kDenseBins : 1];
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, y = tid & 15u, z = tid >> 4, L = d.L;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, L = d.L;
     const Brick B = brick_of(tile_of_block(blockIdx.x, gridDim.x), L / kBrick);
-    const uint32_t s0 = ((B.z * kBrick + z) * L + B.y * kBrick + y) * L + B.x * kBrick;
+    const uint32_t s0 = site_at(B, L, tid * kBrick);
     const uint32_t t = (uint32_t)*d.tdev;
     const uint4 *cp = reinterpret_cast<const uint4 *>(d.codes + (size_t)B.b * kVol + tid * kBrick);
     const uint4 c0 = cp[0], c1 = cp[1];
     const uint32_t nk = min(d.nk[0][B.b], kBrickNodes);
+    // the first round's node entries (a brick rarely has more than 256 nodes)
+    const uint32_t *par = d.parent[0];
+    const uint32_t mine = B.b * kBrickNodes + tid;
+    const uint32_t root0 = tid < nk ? par[mine] : 0u, site0 = tid < nk ? d.node[mine] : 0u;
+    const uint32_t key0 = tid < nk ? d.key[root0] : 0u;
     if (tid < 33u) s_hist[tid] = 0u;
     if constexpr (DENSE) s_dense[tid] = 0u;
     {
@@ -637,10 +704,11 @@ __global__ __launch_bounds__(256) void k_bspin3(Dev d) {
     }
     __syncthreads();
     uint64_t n = 0, mx = 0, sq = 0;
-    const uint32_t *par = d.parent[0];
     for (uint32_t k = tid; k < nk; k += kRows) {
-        const uint32_t node = B.b * kBrickNodes + k, root = par[node], rkey = d.key[root];
-        s_tab[d.nroot[node]] = (uint8_t)(POTTS ? potts_spin(rkey, t, d.q, d.seed_lo, d.seed_hi)
+        const uint32_t node = B.b * kBrickNodes + k;
+        const uint32_t root = k == tid ? root0 : par[node], rkey = k == tid ? key0 : d.key[root];
+        const uint32_t site = k == tid ? site0 : d.node[node];
+        s_tab[site & (kVol - 1u)] = (uint8_t)(POTTS ? potts_spin(rkey, t, d.q, d.seed_lo, d.seed_hi)
                                                : cluster_spin(rkey, t, d.seed_lo, d.seed_hi));
         if (root == node) {
             const uint32_t S = d.nsize[node];
@@ -694,7 +762,7 @@ __global__ __launch_bounds__(256) void k_bspin3(Dev d) {
         gp[GP_E] = (uint64_t)(int64_t)tp[TP_E];
         gp[GP_M] = (uint64_t)(int64_t)tp[TP_M];
     }
-    if (tid < 33u) gp[GP_HIST + tid] = s_hist[tid] + (tid < 12u ? (uint32_t)tp[TP_HIST + tid] : 0u);
+    if (tid < 33u) gp[GP_HIST + tid] = s_hist[tid] + (tid < kTileBins ? (uint32_t)tp[TP_HIST + tid] : 0u);
     if (tid < (uint32_t)kMaxQ) gp[GP_CNT + tid] = POTTS ? (uint32_t)tp[TP_CNT + tid] : 0u;
 }
 
@@ -713,13 +781,13 @@ __global__ __launch_bounds__(256) void k_blabels3(Dev d) {
     __shared__ uint32_t s_lab[kVol];
     const uint32_t tid = threadIdx.x, L = d.L;
     const Brick B = brick_of(tile_of_block(blockIdx.x, gridDim.x), L / kBrick);
-    const uint32_t s0 = ((B.z * kBrick + (tid >> 4)) * L + B.y * kBrick + (tid & 15u)) * L + B.x * kBrick;
+    const uint32_t s0 = site_at(B, L, tid * kBrick);
     for (uint32_t j = 0; j < 16u; ++j) s_lab[tid * kBrick + j] = s0 + j;
     __syncthreads();
     const uint32_t nk = min(d.nk[0][B.b], kBrickNodes);
     for (uint32_t k = tid; k < nk; k += kRows) {
         const uint32_t node = B.b * kBrickNodes + k;
-        s_lab[d.nroot[node] & (kVol - 1u)] = d.key[d.parent[0][node]];
+        s_lab[d.node[node] & (kVol - 1u)] = d.key[d.parent[0][node]];
     }
     __syncthreads();
     const uint16_t *cp = d.codes + (size_t)B.b * kVol + tid * kBrick;

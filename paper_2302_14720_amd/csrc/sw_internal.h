@@ -47,8 +47,9 @@ constexpr uint32_t kDenseBins = 256;  // sizes below this are counted per tile a
 constexpr uint32_t kUG = 4;           // side, in tiles, of a k_ulocal group
 
 // tile partial (int32 words)
-// hist: 12 bins; TP_CNT..: population of each Potts value
-enum { TP_E = 0, TP_M = 1, TP_N = 2, TP_MAX = 3, TP_SQ = 4, TP_HIST = 5, TP_CNT = 17 };
+// hist: kTileBins bins (sizes up to 64 * 64 or 16^3); TP_CNT..: population of each Potts value
+constexpr uint32_t kTileBins = 13;
+enum { TP_E = 0, TP_M = 1, TP_N = 2, TP_MAX = 3, TP_SQ = 4, TP_HIST = 5, TP_CNT = 18 };
 // group partial / accumulator (uint64 words)
 // GP_CNT..: population of each Potts value
 enum { GP_N = 0, GP_MAX = 1, GP_SQ = 2, GP_E = 3, GP_M = 4, GP_HIST = 5, GP_CNT = 38, GP_END = 46 };
@@ -81,7 +82,7 @@ struct Dev {
     uint16_t *codes;      // [nbricks][4096] brick-local index of the site's component's smallest site
     uint16_t *faces;      // [nbricks][6][256] nodes of the sites of the +x, +y, +z faces (0xFFFF unless
                           // bonded through the face) and of the x = 0, y = 0, z = 0 faces
-    uint16_t *nroot;      // [nbricks][kBrickNodes] smallest brick-local site of every node
+    uint32_t *node;       // [nbricks][kBrickNodes] smallest brick-local site | size << 16 of every node
     uint32_t L, tw, ntx, ntiles, ngroups;
     uint32_t T, seed_lo, seed_hi;
     uint32_t ring_cap;

@@ -194,7 +194,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
     __shared__ uint32_t s_xe[EW];
     __shared__ uint32_t s_bf[NW];
     __shared__ uint8_t s_tab[256];
-    __shared__ uint32_t s_hist[12];
+    __shared__ uint32_t s_hist[kTileBins];
     __shared__ uint32_t s_dense[DENSE ? kDenseBins : 1];
     // root | size << 16 of each node; for 64-wide tiles it reuses the bond
     // masks, which are dead once the unions are done
@@ -286,7 +286,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
     for (uint32_t i = tid; i < (uint32_t)NW; i += NT) s_bf[i] = 0u;
     if (tid < EW) s_xe[tid] = 0u;
     if (tid < NPL * EW) s_eup[tid] = 0u;
-    if (tid < 12u) s_hist[tid] = 0u;
+    if (tid < kTileBins) s_hist[tid] = 0u;
     if constexpr (DENSE)
         for (uint32_t i = tid; i < kDenseBins; i += NT) s_dense[i] = 0u;
     if (tid == 0) s_xn = 0;
@@ -670,7 +670,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
             sq += s_red[w][3];
         }
         int32_t n = b0 + b1 + b2;
-        for (int b = 3; b < 12; ++b) n += (int32_t)s_hist[b];
+        for (uint32_t b = 3; b < kTileBins; ++b) n += (int32_t)s_hist[b];
         int32_t *tp = d.tpart + (size_t)tile * kTilePart;
         tp[TP_E] = e;
         tp[TP_M] = m;
@@ -680,7 +680,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
         tp[TP_HIST + 0] = b0;
         tp[TP_HIST + 1] = b1;
         tp[TP_HIST + 2] = b2;
-        for (int b = 3; b < 12; ++b) tp[TP_HIST + b] = (int32_t)s_hist[b];
+        for (uint32_t b = 3; b < kTileBins; ++b) tp[TP_HIST + b] = (int32_t)s_hist[b];
         if constexpr (POTTS) {
             for (int k = 0; k < 8; ++k) {
                 int32_t c = 0;
@@ -1121,7 +1121,7 @@ __device__ __forceinline__ void roots_body(const Dev &d, const uint32_t group) {
             n += (uint32_t)tp[TP_N];
             mx = max(mx, (uint64_t)(uint32_t)tp[TP_MAX]);
             sq += (uint32_t)tp[TP_SQ];
-            for (int b = 0; b < 12; ++b)
+            for (uint32_t b = 0; b < kTileBins; ++b)
                 if (tp[TP_HIST + b]) atomicAdd(&s_hist[b], (uint32_t)tp[TP_HIST + b]);
             if (d.q)
                 for (int k = 0; k < kMaxQ; ++k)
@@ -1483,7 +1483,7 @@ __device__ __forceinline__ void smerge_body(const Dev &d) {
         cn += (uint32_t)tp[TP_N];
         cmx = max(cmx, (uint64_t)(uint32_t)tp[TP_MAX]);
         csq += (uint32_t)tp[TP_SQ];
-        for (int b = 0; b < 12; ++b)
+        for (uint32_t b = 0; b < kTileBins; ++b)
             if (tp[TP_HIST + b]) atomicAdd(&s_acc[GP_HIST + b], (unsigned long long)(uint32_t)tp[TP_HIST + b]);
         if (d.q)
             for (int k = 0; k < kMaxQ; ++k)
