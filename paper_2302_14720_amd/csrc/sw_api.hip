@@ -218,6 +218,7 @@ struct sw_sim {
     uint64_t next_sweep;   // host mirror of *dev.tdev
     uint64_t first_valid;  // first sweep whose record exists
     int device;
+    swmi::StageUser stage_user;
 };
 
 namespace {
@@ -493,16 +494,13 @@ int sw_series(sw_sim *s, int64_t first, int64_t count, sw_obs *out) {
         return fail(SW_ERANGE, "records requested have left the ring");
     int rc = ensure_device(s);
     if (rc != SW_OK) return rc;
-    HIP_TRY(hipStreamSynchronize(s->stream));
     int64_t done = 0;
     while (done < count) {
         const uint64_t idx = (uint64_t)(first + done) % cap;
         const int64_t chunk = (int64_t)std::min<uint64_t>((uint64_t)(count - done), cap - idx);
-        HIP_TRY(hipMemcpyAsync(out + done, s->dev.ring + idx, (size_t)chunk * sizeof(sw_obs), hipMemcpyDeviceToHost,
-                               s->stream));
+        HIP_TRY(swmi::copy_to_host(out + done, s->dev.ring + idx, (size_t)chunk * sizeof(sw_obs), s->stream));
         done += chunk;
     }
-    HIP_TRY(hipStreamSynchronize(s->stream));
     return SW_OK;
 }
 
@@ -520,8 +518,7 @@ int sw_cluster_hist(sw_sim *s, uint64_t *counts, int64_t len) {
     if (s->next_sweep == s->first_valid) return fail(SW_ESTATE, "no sweep has run since the last reset / set_spins");
     int rc = ensure_device(s);
     if (rc != SW_OK) return rc;
-    HIP_TRY(hipMemcpyAsync(counts, s->dev.dense, (size_t)(n + 1) * 8, hipMemcpyDeviceToHost, s->stream));
-    HIP_TRY(hipStreamSynchronize(s->stream));
+    HIP_TRY(swmi::copy_to_host(counts, s->dev.dense, (size_t)(n + 1) * 8, s->stream));
     return SW_OK;
 }
 
@@ -530,8 +527,7 @@ int sw_get_spins(sw_sim *s, int8_t *host, int64_t n) {
     if (n != (int64_t)s->dev.nsite) return fail(SW_ERANGE, "n must equal the number of sites");
     int rc = ensure_device(s);
     if (rc != SW_OK) return rc;
-    HIP_TRY(hipMemcpyAsync(host, s->dev.spins[s->next_sweep & 1u], (size_t)n, hipMemcpyDeviceToHost, s->stream));
-    HIP_TRY(hipStreamSynchronize(s->stream));
+    HIP_TRY(swmi::copy_to_host(host, s->dev.spins[s->next_sweep & 1u], (size_t)n, s->stream));
     return SW_OK;
 }
 
@@ -558,8 +554,7 @@ int sw_get_labels(sw_sim *s, uint32_t *host, int64_t n) {
     int rc = ensure_device(s);
     if (rc != SW_OK) return rc;
     if (s->dev.brick) HIP_TRY(swmi::launch_brick_labels(s->dev, s->stream));
-    HIP_TRY(hipMemcpyAsync(host, s->dev.labels, (size_t)n * 4, hipMemcpyDeviceToHost, s->stream));
-    HIP_TRY(hipStreamSynchronize(s->stream));
+    HIP_TRY(swmi::copy_to_host(host, s->dev.labels, (size_t)n * 4, s->stream));
     return SW_OK;
 }
 
@@ -617,6 +612,7 @@ struct sw_batch {
     uint64_t next_sweep;
     uint64_t first_valid;
     int device;
+    swmi::StageUser stage_user;
 };
 
 namespace {
@@ -976,16 +972,13 @@ int sw_batch_series(sw_batch *b, int32_t r, int64_t first, int64_t count, sw_obs
     if ((uint64_t)(b->next_sweep - (uint64_t)first) > cap) return fail(SW_ERANGE, "records requested have left the ring");
     rc = batch_device(b);
     if (rc != SW_OK) return rc;
-    HIP_TRY(hipStreamSynchronize(b->stream));
     int64_t done = 0;
     while (done < count) {
         const uint64_t idx = (uint64_t)(first + done) % cap;
         const int64_t chunk = (int64_t)std::min<uint64_t>((uint64_t)(count - done), cap - idx);
-        HIP_TRY(hipMemcpyAsync(out + done, d.ring + idx, (size_t)chunk * sizeof(sw_obs), hipMemcpyDeviceToHost,
-                               b->stream));
+        HIP_TRY(swmi::copy_to_host(out + done, d.ring + idx, (size_t)chunk * sizeof(sw_obs), b->stream));
         done += chunk;
     }
-    HIP_TRY(hipStreamSynchronize(b->stream));
     return SW_OK;
 }
 
@@ -1012,8 +1005,7 @@ int sw_batch_get_spins(sw_batch *b, int32_t r, int8_t *host, int64_t n) {
     if (n != (int64_t)d.L * d.L) return fail(SW_ERANGE, "n must equal L*L of the replica");
     rc = batch_device(b);
     if (rc != SW_OK) return rc;
-    HIP_TRY(hipMemcpyAsync(host, d.spins[b->next_sweep & 1u], (size_t)n, hipMemcpyDeviceToHost, b->stream));
-    HIP_TRY(hipStreamSynchronize(b->stream));
+    HIP_TRY(swmi::copy_to_host(host, d.spins[b->next_sweep & 1u], (size_t)n, b->stream));
     return SW_OK;
 }
 

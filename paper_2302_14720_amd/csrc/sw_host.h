@@ -21,6 +21,17 @@ int hip_fail(hipError_t e, const char *what);
 // The thread's last-error message.
 const std::string &last_error();
 
+// Copies n device bytes to host memory after everything enqueued on s, and
+// waits (through pinned staging; without any to be had, a pageable copy).
+hipError_t copy_to_host(void *dst, const void *src, size_t n, hipStream_t s);
+// Held by every object that copies; the last one gives the staging back.
+struct StageUser {
+    StageUser();
+    ~StageUser();
+    StageUser(const StageUser &) = delete;
+    StageUser &operator=(const StageUser &) = delete;
+};
+
 // Bond probability p = 1 - exp(-2 beta J) as a 32-bit threshold.
 uint32_t bond_threshold(double beta, double J);
 

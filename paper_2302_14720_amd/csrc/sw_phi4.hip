@@ -492,6 +492,7 @@ struct sw_phi4 {
     uint64_t next_sweep;
     uint64_t first_valid;
     int device;
+    swmi::StageUser stage_user;
 };
 
 namespace {
@@ -711,13 +712,12 @@ int sw_phi4_series(sw_phi4 *p, int64_t first, int64_t count, sw_phi4_obs *out) {
     if (count == 0) return SW_OK;
     int rc = phi_ensure_device(p);
     if (rc != SW_OK) return rc;
-    HIP_TRY(hipStreamSynchronize(p->stream));
     const int64_t cap = p->dev.ring_cap;
     int64_t done = 0;
     while (done < count) {
         const int64_t slot = (first + done) % cap;
         const int64_t run = std::min(count - done, cap - slot);
-        HIP_TRY(hipMemcpy(out + done, p->dev.ring + slot, (size_t)run * sizeof(sw_phi4_obs), hipMemcpyDeviceToHost));
+        HIP_TRY(swmi::copy_to_host(out + done, p->dev.ring + slot, (size_t)run * sizeof(sw_phi4_obs), p->stream));
         done += run;
     }
     return SW_OK;
@@ -728,8 +728,7 @@ int sw_phi4_get_field(sw_phi4 *p, double *host, int64_t n) {
     if (n != 4 * (int64_t)p->dev.N) return fail(SW_ERANGE, "n must equal 4 L^4");
     int rc = phi_ensure_device(p);
     if (rc != SW_OK) return rc;
-    HIP_TRY(hipStreamSynchronize(p->stream));
-    HIP_TRY(hipMemcpy(host, p->dev.phi, (size_t)n * sizeof(double), hipMemcpyDeviceToHost));
+    HIP_TRY(swmi::copy_to_host(host, p->dev.phi, (size_t)n * sizeof(double), p->stream));
     return SW_OK;
 }
 
@@ -751,8 +750,7 @@ int sw_phi4_get_labels(sw_phi4 *p, uint32_t *host, int64_t n) {
     if (p->next_sweep == p->first_valid) return fail(SW_ESTATE, "no sweep has run since create / reset / set_field");
     int rc = phi_ensure_device(p);
     if (rc != SW_OK) return rc;
-    HIP_TRY(hipStreamSynchronize(p->stream));
-    HIP_TRY(hipMemcpy(host, p->dev.parent, (size_t)n * sizeof(uint32_t), hipMemcpyDeviceToHost));
+    HIP_TRY(swmi::copy_to_host(host, p->dev.parent, (size_t)n * sizeof(uint32_t), p->stream));
     return SW_OK;
 }
 

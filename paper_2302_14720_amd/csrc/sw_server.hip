@@ -110,6 +110,7 @@ struct sw_server {
     bool dirty = true;
     swmi::BatchDev bd[kGroups]{};  // active jobs by launch group (see group_of)
     uint64_t site_updates = 0;
+    swmi::StageUser stage_user;
 };
 
 namespace {
@@ -388,8 +389,7 @@ int sw_server_job_series(sw_server *s, int64_t id, int64_t first, int64_t count,
     if (count == 0) return SW_OK;
     rc = srv_device(s);
     if (rc != SW_OK) return rc;
-    HIP_TRY(hipStreamSynchronize(s->stream));
-    HIP_TRY(hipMemcpy(out, j->dev.ring + first, (size_t)count * sizeof(sw_obs), hipMemcpyDeviceToHost));
+    HIP_TRY(swmi::copy_to_host(out, j->dev.ring + first, (size_t)count * sizeof(sw_obs), s->stream));
     return SW_OK;
 }
 
@@ -402,8 +402,7 @@ int sw_server_job_spins(sw_server *s, int64_t id, int8_t *host, int64_t n) {
     if (n != (int64_t)j->cfg.L * j->cfg.L) return fail(SW_ERANGE, "n must equal L*L of the job");
     rc = srv_device(s);
     if (rc != SW_OK) return rc;
-    HIP_TRY(hipStreamSynchronize(s->stream));
-    HIP_TRY(hipMemcpy(host, j->dev.spins[j->done & 1], (size_t)n, hipMemcpyDeviceToHost));
+    HIP_TRY(swmi::copy_to_host(host, j->dev.spins[j->done & 1], (size_t)n, s->stream));
     return SW_OK;
 }
 
