@@ -146,7 +146,9 @@ int sw_sweep(sw_sim *sim, int64_t n);
  * 1: cross-tile unions, 2: flattening and cluster sizes, 3: spins of
  * cross-tile clusters (Sec. 2.4) and statistics, 4: the record (Sec. 2.5;
  * on lattices of at most 64 groups of 16 tiles stage 3 writes the record
- * and stage 4 launches nothing, so ms[4] is the events' own cost) -- and
+ * and stage 4 launches nothing, so ms[4] is the events' own cost; on those of
+ * at most 16 groups of 4 x 4 tiles, unless labels or the histogram are kept,
+ * stage 1 does the work of all four) -- and
  * ms[5] the closing pass that writes final spins and measures them.
  * nk (the length of ms) must be >= 6; extra entries are zeroed. */
 int sw_profile(sw_sim *sim, int64_t n, double *ms, int32_t nk);
@@ -262,9 +264,10 @@ const char *sw_last_error(void);
  * costs a handful of kernel launches (replayed from one captured graph)
  * instead of five or six per replica.  The cross-tile merge of Sec. 2.3 runs
  * either globally (four launches over all such replicas, the record folded
- * into the last) or, for a replica of at
- * most 16 tiles, entirely in one workgroup's LDS (one launch for all such
- * replicas: SW_MERGE_LDS).  Replica r has its own L[r], beta[r], J[r],
+ * into the last) or, for a replica of at most 16 groups of 4 x 4 tiles, by
+ * one workgroup per group in LDS (one launch for all such replicas); a
+ * replica of at most 16 tiles is one group (SW_MERGE_LDS) unless its caller
+ * asks for the global merge.  Replica r has its own L[r], beta[r], J[r],
  * seed[r] and its own records; its spins, clusters and records are bit for
  * bit those of a plain sim created with the same parameters and swept the
  * same number of times, whatever its tile width and merge.  All replicas

@@ -92,6 +92,20 @@ int validate(const sw_config *c) {
     return SW_OK;
 }
 
+// Lattices whose whole merge is one launch (k_merge): at most 16 groups of 4 x
+// 4 tiles (L <= 1024 with 64-wide tiles, 512 with 32-wide ones), where that
+// beats the four launches of the global merge -- the last workgroup's share
+// grows with the lattice while the launches cost the same.  Sweeps at beta_c,
+// one launch / four: 128^2 36 / 51, 512^2 52 / 71, 1024^2 64 / 75, 1280^2 76 /
+// 78, 1536^2 91 / 82 us; 32-wide tiles: 512^2 55 / 64, 1056^2 93 / 72 us.
+// Labels and the exact histogram need the node tables that the global merge
+// leaves.
+bool merge_in_one(const sw_config &c) {
+    if (c.dims == 3 || (c.flags & (SW_FLAG_LABEL_EQUIV | SW_FLAG_LABELS | SW_FLAG_DENSE_HIST)) != 0u) return false;
+    const uint32_t tw = (uint32_t)resolve_tile(c), ntx = (uint32_t)c.L / tw, ngx = (ntx + kUG - 1u) / kUG;
+    return ngx * ngx <= kMergeGroups;
+}
+
 Layout layout_of(const sw_config &c) {
     const size_t L = (size_t)c.L, N = sites_of(c);
     // the label-equivalence path keeps labels in global memory and no tile
@@ -123,6 +137,13 @@ Layout layout_of(const sw_config &c) {
     o.rspin = brick ? 0 : take(nodes);
     o.edge = brick ? 0 : take(ntiles * 4 * tw);
     o.xb = brick ? 0 : take(ntiles * 16);
+    const size_t mg = merge_in_one(c) ? ((L / tw + kUG - 1) / kUG) * ((L / tw + kUG - 1) / kUG) : 0;
+    o.nref = take(mg ? nodes * 2 : 0);
+    o.gnode = take(mg * kRefSlots * 8);
+    o.gedge = take(mg * kRefSlots * 2);
+    o.gspin = take(mg * kRefSlots);
+    o.gcount = take(mg * 4);
+    o.mpart = take(mg * swmi::kGroupPart * 8);
     o.tpart = take(ntiles * swmi::kTilePart * 4);
     o.gpart = take(ngroups * swmi::kGroupPart * 8);
     o.acc = take(swmi::kAccWords * 8);
@@ -171,6 +192,15 @@ Dev make_dev(const sw_config &c, char *base, const Layout &lo) {
     d.rspin = (int8_t *)(base + lo.rspin);
     d.edge = (uint8_t *)(base + lo.edge);
     d.xb = (uint64_t *)(base + lo.xb);
+    if (merge_in_one(c)) {
+        d.two = 1u;
+        d.nref = (uint16_t *)(base + lo.nref);
+        d.gnode = (uint64_t *)(base + lo.gnode);
+        d.gedge = (uint16_t *)(base + lo.gedge);
+        d.gspin = (uint8_t *)(base + lo.gspin);
+        d.gcount = (uint32_t *)(base + lo.gcount);
+        d.mpart = (uint64_t *)(base + lo.mpart);
+    }
     d.tpart = (int32_t *)(base + lo.tpart);
     d.gpart = (uint64_t *)(base + lo.gpart);
     d.acc = (uint64_t *)(base + lo.acc);
@@ -598,9 +628,9 @@ struct sw_batch {
     swmi::BatchDev bd[kBatchGroups];
     hipStream_t stream;
     bool own_stream;
-    // the LDS merges run on a second stream (default priority) beside the
-    // global merge, forked after the tile kernels and joined before the
-    // next sweep
+    // k_merge runs on a second stream (default priority) beside the global
+    // merge of other replicas, forked after the tile kernels and joined
+    // before the next sweep
     hipStream_t side;
     hipEvent_t fork, join;
     void *ws;
@@ -620,6 +650,14 @@ namespace {
 constexpr int64_t kDefaultBatchRing = 1024;
 
 int batch_group(const Dev &d) { return (d.q ? 2 : 0) + (d.tw == 64 ? 0 : 1); }
+
+// A replica's device view.  k_merge takes every replica it can; one of at most
+// 16 tiles whose caller asked for the global merge gets that.
+Dev replica_dev(const sw_config &c, char *base, const Layout &lo, bool lds) {
+    Dev d = make_dev(c, base, lo);
+    if (!lds && d.ntiles <= swmi::kSmallTiles) d.two = 0u;
+    return d;
+}
 
 struct BatchPlan {
     std::vector<sw_config> cfg;
@@ -671,8 +709,8 @@ int plan_batch(int32_t n, const int32_t *L, const double *beta, const double *J,
         const Layout lo = layout_of(c);
         p->base[(size_t)r] = off;
         off = align_up(off + lo.total);
-        const Dev d = make_dev(c, nullptr, lo);
-        m[batch_group(d)].add((uint32_t)r, d, p->lds[(size_t)r] != 0);
+        m[batch_group(make_dev(c, nullptr, lo))].add((uint32_t)r, replica_dev(c, nullptr, lo, p->lds[(size_t)r] != 0),
+                                                    m[0]);
     }
     p->map_words = 0;
     for (const swmi::BatchMaps &g : m) p->map_words += g.words();
@@ -710,12 +748,12 @@ hipError_t batch_launch_sweep(const sw_batch *b) {
     }
     hipError_t e = hipSuccess;
     for (int g = 0; g < kBatchGroups && e == hipSuccess; ++g) e = swmi::launch_batch_stage(b->bd[g], 0, b->stream);
-    // the LDS merges beside the global merge when both kinds are present
+    // k_merge beside the global merge when both kinds are present
     const bool fork = small && large && b->side != nullptr;
     hipStream_t ss = fork ? b->side : b->stream;
     if (e == hipSuccess && fork) e = hipEventRecord(b->fork, b->stream);
     if (e == hipSuccess && fork) e = hipStreamWaitEvent(b->side, b->fork, 0);
-    for (int g = 0; g < kBatchGroups && e == hipSuccess; ++g) e = swmi::launch_batch_smerge(b->bd[g], ss);
+    for (int g = 0; g < kBatchGroups && e == hipSuccess; ++g) e = swmi::launch_batch_merge(b->bd[g], ss);
     for (int stage = 1; stage < swmi::kStages && e == hipSuccess; ++stage)
         for (int g = 0; g < kBatchGroups && e == hipSuccess; ++g) e = swmi::launch_batch_stage(b->bd[g], stage, b->stream);
     if (e == hipSuccess && fork) e = hipEventRecord(b->join, b->side);
@@ -831,8 +869,8 @@ int batch_create(int32_t n, const int32_t *L, const double *beta, const double *
     b->dev.resize(p.cfg.size());
     swmi::BatchMaps m[kBatchGroups];
     for (size_t r = 0; r < p.cfg.size(); ++r) {
-        b->dev[r] = make_dev(p.cfg[r], base + p.base[r], layout_of(p.cfg[r]));
-        m[batch_group(b->dev[r])].add((uint32_t)r, b->dev[r], p.lds[r] != 0);
+        b->dev[r] = replica_dev(p.cfg[r], base + p.base[r], layout_of(p.cfg[r]), p.lds[r] != 0);
+        m[batch_group(b->dev[r])].add((uint32_t)r, b->dev[r], m[0]);
     }
     std::vector<uint32_t> host;
     host.reserve(p.map_words);

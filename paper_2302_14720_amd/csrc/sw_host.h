@@ -36,7 +36,7 @@ struct StageUser {
 uint32_t bond_threshold(double beta, double J);
 
 struct Layout {
-    size_t spins[2], parent[2], nk[2], key, nsize, rspin, edge, xb, tpart, gpart, acc, tdev, ring, labels,
+    size_t spins[2], parent[2], nk[2], key, nsize, rspin, edge, xb, nref, gnode, gedge, gspin, gcount, mpart, tpart, gpart, acc, tdev, ring, labels,
         dense, tdense, le_mask, le_cnt, le_rsp, le_ctl, codes, faces, node, total;
 };
 
@@ -47,17 +47,19 @@ Dev make_dev(const sw_config &c, char *base, const Layout &lo);
 
 // Host-side work maps of one launch group of a batch (one tile width, Ising
 // or Potts): add() files the replica in slot `slot` of the Dev table under
-// the global merge, or under the LDS merge (k_smerge_b) when `small` is set
-// and it has at most kSmallTiles tiles; emit() appends the maps to `host`
-// (which will be copied to dev_base) and points the BatchDev at them.
+// k_merge (d.two; its units go to `merge`, the maps of the first launch group,
+// since k_merge takes replicas of every kind in one launch) or under the
+// global merge; emit() appends the maps to `host` (which will be copied to
+// dev_base) and points the BatchDev at them.
 struct BatchMaps {
     std::vector<uint32_t> t, w, wn, g, u, r, s, a;  // w / wn: tiles with an E / N group edge
-    void add(uint32_t slot, const Dev &d, bool small) {
+    void add(uint32_t slot, const Dev &d, BatchMaps &merge) {
         const uint32_t tag = slot << kMapShift;
         a.push_back(slot);
         for (uint32_t i = 0; i < d.ntiles; ++i) t.push_back(tag | i);
-        if (small && d.ntiles <= kSmallTiles) {
-            s.push_back(slot);
+        const uint32_t ngx = (d.ntx + kUG - 1u) / kUG;
+        if (d.two) {
+            for (uint32_t i = 0; i < ngx * ngx; ++i) merge.s.push_back(tag | i);
             return;
         }
         r.push_back(slot);
@@ -69,7 +71,6 @@ struct BatchMaps {
             if (ty % kUG == kUG - 1u || ty + 1u == d.ntx) wn.push_back(tag | i);
         }
         for (uint32_t i = 0; i < d.ngroups; ++i) g.push_back(tag | i);
-        const uint32_t ngx = (d.ntx + kUG - 1u) / kUG;
         for (uint32_t i = 0; i < ngx * ngx; ++i) u.push_back(tag | i);
     }
     size_t words() const {

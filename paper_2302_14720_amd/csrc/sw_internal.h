@@ -44,7 +44,10 @@ constexpr int kMaxQ = 8;              // largest q of the Potts model
 constexpr int kAccWords = 64;         // record accumulator + completion counter
 constexpr int kGroupTiles = 16;       // tiles per workgroup in k_flatten / k_roots
 constexpr uint32_t kDenseBins = 256;  // sizes below this are counted per tile and group (dense histogram)
-constexpr uint32_t kUG = 4;           // side, in tiles, of a k_ulocal group
+constexpr uint32_t kUG = 4;           // side, in tiles, of a k_ulocal or k_merge group
+constexpr uint32_t kRef = 8;          // nref: below, a final value
+constexpr uint32_t kRefSlots = 1024;  // clusters of a k_merge group that go on outside it (its perimeter)
+constexpr uint32_t kMergeGroups = 16; // most groups of a lattice merged by k_merge
 
 // tile partial (int32 words)
 // hist: kTileBins bins (sizes up to 64 * 64 or 16^3); TP_CNT..: population of each Potts value
@@ -68,6 +71,13 @@ struct Dev {
     uint64_t *gpart;      // [ngroups][kGroupPart]
     uint64_t *acc;        // [kAccWords]
     uint64_t *tdev;       // [0] = index of the next sweep
+    // lattices merged by k_merge (two = 1)
+    uint16_t *nref;       // [ntiles * kNodeSlots] value of the node's cluster, or kRef + its number in the group
+    uint64_t *gnode;      // [groups][kRefSlots] key | size << 32 of the clusters that go on outside the group
+    uint16_t *gedge;      // [groups][4][256] their numbers at the bonds on the group's E, N, W, S sides (0xFFFF: none)
+    uint8_t *gspin;       // [groups][kRefSlots] their new values
+    uint32_t *gcount;     // [groups] how many
+    uint64_t *mpart;      // [groups][kGroupPart] partial statistics
     sw_obs *ring;         // [ring_cap]
     uint32_t *labels;     // [N] or nullptr
     uint64_t *dense;      // [N + 1] or nullptr
@@ -89,6 +99,7 @@ struct Dev {
     uint32_t le_grid;     // workgroups of the cooperative labelling kernel (0: tile path)
     uint32_t q;           // 0: Ising; 2..kMaxQ: q-state Potts (label-equivalence path)
     uint32_t dims;        // 2: L x L; 3: L x L x L (labels in global memory)
+    uint32_t two;         // 1: merged by k_merge (one launch)
     uint32_t brick;       // 1: simple cubic lattice on kBrick^3 bricks (else label equivalence)
     uint64_t nsite;       // N = L^dims
     double J;
@@ -113,8 +124,7 @@ constexpr uint32_t kMapNone = 0xFFFFFFFFu;
 constexpr int32_t kMaxReplicas = 4095;
 static_assert(((uint32_t)(kMaxReplicas - 1) << kMapShift | kMapMask) != kMapNone, "map entry collides with kMapNone");
 
-// Replicas of at most kSmallTiles tiles may run their whole merge in one
-// workgroup, in LDS (k_smerge_b); the others run the global merge.
+// The LDS merge a caller can ask for in a batch takes at most kSmallTiles tiles.
 constexpr uint32_t kSmallTiles = 16;
 
 struct BatchDev {
@@ -124,7 +134,7 @@ struct BatchDev {
     const uint32_t *gmap;  // [ngroups] one per group of kGroupTiles tiles (k_flatten, k_roots)
     const uint32_t *umap;  // [nugroups] one per kUG x kUG group of tiles (k_ulocal)
     const uint32_t *rmap;  // [n] the replicas (indices into devs) of the global merge
-    const uint32_t *smap;  // [nsmall] the replicas merged in LDS
+    const uint32_t *smap;  // [nsmall] one per kUG x kUG group of tiles of the replicas merged by k_merge
     const uint32_t *amap;  // [nall] every replica of the launch (records after k_resolve)
     uint32_t n, ntiles, nwmap, ngroups, nugroups, tw;
     uint32_t nwE, nsmall, nall;
@@ -148,12 +158,13 @@ hipError_t launch_brick_measure(const Dev &d, hipStream_t s);
 hipError_t launch_brick_labels(const Dev &d, hipStream_t s);
 
 // Stage 0 is the tile kernel of every replica; stages 1..4 the global merge;
-// launch_batch_smerge the LDS merge of the small replicas, which may run
-// beside stages 1..4 once stage 0 is done.  launch_batch_sweep runs them
-// all in order on one stream.
+// launch_batch_merge the replicas merged by k_merge (whatever their launch
+// group, they are all in the maps of the first), which may run beside stages
+// 1..4 once stage 0 is done.  launch_batch_sweep runs them all in order on one
+// stream.
 hipError_t launch_batch_stage(const BatchDev &b, int stage, hipStream_t s);
-hipError_t launch_batch_smerge(const BatchDev &b, hipStream_t s);
-hipError_t launch_batch_sweep(const BatchDev &b, hipStream_t s);
+hipError_t launch_batch_merge(const BatchDev &b, hipStream_t s);
+hipError_t launch_batch_sweep(const BatchDev *b, int ngroups, hipStream_t s);
 hipError_t launch_batch_resolve(const BatchDev &b, hipStream_t s);
 
 }  // namespace swmi

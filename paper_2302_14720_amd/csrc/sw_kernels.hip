@@ -46,13 +46,30 @@ __device__ __forceinline__ typename RowOf<TW>::T row_gather(uint32_t piece) {
     }
 }
 
-// Spin (+1/-1) encoded by a byte of the previous sweep's output that belongs
-// to tile `tile`: final spins are 0x01 / 0xFF, a code 2 + k refers to node k
-// of that tile, whose cluster's new spin k_roots stored at the node.
-__device__ __forceinline__ int8_t resolve_byte(uint32_t b, uint32_t tile, const int8_t *nspin) {
-    const uint32_t k = b - 2u;
-    if (k < 252u) return nspin[tile * kNodeSlots + k];
-    return (int8_t)b;
+// New value of a node's cluster in the previous sweep: the Potts value, or 1
+// for spin +1 and 0 for -1 (Ising).  Lattices merged by k_merge keep a
+// reference per node: the value itself, or kRef + j for cluster j of the
+// tile's group, whose table starts at gb (kRefSlots per group); the others
+// keep the spin.  Both steps are loads without a compare behind them, so that
+// the loads of several nodes overlap (a compare between them makes the tile
+// kernel wait for each: 0.93 -> 0.97 ms at 16384^2).
+// TWO: 1 merged by k_merge, 0 not, 2 as d.two says (batches of both): the
+// test alone cost the tile kernel 2 % at 1600^2.
+template <int TWO> __device__ __forceinline__ bool has_refs(const Dev &d) { return TWO == 1 || (TWO == 2 && d.two); }
+template <int TWO> __device__ __forceinline__ uint32_t node_ref(const Dev &d, uint32_t node) {
+    return has_refs<TWO>(d) ? d.nref[node] : (uint32_t)(int32_t)d.rspin[node];
+}
+template <int TWO> __device__ __forceinline__ uint32_t follow_ref(const Dev &d, uint32_t ref, uint32_t gb) {
+    if (has_refs<TWO>(d) && ref >= kRef) return d.gspin[gb + ref - kRef];
+    return ref;
+}
+template <bool POTTS, int TWO> __device__ __forceinline__ uint32_t value_of(const Dev &d, uint32_t v) {
+    if (POTTS || has_refs<TWO>(d)) return v;
+    return (uint32_t)((int32_t)v > 0);
+}
+// Start of the cluster table of the group that holds tile (tx, ty).
+__device__ __forceinline__ uint32_t ref_base(const Dev &d, uint32_t tx, uint32_t ty) {
+    return ((ty / kUG) * ((d.ntx + kUG - 1u) / kUG) + tx / kUG) * kRefSlots;
 }
 
 __device__ __forceinline__ uint32_t byte_at(const uint4 &v, int q) {
@@ -73,8 +90,8 @@ template <int TW> constexpr uint32_t potts_code() { return TW == 64 ? 4u : 8u; }
 
 // The node spins are loaded whether or not the node exists (every slot is
 // in bounds), so that this load does not wait for the node count.
-template <int TW, bool POTTS>
-__device__ __forceinline__ void load_table(const Dev &d, uint32_t tile, uint32_t pp, uint8_t *s_tab,
+template <int TW, bool POTTS, int TWO>
+__device__ __forceinline__ void load_table(const Dev &d, uint32_t tile, uint32_t gb, uint32_t pp, uint8_t *s_tab,
                                            uint32_t tid) {
     constexpr int NT = TW * TW / 16;
     const uint32_t kprev = min(d.nk[pp][tile], 252u);
@@ -88,8 +105,9 @@ __device__ __forceinline__ void load_table(const Dev &d, uint32_t tile, uint32_t
             val = b == 0xFFu ? 0u : 1u;
             k = b - 2u;
         }
-        const int8_t ns = k < 252u ? d.rspin[tile * kNodeSlots + k] : (int8_t)0;
-        if (k < kprev) val = POTTS ? (uint8_t)((uint32_t)ns & 7u) : (ns > 0 ? 1u : 0u);
+        const uint32_t ref = k < 252u ? node_ref<TWO>(d, tile * kNodeSlots + k) : 0u;
+        const uint32_t ns = value_of<POTTS, TWO>(d, follow_ref<TWO>(d, k < kprev ? ref : 0u, gb));
+        if (k < kprev) val = (uint8_t)ns;
         s_tab[b] = val;
     }
 }
@@ -102,19 +120,35 @@ __device__ __forceinline__ uint32_t decode16(const uint4 &v, const uint8_t *s_ta
     return up;
 }
 
-__device__ __forceinline__ uint32_t decode16_remote(const uint4 &v, uint32_t tile, const int8_t *nspin) {
-    uint32_t up = 0;
+// Values (Ising: up bits) of N bytes of tile `tile`'s previous output, which
+// is not this workgroup's: final bytes as they are, a code refers to a node.
+template <int TW, bool POTTS, int TWO, int N>
+__device__ __forceinline__ void remote_values(const Dev &d, const uint32_t *b, uint32_t tile, uint32_t gb, uint32_t *val) {
+    constexpr uint32_t CB = POTTS ? potts_code<TW>() : 2u;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) up |= (uint32_t)(resolve_byte(byte_at(v, q), tile, nspin) > 0) << q;
-    return up;
+    for (int q = 0; q < N; ++q) {
+        const uint32_t k = b[q] - CB;
+        val[q] = POTTS ? b[q] : has_refs<TWO>(d) ? (uint32_t)(b[q] == 1u) : (uint32_t)(int32_t)(int8_t)b[q];
+        if (k < 252u) val[q] = node_ref<TWO>(d, tile * kNodeSlots + k);
+    }
+    if (has_refs<TWO>(d)) {
+#pragma unroll
+        for (int q = 0; q < N; ++q)
+            if (b[q] - CB < 252u) val[q] = follow_ref<TWO>(d, val[q], gb);
+    }
+#pragma unroll
+    for (int q = 0; q < N; ++q) val[q] = value_of<POTTS, TWO>(d, val[q]);
 }
 
-// Potts value (0..7) of a byte of tile `tile`'s previous output.
-template <int TW>
-__device__ __forceinline__ uint32_t potts_byte(uint32_t b, uint32_t tile, const int8_t *nspin) {
-    const uint32_t k = b - potts_code<TW>();
-    if (k < 252u) return (uint32_t)nspin[tile * kNodeSlots + k] & 7u;
-    return b & 7u;
+template <int TWO>
+__device__ __forceinline__ uint32_t decode16_remote(const Dev &d, const uint4 &v, uint32_t tile, uint32_t gb) {
+    uint32_t b[16], x[16], up = 0;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) b[q] = byte_at(v, q);
+    remote_values<64, false, TWO, 16>(d, b, tile, gb, x);
+#pragma unroll
+    for (int q = 0; q < 16; ++q) up |= x[q] << q;
+    return up;
 }
 
 // Values of 16 sites as three bit planes (bit q of pl[i] = bit i of site q).
@@ -129,16 +163,19 @@ __device__ __forceinline__ void decode16_potts(const uint4 &v, const uint8_t *s_
     }
 }
 
-template <int TW>
-__device__ __forceinline__ void decode16_potts_remote(const uint4 &v, uint32_t tile, const int8_t *nspin,
+template <int TW, int TWO>
+__device__ __forceinline__ void decode16_potts_remote(const Dev &d, const uint4 &v, uint32_t tile, uint32_t gb,
                                                       uint32_t pl[3]) {
+    uint32_t b[16], x[16];
+#pragma unroll
+    for (int q = 0; q < 16; ++q) b[q] = byte_at(v, q);
+    remote_values<TW, true, TWO, 16>(d, b, tile, gb, x);
     pl[0] = pl[1] = pl[2] = 0u;
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
-        const uint32_t x = potts_byte<TW>(byte_at(v, q), tile, nspin);
-        pl[0] |= (x & 1u) << q;
-        pl[1] |= ((x >> 1) & 1u) << q;
-        pl[2] |= (x >> 2) << q;
+        pl[0] |= (x[q] & 1u) << q;
+        pl[1] |= ((x[q] >> 1) & 1u) << q;
+        pl[2] |= ((x[q] >> 2) & 1u) << q;
     }
 }
 
@@ -161,7 +198,7 @@ __device__ __forceinline__ void decode16_potts_remote(const uint4 &v, uint32_t t
 // DENSE: interior clusters also go to the exact size histogram -- those
 // below kDenseBins sites through LDS counts that leave with the tile
 // (tdense) and are added up per group in k_roots.
-template <int TW, bool POTTS = false, bool DENSE = false>
+template <int TW, bool POTTS, bool DENSE, int TWO>
 __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
     using Row = typename RowOf<TW>::T;
     constexpr int NT = TW * TW / 16;
@@ -216,6 +253,8 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
     const uint32_t gy = ty * TW + ly, gx0 = tx * TW + x0;
     const uint32_t east = ty * ntx + (tx + 1u == ntx ? 0u : tx + 1u);
     const uint32_t north = (ty + 1u == ntx ? 0u : ty + 1u) * ntx + tx;
+    const uint32_t gbe = ref_base(d, tx + 1u == ntx ? 0u : tx + 1u, ty);
+    const uint32_t gbn = ref_base(d, tx, ty + 1u == ntx ? 0u : ty + 1u);
     const uint32_t rowbase = ly * PS;  // padded index of the row's first site
     const uint32_t rowoff = 4u * rowbase;  // its byte offset
     const uint32_t srow = ly * TW;     // site index of the row's first site
@@ -253,7 +292,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
             rN |= ((uint32_t)(w1 < T) << (2 * j)) | ((uint32_t)(w3 < T) << (2 * j + 1));
         }
     }
-    load_table<TW, POTTS>(d, tile, pp, s_tab, tid);
+    load_table<TW, POTTS, TWO>(d, tile, ref_base(d, tx, ty), pp, s_tab, tid);
 
     // Potts: the value each of this lane's 16 sites would give its cluster
     // as its root (4 bits per site): word i of the output for counter
@@ -305,13 +344,14 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
         for (int b = 0; b < 3; ++b) reinterpret_cast<uint16_t *>(s_up + b * (TW + 1))[ly * RPT + seg] = (uint16_t)pl[b];
         if (ly == TW - 1) {
             uint32_t pn[3];
-            decode16_potts_remote<TW>(vn, north, d.rspin, pn);
+            decode16_potts_remote<TW, TWO>(d, vn, north, gbn, pn);
 #pragma unroll
             for (int b = 0; b < 3; ++b)
                 reinterpret_cast<uint16_t *>(s_up + b * (TW + 1))[TW * RPT + seg] = (uint16_t)pn[b];
         }
         if (seg == RPT - 1) {
-            const uint32_t ev = potts_byte<TW>(ve, east, d.rspin);
+            uint32_t ev;
+            remote_values<TW, true, TWO, 1>(d, &ve, east, gbe, &ev);
 #pragma unroll
             for (uint32_t b = 0; b < 3u; ++b)
                 if ((ev >> b) & 1u) atomicOr(&s_eup[b * EW + (ly >> 5)], 1u << (ly & 31u));
@@ -322,10 +362,11 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
         const uint32_t upA = (uint32_t)__shfl_down((int)up, (int)RPT, 64);
         const uint32_t upR = (uint32_t)__shfl_down((int)up, 1, 64);
         if (wlast)
-            upN = ly == TW - 1 ? decode16_remote(vn, north, d.rspin) : decode16<TW>(vn, s_tab);
+            upN = ly == TW - 1 ? decode16_remote<TWO>(d, vn, north, gbn) : decode16<TW>(vn, s_tab);
         else
             upN = upA;
-        ebit = seg == RPT - 1 ? (uint32_t)(resolve_byte(ve, east, d.rspin) > 0) : (upR & 1u);
+        ebit = upR & 1u;
+        if (seg == RPT - 1) remote_values<TW, false, TWO, 1>(d, &ve, east, gbe, &ebit);
     }
 
     // ---- bonds (Sec. 2.1) and energy / magnetisation of the incoming spins
@@ -700,18 +741,18 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
 // LDS allows (8 wavefronts per SIMD) all fit.
 constexpr int kTileWavesPerEU = 8;
 
-template <int TW, bool POTTS = false, bool DENSE = false>
+template <int TW, bool POTTS, bool DENSE, int TWO>
 __global__ __launch_bounds__(TW *TW / 16, TW == 64 && !DENSE ? kTileWavesPerEU : 1) void k_tile(Dev d) {
-    tile_body<TW, POTTS, DENSE>(d, tile_of_block(blockIdx.x, d.ntiles));
+    tile_body<TW, POTTS, DENSE, TWO>(d, tile_of_block(blockIdx.x, d.ntiles));
 }
 
 // Batched launches run the same bodies over a table of replicas (map
 // entries replica << kMapShift | unit index), so every replica's bits are
 // those of its own plain sweep.
-template <int TW, bool POTTS = false>
+template <int TW, bool POTTS, int TWO>
 __global__ __launch_bounds__(TW *TW / 16, TW == 64 ? kTileWavesPerEU : 1) void k_tile_b(const Dev *devs, const uint32_t *map) {
     const uint32_t e = map[tile_of_block(blockIdx.x, gridDim.x)];
-    tile_body<TW, POTTS>(devs[e >> kMapShift], e & kMapMask);
+    tile_body<TW, POTTS, false, TWO>(devs[e >> kMapShift], e & kMapMask);
 }
 
 // =====================================================================
@@ -1380,143 +1421,462 @@ __global__ __launch_bounds__(256) void k_roots_b(const Dev *devs, const uint32_t
 }
 
 // =====================================================================
-// k_smerge_b: the whole cross-tile part of a sweep of one small replica
-// (at most kSmallTiles tiles) in one workgroup, in LDS: unions across every
-// tile edge (Sec. 2.3), every node to its root with the cluster's size and
-// smallest site, the new spin of every node's cluster (Sec. 2.4), the
-// cluster statistics and the record (Sec. 2.5) -- the work of k_ulocal,
-// k_union, k_flatten, k_roots and k_record for that replica, same results.
-// Nodes are numbered locally in global-index order (tile by tile), so the
-// root of a set is its node with the smallest global index, as in the
-// global merge.
+// k_merge: the whole cross-tile part of a sweep (Sec. 2.3-2.5) of a lattice
+// of few tiles in one launch: the work of k_ulocal, k_union, k_flatten,
+// k_roots and k_record, same results.  On such lattices each of those is a few
+// chains of dependent loads on an idle GPU (42 of 63 us a sweep at 512^2), so
+// one workgroup of 1024 threads per kUG x kUG group of tiles takes them
+// together, in LDS:
+//   level 1  unions across the tile edges inside the group; sizes and smallest
+//            sites at the roots; a cluster with no bond out of the group is
+//            complete and draws its spin
+//   level 2  the other clusters, numbered per group (kRefSlots slots; each
+//            holds a bond on the group's perimeter, of at most 1024 sites): the
+//            last workgroup of the lattice to count itself in unites them
+//            across the group edges, draws their spins and writes the record
+// A lattice of one group (at most 16 tiles) has its periodic wrap inside
+// level 1 and no level 2.  Nodes keep a reference (nref) that the next
+// k_tile or k_resolve follows, so no workgroup has to visit them again.
+// What goes from the groups to the last workgroup is written and read with
+// agent-scope accesses, completed before the count (no cache fences).
 // =====================================================================
-constexpr uint32_t kSmallNodes = kSmallTiles * 252u;
+constexpr uint32_t kMergeThreads = 1024;
+constexpr uint32_t kMergeWaves = kMergeThreads / 64;
+constexpr uint32_t kNoRef = 0xFFFFu;
+static_assert(kUG * kUG == kMergeWaves, "one wavefront per tile of a group");
 
-__device__ __forceinline__ void smerge_body(const Dev &d) {
-    __shared__ uint32_t s_par[kSmallNodes];
-    __shared__ uint32_t s_key[kSmallNodes];
-    __shared__ uint32_t s_sz[kSmallNodes];
-    __shared__ uint32_t s_off[kSmallTiles + 1];
+__device__ __forceinline__ uint32_t new_value(const Dev &d, uint32_t key, uint32_t t) {
+    return d.q ? (uint32_t)potts_spin(key, t, d.q, d.seed_lo, d.seed_hi)
+               : (uint32_t)(cluster_spin(key, t, d.seed_lo, d.seed_hi) > 0);
+}
+
+template <class T> __device__ __forceinline__ T ag_load(const T *p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class T> __device__ __forceinline__ void ag_store(T *p, T v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Cluster statistics of a workgroup: per-thread sums, then LDS totals.
+struct Stats {
+    uint32_t n = 0, mx = 0;
+    uint64_t sq = 0;
+    __device__ __forceinline__ void add(uint32_t S, unsigned long long *acc) {
+        ++n;
+        mx = max(mx, S);
+        sq += (uint64_t)S * S;
+        atomicAdd(&acc[GP_HIST + 31 - __clz((int)max(S, 1u))], 1ull);
+    }
+    __device__ __forceinline__ void flush(unsigned long long *acc) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            n += __shfl_xor(n, o, 64);
+            mx = max(mx, (uint32_t)__shfl_xor((int)mx, o, 64));
+            sq += __shfl_xor(sq, o, 64);
+        }
+        if ((threadIdx.x & 63u) == 0u && n != 0u) {
+            atomicAdd(&acc[GP_N], (unsigned long long)n);
+            atomicMax(&acc[GP_MAX], (unsigned long long)mx);
+            atomicAdd(&acc[GP_SQ], (unsigned long long)sq);
+        }
+        n = mx = 0u;
+        sq = 0u;
+    }
+};
+
+// Unions of the pairs (a[u], b[u]) of this wavefront's lanes, a[u] kEmpty
+// where there is none; a pair equal to that of the lane below is dropped, the
+// others are packed in the wavefront's own part of an LDS list (R * 64 words,
+// indices below 2^16) and taken 64 at a time: a quarter of the edge positions
+// have a union, and a round costs what its slowest lane does.  (Joining all
+// pairs in rounds -- hook every larger root under the smallest it meets,
+// compress, until no pair is left -- was measured and dropped: three barriers
+// of 1024 threads a round made level 2 of 512^2 7.3 us instead of 5.2.)
+template <uint32_t R>
+__device__ __forceinline__ void join_pairs(uint32_t *par, uint32_t *list, const uint32_t *a, const uint32_t *b) {
+    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t n = 0u;
+#pragma unroll
+    for (uint32_t u = 0; u < R; ++u) {
+        const uint32_t pa = __shfl_up(a[u], 1, 64), pb = __shfl_up(b[u], 1, 64);
+        const bool has = a[u] != kEmpty && !(lane > 0u && pa == a[u] && pb == b[u]);
+        const uint64_t bal = __ballot(has);
+        if (has)
+            list[n + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u))] =
+                a[u] | (b[u] << 16);
+        n += (uint32_t)__popcll(bal);
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    for (uint32_t k = lane; k < n; k += 64u) lds_union(par, list[k] & 0xFFFFu, list[k] >> 16);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// What level 2 loads of the groups' results, in batches whose loads overlap;
+// the first batch is loaded while the clusters are being counted.  Clusters:
+// a wavefront takes a group at a time, kEnt rounds of 64 (about 200 are
+// open).  Bonds: position f of the groups' E and N sides, one per thread and
+// round.
+struct TopLoads {
+    static constexpr uint32_t kEnt = 5, kPos = 8;
+    uint64_t e[kEnt];
+    uint32_t a[kPos], b[kPos];  // clusters on both sides (kNoRef: no bond)
+
+    __device__ __forceinline__ void clusters(const Dev &d, uint32_t g, uint32_t ng, uint32_t j0) {
+#pragma unroll
+        for (uint32_t u = 0; u < kEnt; ++u) {
+            const uint32_t j = j0 + 64u * u + (threadIdx.x & 63u);
+            e[u] = g < ng && j < kRefSlots ? ag_load(&d.gnode[(size_t)g * kRefSlots + j]) : 0u;
+        }
+    }
+    // group g, its neighbour nb and the place p of position f
+    static __device__ __forceinline__ bool place(const Dev &d, uint32_t f, uint32_t ngx, uint32_t &g, uint32_t &nb,
+                                                 uint32_t &dir, uint32_t &p) {
+        const uint32_t lw = d.tw == 64u ? 6u : 5u, per = 8u << lw;
+        const bool in = f < ngx * ngx * per;
+        g = in ? f >> (lw + 3u) : 0u;
+        dir = (f >> (lw + 2u)) & 1u;
+        p = f & ((4u << lw) - 1u);
+        const uint32_t gy = g / ngx, gx = g - gy * ngx;
+        nb = dir == 0u ? gy * ngx + (gx + 1u == ngx ? 0u : gx + 1u) : (gy + 1u == ngx ? 0u : gy + 1u) * ngx + gx;
+        return in && (dir == 0u ? gy : gx) * kUG + (p >> lw) < d.ntx;
+    }
+    __device__ __forceinline__ void bonds(const Dev &d, uint32_t f0, uint32_t ngx) {
+#pragma unroll
+        for (uint32_t u = 0; u < kPos; ++u) {
+            uint32_t g, nb, dir, p;
+            const bool ok = place(d, f0 + kMergeThreads * u + threadIdx.x, ngx, g, nb, dir, p);
+            a[u] = ok ? ag_load(&d.gedge[(size_t)g * kRefSlots + dir * 256u + p]) : kNoRef;
+            b[u] = ok ? ag_load(&d.gedge[(size_t)nb * kRefSlots + (2u + dir) * 256u + p]) : kNoRef;
+        }
+    }
+};
+
+// Level 2 over the m = s_off[ng] open clusters of all groups; the union-find
+// arrays are in LDS, or (more clusters than fit) in the lattice's node tables,
+// which level 1 has finished with.
+template <bool LDS>
+__device__ __forceinline__ void merge_top(const Dev &d, uint32_t ng, uint32_t ngx, uint32_t t, const uint32_t *s_off,
+                                          TopLoads &ld1, uint32_t *par, uint32_t *sz, uint32_t *key,
+                                          unsigned long long *s_acc) {
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wv = tid >> 6;
+    auto ld = [](uint32_t *p) { return LDS ? lds_load(p) : g_load(p); };
+    auto st = [](uint32_t *p, uint32_t v) {
+        if (LDS)
+            *p = v;
+        else
+            g_store(p, v);
+    };
+    // global accesses of this workgroup complete before it goes on
+    auto barrier = [] {
+        if (!LDS) __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+    };
+    const uint32_t m = s_off[ng];
+    for (uint32_t i = tid; i < m; i += kMergeThreads) st(&par[i], i);
+    barrier();
+    // bonds across the E and N edges of every group
+    const uint32_t np = ng * 8u * d.tw;
+    for (uint32_t f0 = 0; f0 < np; f0 += kMergeThreads * TopLoads::kPos) {
+        if (f0 != 0u) ld1.bonds(d, f0, ngx);
+#pragma unroll
+        for (uint32_t u = 0; u < TopLoads::kPos; ++u) {
+            uint32_t g, nb, dir, p;
+            TopLoads::place(d, f0 + kMergeThreads * u + tid, ngx, g, nb, dir, p);
+            const bool has = ld1.a[u] != kNoRef && ld1.b[u] != kNoRef;
+            ld1.a[u] = has ? s_off[g] + ld1.a[u] : kEmpty;
+            ld1.b[u] = has ? s_off[nb] + ld1.b[u] : kEmpty;
+        }
+        if (LDS) {  // the lists lie where sizes and keys go afterwards
+            join_pairs<TopLoads::kPos>(par, sz + wv * 64u * TopLoads::kPos, ld1.a, ld1.b);
+        } else {
+#pragma unroll
+            for (uint32_t u = 0; u < TopLoads::kPos; ++u)
+                if (ld1.a[u] != kEmpty) g_union(par, ld1.a[u], ld1.b[u]);
+        }
+    }
+    if (LDS) __syncthreads();
+    for (uint32_t g = wv; g < ng; g += kMergeWaves) {
+        const uint32_t off = s_off[g], n = s_off[g + 1u] - off;
+        for (uint32_t j0 = 0; j0 < n; j0 += 64u * TopLoads::kEnt) {
+            if (g != wv || j0 != 0u) ld1.clusters(d, g, ng, j0);
+#pragma unroll
+            for (uint32_t u = 0; u < TopLoads::kEnt; ++u) {
+                const uint32_t j = j0 + 64u * u + lane, i = off + j;
+                if (j >= n) continue;
+                st(&sz[i], (uint32_t)(ld1.e[u] >> 32));
+                st(&key[i], (uint32_t)ld1.e[u]);
+            }
+        }
+    }
+    barrier();
+    for (uint32_t i = tid; i < m; i += kMergeThreads) {
+        uint32_t r = i, q = ld(&par[r]);
+        while (q != r) {
+            r = q;
+            q = ld(&par[r]);
+        }
+        if (r == i) continue;
+        st(&par[i], r);  // (an ancestor of i and of every other chain through i)
+        atomicAdd(&sz[r], ld(&sz[i]));
+        atomicMin(&key[r], ld(&key[i]));
+    }
+    barrier();
+    Stats cs;
+    for (uint32_t g = wv; g < ng; g += kMergeWaves)
+        for (uint32_t j = lane; j < s_off[g + 1u] - s_off[g]; j += 64u) {
+            const uint32_t i = s_off[g] + j, r = ld(&par[i]);
+            d.gspin[(size_t)g * kRefSlots + j] = (uint8_t)new_value(d, ld(&key[r]), t);
+            if (r == i) cs.add(ld(&sz[i]), s_acc);
+        }
+    cs.flush(s_acc);
+}
+
+// Open clusters that level 2 holds in LDS (two workgroups share a CU); a group
+// of 64-wide tiles has at most about 270 (beta = 0.4), so that 16 groups fit;
+// more goes through the node tables.
+constexpr uint32_t kTopLds = 6144;
+
+__device__ __forceinline__ void merge_body(const Dev &d, const uint32_t ug) {
+    constexpr uint32_t NL = kUG * kUG * kNodeSlots;  // local node = tile-in-group * kNodeSlots + node
+    static_assert(kTopLds >= NL + 128u * kMergeWaves, "level 1 uses the same arrays, with its lists behind the parents");
+    static_assert(2u * kTopLds >= 64u * TopLoads::kPos * kMergeWaves, "level 2's lists lie in the sizes and keys");
+    __shared__ uint32_t s_buf[3u * kTopLds];
+    __shared__ uint32_t s_link[NL / 32], s_pre[NL / 32];  // roots of clusters that go on outside, and their numbers
+    __shared__ uint32_t s_off[kMergeGroups + 1u];
     __shared__ unsigned long long s_acc[GP_END];
-    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    __shared__ int s_last;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wv = tid >> 6;
     const uint64_t tsw = *d.tdev;
     const uint32_t t = (uint32_t)tsw, pc = (uint32_t)(tsw & 1u);
-    const uint32_t nt = d.ntiles, tw = d.tw, ntx = d.ntx;
-    uint32_t *par = d.parent[pc];
-    if (tid == 0u) {
-        uint32_t o = 0u;
-        for (uint32_t T = 0; T < nt; ++T) {
-            s_off[T] = o;
-            o += min(d.nk[pc][T], tw == 64u ? 252u : 124u);
-        }
-        s_off[nt] = o;
-    }
-    if (tid < (uint32_t)GP_END) s_acc[tid] = 0ull;
-    __syncthreads();
-    const uint32_t n = s_off[nt];
-    // local node i: tile T (s_off[T] <= i < s_off[T + 1]), slot i - s_off[T]
-    auto tile_of = [&](uint32_t i) {
-        uint32_t T = 0u;
-        while (T + 1u < nt && s_off[T + 1u] <= i) ++T;
-        return T;
-    };
-    for (uint32_t i = tid; i < n; i += 256u) {
-        const uint32_t T = tile_of(i), node = T * kNodeSlots + (i - s_off[T]);
-        s_par[i] = i;
-        s_key[i] = d.key[node];
-        s_sz[i] = d.nsize[node];
-    }
-    __syncthreads();
-    // bonds across every tile edge, E and N, periodic; a run of bonds along
-    // an edge between the same two nodes needs one union
-    for (uint32_t f0 = 0; f0 < nt * 2u * tw; f0 += 256u) {
-        const uint32_t f = f0 + tid;
-        const bool in = f < nt * 2u * tw;
-        const uint32_t T = in ? f / (2u * tw) : 0u, dir = (f / tw) & 1u, i = f % tw;
-        const uint32_t tx = T % ntx, ty = T / ntx;
-        const uint32_t nb = dir == 0u ? ty * ntx + (tx + 1u == ntx ? 0u : tx + 1u)
-                                      : (ty + 1u == ntx ? 0u : ty + 1u) * ntx + tx;
-        const uint8_t *ea = d.edge + (size_t)T * 4u * tw, *eb = d.edge + (size_t)nb * 4u * tw;
-        const bool has = in && ((d.xb[2u * T + dir] >> i) & 1u);
-        const uint32_t a = s_off[T] + (dir == 0u ? ea[1u * tw + i] : ea[3u * tw + i]);
-        const uint32_t b = s_off[nb] + (dir == 0u ? eb[0u * tw + i] : eb[2u * tw + i]);
-        const uint32_t pa = __shfl_up(a, 1, 64), pb = __shfl_up(b, 1, 64);
-        const int ph = __shfl_up((int)has, 1, 64);
-        const bool dup = i > 0u && lane > 0u && ph && pa == a && pb == b;
-        if (has && !dup) lds_union(s_par, a, b);
-    }
-    __syncthreads();
-    // every node to its root; sizes and smallest sites into the roots
-    for (uint32_t i = tid; i < n; i += 256u) {
-        const uint32_t r = lds_root(s_par, i);
-        if (r != i) {
-            atomicMin(&s_key[r], s_key[i]);
-            atomicAdd(&s_sz[r], s_sz[i]);
-            const uint32_t T = tile_of(i), Tr = tile_of(r);
-            par[T * kNodeSlots + (i - s_off[T])] = Tr * kNodeSlots + (r - s_off[Tr]);
-        }
-    }
-    __syncthreads();
-    // the new spin of every node's cluster, drawn from its smallest site;
-    // statistics of the cross-tile clusters
-    uint64_t cn = 0, cmx = 0, csq = 0;
-    for (uint32_t i = tid; i < n; i += 256u) {
-        const uint32_t r = lds_root(s_par, i), T = tile_of(i);
-        const uint32_t rkey = s_key[r];
-        d.rspin[T * kNodeSlots + (i - s_off[T])] =
-            d.q ? potts_spin(rkey, t, d.q, d.seed_lo, d.seed_hi) : cluster_spin(rkey, t, d.seed_lo, d.seed_hi);
-        if (r == i) {
-            const uint32_t S = s_sz[i];
-            ++cn;
-            cmx = max(cmx, (uint64_t)S);
-            csq += (uint64_t)S * S;
-            atomicAdd(&s_acc[GP_HIST + 31 - __clz((int)max(S, 1u))], 1ull);
-        }
-    }
-    // the tile partials (interior clusters, energy and magnetisation of the
-    // incoming configuration, Potts populations)
-    int64_t ce = 0, cm = 0;
-    for (uint32_t T = tid; T < nt; T += 256u) {
-        const int32_t *tp = d.tpart + (size_t)T * kTilePart;
-        ce += tp[TP_E];
-        cm += tp[TP_M];
-        cn += (uint32_t)tp[TP_N];
-        cmx = max(cmx, (uint64_t)(uint32_t)tp[TP_MAX]);
-        csq += (uint32_t)tp[TP_SQ];
-        for (uint32_t b = 0; b < kTileBins; ++b)
-            if (tp[TP_HIST + b]) atomicAdd(&s_acc[GP_HIST + b], (unsigned long long)(uint32_t)tp[TP_HIST + b]);
-        if (d.q)
-            for (int k = 0; k < kMaxQ; ++k)
-                if (tp[TP_CNT + k]) atomicAdd(&s_acc[GP_CNT + k], (unsigned long long)(uint32_t)tp[TP_CNT + k]);
-    }
+    const uint32_t ntx = d.ntx, tw = d.tw, lw = tw == 64u ? 6u : 5u;
+    const uint32_t ngx = (ntx + kUG - 1u) / kUG, ng = ngx * ngx, gy = ug / ngx, gx = ug - gy * ngx;
+    const bool whole = ng == 1u;
+    uint32_t *const s_par = s_buf, *const s_sz = s_buf + kTopLds, *const s_key = s_buf + 2u * kTopLds;
+
+    // edge positions: E and N of every tile (two per thread, one with 32-wide
+    // tiles), and W and S of the tiles on the group's low sides (bonds that
+    // come in); all loads before any is waited on
+    uint32_t ua[2], ub[2];     // nodes joined; ub kEmpty: the bond leaves the group
+    uint32_t uo[2];            // its place on the group's perimeter
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        cn += __shfl_xor(cn, o, 64);
-        cmx = max(cmx, (uint64_t)__shfl_xor((unsigned long long)cmx, o, 64));
-        csq += __shfl_xor(csq, o, 64);
-        ce += __shfl_xor(ce, o, 64);
-        cm += __shfl_xor(cm, o, 64);
+    for (uint32_t u = 0; u < 2u; ++u) {
+        const uint32_t f = tid + kMergeThreads * u, T = (f >> (lw + 1u)) & 15u, dir = (f >> lw) & 1u, i = f & (tw - 1u);
+        const uint32_t lx = T % kUG, ly = T / kUG, tx = gx * kUG + lx, ty = gy * kUG + ly;
+        const bool ok = f < (32u << lw) && tx < ntx && ty < ntx;
+        const uint32_t A = ok ? ty * ntx + tx : 0u;
+        const uint32_t nx = dir == 0u ? (tx + 1u == ntx ? 0u : tx + 1u) : tx;
+        const uint32_t ny = dir == 0u ? ty : (ty + 1u == ntx ? 0u : ty + 1u);
+        const bool inside = whole || (dir == 0u ? lx + 1u < kUG && tx + 1u < ntx : ly + 1u < kUG && ty + 1u < ntx);
+        const uint32_t B = ok ? ny * ntx + nx : 0u, TB = whole ? ny * kUG + nx : T + (dir == 0u ? 1u : kUG);
+        const uint64_t bits = d.xb[2u * A + dir];
+        const uint32_t an = d.edge[((size_t)A * 4u + (dir == 0u ? 1u : 3u)) * tw + i];
+        const uint32_t bn = d.edge[((size_t)B * 4u + (dir == 0u ? 0u : 2u)) * tw + i];
+        const bool has = ok && ((bits >> i) & 1u);
+        ua[u] = has ? T * kNodeSlots + an : kEmpty;
+        ub[u] = inside ? TB * kNodeSlots + bn : kEmpty;
+        uo[u] = ok && !inside ? dir * 256u + (dir == 0u ? ly : lx) * tw + i : kEmpty;
     }
-    if (lane == 0u) {
-        atomicAdd(&s_acc[GP_N], (unsigned long long)cn);
-        atomicMax(&s_acc[GP_MAX], (unsigned long long)cmx);
-        atomicAdd(&s_acc[GP_SQ], (unsigned long long)csq);
-        atomicAdd(&s_acc[GP_E], (unsigned long long)ce);
-        atomicAdd(&s_acc[GP_M], (unsigned long long)cm);
+    uint32_t va = kEmpty, vo = kEmpty;  // incoming: node, place
+    if (!whole) {
+        const uint32_t dir = (tid >> (lw + 2u)) & 1u, l = (tid >> lw) & 3u, i = tid & (tw - 1u);
+        const uint32_t tx = gx * kUG + (dir == 0u ? 0u : l), ty = gy * kUG + (dir == 0u ? l : 0u);
+        const bool ok = tid < (8u << lw) && tx < ntx && ty < ntx;
+        const uint32_t A = ok ? ty * ntx + tx : 0u;
+        const uint32_t px = dir == 0u ? (tx == 0u ? ntx - 1u : tx - 1u) : tx, py = dir == 0u ? ty : (ty == 0u ? ntx - 1u : ty - 1u);
+        const uint32_t P = ok ? py * ntx + px : 0u;
+        const uint64_t bits = d.xb[2u * P + dir];
+        const uint32_t an = d.edge[((size_t)A * 4u + (dir == 0u ? 0u : 2u)) * tw + i];
+        if (ok && ((bits >> i) & 1u)) va = (dir == 0u ? l * kUG : l) * kNodeSlots + an;
+        if (ok) vo = (2u + dir) * 256u + l * tw + i;
+    }
+    // nodes: wavefront wv has tile wv of the group, its node slots lane + 64 j
+    const uint32_t mx = gx * kUG + wv % kUG, my = gy * kUG + wv / kUG;
+    const bool mok = mx < ntx && my < ntx;
+    const uint32_t mtile = mok ? my * ntx + mx : 0u;
+    const uint32_t nk = mok ? min(nk_either(d, pc, mtile), 252u) : 0u;
+    constexpr uint32_t NJ = kNodeSlots / 64u;
+    uint32_t kk[NJ], kz[NJ];
+#pragma unroll
+    for (uint32_t j = 0; j < NJ; ++j) {
+        const uint32_t node = mtile * kNodeSlots + 64u * j + lane;
+        const bool in = j == 0u || 64u * j < nk;  // the first round is loaded without waiting for nk
+        kk[j] = in ? d.key[node] : 0u;
+        kz[j] = in ? d.nsize[node] : 0u;
+    }
+    if (tid < NL / 32u) s_link[tid] = 0u;
+    if (tid < (uint32_t)GP_END) s_acc[tid] = 0ull;
+#pragma unroll
+    for (uint32_t j = 0; j < NJ; ++j) {
+        const uint32_t k = 64u * j + lane, li = wv * kNodeSlots + k;
+        if (k >= nk) continue;
+        s_par[li] = li;
+        s_sz[li] = kz[j];
+        s_key[li] = kk[j];
+    }
+    __syncthreads();
+    {
+        uint32_t ja[2];
+#pragma unroll
+        for (uint32_t u = 0; u < 2u; ++u) ja[u] = ub[u] == kEmpty ? kEmpty : ua[u];
+        join_pairs<2>(s_par, s_buf + NL + 128u * wv, ja, ub);
+    }
+    __syncthreads();
+    uint32_t rt[NJ];
+#pragma unroll
+    for (uint32_t j = 0; j < NJ; ++j) {
+        const uint32_t k = 64u * j + lane, li = wv * kNodeSlots + k;
+        rt[j] = li;
+        if (k >= nk) continue;
+        rt[j] = lds_find(s_par, li);
+        if (rt[j] != li) {
+            atomicAdd(&s_sz[rt[j]], kz[j]);
+            atomicMin(&s_key[rt[j]], kk[j]);
+        }
+    }
+    uint32_t ur[2] = {kEmpty, kEmpty}, vr = kEmpty;  // roots at the perimeter's bonds
+    if (!whole) {
+#pragma unroll
+        for (uint32_t u = 0; u < 2u; ++u)
+            if (ua[u] != kEmpty && uo[u] != kEmpty) ur[u] = lds_find(s_par, ua[u]);
+        if (va != kEmpty) vr = lds_find(s_par, va);
+#pragma unroll
+        for (uint32_t u = 0; u < 2u; ++u)
+            if (ur[u] != kEmpty) atomicOr(&s_link[ur[u] >> 5], 1u << (ur[u] & 31u));
+        if (vr != kEmpty) atomicOr(&s_link[vr >> 5], 1u << (vr & 31u));
+    }
+    __syncthreads();
+    uint32_t open = 0u;  // clusters that go on outside (in wavefront 0)
+    if (!whole) {
+        if (wv == 0u) {
+            const uint32_t ca = __popc(s_link[2u * lane]), c = ca + __popc(s_link[2u * lane + 1u]);
+            uint32_t incl = c;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t n = __shfl_up(incl, o, 64);
+                if (lane >= (uint32_t)o) incl += n;
+            }
+            s_pre[2u * lane] = incl - c;
+            s_pre[2u * lane + 1u] = incl - c + ca;
+            open = min((uint32_t)__shfl((int)incl, 63, 64), kRefSlots);
+        }
+        __syncthreads();
+    }
+    auto number = [&](uint32_t r) {
+        return min(s_pre[r >> 5] + __popc(s_link[r >> 5] & ((1u << (r & 31u)) - 1u)), kRefSlots - 1u);
+    };
+    Stats cs;
+#pragma unroll
+    for (uint32_t j = 0; j < NJ; ++j) {
+        const uint32_t k = 64u * j + lane, li = wv * kNodeSlots + k, r = rt[j];
+        if (k >= nk) continue;
+        uint32_t ref;
+        if ((s_link[r >> 5] >> (r & 31u)) & 1u) {
+            const uint32_t n = number(r);
+            ref = kRef + n;
+            if (r == li) ag_store(&d.gnode[(size_t)ug * kRefSlots + n], (uint64_t)s_key[r] | ((uint64_t)s_sz[r] << 32));
+        } else {
+            ref = new_value(d, s_key[r], t);
+            if (r == li) cs.add(s_sz[r], s_acc);
+        }
+        d.nref[mtile * kNodeSlots + k] = (uint16_t)ref;
+    }
+    if (!whole) {
+        uint16_t *ge = d.gedge + (size_t)ug * kRefSlots;
+#pragma unroll
+        for (uint32_t u = 0; u < 2u; ++u)
+            if (uo[u] != kEmpty) ag_store(&ge[uo[u]], (uint16_t)(ur[u] == kEmpty ? kNoRef : number(ur[u])));
+        if (vo != kEmpty) ag_store(&ge[vo], (uint16_t)(vr == kEmpty ? kNoRef : number(vr)));
+    }
+    cs.flush(s_acc);
+    // the tiles' partials (interior clusters, energy and magnetisation of the
+    // incoming configuration, Potts populations): wavefront wv its tile's,
+    // one word per lane
+    if (mok && lane < (uint32_t)TP_CNT + (uint32_t)kMaxQ) {
+        const int32_t v = d.tpart[(size_t)mtile * kTilePart + lane];
+        uint32_t f = 0u;
+        if (lane == (uint32_t)TP_E)
+            f = GP_E;
+        else if (lane == (uint32_t)TP_M)
+            f = GP_M;
+        else if (lane == (uint32_t)TP_N)
+            f = GP_N;
+        else if (lane == (uint32_t)TP_MAX)
+            f = GP_MAX;
+        else if (lane == (uint32_t)TP_SQ)
+            f = GP_SQ;
+        else if (lane < (uint32_t)TP_CNT)
+            f = (uint32_t)GP_HIST + lane - (uint32_t)TP_HIST;
+        else
+            f = (uint32_t)GP_CNT + lane - (uint32_t)TP_CNT;
+        if (f == (uint32_t)GP_MAX)
+            atomicMax(&s_acc[f], (unsigned long long)v);
+        else if (v != 0 && (f < (uint32_t)GP_CNT || d.q))
+            atomicAdd(&s_acc[f], (unsigned long long)(int64_t)v);
+    }
+    if (!whole) {
+        __syncthreads();
+        if (tid < (uint32_t)GP_END) ag_store(&d.mpart[(size_t)ug * kGroupPart + tid], (uint64_t)s_acc[tid]);
+        if (tid == 0u) ag_store(&d.gcount[ug], open);
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        unsigned long long *acc = reinterpret_cast<unsigned long long *>(d.acc);
+        if (tid == 0u) s_last = atomicAdd(&acc[ACC_COUNT], 1ull) == (unsigned long long)ng - 1ull;
+        if (tid < (uint32_t)GP_END) s_acc[tid] = 0ull;
+        __syncthreads();
+        if (!s_last) return;
+        if (tid == 0u) ag_store(&d.acc[ACC_COUNT], (uint64_t)0);
+        TopLoads top;
+        top.clusters(d, wv, ng, 0u);
+        top.bonds(d, 0u, ngx);
+        // the groups' partials, and in wavefront 0 the first cluster of every group
+        uint64_t v = 0u;
+        for (uint32_t g = wv; g < ng; g += kMergeWaves) {
+            const uint64_t x = lane < (uint32_t)GP_END ? ag_load(&d.mpart[(size_t)g * kGroupPart + lane]) : 0u;
+            v = lane == (uint32_t)GP_MAX ? max(v, x) : v + x;
+        }
+        if (wv == 0u) {
+            uint32_t c[2];
+#pragma unroll
+            for (uint32_t h = 0; h < 2u; ++h) c[h] = 2u * lane + h < ng ? min(ag_load(&d.gcount[2u * lane + h]), kRefSlots) : 0u;
+            uint32_t incl = c[0] + c[1];
+            const uint32_t own = incl;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const uint32_t n = __shfl_up(incl, o, 64);
+                if (lane >= (uint32_t)o) incl += n;
+            }
+            const uint32_t pre = incl - own;
+            if (2u * lane <= ng) s_off[2u * lane] = pre;
+            if (2u * lane + 1u <= ng) s_off[2u * lane + 1u] = pre + c[0];
+        }
+        if (lane == (uint32_t)GP_MAX)
+            atomicMax(&s_acc[lane], (unsigned long long)v);
+        else if (v && lane < (uint32_t)GP_END)
+            atomicAdd(&s_acc[lane], (unsigned long long)v);
+        __syncthreads();
+        if (s_off[ng] <= kTopLds)
+            merge_top<true>(d, ng, ngx, t, s_off, top, s_par, s_sz, s_key, s_acc);
+        else
+            merge_top<false>(d, ng, ngx, t, s_off, top, d.parent[pc], d.nsize, d.key, s_acc);
     }
     __syncthreads();
     record_write(d, reinterpret_cast<const uint64_t *>(s_acc), 0);
 }
 
-__global__ __launch_bounds__(256) void k_smerge_b(const Dev *devs, const uint32_t *smap) {
-    smerge_body(devs[smap[blockIdx.x]]);
+__global__ __launch_bounds__(kMergeThreads) void k_merge(Dev d) { merge_body(d, blockIdx.x); }
+
+__global__ __launch_bounds__(kMergeThreads) void k_merge_b(const Dev *devs, const uint32_t *map) {
+    const uint32_t e = map[blockIdx.x];
+    merge_body(devs[e >> kMapShift], e & kMapMask);
 }
 
 // =====================================================================
 // k_resolve: replace node codes by final spins in place and measure the
 // configuration (runs once at the end of every sw_sweep call).
 // =====================================================================
-template <int TW, bool POTTS = false>
+template <int TW, bool POTTS, int TWO>
 __device__ __forceinline__ void resolve_body(const Dev &d, const uint32_t tile) {
     constexpr int NT = TW * TW / 16;
     constexpr uint32_t RPT = TW / 16;
@@ -1539,6 +1899,8 @@ __device__ __forceinline__ void resolve_body(const Dev &d, const uint32_t tile) 
     const uint32_t gy = ty * TW + ly, gx0 = tx * TW + x0;
     const uint32_t east = ty * ntx + (tx + 1u == ntx ? 0u : tx + 1u);
     const uint32_t north = (ty + 1u == ntx ? 0u : ty + 1u) * ntx + tx;
+    const uint32_t gbe = ref_base(d, tx + 1u == ntx ? 0u : tx + 1u, ty);
+    const uint32_t gbn = ref_base(d, tx, ty + 1u == ntx ? 0u : ty + 1u);
 
     const uint4 v = *reinterpret_cast<const uint4 *>(sp + (size_t)gy * L + gx0);
     uint4 vn = make_uint4(0u, 0u, 0u, 0u);
@@ -1551,7 +1913,7 @@ __device__ __forceinline__ void resolve_body(const Dev &d, const uint32_t tile) 
         const uint32_t gxe = (gx0 + 16u == L) ? 0u : gx0 + 16u;
         ve = (uint8_t)sp[(size_t)gy * L + gxe];
     }
-    load_table<TW, POTTS>(d, tile, pp, s_tab, tid);
+    load_table<TW, POTTS, TWO>(d, tile, ref_base(d, tx, ty), pp, s_tab, tid);
     if (tid < NPL * EW) s_eup[tid] = 0u;
     __syncthreads();
     uint32_t up = 0u, pl[3] = {0u, 0u, 0u};
@@ -1561,13 +1923,14 @@ __device__ __forceinline__ void resolve_body(const Dev &d, const uint32_t tile) 
         for (int b = 0; b < 3; ++b) reinterpret_cast<uint16_t *>(s_up + b * (TW + 1))[ly * RPT + seg] = (uint16_t)pl[b];
         if (ly == TW - 1) {
             uint32_t pn[3];
-            decode16_potts_remote<TW>(vn, north, d.rspin, pn);
+            decode16_potts_remote<TW, TWO>(d, vn, north, gbn, pn);
 #pragma unroll
             for (int b = 0; b < 3; ++b)
                 reinterpret_cast<uint16_t *>(s_up + b * (TW + 1))[TW * RPT + seg] = (uint16_t)pn[b];
         }
         if (seg == RPT - 1) {
-            const uint32_t ev = potts_byte<TW>(ve, east, d.rspin);
+            uint32_t ev;
+            remote_values<TW, true, TWO, 1>(d, &ve, east, gbe, &ev);
 #pragma unroll
             for (uint32_t b = 0; b < 3u; ++b)
                 if ((ev >> b) & 1u) atomicOr(&s_eup[b * EW + (ly >> 5)], 1u << (ly & 31u));
@@ -1576,11 +1939,13 @@ __device__ __forceinline__ void resolve_body(const Dev &d, const uint32_t tile) 
         up = decode16<TW>(v, s_tab);
         reinterpret_cast<uint16_t *>(s_up)[ly * RPT + seg] = (uint16_t)up;
         if (ly == TW - 1) {
-            const uint32_t upn = decode16_remote(vn, north, d.rspin);
+            const uint32_t upn = decode16_remote<TWO>(d, vn, north, gbn);
             reinterpret_cast<uint16_t *>(s_up)[TW * RPT + seg] = (uint16_t)upn;
         }
         if (seg == RPT - 1) {
-            if (resolve_byte(ve, east, d.rspin) > 0) atomicOr(&s_eup[ly >> 5], 1u << (ly & 31u));
+            uint32_t ev;
+            remote_values<TW, false, TWO, 1>(d, &ve, east, gbe, &ev);
+            if (ev) atomicOr(&s_eup[ly >> 5], 1u << (ly & 31u));
         }
     }
     __syncthreads();
@@ -1654,15 +2019,15 @@ __device__ __forceinline__ void resolve_body(const Dev &d, const uint32_t tile) 
     }
 }
 
-template <int TW, bool POTTS = false>
+template <int TW, bool POTTS, int TWO>
 __global__ __launch_bounds__(TW *TW / 16) void k_resolve(Dev d) {
-    resolve_body<TW, POTTS>(d, tile_of_block(blockIdx.x, d.ntiles));
+    resolve_body<TW, POTTS, TWO>(d, tile_of_block(blockIdx.x, d.ntiles));
 }
 
-template <int TW, bool POTTS = false>
+template <int TW, bool POTTS, int TWO>
 __global__ __launch_bounds__(TW *TW / 16) void k_resolve_b(const Dev *devs, const uint32_t *map) {
     const uint32_t e = map[tile_of_block(blockIdx.x, gridDim.x)];
-    resolve_body<TW, POTTS>(devs[e >> kMapShift], e & kMapMask);
+    resolve_body<TW, POTTS, TWO>(devs[e >> kMapShift], e & kMapMask);
 }
 
 // Initial spins (Fig. 1): hot = bit 0 of word 0 of Philox({s, 0, 2, 0}),
@@ -1701,6 +2066,54 @@ inline uint32_t grid_for(size_t n, uint32_t per_block, uint32_t cap) {
     return (uint32_t)g;
 }
 
+template <bool DENSE, int TWO>
+void launch_tile(const Dev &d, hipStream_t s) {
+    if (d.q && d.tw == 64)
+        k_tile<64, true, DENSE, TWO><<<d.ntiles, 256, 0, s>>>(d);
+    else if (d.q)
+        k_tile<32, true, DENSE, TWO><<<d.ntiles, 64, 0, s>>>(d);
+    else if (d.tw == 64)
+        k_tile<64, false, DENSE, TWO><<<d.ntiles, 256, 0, s>>>(d);
+    else
+        k_tile<32, false, DENSE, TWO><<<d.ntiles, 64, 0, s>>>(d);
+}
+
+template <int TWO>
+void resolve_tiles(const Dev &d, hipStream_t s) {
+    if (d.q && d.tw == 64)
+        k_resolve<64, true, TWO><<<d.ntiles, 256, 0, s>>>(d);
+    else if (d.q)
+        k_resolve<32, true, TWO><<<d.ntiles, 64, 0, s>>>(d);
+    else if (d.tw == 64)
+        k_resolve<64, false, TWO><<<d.ntiles, 256, 0, s>>>(d);
+    else
+        k_resolve<32, false, TWO><<<d.ntiles, 64, 0, s>>>(d);
+}
+
+template <int TWO>
+void launch_tile_b(const BatchDev &b, hipStream_t s) {
+    if (b.potts && b.tw == 64)
+        k_tile_b<64, true, TWO><<<b.ntiles, 256, 0, s>>>(b.devs, b.tmap);
+    else if (b.potts)
+        k_tile_b<32, true, TWO><<<b.ntiles, 64, 0, s>>>(b.devs, b.tmap);
+    else if (b.tw == 64)
+        k_tile_b<64, false, TWO><<<b.ntiles, 256, 0, s>>>(b.devs, b.tmap);
+    else
+        k_tile_b<32, false, TWO><<<b.ntiles, 64, 0, s>>>(b.devs, b.tmap);
+}
+
+template <int TWO>
+void resolve_tiles_b(const BatchDev &b, hipStream_t s) {
+    if (b.potts && b.tw == 64)
+        k_resolve_b<64, true, TWO><<<b.ntiles, 256, 0, s>>>(b.devs, b.tmap);
+    else if (b.potts)
+        k_resolve_b<32, true, TWO><<<b.ntiles, 64, 0, s>>>(b.devs, b.tmap);
+    else if (b.tw == 64)
+        k_resolve_b<64, false, TWO><<<b.ntiles, 256, 0, s>>>(b.devs, b.tmap);
+    else
+        k_resolve_b<32, false, TWO><<<b.ntiles, 64, 0, s>>>(b.devs, b.tmap);
+}
+
 }  // namespace
 
 hipError_t launch_init(const Dev &d, int cold, hipStream_t s) {
@@ -1720,31 +2133,23 @@ hipError_t launch_stage(const Dev &d, int stage, hipStream_t s) {
         k_record<<<(d.ngroups + kRecordGroups - 1) / kRecordGroups, 256, 0, s>>>(d, d.ngroups, d.brick ? 0 : 2);
         return hipGetLastError();
     }
+    if (d.two && stage > 1) return hipSuccess;  // k_merge does it all
     switch (stage) {
     case 0:  // bonds + tile-local clusters
         if (d.dense) {
             k_zero_u64<<<grid_for(n + 1, 256, 65536), 256, 0, s>>>(d.dense, n + 1);
-            if (d.q && d.tw == 64)
-                k_tile<64, true, true><<<d.ntiles, 256, 0, s>>>(d);
-            else if (d.q)
-                k_tile<32, true, true><<<d.ntiles, 64, 0, s>>>(d);
-            else if (d.tw == 64)
-                k_tile<64, false, true><<<d.ntiles, 256, 0, s>>>(d);
-            else
-                k_tile<32, false, true><<<d.ntiles, 64, 0, s>>>(d);
-        } else if (d.q && d.tw == 64) {
-            k_tile<64, true><<<d.ntiles, 256, 0, s>>>(d);
-        } else if (d.q) {
-            k_tile<32, true><<<d.ntiles, 64, 0, s>>>(d);
-        } else if (d.tw == 64) {
-            k_tile<64><<<d.ntiles, 256, 0, s>>>(d);
+            launch_tile<true, 0>(d, s);
+        } else if (d.two) {
+            launch_tile<false, 1>(d, s);
         } else {
-            k_tile<32><<<d.ntiles, 64, 0, s>>>(d);
+            launch_tile<false, 0>(d, s);
         }
         break;
-    case 1: {  // cross-tile unions: inside groups of tiles, then between groups
+    case 1: {  // the whole merge, or cross-tile unions: inside groups of tiles, then between groups
         const uint32_t ngx = (d.ntx + kUG - 1u) / kUG, nwaves = 2u * ngx * d.ntx;
-        if (d.tw == 64) {
+        if (d.two) {
+            k_merge<<<ngx * ngx, kMergeThreads, 0, s>>>(d);
+        } else if (d.tw == 64) {
             k_ulocal<64><<<ngx * ngx, 256, 0, s>>>(d);
             k_union<64><<<(nwaves + 3u) / 4u, 256, 0, s>>>(d);
         } else {
@@ -1795,21 +2200,17 @@ hipError_t launch_resolve(const Dev &d, hipStream_t s) {
         k_record<<<(d.ntiles + kRecordTiles - 1) / kRecordTiles, 256, 0, s>>>(d, d.ntiles, 1);
         return hipGetLastError();
     }
-    if (d.q && d.tw == 64)
-        k_resolve<64, true><<<d.ntiles, 256, 0, s>>>(d);
-    else if (d.q)
-        k_resolve<32, true><<<d.ntiles, 64, 0, s>>>(d);
-    else if (d.tw == 64)
-        k_resolve<64><<<d.ntiles, 256, 0, s>>>(d);
+    if (d.two)
+        resolve_tiles<1>(d, s);
     else
-        k_resolve<32><<<d.ntiles, 64, 0, s>>>(d);
+        resolve_tiles<0>(d, s);
     k_record<<<(d.ntiles + kRecordTiles - 1) / kRecordTiles, 256, 0, s>>>(d, d.ntiles, 1);
     return hipGetLastError();
 }
 
-hipError_t launch_batch_smerge(const BatchDev &b, hipStream_t s) {
+hipError_t launch_batch_merge(const BatchDev &b, hipStream_t s) {
     if (b.nsmall == 0) return hipSuccess;
-    k_smerge_b<<<b.nsmall, 256, 0, s>>>(b.devs, b.smap);
+    k_merge_b<<<b.nsmall, kMergeThreads, 0, s>>>(b.devs, b.smap);
     return hipGetLastError();
 }
 
@@ -1818,14 +2219,13 @@ hipError_t launch_batch_stage(const BatchDev &b, int stage, hipStream_t s) {
     if (b.n == 0 && stage != 0) return hipSuccess;  // stages 1..4: replicas of the global merge
     switch (stage) {
     case 0:
-        if (b.potts && b.tw == 64)
-            k_tile_b<64, true><<<b.ntiles, 256, 0, s>>>(b.devs, b.tmap);
-        else if (b.potts)
-            k_tile_b<32, true><<<b.ntiles, 64, 0, s>>>(b.devs, b.tmap);
-        else if (b.tw == 64)
-            k_tile_b<64><<<b.ntiles, 256, 0, s>>>(b.devs, b.tmap);
+        // b.n replicas of the global merge, the others of k_merge
+        if (b.n == 0)
+            launch_tile_b<1>(b, s);
+        else if (b.n == b.nall)
+            launch_tile_b<0>(b, s);
         else
-            k_tile_b<32><<<b.ntiles, 64, 0, s>>>(b.devs, b.tmap);
+            launch_tile_b<2>(b, s);
         break;
     case 1:
         if (b.tw == 64) {
@@ -1850,25 +2250,23 @@ hipError_t launch_batch_stage(const BatchDev &b, int stage, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_batch_sweep(const BatchDev &b, hipStream_t s) {
-    for (int stage = 0; stage < kStages; ++stage) {
-        hipError_t e = launch_batch_stage(b, stage, s);
-        if (e == hipSuccess && stage == 0) e = launch_batch_smerge(b, s);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+hipError_t launch_batch_sweep(const BatchDev *b, int ngroups, hipStream_t s) {
+    hipError_t e = hipSuccess;
+    for (int g = 0; g < ngroups && e == hipSuccess; ++g) e = launch_batch_stage(b[g], 0, s);
+    for (int g = 0; g < ngroups && e == hipSuccess; ++g) e = launch_batch_merge(b[g], s);
+    for (int stage = 1; stage < kStages; ++stage)
+        for (int g = 0; g < ngroups && e == hipSuccess; ++g) e = launch_batch_stage(b[g], stage, s);
+    return e;
 }
 
 hipError_t launch_batch_resolve(const BatchDev &b, hipStream_t s) {
     if (b.nall == 0) return hipSuccess;
-    if (b.potts && b.tw == 64)
-        k_resolve_b<64, true><<<b.ntiles, 256, 0, s>>>(b.devs, b.tmap);
-    else if (b.potts)
-        k_resolve_b<32, true><<<b.ntiles, 64, 0, s>>>(b.devs, b.tmap);
-    else if (b.tw == 64)
-        k_resolve_b<64><<<b.ntiles, 256, 0, s>>>(b.devs, b.tmap);
+    if (b.n == 0)
+        resolve_tiles_b<1>(b, s);
+    else if (b.n == b.nall)
+        resolve_tiles_b<0>(b, s);
     else
-        k_resolve_b<32><<<b.ntiles, 64, 0, s>>>(b.devs, b.tmap);
+        resolve_tiles_b<2>(b, s);
     k_record_b<<<b.nall, 256, 0, s>>>(b.devs, b.amap, 1);
     return hipGetLastError();
 }

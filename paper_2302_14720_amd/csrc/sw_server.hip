@@ -152,7 +152,7 @@ int upload_maps(sw_server *s, swmi::BatchMaps *m, swmi::BatchDev *bd, int ngroup
 int rebuild_active(sw_server *s) {
     HIP_TRY(hipStreamSynchronize(s->stream));
     swmi::BatchMaps m[kGroups];
-    for (Job *j : s->active) m[group_of(j->dev)].add((uint32_t)j->slot, j->dev, true);
+    for (Job *j : s->active) m[group_of(j->dev)].add((uint32_t)j->slot, j->dev, m[0]);
     set_groups(s->bd);
     const int rc = upload_maps(s, m, s->bd, kGroups);
     if (rc == SW_OK) s->dirty = false;
@@ -318,7 +318,7 @@ int sw_server_step(sw_server *s, int64_t n, int64_t *done_ids, int32_t cap, int3
         int64_t k = left;
         for (const Job *j : s->active) k = std::min(k, j->target - j->done);
         for (int64_t i = 0; i < k; ++i)
-            for (int g = 0; g < kGroups; ++g) HIP_TRY(swmi::launch_batch_sweep(s->bd[g], s->stream));
+            HIP_TRY(swmi::launch_batch_sweep(s->bd, kGroups, s->stream));
         uint64_t sites = 0;
         for (Job *j : s->active) {
             j->done += k;
@@ -334,7 +334,7 @@ int sw_server_step(sw_server *s, int64_t n, int64_t *done_ids, int32_t cap, int3
         HIP_TRY(hipStreamSynchronize(s->stream));
         swmi::BatchMaps m[kGroups];
         swmi::BatchDev rb[kGroups]{};
-        for (Job *j : fin) m[group_of(j->dev)].add((uint32_t)j->slot, j->dev, true);
+        for (Job *j : fin) m[group_of(j->dev)].add((uint32_t)j->slot, j->dev, m[0]);
         set_groups(rb);
         rc = upload_maps(s, m, rb, kGroups);
         if (rc != SW_OK) return rc;

@@ -13,6 +13,9 @@ namespace swmi {
 __device__ __forceinline__ uint32_t lds_load(uint32_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
+__device__ __forceinline__ void lds_store(uint32_t *p, uint32_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
 // Path halving lowers entries with atomicMin: a plain store could overwrite
 // a fully compressed entry (the root) with a larger ancestor read earlier by
 // another thread, whereas with min-updates every entry only ever decreases
@@ -36,10 +39,24 @@ __device__ __forceinline__ uint32_t lds_root(const uint32_t *par, uint32_t a) {
         a = p;
     }
 }
+// Both finds advance together, one level per round of loads, with path
+// splitting: every entry passed is re-pointed at its grandparent, which is an
+// ancestor whatever other unions did meanwhile (a plain store: an entry that
+// was not a root never is again).  The two paths meeting below their roots (a
+// common parent) already shows one set.
 __device__ __forceinline__ void lds_union(uint32_t *par, uint32_t a, uint32_t b) {
     while (true) {
-        a = lds_find(par, a);
-        b = lds_find(par, b);
+        uint32_t pa = lds_load(&par[a]), pb = lds_load(&par[b]);
+        while (pa != a || pb != b) {
+            if (pa == pb) return;
+            const uint32_t ga = lds_load(&par[pa]), gb = lds_load(&par[pb]);
+            if (ga != pa) lds_store(&par[a], ga);
+            if (gb != pb) lds_store(&par[b], gb);
+            a = pa;
+            b = pb;
+            pa = ga;
+            pb = gb;
+        }
         if (a == b) return;
         if (a > b) { const uint32_t tmp = a; a = b; b = tmp; }
         uint32_t expected = b;
@@ -109,11 +126,7 @@ __device__ __forceinline__ uint32_t g_load(uint32_t *p) {
 __device__ __forceinline__ void g_store(uint32_t *p, uint32_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-// Union in global memory.  Both finds advance together, one level per
-// round of loads (their loads overlap), with path splitting: every entry
-// passed is re-pointed at its grandparent, which is an ancestor whatever
-// other unions did meanwhile.  The two paths meeting below their roots (a
-// common parent) already shows one set.
+// Union in global memory, as lds_union.
 __device__ __forceinline__ void g_union(uint32_t *par, uint32_t a, uint32_t b) {
     while (true) {
         uint32_t pa = g_load(&par[a]), pb = g_load(&par[b]);
