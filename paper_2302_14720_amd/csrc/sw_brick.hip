@@ -257,12 +257,12 @@ __global__ __launch_bounds__(256, kBrickWavesPerEU) void k_brick3(Dev d) {
     // {s, t, 4, 0} for +x, +y, +z
     uint32_t EX = 0u, EY = 0u, EZ = 0u;
 #pragma unroll 4
-    for (uint32_t j = 0; j < 16u; ++j) {
+    for (uint32_t j = 15u; j < 16u; --j) {
         uint32_t w0 = s0 + j, w1 = t, w2 = 4u, w3 = 0u;
         philox10(w0, w1, w2, w3, d.seed_lo, d.seed_hi);
-        EX |= (uint32_t)(w0 < T) << j;
-        EY |= (uint32_t)(w1 < T) << j;
-        EZ |= (uint32_t)(w2 < T) << j;
+        EX = shift_in_below(EX, w0, T);
+        EY = shift_in_below(EY, w1, T);
+        EZ = shift_in_below(EZ, w2, T);
     }
     EX &= eq.x;
     EY &= eq.y;

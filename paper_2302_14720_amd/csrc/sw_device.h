@@ -15,6 +15,13 @@ __device__ __forceinline__ uint32_t tile_of_block(uint32_t b, uint32_t n) {
     return b;
 }
 
+// m shifted left by one, with w < T as the bit below: a compare and an add
+// with carry (the compiler makes a compare, a select and a shift-or of it).
+__device__ __forceinline__ uint32_t shift_in_below(uint32_t m, uint32_t w, uint32_t T) {
+    asm("v_cmp_gt_u32 vcc, %2, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(m) : "v"(w), "s"(T) : "vcc");
+    return m;
+}
+
 // Equal-neighbour masks of 16 sites from their bit planes and those of the
 // E and N neighbours; equal pairs and the population of every value 0..7
 // (two 16-bit counts per word).

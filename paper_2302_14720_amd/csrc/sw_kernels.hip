@@ -179,6 +179,14 @@ __device__ __forceinline__ void decode16_potts_remote(const Dev &d, const uint4 
     }
 }
 
+// Bits 0-7 of v at the even positions of a 16-bit mask.
+__device__ __forceinline__ uint32_t spread8(uint32_t v) {
+    v &= 0xFFu;
+    v = (v | (v << 4)) & 0x0F0Fu;
+    v = (v | (v << 2)) & 0x3333u;
+    return (v | (v << 1)) & 0x5555u;
+}
+
 // =====================================================================
 // k_tile: bonds (Sec. 2.1), tile-local clusters (Sec. 2.3), new spins of
 // tile-interior clusters (Sec. 2.4), measurement of the incoming
@@ -227,6 +235,8 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
     Row *const s_eb = s_ebnb;
     __shared__ Row s_fb[TW];
     __shared__ Row s_xn;
+    __shared__ Row s_pw;          // permitted incoming bonds by row (from the W tile's last column)
+    __shared__ uint32_t s_ps[2];  // and by column, even and odd (from the S tile's last row)
     __shared__ uint32_t s_eup[NPL * EW];
     __shared__ uint32_t s_xe[EW];
     __shared__ uint32_t s_bf[NW];
@@ -253,6 +263,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
     const uint32_t gy = ty * TW + ly, gx0 = tx * TW + x0;
     const uint32_t east = ty * ntx + (tx + 1u == ntx ? 0u : tx + 1u);
     const uint32_t north = (ty + 1u == ntx ? 0u : ty + 1u) * ntx + tx;
+    const uint32_t txw = tx == 0u ? ntx - 1u : tx - 1u, tys = ty == 0u ? ntx - 1u : ty - 1u;
     const uint32_t gbe = ref_base(d, tx + 1u == ntx ? 0u : tx + 1u, ty);
     const uint32_t gbn = ref_base(d, tx, ty + 1u == ntx ? 0u : ty + 1u);
     const uint32_t rowbase = ly * PS;  // padded index of the row's first site
@@ -277,6 +288,12 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
         const uint32_t gxe = (gx0 + 16u == L) ? 0u : gx0 + 16u;
         ve = (uint8_t)sin[(size_t)gy * L + gxe];
     }
+    // and the neighbours whose bonds come in through the W and S edges
+    uint4 vs = make_uint4(0u, 0u, 0u, 0u);
+    const uint32_t xw = txw * TW + TW - 1u, ys = tys * TW + TW - 1u;
+    uint32_t vw = 0u;
+    if (ly == 0u) vs = *reinterpret_cast<const uint4 *>(sin + (size_t)ys * L + gx0);
+    if (seg == 0u) vw = (uint8_t)sin[(size_t)gy * L + xw];
     // the bond words of this lane's 16 sites (Sec. 2.1), drawn while the
     // loads are in flight: bit 2j (2j+1) of rE / rN is the E / N edge of
     // site 2j (2j+1) past the lane's first site, set iff its word is below T
@@ -285,11 +302,11 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
         const uint32_t c0 = (gy * L + gx0) >> 1;
         const uint32_t T = d.T;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
+        for (int j = 7; j >= 0; --j) {
             uint32_t w0 = c0 + (uint32_t)j, w1 = t, w2 = 0u, w3 = 0u;
             philox10(w0, w1, w2, w3, d.seed_lo, d.seed_hi);
-            rE |= ((uint32_t)(w0 < T) << (2 * j)) | ((uint32_t)(w2 < T) << (2 * j + 1));
-            rN |= ((uint32_t)(w1 < T) << (2 * j)) | ((uint32_t)(w3 < T) << (2 * j + 1));
+            rE = shift_in_below(shift_in_below(rE, w2, T), w0, T);
+            rN = shift_in_below(shift_in_below(rN, w3, T), w1, T);
         }
     }
     load_table<TW, POTTS, TWO>(d, tile, ref_base(d, tx, ty), pp, s_tab, tid);
@@ -322,6 +339,27 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
             s_fb[tid] = q == 0 ? w0 : q == 1 ? w1 : q == 2 ? w2 : w3;
         }
     }
+    // The neighbours' words of the bonds that come in (they own those edges):
+    // one lane per row (site (xw, y), whose E word is word 2: xw is odd) and
+    // one per two columns, 1.5 calls per 64 of a tile side beside its 8 per 16
+    // sites.  With them only clusters that do go on outside become nodes: 48
+    // of the 80 that touch the edge of a 64-wide tile at beta_c.
+    {
+        const uint32_t r = TW == 64 ? tid - 64u : tid, c = TW == 64 ? tid - 128u : tid - 32u;
+        const bool isw = r < (uint32_t)TW, iss = c < (uint32_t)TW / 2u;
+        if (TW == 32 || (tid >= 64u && tid < 192u)) {
+            uint32_t w0 = (isw ? (ty * TW + r) * L + xw : iss ? ys * L + tx * TW + 2u * c : 0u) >> 1;
+            uint32_t w1 = t, w2 = 0u, w3 = 0u;
+            philox10(w0, w1, w2, w3, d.seed_lo, d.seed_hi);
+            const uint64_t bw = __ballot(isw && w2 < d.T);
+            const uint64_t b0 = __ballot(iss && w1 < d.T), b1 = __ballot(iss && w3 < d.T);
+            if (r == 0u) s_pw = (Row)bw;
+            if (c == 0u) {
+                s_ps[0] = (uint32_t)(TW == 64 ? b0 : b0 >> 32);
+                s_ps[1] = (uint32_t)(TW == 64 ? b1 : b1 >> 32);
+            }
+        }
+    }
     for (uint32_t i = tid; i < (uint32_t)NW; i += NT) s_bf[i] = 0u;
     if (tid < EW) s_xe[tid] = 0u;
     if (tid < NPL * EW) s_eup[tid] = 0u;
@@ -338,6 +376,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
     // the east tile).  Potts: three bit planes per row, through LDS.
     uint32_t up = 0u, pl[3] = {0u, 0u, 0u};
     uint32_t upN = 0u, ebit = 0u;
+    uint32_t inS = 0u, inW = 0u;  // equal neighbours across the S edge (first row) and W edge (first column)
     if constexpr (POTTS) {
         decode16_potts(v, s_tab, pl);
 #pragma unroll
@@ -356,9 +395,26 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
             for (uint32_t b = 0; b < 3u; ++b)
                 if ((ev >> b) & 1u) atomicOr(&s_eup[b * EW + (ly >> 5)], 1u << (ly & 31u));
         }
+        // bit 0: the W neighbour's value equals this row's first site's
+        if (ly == 0u) {
+            uint32_t pn[3];
+            decode16_potts_remote<TW, TWO>(d, vs, tys * ntx + tx, ref_base(d, tx, tys), pn);
+            inS = ~((pl[0] ^ pn[0]) | (pl[1] ^ pn[1]) | (pl[2] ^ pn[2])) & 0xFFFFu;
+        }
+        if (seg == 0u) {
+            uint32_t wv;
+            remote_values<TW, true, TWO, 1>(d, &vw, ty * ntx + txw, ref_base(d, txw, ty), &wv);
+            inW = wv == ((pl[0] & 1u) | ((pl[1] & 1u) << 1) | ((pl[2] & 1u) << 2)) ? 1u : 0u;
+        }
         __syncthreads();
     } else {
         up = decode16<TW>(v, s_tab);
+        if (ly == 0u) inS = ~(up ^ decode16_remote<TWO>(d, vs, tys * ntx + tx, ref_base(d, tx, tys))) & 0xFFFFu;
+        if (seg == 0u) {
+            uint32_t wv;
+            remote_values<TW, false, TWO, 1>(d, &vw, ty * ntx + txw, ref_base(d, txw, ty), &wv);
+            inW = ~(up ^ wv) & 1u;
+        }
         const uint32_t upA = (uint32_t)__shfl_down((int)up, (int)RPT, 64);
         const uint32_t upR = (uint32_t)__shfl_down((int)up, 1, 64);
         if (wlast)
@@ -376,6 +432,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
     int32_t e_part, m_part;
     uint32_t cpk[4] = {0u, 0u, 0u, 0u};
     uint32_t bE, bN;
+    uint32_t linked = 0u;  // this lane's sites with a bond out of the tile, either way
     {
         uint32_t eqE, eqN;
         if constexpr (POTTS) {
@@ -406,12 +463,16 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
         bN = eqN & rN;
         if (seg == RPT - 1) {
             if (bE >> 15) atomicOr(&s_xe[ly >> 5], 1u << (ly & 31u));
+            linked = bE & 0x8000u;
             bE &= 0x7FFFu;
         }
         if (ly == TW - 1) {
             reinterpret_cast<uint16_t *>(&s_xn)[seg] = (uint16_t)bN;
+            linked |= bN;
             bN = 0u;
         }
+        if (ly == 0u) linked |= inS & (spread8(s_ps[0] >> (x0 / 2u)) | (spread8(s_ps[1] >> (x0 / 2u)) << 1));
+        if (seg == 0u) linked |= inW & (uint32_t)(s_pw >> ly);
         reinterpret_cast<uint16_t *>(s_eb)[ly * RPT + seg] = (uint16_t)bE;
     }
     const Row E0 = row_gather<TW>(bE);  // this row's E bonds inside the tile
@@ -482,11 +543,9 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
     // ---- cluster sizes.  Every run start in this lane's 16 sites is pointed
     // at its root and adds the whole run's length (read off the row's
     // run-start mask; the run may go on into the next lanes' sites).  Runs
-    // that touch the tile edge mark their root: the S and N rows, the first
-    // run of every row (x = 0) and the run holding x = TW - 1.
+    // with a bond out of the tile mark their root.
     uint32_t rootmask = 0u;
     {
-        const bool edge_row = ly == 0u || ly == TW - 1u;
         // where the run holding the lane's last site ends: the first run
         // start past the lane's 16 sites, or the row's end
         uint32_t end_out = (uint32_t)TW;
@@ -507,7 +566,9 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
                 __hip_atomic_store(word_at(s_par, n), root, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             else
                 rootmask |= 1u << i;
-            if (edge_row || (seg == 0u && i == 0u) || (seg == RPT - 1u && m == 0u)) {
+            // the run's sites in this lane: up to the next start or the lane's last
+            const uint32_t upto = m ? (m & (0u - m)) - 1u : 0xFFFFu;
+            if ((linked & upto) >> i) {
                 const uint32_t rsite = root / 4u - root / (4u * PS);
                 atomicOr(&s_bf[rsite >> 5], 1u << (rsite & 31u));
             }
@@ -522,9 +583,8 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
         if (acc_len != 0u)
             __hip_atomic_fetch_add(word_at(s_par, acc_root), acc_len << 16, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_WORKGROUP);
-        // a segment that starts inside a run which reaches the S or N edge,
-        // or (last segment of a row) holds no run start of its own
-        if (!(st & 1u) && (edge_row || (seg == RPT - 1u && st == 0u))) {
+        // a segment that starts inside a run: its sites before the first start
+        if (linked & (st ? (st & (0u - st)) - 1u : 0xFFFFu)) {
             const uint32_t root = lds_root_b(s_par, rs0);
             const uint32_t rsite = root / 4u - root / (4u * PS);
             atomicOr(&s_bf[rsite >> 5], 1u << (rsite & 31u));
@@ -532,7 +592,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
     }
     __syncthreads();
 
-    // ---- number the boundary clusters (nodes) in site order: every
+    // ---- number the clusters that go on outside (nodes) in site order: every
     // wavefront scans the marks itself, lane l holding the prefix of mark
     // words (NW / 64) l .. (NW / 64) (l + 1) - 1
     uint32_t pf_a, pf_b, n_nodes;
@@ -554,14 +614,15 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
         }
         pf_a = incl - c;
         pf_b = pf_a + __popc(wa);
-        // at most 4 (TW - 1) boundary clusters; the bound keeps the node
+        // at most 4 (TW - 1) of them; the bound keeps the node
         // tables in their slots whatever the marks
         n_nodes = min((uint32_t)__shfl((int)incl, 63, 64), 4u * ((uint32_t)TW - 1u));
     }
 
     // ---- roots: output byte into the root's word; node entries staged in
-    // LDS; interior-cluster statistics (size classes 0-2 packed in one
-    // register, 10 bits each)
+    // LDS; statistics of the clusters complete in the tile (size classes 0-2
+    // packed in one register, 11, 10 and 11 bits: a wavefront's 1024 sites may
+    // all be single)
     uint32_t max_int = 0u, sq_int = 0u, hpk = 0u;
     {
         const uint32_t sbase = srow + x0;  // site index of this lane's first site
@@ -598,7 +659,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
                 sq_int += S * S;
                 const uint32_t bin = 31u - (uint32_t)__clz((int)S);
                 if (bin < 3u)
-                    hpk += 1u << (10u * bin);
+                    hpk += 1u << (11u * bin - (bin >> 1));
                 else
                     atomicAdd(&s_hist[bin], 1u);
                 if constexpr (DENSE) {
@@ -655,16 +716,19 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
         lp[3] = make_uint4(lab[12], lab[13], lab[14], lab[15]);
     }
     {
-        // node index of every edge site (all of them belong to nodes)
+        // node index of every edge site that belongs to a node (read only
+        // where the bond through the edge is set): bytes less CB
         uint8_t *eg = d.edge + (size_t)tile * 4u * TW;
-        // (every edge byte is a node code, so the bytewise subtraction never borrows)
-        constexpr uint32_t CB4 = CB * 0x01010101u;
+        auto less = [](uint32_t w) {  // bytewise, without borrows between the bytes
+            constexpr uint32_t CB4 = CB * 0x01010101u, H = 0x80808080u;
+            return ((w | H) - CB4) ^ (~w & H);
+        };
         if (seg == 0u) eg[0 * TW + ly] = (uint8_t)((out[0] & 0xFFu) - CB);
         if (seg == RPT - 1u) eg[1 * TW + ly] = (uint8_t)((out[3] >> 24) - CB);
         if (ly == 0u)
-            *reinterpret_cast<uint4 *>(eg + 2 * TW + x0) = make_uint4(out[0] - CB4, out[1] - CB4, out[2] - CB4, out[3] - CB4);
+            *reinterpret_cast<uint4 *>(eg + 2 * TW + x0) = make_uint4(less(out[0]), less(out[1]), less(out[2]), less(out[3]));
         if (ly == (uint32_t)TW - 1u)
-            *reinterpret_cast<uint4 *>(eg + 3 * TW + x0) = make_uint4(out[0] - CB4, out[1] - CB4, out[2] - CB4, out[3] - CB4);
+            *reinterpret_cast<uint4 *>(eg + 3 * TW + x0) = make_uint4(less(out[0]), less(out[1]), less(out[2]), less(out[3]));
     }
     // energy and magnetisation packed as (e + 32) | (m + 16) << 16 per lane:
     // the wavefront sums stay below 2^13 and 2^12
@@ -704,9 +768,9 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
                 e += (int32_t)(ew & 0xFFFFu) - 32 * 64;
                 m += (int32_t)(ew >> 16) - 16 * 64;
             }
-            b0 += (int32_t)(hw & 0x3FFu);
-            b1 += (int32_t)((hw >> 10) & 0x3FFu);
-            b2 += (int32_t)(hw >> 20);
+            b0 += (int32_t)(hw & 0x7FFu);
+            b1 += (int32_t)((hw >> 11) & 0x3FFu);
+            b2 += (int32_t)(hw >> 21);
             mx = max(mx, s_red[w][2]);
             sq += s_red[w][3];
         }
@@ -867,7 +931,7 @@ __device__ __forceinline__ void ulocal_body(const Dev &d, const uint32_t ugroup)
     const uint32_t gt = tile_of(mt);
     for (uint32_t k = mk; k < nkt; k += 16u) {
         const uint32_t li = mt * kNodeSlots + k;
-        const uint32_t r = lds_root(s_p, li);
+        const uint32_t r = lds_find(s_p, li);
         if (r != li) par[gt * kNodeSlots + k] = tile_of(r / kNodeSlots) * kNodeSlots + r % kNodeSlots;
     }
 }
@@ -1513,6 +1577,26 @@ __device__ __forceinline__ void join_pairs(uint32_t *par, uint32_t *list, const 
     __builtin_amdgcn_wave_barrier();
 }
 
+// A first step for join_pairs: every pair hooks its larger index under the
+// smallest it meets, compress() points all entries at their roots, and pairs
+// that share a root are done.  Level 2 of 1024^2 (beta = 0.44, 3264 clusters):
+// unions 9.6 -> 6.8 us; of 512^2 (758) 4.4 -> 4.7.
+template <uint32_t R, class Compress>
+__device__ __forceinline__ void hook_pairs(uint32_t *par, uint32_t *a, uint32_t *b, Compress &&compress) {
+#pragma unroll
+    for (uint32_t u = 0; u < R; ++u)
+        if (a[u] != kEmpty) atomicMin(&par[max(a[u], b[u])], min(a[u], b[u]));
+    __syncthreads();
+    compress();
+    __syncthreads();
+#pragma unroll
+    for (uint32_t u = 0; u < R; ++u) {
+        const uint32_t ra = a[u] != kEmpty ? lds_load(&par[a[u]]) : kEmpty, rb = a[u] != kEmpty ? lds_load(&par[b[u]]) : kEmpty;
+        a[u] = ra == rb ? kEmpty : ra;
+        b[u] = rb;
+    }
+}
+
 // What level 2 loads of the groups' results, in batches whose loads overlap;
 // the first batch is loaded while the clusters are being counted.  Clusters:
 // a wavefront takes a group at a time, kEnt rounds of 64 (about 200 are
@@ -1530,14 +1614,18 @@ struct TopLoads {
             e[u] = g < ng && j < kRefSlots ? ag_load(&d.gnode[(size_t)g * kRefSlots + j]) : 0u;
         }
     }
-    // group g, its neighbour nb and the place p of position f
-    static __device__ __forceinline__ bool place(const Dev &d, uint32_t f, uint32_t ngx, uint32_t &g, uint32_t &nb,
+    // Group g, its neighbour nb, the direction and the place p of position f,
+    // the f0-th and following 64 of a wavefront: all but the place (and, with
+    // 32-wide tiles, the tile it lies in) are the same for its lanes and
+    // computed once, on the scalar unit.
+    static __device__ __forceinline__ bool place(const Dev &d, uint32_t f0, uint32_t ngx, uint32_t &g, uint32_t &nb,
                                                  uint32_t &dir, uint32_t &p) {
         const uint32_t lw = d.tw == 64u ? 6u : 5u, per = 8u << lw;
-        const bool in = f < ngx * ngx * per;
-        g = in ? f >> (lw + 3u) : 0u;
-        dir = (f >> (lw + 2u)) & 1u;
-        p = f & ((4u << lw) - 1u);
+        const uint32_t fw = (uint32_t)__builtin_amdgcn_readfirstlane((int)f0);
+        const bool in = fw < ngx * ngx * per;
+        g = in ? fw >> (lw + 3u) : 0u;
+        dir = (fw >> (lw + 2u)) & 1u;
+        p = (fw & ((4u << lw) - 1u)) + (threadIdx.x & 63u);
         const uint32_t gy = g / ngx, gx = g - gy * ngx;
         nb = dir == 0u ? gy * ngx + (gx + 1u == ngx ? 0u : gx + 1u) : (gy + 1u == ngx ? 0u : gy + 1u) * ngx + gx;
         return in && (dir == 0u ? gy : gx) * kUG + (p >> lw) < d.ntx;
@@ -1546,7 +1634,7 @@ struct TopLoads {
 #pragma unroll
         for (uint32_t u = 0; u < kPos; ++u) {
             uint32_t g, nb, dir, p;
-            const bool ok = place(d, f0 + kMergeThreads * u + threadIdx.x, ngx, g, nb, dir, p);
+            const bool ok = place(d, f0 + kMergeThreads * u + (threadIdx.x & ~63u), ngx, g, nb, dir, p);
             a[u] = ok ? ag_load(&d.gedge[(size_t)g * kRefSlots + dir * 256u + p]) : kNoRef;
             b[u] = ok ? ag_load(&d.gedge[(size_t)nb * kRefSlots + (2u + dir) * 256u + p]) : kNoRef;
         }
@@ -1560,7 +1648,7 @@ template <bool LDS>
 __device__ __forceinline__ void merge_top(const Dev &d, uint32_t ng, uint32_t ngx, uint32_t t, const uint32_t *s_off,
                                           TopLoads &ld1, uint32_t *par, uint32_t *sz, uint32_t *key,
                                           unsigned long long *s_acc) {
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, wv = tid >> 6;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     auto ld = [](uint32_t *p) { return LDS ? lds_load(p) : g_load(p); };
     auto st = [](uint32_t *p, uint32_t v) {
         if (LDS)
@@ -1583,12 +1671,15 @@ __device__ __forceinline__ void merge_top(const Dev &d, uint32_t ng, uint32_t ng
 #pragma unroll
         for (uint32_t u = 0; u < TopLoads::kPos; ++u) {
             uint32_t g, nb, dir, p;
-            TopLoads::place(d, f0 + kMergeThreads * u + tid, ngx, g, nb, dir, p);
+            TopLoads::place(d, f0 + kMergeThreads * u + (tid & ~63u), ngx, g, nb, dir, p);
             const bool has = ld1.a[u] != kNoRef && ld1.b[u] != kNoRef;
             ld1.a[u] = has ? s_off[g] + ld1.a[u] : kEmpty;
             ld1.b[u] = has ? s_off[nb] + ld1.b[u] : kEmpty;
         }
         if (LDS) {  // the lists lie where sizes and keys go afterwards
+            hook_pairs<TopLoads::kPos>(par, ld1.a, ld1.b, [&] {
+                for (uint32_t i = tid; i < m; i += kMergeThreads) lds_store(&par[i], lds_find(par, i));
+            });
             join_pairs<TopLoads::kPos>(par, sz + wv * 64u * TopLoads::kPos, ld1.a, ld1.b);
         } else {
 #pragma unroll
@@ -1647,7 +1738,10 @@ __device__ __forceinline__ void merge_body(const Dev &d, const uint32_t ug) {
     __shared__ uint32_t s_off[kMergeGroups + 1u];
     __shared__ unsigned long long s_acc[GP_END];
     __shared__ int s_last;
-    const uint32_t tid = threadIdx.x, lane = tid & 63u, wv = tid >> 6;
+    // (index arithmetic that is the same for a wavefront's lanes goes to the
+    // scalar unit: a workgroup of 16 wavefronts on one CU is bound by the
+    // instructions it issues)
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wv = (uint32_t)__builtin_amdgcn_readfirstlane((int)(tid >> 6));
     const uint64_t tsw = *d.tdev;
     const uint32_t t = (uint32_t)tsw, pc = (uint32_t)(tsw & 1u);
     const uint32_t ntx = d.ntx, tw = d.tw, lw = tw == 64u ? 6u : 5u;
@@ -1662,9 +1756,10 @@ __device__ __forceinline__ void merge_body(const Dev &d, const uint32_t ug) {
     uint32_t uo[2];            // its place on the group's perimeter
 #pragma unroll
     for (uint32_t u = 0; u < 2u; ++u) {
-        const uint32_t f = tid + kMergeThreads * u, T = (f >> (lw + 1u)) & 15u, dir = (f >> lw) & 1u, i = f & (tw - 1u);
+        const uint32_t fw = 64u * wv + kMergeThreads * u, T = (fw >> (lw + 1u)) & 15u;  // (the tile is the wavefront's)
+        const uint32_t f = fw + lane, dir = (f >> lw) & 1u, i = f & (tw - 1u);
         const uint32_t lx = T % kUG, ly = T / kUG, tx = gx * kUG + lx, ty = gy * kUG + ly;
-        const bool ok = f < (32u << lw) && tx < ntx && ty < ntx;
+        const bool ok = fw < (32u << lw) && tx < ntx && ty < ntx;
         const uint32_t A = ok ? ty * ntx + tx : 0u;
         const uint32_t nx = dir == 0u ? (tx + 1u == ntx ? 0u : tx + 1u) : tx;
         const uint32_t ny = dir == 0u ? ty : (ty + 1u == ntx ? 0u : ty + 1u);

@@ -2,7 +2,12 @@
 // and in global memory (device scope).  Roots are the smallest index of
 // their set: a root is linked under the root with the smaller index, so
 // every parent is smaller than its child and the structure stays a forest
-// whatever order concurrent unions run in.
+// whatever order concurrent unions run in.  (Linking in the order of the
+// bit-reversed indices makes shallower trees -- k_union 66 -> 53 us at
+// 16384^2, beta_c -- but roots whose smallest site lies elsewhere in the
+// cluster: the minimum of the sites then takes one more atomic per workgroup
+// and root, and k_flatten went from 80 to 101 us, the cubic k_bflat3 from 175
+// to 234.)
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -16,25 +21,10 @@ __device__ __forceinline__ uint32_t lds_load(uint32_t *p) {
 __device__ __forceinline__ void lds_store(uint32_t *p, uint32_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
-// Path halving lowers entries with atomicMin: a plain store could overwrite
-// a fully compressed entry (the root) with a larger ancestor read earlier by
-// another thread, whereas with min-updates every entry only ever decreases
-// towards its root.
+// Root of a once the unions are done (read-only).
 __device__ __forceinline__ uint32_t lds_find(uint32_t *par, uint32_t a) {
     while (true) {
         const uint32_t p = lds_load(&par[a]);
-        if (p == a) return a;
-        const uint32_t gp = lds_load(&par[p]);
-        if (gp == p) return p;
-        atomicMin(&par[a], gp);
-        a = gp;
-    }
-}
-// Root of a once the unions are done (read-only; parents are the low 16
-// bits, the high half of a root's word may hold other data).
-__device__ __forceinline__ uint32_t lds_root(const uint32_t *par, uint32_t a) {
-    while (true) {
-        const uint32_t p = par[a] & 0xFFFFu;
         if (p == a) return a;
         a = p;
     }
