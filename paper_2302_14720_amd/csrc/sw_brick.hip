@@ -117,7 +117,7 @@ __device__ __forceinline__ void brick_measure(const Dev &d, uint32_t b, const Eq
     // Ising: both sums offset to be non-negative, 16 bits each per wavefront
     uint32_t em = POTTS ? (uint32_t)eq : (uint32_t)eq | ((uint32_t)__popc(pl[0]) << 16);
     uint32_t cpk[4] = {0u, 0u, 0u, 0u};
-    if constexpr (POTTS) potts_counts(pl, cpk);
+    if constexpr (POTTS) potts_counts<0xFFFFu>(pl, cpk);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         em += __shfl_xor(em, o, 64);

@@ -24,7 +24,8 @@ __device__ __forceinline__ uint32_t shift_in_below(uint32_t m, uint32_t w, uint3
 
 // Equal-neighbour masks of 16 sites from their bit planes and those of the
 // E and N neighbours; equal pairs and the population of every value 0..7
-// (two 16-bit counts per word).
+// (two 16-bit counts per word).  M: the sites of the masks.
+template <uint32_t M>
 __device__ __forceinline__ void potts_counts(const uint32_t pl[3], uint32_t cpk[4]) {
 #pragma unroll
     for (int k = 0; k < 8; k += 2) {
@@ -33,7 +34,7 @@ __device__ __forceinline__ void potts_counts(const uint32_t pl[3], uint32_t cpk[
         for (int h = 0; h < 2; ++h) {
             const int v = k + h;
             const uint32_t m = ~((pl[0] ^ ((v & 1) ? 0xFFFFu : 0u)) | (pl[1] ^ ((v & 2) ? 0xFFFFu : 0u)) |
-                                 (pl[2] ^ ((v & 4) ? 0xFFFFu : 0u))) & 0xFFFFu;
+                                 (pl[2] ^ ((v & 4) ? 0xFFFFu : 0u))) & M;
             c[h] = (uint32_t)__popc(m);
         }
         cpk[k >> 1] = c[0] | (c[1] << 16);

@@ -27,17 +27,60 @@ __device__ __forceinline__ uint32_t hsb_le(uint32_t B, uint32_t x) {
     return 31u - (uint32_t)__clz((int)m);
 }
 
-// The TW-bit row mask whose 16-bit pieces (piece k at bit 16 k) are held by
-// the RPT = TW / 16 consecutive lanes of a tile row (a quad for TW = 64, a
-// pair for TW = 32): data-parallel moves within quads, no LDS.
+// A lane's segment of SPT consecutive sites (bytes).
+template <int SPT> struct Seg {
+    uint32_t w[SPT / 4];
+};
+template <int SPT> __device__ __forceinline__ Seg<SPT> load_seg(const int8_t *p) {
+    Seg<SPT> v;
+    if constexpr (SPT == 16) {
+        const uint4 x = *reinterpret_cast<const uint4 *>(p);
+        v.w[0] = x.x;
+        v.w[1] = x.y;
+        v.w[2] = x.z;
+        v.w[3] = x.w;
+    } else {
+        v.w[0] = *reinterpret_cast<const uint32_t *>(p);
+    }
+    return v;
+}
+template <int SPT> __device__ __forceinline__ void store_seg(void *p, const uint32_t *w) {
+    if constexpr (SPT == 16)
+        *reinterpret_cast<uint4 *>(p) = make_uint4(w[0], w[1], w[2], w[3]);
+    else
+        *reinterpret_cast<uint32_t *>(p) = w[0];
+}
+template <int SPT> __device__ __forceinline__ uint32_t byte_at(const Seg<SPT> &v, int q) {
+    return (v.w[q >> 2] >> (8 * (q & 3))) & 0xFFu;
+}
+
+// The TW-bit row mask whose SPT-bit pieces are held by the TW / SPT
+// consecutive lanes of a tile row: data-parallel moves within rows of 16
+// lanes, no LDS.  Four lanes (a quad) or two exchange their 16-bit pieces;
+// sixteen or eight or together their 4-bit pieces, each at its place.
+template <int CTRL> __device__ __forceinline__ uint32_t dpp(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, false);
+}
 template <int K, int RPT>
 __device__ __forceinline__ uint32_t row_piece(uint32_t v) {
-    constexpr int ctrl = RPT == 4 ? K * 0x55 : (K | (K << 2) | ((2 + K) << 4) | ((2 + K) << 6));
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, ctrl, 0xF, 0xF, false);
+    return dpp<RPT == 4 ? K * 0x55 : (K | (K << 2) | ((2 + K) << 4) | ((2 + K) << 6))>(v);
 }
-template <int TW>
-__device__ __forceinline__ typename RowOf<TW>::T row_gather(uint32_t piece) {
-    if constexpr (TW == 64) {
+template <int RPT> __device__ __forceinline__ uint32_t row_or(uint32_t v) {
+    v |= dpp<0xB1>(v);   // lane ^ 1
+    v |= dpp<0x4E>(v);   // lane ^ 2
+    v |= dpp<0x141>(v);  // the other quad of 8 lanes
+    if constexpr (RPT == 16) v |= dpp<0x140>(v);  // the other half of 16
+    return v;
+}
+template <int TW, int SPT>
+__device__ __forceinline__ typename RowOf<TW>::T row_gather(uint32_t piece, uint32_t seg) {
+    if constexpr (SPT == 4 && TW == 64) {
+        const uint32_t v = piece << (4u * (seg & 7u));
+        const uint32_t lo = row_or<16>(seg < 8u ? v : 0u), hi = row_or<16>(seg < 8u ? 0u : v);
+        return lo | ((uint64_t)hi << 32);
+    } else if constexpr (SPT == 4) {
+        return row_or<8>(piece << (4u * seg));
+    } else if constexpr (TW == 64) {
         const uint64_t lo = row_piece<0, 4>(piece) | (row_piece<1, 4>(piece) << 16);
         const uint64_t hi = row_piece<2, 4>(piece) | (row_piece<3, 4>(piece) << 16);
         return lo | (hi << 32);
@@ -72,11 +115,6 @@ __device__ __forceinline__ uint32_t ref_base(const Dev &d, uint32_t tx, uint32_t
     return ((ty / kUG) * ((d.ntx + kUG - 1u) / kUG) + tx / kUG) * kRefSlots;
 }
 
-__device__ __forceinline__ uint32_t byte_at(const uint4 &v, int q) {
-    const uint32_t w = q < 4 ? v.x : q < 8 ? v.y : q < 12 ? v.z : v.w;
-    return (w >> (8 * (q & 3))) & 0xFFu;
-}
-
 // Shared front end of k_tile and k_resolve: the table that maps every byte
 // of this tile's previous output to its spin as an up bit (1 for +1): final
 // spins 0x01 / 0xFF map to themselves, node code 2 + k to the spin of node
@@ -90,10 +128,9 @@ template <int TW> constexpr uint32_t potts_code() { return TW == 64 ? 4u : 8u; }
 
 // The node spins are loaded whether or not the node exists (every slot is
 // in bounds), so that this load does not wait for the node count.
-template <int TW, bool POTTS, int TWO>
+template <int TW, bool POTTS, int TWO, int NT>
 __device__ __forceinline__ void load_table(const Dev &d, uint32_t tile, uint32_t gb, uint32_t pp, uint8_t *s_tab,
                                            uint32_t tid) {
-    constexpr int NT = TW * TW / 16;
     const uint32_t kprev = min(d.nk[pp][tile], 252u);
     for (uint32_t b = tid; b < 256u; b += NT) {
         uint8_t val;
@@ -112,11 +149,11 @@ __device__ __forceinline__ void load_table(const Dev &d, uint32_t tile, uint32_t
     }
 }
 
-template <int TW>
-__device__ __forceinline__ uint32_t decode16(const uint4 &v, const uint8_t *s_tab) {
+template <int SPT>
+__device__ __forceinline__ uint32_t decode(const Seg<SPT> &v, const uint8_t *s_tab) {
     uint32_t up = 0;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) up |= (uint32_t)s_tab[byte_at(v, q)] << q;
+    for (int q = 0; q < SPT; ++q) up |= (uint32_t)s_tab[byte_at(v, q)] << q;
     return up;
 }
 
@@ -140,22 +177,24 @@ __device__ __forceinline__ void remote_values(const Dev &d, const uint32_t *b, u
     for (int q = 0; q < N; ++q) val[q] = value_of<POTTS, TWO>(d, val[q]);
 }
 
-template <int TWO>
-__device__ __forceinline__ uint32_t decode16_remote(const Dev &d, const uint4 &v, uint32_t tile, uint32_t gb) {
-    uint32_t b[16], x[16], up = 0;
+template <int TWO, int SPT>
+__device__ __forceinline__ uint32_t decode_remote(const Dev &d, const Seg<SPT> &v, uint32_t tile, uint32_t gb) {
+    uint32_t b[SPT], x[SPT], up = 0;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) b[q] = byte_at(v, q);
-    remote_values<64, false, TWO, 16>(d, b, tile, gb, x);
+    for (int q = 0; q < SPT; ++q) b[q] = byte_at(v, q);
+    remote_values<64, false, TWO, SPT>(d, b, tile, gb, x);
 #pragma unroll
-    for (int q = 0; q < 16; ++q) up |= x[q] << q;
+    for (int q = 0; q < SPT; ++q) up |= x[q] << q;
     return up;
 }
 
-// Values of 16 sites as three bit planes (bit q of pl[i] = bit i of site q).
-__device__ __forceinline__ void decode16_potts(const uint4 &v, const uint8_t *s_tab, uint32_t pl[3]) {
+// Values of a segment's sites as three bit planes (bit q of pl[i] = bit i of
+// site q).
+template <int SPT>
+__device__ __forceinline__ void decode_potts(const Seg<SPT> &v, const uint8_t *s_tab, uint32_t pl[3]) {
     pl[0] = pl[1] = pl[2] = 0u;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
+    for (int q = 0; q < SPT; ++q) {
         const uint32_t x = s_tab[byte_at(v, q)];
         pl[0] |= (x & 1u) << q;
         pl[1] |= ((x >> 1) & 1u) << q;
@@ -163,16 +202,16 @@ __device__ __forceinline__ void decode16_potts(const uint4 &v, const uint8_t *s_
     }
 }
 
-template <int TW, int TWO>
-__device__ __forceinline__ void decode16_potts_remote(const Dev &d, const uint4 &v, uint32_t tile, uint32_t gb,
-                                                      uint32_t pl[3]) {
-    uint32_t b[16], x[16];
+template <int TW, int TWO, int SPT>
+__device__ __forceinline__ void decode_potts_remote(const Dev &d, const Seg<SPT> &v, uint32_t tile, uint32_t gb,
+                                                    uint32_t pl[3]) {
+    uint32_t b[SPT], x[SPT];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) b[q] = byte_at(v, q);
-    remote_values<TW, true, TWO, 16>(d, b, tile, gb, x);
+    for (int q = 0; q < SPT; ++q) b[q] = byte_at(v, q);
+    remote_values<TW, true, TWO, SPT>(d, b, tile, gb, x);
     pl[0] = pl[1] = pl[2] = 0u;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
+    for (int q = 0; q < SPT; ++q) {
         pl[0] |= (x[q] & 1u) << q;
         pl[1] |= ((x[q] >> 1) & 1u) << q;
         pl[2] |= ((x[q] >> 2) & 1u) << q;
@@ -206,11 +245,17 @@ __device__ __forceinline__ uint32_t spread8(uint32_t v) {
 // DENSE: interior clusters also go to the exact size histogram -- those
 // below kDenseBins sites through LDS counts that leave with the tile
 // (tdense) and are added up per group in k_roots.
-template <int TW, bool POTTS, bool DENSE, int TWO>
+// SPT: sites per thread, 16 or 4.  With 16 the row masks cost least per site
+// and the tiles of a large lattice fill the GPU; a lattice of few tiles leaves
+// a wavefront or less per SIMD, which waits through every chain of its 16
+// sites alone, so there four times as many threads take 4 each (512^2,
+// beta_c: 22 -> 14 us).
+template <int TW, bool POTTS, bool DENSE, int TWO, int SPT>
 __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
     using Row = typename RowOf<TW>::T;
-    constexpr int NT = TW * TW / 16;
-    constexpr uint32_t RPT = TW / 16;
+    constexpr int NT = TW * TW / SPT;
+    constexpr uint32_t RPT = TW / SPT;  // lanes per row
+    constexpr uint32_t M = (1u << SPT) - 1u, TOP = 1u << (SPT - 1);  // a lane's sites, its last
     constexpr int NS = TW * TW;
     constexpr int NW = NS / 32;
     constexpr int NWAVE = (NT + 63) / 64;
@@ -259,7 +304,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
     int8_t *__restrict__ sout = d.spins[pp];
     uint32_t *__restrict__ par_cur = d.parent[pc];
 
-    const uint32_t ly = tid / RPT, seg = tid % RPT, x0 = seg * 16u;
+    const uint32_t ly = tid / RPT, seg = tid % RPT, x0 = seg * (uint32_t)SPT;
     const uint32_t gy = ty * TW + ly, gx0 = tx * TW + x0;
     const uint32_t east = ty * ntx + (tx + 1u == ntx ? 0u : tx + 1u);
     const uint32_t north = (ty + 1u == ntx ? 0u : ty + 1u) * ntx + tx;
@@ -277,24 +322,24 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
     const bool wlast = (ly % RPW) == RPW - 1u;
 
     // ---- issue the spin loads first, then build the node table
-    const uint4 v = *reinterpret_cast<const uint4 *>(sin + (size_t)gy * L + gx0);
-    uint4 vn = make_uint4(0u, 0u, 0u, 0u);
+    const Seg<SPT> v = load_seg<SPT>(sin + (size_t)gy * L + gx0);
+    Seg<SPT> vn{};
     if (POTTS ? ly == TW - 1 : wlast) {
         const uint32_t gyn = (gy + 1u == L) ? 0u : gy + 1u;
-        vn = *reinterpret_cast<const uint4 *>(sin + (size_t)gyn * L + gx0);
+        vn = load_seg<SPT>(sin + (size_t)gyn * L + gx0);
     }
     uint32_t ve = 0;
     if (seg == RPT - 1) {
-        const uint32_t gxe = (gx0 + 16u == L) ? 0u : gx0 + 16u;
+        const uint32_t gxe = (gx0 + SPT == L) ? 0u : gx0 + SPT;
         ve = (uint8_t)sin[(size_t)gy * L + gxe];
     }
     // and the neighbours whose bonds come in through the W and S edges
-    uint4 vs = make_uint4(0u, 0u, 0u, 0u);
+    Seg<SPT> vs{};
     const uint32_t xw = txw * TW + TW - 1u, ys = tys * TW + TW - 1u;
     uint32_t vw = 0u;
-    if (ly == 0u) vs = *reinterpret_cast<const uint4 *>(sin + (size_t)ys * L + gx0);
+    if (ly == 0u) vs = load_seg<SPT>(sin + (size_t)ys * L + gx0);
     if (seg == 0u) vw = (uint8_t)sin[(size_t)gy * L + xw];
-    // the bond words of this lane's 16 sites (Sec. 2.1), drawn while the
+    // the bond words of this lane's sites (Sec. 2.1), drawn while the
     // loads are in flight: bit 2j (2j+1) of rE / rN is the E / N edge of
     // site 2j (2j+1) past the lane's first site, set iff its word is below T
     uint32_t rE = 0u, rN = 0u;
@@ -302,23 +347,23 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
         const uint32_t c0 = (gy * L + gx0) >> 1;
         const uint32_t T = d.T;
 #pragma unroll
-        for (int j = 7; j >= 0; --j) {
+        for (int j = SPT / 2 - 1; j >= 0; --j) {
             uint32_t w0 = c0 + (uint32_t)j, w1 = t, w2 = 0u, w3 = 0u;
             philox10(w0, w1, w2, w3, d.seed_lo, d.seed_hi);
             rE = shift_in_below(shift_in_below(rE, w2, T), w0, T);
             rN = shift_in_below(shift_in_below(rN, w3, T), w1, T);
         }
     }
-    load_table<TW, POTTS, TWO>(d, tile, ref_base(d, tx, ty), pp, s_tab, tid);
+    load_table<TW, POTTS, TWO, NT>(d, tile, ref_base(d, tx, ty), pp, s_tab, tid);
 
-    // Potts: the value each of this lane's 16 sites would give its cluster
+    // Potts: the value each of this lane's sites would give its cluster
     // as its root (4 bits per site): word i of the output for counter
     // {s >> 2, t, 3, 0} for site s = 4j + i past the lane's first site
     uint64_t pv = 0;
     if constexpr (POTTS) {
         const uint32_t r0 = gy * L + gx0, q = d.q;
 #pragma unroll
-        for (uint32_t j = 0; j < 4u; ++j) {
+        for (uint32_t j = 0; j < SPT / 4u; ++j) {
             uint32_t w0 = (r0 >> 2) + j, w1 = t, w2 = 3u, w3 = 0u;
             philox10(w0, w1, w2, w3, d.seed_lo, d.seed_hi);
             const uint64_t v4 = (uint64_t)(((uint64_t)w0 * q) >> 32) | ((((uint64_t)w1 * q) >> 32) << 4) |
@@ -345,9 +390,10 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
     // sites.  With them only clusters that do go on outside become nodes: 48
     // of the 80 that touch the edge of a 64-wide tile at beta_c.
     {
-        const uint32_t r = TW == 64 ? tid - 64u : tid, c = TW == 64 ? tid - 128u : tid - 32u;
+        constexpr uint32_t W0 = NT > 64 ? 64u : 0u;  // a wavefront other than the one above, if there is one
+        const uint32_t r = tid - W0, c = TW == 64 ? tid - 128u : tid - W0 - 32u;
         const bool isw = r < (uint32_t)TW, iss = c < (uint32_t)TW / 2u;
-        if (TW == 32 || (tid >= 64u && tid < 192u)) {
+        if (tid >= W0 && tid < W0 + (TW == 64 ? 128u : 64u)) {
             uint32_t w0 = (isw ? (ty * TW + r) * L + xw : iss ? ys * L + tx * TW + 2u * c : 0u) >> 1;
             uint32_t w1 = t, w2 = 0u, w3 = 0u;
             philox10(w0, w1, w2, w3, d.seed_lo, d.seed_hi);
@@ -370,23 +416,31 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
     __syncthreads();
 
     // ---- decode the incoming configuration (Sec. 2.5 measures it; Sec. 2.1
-    // bonds it).  Ising: the up-spin mask of the lane's 16 sites, of the 16
+    // bonds it).  Ising: the up-spin mask of the lane's sites, of the
     // sites above (lanes RPT further on, or decoded here by a wavefront's
     // last row) and the east neighbour of its last site (the next lane, or
     // the east tile).  Potts: three bit planes per row, through LDS.
+    // a lane's piece of a row mask in LDS
+    auto put_piece = [&](Row *row, uint32_t piece) {
+        if constexpr (SPT == 16) {
+            reinterpret_cast<uint16_t *>(row)[seg] = (uint16_t)piece;
+        } else {
+            const Row m = row_gather<TW, SPT>(piece, seg);
+            if (seg == 0u) *row = m;
+        }
+    };
     uint32_t up = 0u, pl[3] = {0u, 0u, 0u};
     uint32_t upN = 0u, ebit = 0u;
     uint32_t inS = 0u, inW = 0u;  // equal neighbours across the S edge (first row) and W edge (first column)
     if constexpr (POTTS) {
-        decode16_potts(v, s_tab, pl);
+        decode_potts(v, s_tab, pl);
 #pragma unroll
-        for (int b = 0; b < 3; ++b) reinterpret_cast<uint16_t *>(s_up + b * (TW + 1))[ly * RPT + seg] = (uint16_t)pl[b];
+        for (int b = 0; b < 3; ++b) put_piece(s_up + b * (TW + 1) + ly, pl[b]);
         if (ly == TW - 1) {
             uint32_t pn[3];
-            decode16_potts_remote<TW, TWO>(d, vn, north, gbn, pn);
+            decode_potts_remote<TW, TWO>(d, vn, north, gbn, pn);
 #pragma unroll
-            for (int b = 0; b < 3; ++b)
-                reinterpret_cast<uint16_t *>(s_up + b * (TW + 1))[TW * RPT + seg] = (uint16_t)pn[b];
+            for (int b = 0; b < 3; ++b) put_piece(s_up + b * (TW + 1) + TW, pn[b]);
         }
         if (seg == RPT - 1) {
             uint32_t ev;
@@ -398,8 +452,8 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
         // bit 0: the W neighbour's value equals this row's first site's
         if (ly == 0u) {
             uint32_t pn[3];
-            decode16_potts_remote<TW, TWO>(d, vs, tys * ntx + tx, ref_base(d, tx, tys), pn);
-            inS = ~((pl[0] ^ pn[0]) | (pl[1] ^ pn[1]) | (pl[2] ^ pn[2])) & 0xFFFFu;
+            decode_potts_remote<TW, TWO>(d, vs, tys * ntx + tx, ref_base(d, tx, tys), pn);
+            inS = ~((pl[0] ^ pn[0]) | (pl[1] ^ pn[1]) | (pl[2] ^ pn[2])) & M;
         }
         if (seg == 0u) {
             uint32_t wv;
@@ -408,8 +462,8 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
         }
         __syncthreads();
     } else {
-        up = decode16<TW>(v, s_tab);
-        if (ly == 0u) inS = ~(up ^ decode16_remote<TWO>(d, vs, tys * ntx + tx, ref_base(d, tx, tys))) & 0xFFFFu;
+        up = decode(v, s_tab);
+        if (ly == 0u) inS = ~(up ^ decode_remote<TWO>(d, vs, tys * ntx + tx, ref_base(d, tx, tys))) & M;
         if (seg == 0u) {
             uint32_t wv;
             remote_values<TW, false, TWO, 1>(d, &vw, ty * ntx + txw, ref_base(d, txw, ty), &wv);
@@ -418,7 +472,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
         const uint32_t upA = (uint32_t)__shfl_down((int)up, (int)RPT, 64);
         const uint32_t upR = (uint32_t)__shfl_down((int)up, 1, 64);
         if (wlast)
-            upN = ly == TW - 1 ? decode16_remote<TWO>(d, vn, north, gbn) : decode16<TW>(vn, s_tab);
+            upN = ly == TW - 1 ? decode_remote<TWO>(d, vn, north, gbn) : decode(vn, s_tab);
         else
             upN = upA;
         ebit = upR & 1u;
@@ -440,45 +494,47 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
 #pragma unroll
             for (int b = 0; b < 3; ++b) {
                 const Row rowv = s_up[b * (TW + 1) + ly];
-                const uint32_t pN = (uint32_t)(s_up[b * (TW + 1) + ly + 1] >> x0) & 0xFFFFu;
+                const uint32_t pN = (uint32_t)(s_up[b * (TW + 1) + ly + 1] >> x0) & M;
                 const uint32_t eb = (s_eup[b * EW + (ly >> 5)] >> (ly & 31u)) & 1u;
-                const uint32_t nxt = (x0 + 16u < (uint32_t)TW) ? ((uint32_t)(rowv >> (x0 + 16u)) & 1u) : eb;
-                const uint32_t pE = (pl[b] >> 1) | (nxt << 15);
+                const uint32_t nxt = (x0 + SPT < (uint32_t)TW) ? ((uint32_t)(rowv >> (x0 + SPT)) & 1u) : eb;
+                const uint32_t pE = (pl[b] >> 1) | (nxt << (SPT - 1));
                 dE |= pl[b] ^ pE;
                 dN |= pl[b] ^ pN;
             }
-            eqE = ~dE & 0xFFFFu;
-            eqN = ~dN & 0xFFFFu;
+            eqE = ~dE & M;
+            eqN = ~dN & M;
             e_part = __popc(eqE) + __popc(eqN);
             m_part = 0;
-            potts_counts(pl, cpk);
+            potts_counts<M>(pl, cpk);
         } else {
-            const uint32_t upE = (up >> 1) | (ebit << 15);
-            eqE = ~(up ^ upE) & 0xFFFFu;
-            eqN = ~(up ^ upN) & 0xFFFFu;
-            e_part = 2 * (__popc(eqE) + __popc(eqN)) - 32;
-            m_part = 2 * __popc(up) - 16;
+            const uint32_t upE = (up >> 1) | (ebit << (SPT - 1));
+            eqE = ~(up ^ upE) & M;
+            eqN = ~(up ^ upN) & M;
+            e_part = 2 * (__popc(eqE) + __popc(eqN)) - 2 * SPT;
+            m_part = 2 * __popc(up) - SPT;
         }
         bE = eqE & rE;
         bN = eqN & rN;
         if (seg == RPT - 1) {
-            if (bE >> 15) atomicOr(&s_xe[ly >> 5], 1u << (ly & 31u));
-            linked = bE & 0x8000u;
-            bE &= 0x7FFFu;
+            if (bE & TOP) atomicOr(&s_xe[ly >> 5], 1u << (ly & 31u));
+            linked = bE & TOP;
+            bE &= TOP - 1u;
         }
         if (ly == TW - 1) {
-            reinterpret_cast<uint16_t *>(&s_xn)[seg] = (uint16_t)bN;
+            put_piece(&s_xn, bN);
             linked |= bN;
             bN = 0u;
         }
-        if (ly == 0u) linked |= inS & (spread8(s_ps[0] >> (x0 / 2u)) | (spread8(s_ps[1] >> (x0 / 2u)) << 1));
+        if (ly == 0u) linked |= M & inS & (spread8(s_ps[0] >> (x0 / 2u)) | (spread8(s_ps[1] >> (x0 / 2u)) << 1));
         if (seg == 0u) linked |= inW & (uint32_t)(s_pw >> ly);
-        reinterpret_cast<uint16_t *>(s_eb)[ly * RPT + seg] = (uint16_t)bE;
+        if constexpr (SPT == 16) put_piece(&s_eb[ly], bE);
     }
-    const Row E0 = row_gather<TW>(bE);  // this row's E bonds inside the tile
-    const Row V = row_gather<TW>(bN);   // this row's N bonds inside the tile
+    const Row E0 = row_gather<TW, SPT>(bE, seg);  // this row's E bonds inside the tile
+    const Row V = row_gather<TW, SPT>(bN, seg);   // this row's N bonds inside the tile
+    if constexpr (SPT != 16)
+        if (seg == 0u) s_eb[ly] = E0;
     const Row B0 = (Row)~(Row)(E0 << 1);
-    const uint32_t st = (uint32_t)(B0 >> x0) & 0xFFFFu;
+    const uint32_t st = (uint32_t)(B0 >> x0) & M;
     const uint32_t rs0 = rowoff + 4u * hsb_le(B0, x0);  // byte offset of the run start at x0
     // the 64-wide Potts tile keeps its planes in s_par: wait until every
     // lane has read them
@@ -486,7 +542,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
     {
         uint32_t cur = rs0;
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
+        for (int q = 0; q < SPT; ++q) {
             if ((st >> q) & 1u) cur = rowoff + 4u * (x0 + (uint32_t)q);
             s_par[rowbase + x0 + q] = cur;
         }
@@ -505,7 +561,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
     if (ly + 1u < (uint32_t)TW) {
         const Row E1 = s_eb[ly + 1];
         const Row R = V & (Row)~(Row)((V << 1) & (E0 << 1) & (E1 << 1));
-        r = (uint32_t)(R >> x0) & 0xFFFFu;
+        r = (uint32_t)(R >> x0) & M;
     }
     const uint32_t lane = tid & 63u;
     const uint32_t wbase = (tid >> 6) * (64u / RPT) * PS;
@@ -515,7 +571,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
         uint32_t pre = 0u;
         nlist = 0u;
 #pragma unroll
-        for (int j = 0; j < 5; ++j) {
+        for (int j = 0; j < (SPT == 16 ? 5 : 3); ++j) {  // the bits of a count up to SPT
             const uint64_t bal = __ballot((c >> j) & 1u);
             pre += (uint32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
                                                       __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u))
@@ -540,18 +596,18 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
     }
     __syncthreads();
 
-    // ---- cluster sizes.  Every run start in this lane's 16 sites is pointed
+    // ---- cluster sizes.  Every run start in this lane's sites is pointed
     // at its root and adds the whole run's length (read off the row's
     // run-start mask; the run may go on into the next lanes' sites).  Runs
     // with a bond out of the tile mark their root.
     uint32_t rootmask = 0u;
     {
         // where the run holding the lane's last site ends: the first run
-        // start past the lane's 16 sites, or the row's end
+        // start past the lane's sites, or the row's end
         uint32_t end_out = (uint32_t)TW;
-        if (x0 + 16u < (uint32_t)TW) {
-            const Row past = (Row)(B0 >> (x0 + 16u));
-            if (past) end_out = x0 + 16u + (uint32_t)__builtin_ctzll((unsigned long long)past);
+        if (x0 + SPT < (uint32_t)TW) {
+            const Row past = (Row)(B0 >> (x0 + SPT));
+            if (past) end_out = x0 + SPT + (uint32_t)__builtin_ctzll((unsigned long long)past);
         }
         // lengths of consecutive runs with the same root are summed in a
         // register (at most TW per lane) and added with one atomic
@@ -567,7 +623,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
             else
                 rootmask |= 1u << i;
             // the run's sites in this lane: up to the next start or the lane's last
-            const uint32_t upto = m ? (m & (0u - m)) - 1u : 0xFFFFu;
+            const uint32_t upto = m ? (m & (0u - m)) - 1u : M;
             if ((linked & upto) >> i) {
                 const uint32_t rsite = root / 4u - root / (4u * PS);
                 atomicOr(&s_bf[rsite >> 5], 1u << (rsite & 31u));
@@ -584,7 +640,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
             __hip_atomic_fetch_add(word_at(s_par, acc_root), acc_len << 16, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_WORKGROUP);
         // a segment that starts inside a run: its sites before the first start
-        if (linked & (st ? (st & (0u - st)) - 1u : 0xFFFFu)) {
+        if (linked & (st ? (st & (0u - st)) - 1u : M)) {
             const uint32_t root = lds_root_b(s_par, rs0);
             const uint32_t rsite = root / 4u - root / (4u * PS);
             atomicOr(&s_bf[rsite >> 5], 1u << (rsite & 31u));
@@ -628,7 +684,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
         const uint32_t sbase = srow + x0;  // site index of this lane's first site
         const uint32_t bfw = s_bf[sbase >> 5];
         const uint32_t bsh = sbase & 31u;
-        const uint32_t bmask = (bfw >> bsh) & 0xFFFFu;
+        const uint32_t bmask = (bfw >> bsh) & M;
         // prefix of mark word sbase >> 5, held by lane (sbase >> 5) / (NW / 64)
         uint32_t pf;
         if constexpr (NW == 128) {
@@ -639,7 +695,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
             pf = (uint32_t)__shfl((int)pf_a, (int)(sbase >> 5), 64);
         }
         const uint32_t kbase = pf + __popc(bfw & ((1u << bsh) - 1u));
-        const uint32_t fl = POTTS ? 0u : (uint32_t)(s_fb[ly] >> x0) & 0xFFFFu;
+        const uint32_t fl = POTTS ? 0u : (uint32_t)(s_fb[ly] >> x0) & M;
         while (rootmask) {
             const uint32_t q = (uint32_t)__ffs((int)rootmask) - 1u;
             rootmask &= rootmask - 1u;
@@ -685,23 +741,23 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
     }
 
     // ---- outputs: one byte per site (final spin or node code)
-    uint32_t out[4] = {0u, 0u, 0u, 0u};
+    uint32_t out[SPT / 4] = {};
     {
         uint32_t cur = rs0;
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
+        for (int q = 0; q < SPT; ++q) {
             if ((st >> q) & 1u) cur = rowoff + 4u * (x0 + (uint32_t)q);
             const uint32_t root = lo16_at(s_par, cur);
             const uint32_t code = hi16_at(s_par, root);
             out[q >> 2] |= code << (8 * (q & 3));
         }
     }
-    *reinterpret_cast<uint4 *>(sout + (size_t)gy * L + gx0) = make_uint4(out[0], out[1], out[2], out[3]);
+    store_seg<SPT>(sout + (size_t)gy * L + gx0, out);
     if (d.labels) {
-        uint32_t lab[16];
+        uint32_t lab[SPT];
         uint32_t cur = rs0;
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
+        for (int q = 0; q < SPT; ++q) {
             if ((st >> q) & 1u) cur = rowoff + 4u * (x0 + (uint32_t)q);
             const uint32_t root = lo16_at(s_par, cur);
             const uint32_t rsite = root / 4u - root / (4u * PS);
@@ -710,10 +766,8 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
                                                       : (ty * TW + rsite / TW) * L + tx * TW + rsite % TW;
         }
         uint4 *lp = reinterpret_cast<uint4 *>(d.labels + (size_t)gy * L + gx0);
-        lp[0] = make_uint4(lab[0], lab[1], lab[2], lab[3]);
-        lp[1] = make_uint4(lab[4], lab[5], lab[6], lab[7]);
-        lp[2] = make_uint4(lab[8], lab[9], lab[10], lab[11]);
-        lp[3] = make_uint4(lab[12], lab[13], lab[14], lab[15]);
+#pragma unroll
+        for (int q = 0; q < SPT / 4; ++q) lp[q] = make_uint4(lab[4 * q], lab[4 * q + 1], lab[4 * q + 2], lab[4 * q + 3]);
     }
     {
         // node index of every edge site that belongs to a node (read only
@@ -724,16 +778,18 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
             return ((w | H) - CB4) ^ (~w & H);
         };
         if (seg == 0u) eg[0 * TW + ly] = (uint8_t)((out[0] & 0xFFu) - CB);
-        if (seg == RPT - 1u) eg[1 * TW + ly] = (uint8_t)((out[3] >> 24) - CB);
-        if (ly == 0u)
-            *reinterpret_cast<uint4 *>(eg + 2 * TW + x0) = make_uint4(less(out[0]), less(out[1]), less(out[2]), less(out[3]));
-        if (ly == (uint32_t)TW - 1u)
-            *reinterpret_cast<uint4 *>(eg + 3 * TW + x0) = make_uint4(less(out[0]), less(out[1]), less(out[2]), less(out[3]));
+        if (seg == RPT - 1u) eg[1 * TW + ly] = (uint8_t)((out[SPT / 4 - 1] >> 24) - CB);
+        if (ly == 0u || ly == (uint32_t)TW - 1u) {
+            uint32_t e[SPT / 4];
+#pragma unroll
+            for (int q = 0; q < SPT / 4; ++q) e[q] = less(out[q]);
+            store_seg<SPT>(eg + (ly == 0u ? 2 : 3) * TW + x0, e);
+        }
     }
-    // energy and magnetisation packed as (e + 32) | (m + 16) << 16 per lane:
-    // the wavefront sums stay below 2^13 and 2^12
-    // (Potts: the equal pairs alone, at most 32 per lane)
-    uint32_t em = POTTS ? (uint32_t)e_part : (uint32_t)(e_part + 32) | ((uint32_t)(m_part + 16) << 16);
+    // energy and magnetisation packed as (e + 2 SPT) | (m + SPT) << 16 per
+    // lane: the wavefront sums stay below 2^13 and 2^12
+    // (Potts: the equal pairs alone, at most 2 SPT per lane)
+    uint32_t em = POTTS ? (uint32_t)e_part : (uint32_t)(e_part + 2 * SPT) | ((uint32_t)(m_part + SPT) << 16);
 
     // ---- workgroup reductions -> tile partial
 #pragma unroll
@@ -765,8 +821,8 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
             if constexpr (POTTS) {
                 e += (int32_t)ew;
             } else {
-                e += (int32_t)(ew & 0xFFFFu) - 32 * 64;
-                m += (int32_t)(ew >> 16) - 16 * 64;
+                e += (int32_t)(ew & 0xFFFFu) - 2 * SPT * 64;
+                m += (int32_t)(ew >> 16) - SPT * 64;
             }
             b0 += (int32_t)(hw & 0x7FFu);
             b1 += (int32_t)((hw >> 11) & 0x3FFu);
@@ -805,18 +861,18 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
 // LDS allows (8 wavefronts per SIMD) all fit.
 constexpr int kTileWavesPerEU = 8;
 
-template <int TW, bool POTTS, bool DENSE, int TWO>
-__global__ __launch_bounds__(TW *TW / 16, TW == 64 && !DENSE ? kTileWavesPerEU : 1) void k_tile(Dev d) {
-    tile_body<TW, POTTS, DENSE, TWO>(d, tile_of_block(blockIdx.x, d.ntiles));
+template <int TW, bool POTTS, bool DENSE, int TWO, int SPT>
+__global__ __launch_bounds__(TW *TW / SPT, TW == 64 && SPT == 16 && !DENSE ? kTileWavesPerEU : 1) void k_tile(Dev d) {
+    tile_body<TW, POTTS, DENSE, TWO, SPT>(d, tile_of_block(blockIdx.x, d.ntiles));
 }
 
 // Batched launches run the same bodies over a table of replicas (map
 // entries replica << kMapShift | unit index), so every replica's bits are
 // those of its own plain sweep.
-template <int TW, bool POTTS, int TWO>
-__global__ __launch_bounds__(TW *TW / 16, TW == 64 ? kTileWavesPerEU : 1) void k_tile_b(const Dev *devs, const uint32_t *map) {
+template <int TW, bool POTTS, int TWO, int SPT>
+__global__ __launch_bounds__(TW *TW / SPT, TW == 64 && SPT == 16 ? kTileWavesPerEU : 1) void k_tile_b(const Dev *devs, const uint32_t *map) {
     const uint32_t e = map[tile_of_block(blockIdx.x, gridDim.x)];
-    tile_body<TW, POTTS, false, TWO>(devs[e >> kMapShift], e & kMapMask);
+    tile_body<TW, POTTS, false, TWO, SPT>(devs[e >> kMapShift], e & kMapMask);
 }
 
 // =====================================================================
@@ -1997,28 +2053,28 @@ __device__ __forceinline__ void resolve_body(const Dev &d, const uint32_t tile) 
     const uint32_t gbe = ref_base(d, tx + 1u == ntx ? 0u : tx + 1u, ty);
     const uint32_t gbn = ref_base(d, tx, ty + 1u == ntx ? 0u : ty + 1u);
 
-    const uint4 v = *reinterpret_cast<const uint4 *>(sp + (size_t)gy * L + gx0);
-    uint4 vn = make_uint4(0u, 0u, 0u, 0u);
+    const Seg<16> v = load_seg<16>(sp + (size_t)gy * L + gx0);
+    Seg<16> vn{};
     if (ly == TW - 1) {
         const uint32_t gyn = (gy + 1u == L) ? 0u : gy + 1u;
-        vn = *reinterpret_cast<const uint4 *>(sp + (size_t)gyn * L + gx0);
+        vn = load_seg<16>(sp + (size_t)gyn * L + gx0);
     }
     uint32_t ve = 0;
     if (seg == RPT - 1) {
         const uint32_t gxe = (gx0 + 16u == L) ? 0u : gx0 + 16u;
         ve = (uint8_t)sp[(size_t)gy * L + gxe];
     }
-    load_table<TW, POTTS, TWO>(d, tile, ref_base(d, tx, ty), pp, s_tab, tid);
+    load_table<TW, POTTS, TWO, NT>(d, tile, ref_base(d, tx, ty), pp, s_tab, tid);
     if (tid < NPL * EW) s_eup[tid] = 0u;
     __syncthreads();
     uint32_t up = 0u, pl[3] = {0u, 0u, 0u};
     if constexpr (POTTS) {
-        decode16_potts(v, s_tab, pl);
+        decode_potts(v, s_tab, pl);
 #pragma unroll
         for (int b = 0; b < 3; ++b) reinterpret_cast<uint16_t *>(s_up + b * (TW + 1))[ly * RPT + seg] = (uint16_t)pl[b];
         if (ly == TW - 1) {
             uint32_t pn[3];
-            decode16_potts_remote<TW, TWO>(d, vn, north, gbn, pn);
+            decode_potts_remote<TW, TWO>(d, vn, north, gbn, pn);
 #pragma unroll
             for (int b = 0; b < 3; ++b)
                 reinterpret_cast<uint16_t *>(s_up + b * (TW + 1))[TW * RPT + seg] = (uint16_t)pn[b];
@@ -2031,10 +2087,10 @@ __device__ __forceinline__ void resolve_body(const Dev &d, const uint32_t tile) 
                 if ((ev >> b) & 1u) atomicOr(&s_eup[b * EW + (ly >> 5)], 1u << (ly & 31u));
         }
     } else {
-        up = decode16<TW>(v, s_tab);
+        up = decode(v, s_tab);
         reinterpret_cast<uint16_t *>(s_up)[ly * RPT + seg] = (uint16_t)up;
         if (ly == TW - 1) {
-            const uint32_t upn = decode16_remote<TWO>(d, vn, north, gbn);
+            const uint32_t upn = decode_remote<TWO>(d, vn, north, gbn);
             reinterpret_cast<uint16_t *>(s_up)[TW * RPT + seg] = (uint16_t)upn;
         }
         if (seg == RPT - 1) {
@@ -2059,7 +2115,7 @@ __device__ __forceinline__ void resolve_body(const Dev &d, const uint32_t tile) 
             dN |= pl[b] ^ pN;
         }
         e_part = __popc(~dE & 0xFFFFu) + __popc(~dN & 0xFFFFu);
-        potts_counts(pl, cpk);
+        potts_counts<0xFFFFu>(pl, cpk);
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
             const uint32_t x = ((pl[0] >> q) & 1u) | (((pl[1] >> q) & 1u) << 1) | (((pl[2] >> q) & 1u) << 2);
@@ -2161,16 +2217,34 @@ inline uint32_t grid_for(size_t n, uint32_t per_block, uint32_t cap) {
     return (uint32_t)g;
 }
 
-template <bool DENSE, int TWO>
+template <bool DENSE, int TWO, int SPT>
 void launch_tile(const Dev &d, hipStream_t s) {
     if (d.q && d.tw == 64)
-        k_tile<64, true, DENSE, TWO><<<d.ntiles, 256, 0, s>>>(d);
+        k_tile<64, true, DENSE, TWO, SPT><<<d.ntiles, 4096 / SPT, 0, s>>>(d);
     else if (d.q)
-        k_tile<32, true, DENSE, TWO><<<d.ntiles, 64, 0, s>>>(d);
+        k_tile<32, true, DENSE, TWO, SPT><<<d.ntiles, 1024 / SPT, 0, s>>>(d);
     else if (d.tw == 64)
-        k_tile<64, false, DENSE, TWO><<<d.ntiles, 256, 0, s>>>(d);
+        k_tile<64, false, DENSE, TWO, SPT><<<d.ntiles, 4096 / SPT, 0, s>>>(d);
     else
-        k_tile<32, false, DENSE, TWO><<<d.ntiles, 64, 0, s>>>(d);
+        k_tile<32, false, DENSE, TWO, SPT><<<d.ntiles, 1024 / SPT, 0, s>>>(d);
+}
+
+// Whether the tile kernels of a launch take 4 sites per thread (else 16): while
+// the GPU would not be filled with 16.  Sweeps with 4 / 16 sites at beta_c:
+// 64-wide tiles, 1024^2 53 / 64, 1280^2 (400 tiles) 72 / 76, 1536^2 82 / 79,
+// 2048^2 91 / 84 us; 32-wide, 512^2 43 / 57, 1056^2 63 / 73, 1536^2 (2304
+// tiles) 74 / 77, 2080^2 89 / 88 us.  64-wide Potts tiles take more registers:
+// q = 3, 1024^2 (256 tiles) 55 / 68, 1280^2 86 / 78 us.
+bool few_tiles(uint32_t ntiles, uint32_t tw, bool potts) {
+    return ntiles <= (tw == 32u ? 2304u : potts ? 256u : 400u);
+}
+
+template <bool DENSE, int TWO>
+void launch_tile(const Dev &d, hipStream_t s) {
+    if (few_tiles(d.ntiles, d.tw, d.q != 0u))
+        launch_tile<DENSE, TWO, 4>(d, s);
+    else
+        launch_tile<DENSE, TWO, 16>(d, s);
 }
 
 template <int TWO>
@@ -2185,16 +2259,24 @@ void resolve_tiles(const Dev &d, hipStream_t s) {
         k_resolve<32, false, TWO><<<d.ntiles, 64, 0, s>>>(d);
 }
 
-template <int TWO>
+template <int TWO, int SPT>
 void launch_tile_b(const BatchDev &b, hipStream_t s) {
     if (b.potts && b.tw == 64)
-        k_tile_b<64, true, TWO><<<b.ntiles, 256, 0, s>>>(b.devs, b.tmap);
+        k_tile_b<64, true, TWO, SPT><<<b.ntiles, 4096 / SPT, 0, s>>>(b.devs, b.tmap);
     else if (b.potts)
-        k_tile_b<32, true, TWO><<<b.ntiles, 64, 0, s>>>(b.devs, b.tmap);
+        k_tile_b<32, true, TWO, SPT><<<b.ntiles, 1024 / SPT, 0, s>>>(b.devs, b.tmap);
     else if (b.tw == 64)
-        k_tile_b<64, false, TWO><<<b.ntiles, 256, 0, s>>>(b.devs, b.tmap);
+        k_tile_b<64, false, TWO, SPT><<<b.ntiles, 4096 / SPT, 0, s>>>(b.devs, b.tmap);
     else
-        k_tile_b<32, false, TWO><<<b.ntiles, 64, 0, s>>>(b.devs, b.tmap);
+        k_tile_b<32, false, TWO, SPT><<<b.ntiles, 1024 / SPT, 0, s>>>(b.devs, b.tmap);
+}
+
+template <int TWO>
+void launch_tile_b(const BatchDev &b, hipStream_t s) {
+    if (few_tiles(b.ntiles, b.tw, b.potts != 0u))
+        launch_tile_b<TWO == 1 ? 1 : 2, 4>(b, s);
+    else
+        launch_tile_b<TWO, 16>(b, s);
 }
 
 template <int TWO>
