@@ -617,9 +617,7 @@ void sw_destroy(sw_sim *s) {
 
 // ===================================================================== batches
 
-// Launch groups of a batch: Ising and Potts replicas, each with 64-wide or
-// 32-wide tiles, run different instantiations of the tile kernels.
-constexpr int kBatchGroups = 4;
+using swmi::kBatchGroups;
 
 struct sw_batch {
     std::vector<sw_config> cfg;
@@ -628,11 +626,7 @@ struct sw_batch {
     swmi::BatchDev bd[kBatchGroups];
     hipStream_t stream;
     bool own_stream;
-    // k_merge runs on a second stream (default priority) beside the global
-    // merge of other replicas, forked after the tile kernels and joined
-    // before the next sweep
-    hipStream_t side;
-    hipEvent_t fork, join;
+    swmi::Forks forks;
     void *ws;
     size_t ws_bytes;
     bool own_ws;
@@ -648,8 +642,6 @@ struct sw_batch {
 namespace {
 
 constexpr int64_t kDefaultBatchRing = 1024;
-
-int batch_group(const Dev &d) { return (d.q ? 2 : 0) + (d.tw == 64 ? 0 : 1); }
 
 // A replica's device view.  k_merge takes every replica it can; one of at most
 // 16 tiles whose caller asked for the global merge gets that.
@@ -709,8 +701,7 @@ int plan_batch(int32_t n, const int32_t *L, const double *beta, const double *J,
         const Layout lo = layout_of(c);
         p->base[(size_t)r] = off;
         off = align_up(off + lo.total);
-        m[batch_group(make_dev(c, nullptr, lo))].add((uint32_t)r, replica_dev(c, nullptr, lo, p->lds[(size_t)r] != 0),
-                                                    m[0]);
+        swmi::BatchMaps::add((uint32_t)r, replica_dev(c, nullptr, lo, p->lds[(size_t)r] != 0), m);
     }
     p->map_words = 0;
     for (const swmi::BatchMaps &g : m) p->map_words += g.words();
@@ -741,24 +732,7 @@ void batch_drop_graph(sw_batch *b) {
 }
 
 hipError_t batch_launch_sweep(const sw_batch *b) {
-    bool small = false, large = false;
-    for (int g = 0; g < kBatchGroups; ++g) {
-        small = small || b->bd[g].nsmall > 0;
-        large = large || b->bd[g].n > 0;
-    }
-    hipError_t e = hipSuccess;
-    for (int g = 0; g < kBatchGroups && e == hipSuccess; ++g) e = swmi::launch_batch_stage(b->bd[g], 0, b->stream);
-    // k_merge beside the global merge when both kinds are present
-    const bool fork = small && large && b->side != nullptr;
-    hipStream_t ss = fork ? b->side : b->stream;
-    if (e == hipSuccess && fork) e = hipEventRecord(b->fork, b->stream);
-    if (e == hipSuccess && fork) e = hipStreamWaitEvent(b->side, b->fork, 0);
-    for (int g = 0; g < kBatchGroups && e == hipSuccess; ++g) e = swmi::launch_batch_merge(b->bd[g], ss);
-    for (int stage = 1; stage < swmi::kStages && e == hipSuccess; ++stage)
-        for (int g = 0; g < kBatchGroups && e == hipSuccess; ++g) e = swmi::launch_batch_stage(b->bd[g], stage, b->stream);
-    if (e == hipSuccess && fork) e = hipEventRecord(b->join, b->side);
-    if (e == hipSuccess && fork) e = hipStreamWaitEvent(b->stream, b->join, 0);
-    return e;
+    return swmi::launch_batch_sweep(b->bd, kBatchGroups, b->stream, b->forks);
 }
 
 // One batched sweep captured as a graph; on any capture failure the kernels
@@ -853,16 +827,6 @@ int batch_create(int32_t n, const int32_t *L, const double *beta, const double *
             b->own_stream = true;
         }
     }
-    if (b->stream != nullptr) {  // (the legacy null stream runs everything in order on itself)
-        e = hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&b->fork, hipEventDisableTiming);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&b->join, hipEventDisableTiming);
-        if (e != hipSuccess) {
-            rc = hip_fail(e, "creating the batch's second stream");
-            sw_batch_destroy(b);
-            return rc;
-        }
-    }
     char *base = (char *)b->ws;
     b->cfg = p.cfg;
     b->lds = p.lds;
@@ -870,18 +834,26 @@ int batch_create(int32_t n, const int32_t *L, const double *beta, const double *
     swmi::BatchMaps m[kBatchGroups];
     for (size_t r = 0; r < p.cfg.size(); ++r) {
         b->dev[r] = replica_dev(p.cfg[r], base + p.base[r], layout_of(p.cfg[r]), p.lds[r] != 0);
-        m[batch_group(b->dev[r])].add((uint32_t)r, b->dev[r], m[0]);
+        swmi::BatchMaps::add((uint32_t)r, b->dev[r], m);
     }
     std::vector<uint32_t> host;
     host.reserve(p.map_words);
     const uint32_t *dmaps = (const uint32_t *)(base + p.maps);
+    for (int g = 0; g < kBatchGroups; ++g) b->bd[g] = swmi::BatchDev{};
+    swmi::set_groups(b->bd);
     for (int g = 0; g < kBatchGroups; ++g) {
         swmi::BatchDev &bd = b->bd[g];
-        bd = swmi::BatchDev{};
         bd.devs = (const Dev *)(base + p.devs);
-        bd.tw = (g & 1) ? 32u : 64u;
-        bd.potts = g >= 2 ? 1u : 0u;
         m[g].emit(host, dmaps, bd);
+    }
+
+    if (b->stream != nullptr) {  // (the legacy null stream runs everything in order on itself)
+        e = swmi::forks_create(b->forks, swmi::forks_wanted(b->bd, kBatchGroups));
+        if (e != hipSuccess) {
+            rc = hip_fail(e, "creating the batch's side streams");
+            sw_batch_destroy(b);
+            return rc;
+        }
     }
 
     e = hipMemsetAsync(b->ws, 0, p.total, b->stream);
@@ -1075,12 +1047,7 @@ void sw_batch_destroy(sw_batch *b) {
     (void)batch_device(b);
     (void)hipStreamSynchronize(b->stream);
     batch_drop_graph(b);
-    if (b->side) {
-        (void)hipStreamSynchronize(b->side);
-        (void)hipStreamDestroy(b->side);
-    }
-    if (b->fork) (void)hipEventDestroy(b->fork);
-    if (b->join) (void)hipEventDestroy(b->join);
+    swmi::forks_destroy(b->forks);
     if (b->own_ws && b->ws) (void)hipFree(b->ws);
     if (b->own_stream && b->stream) (void)hipStreamDestroy(b->stream);
     delete b;

@@ -45,15 +45,30 @@ int validate(const sw_config *c);
 Layout layout_of(const sw_config &c);
 Dev make_dev(const sw_config &c, char *base, const Layout &lo);
 
-// Host-side work maps of one launch group of a batch (one tile width, Ising
-// or Potts): add() files the replica in slot `slot` of the Dev table under
-// k_merge (d.two; its units go to `merge`, the maps of the first launch group,
-// since k_merge takes replicas of every kind in one launch) or under the
-// global merge; emit() appends the maps to `host` (which will be copied to
-// dev_base) and points the BatchDev at them.
+// Launch groups of a batch: Ising and Potts replicas, each with 64-wide or
+// 32-wide tiles, run different instantiations of the tile kernels.
+constexpr int kBatchGroups = 4;
+inline int batch_group(const Dev &d) { return (d.q ? 2 : 0) + (d.tw == 64 ? 0 : 1); }
+inline void set_groups(BatchDev *bd) {
+    for (int g = 0; g < kBatchGroups; ++g) {
+        bd[g].tw = (g & 1) ? 32u : 64u;
+        bd[g].potts = g >= 2 ? 1u : 0u;
+    }
+}
+
+// Host-side work maps of one launch group: add() files the replica in slot
+// `slot` of the Dev table, whose launch group is one of the kBatchGroups `all`,
+// under k_merge (d.two) or under the global merge; emit() appends the maps to
+// `host` (which will be copied to dev_base) and points the BatchDev at them.
+// Only the tile kernels differ by group: k_merge, k_flatten and k_roots take
+// replicas of every kind and have all their units in the first group's maps,
+// the unions depend on the tile width and have theirs in the Ising group's of
+// that width -- four kernels of a few us each, once a sweep instead of once
+// per group.
 struct BatchMaps {
     std::vector<uint32_t> t, w, wn, g, u, r, s, a;  // w / wn: tiles with an E / N group edge
-    void add(uint32_t slot, const Dev &d, BatchMaps &merge) {
+    static void add(uint32_t slot, const Dev &d, BatchMaps *all) { all[batch_group(d)].add_to(slot, d, all[0], all[batch_group(d) & 1]); }
+    void add_to(uint32_t slot, const Dev &d, BatchMaps &merge, BatchMaps &edges) {
         const uint32_t tag = slot << kMapShift;
         a.push_back(slot);
         for (uint32_t i = 0; i < d.ntiles; ++i) t.push_back(tag | i);
@@ -67,11 +82,11 @@ struct BatchMaps {
         // joined by k_ulocal): the last tile column / row of every group
         for (uint32_t i = 0; i < d.ntiles; ++i) {
             const uint32_t tx = i % d.ntx, ty = i / d.ntx;
-            if (tx % kUG == kUG - 1u || tx + 1u == d.ntx) w.push_back(tag | i);
-            if (ty % kUG == kUG - 1u || ty + 1u == d.ntx) wn.push_back(tag | i);
+            if (tx % kUG == kUG - 1u || tx + 1u == d.ntx) edges.w.push_back(tag | i);
+            if (ty % kUG == kUG - 1u || ty + 1u == d.ntx) edges.wn.push_back(tag | i);
         }
-        for (uint32_t i = 0; i < d.ngroups; ++i) g.push_back(tag | i);
-        for (uint32_t i = 0; i < ngx * ngx; ++i) u.push_back(tag | i);
+        for (uint32_t i = 0; i < d.ngroups; ++i) merge.g.push_back(tag | i);
+        for (uint32_t i = 0; i < ngx * ngx; ++i) edges.u.push_back(tag | i);
     }
     size_t words() const {
         return t.size() + ((w.size() + wn.size() + 3u) & ~size_t(3)) + g.size() + u.size() + r.size() + s.size() +

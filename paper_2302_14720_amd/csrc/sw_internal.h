@@ -158,14 +158,24 @@ hipError_t launch_brick_stage(const Dev &d, int stage, hipStream_t s);
 hipError_t launch_brick_measure(const Dev &d, hipStream_t s);
 hipError_t launch_brick_labels(const Dev &d, hipStream_t s);
 
-// Stage 0 is the tile kernel of every replica; stages 1..4 the global merge;
-// launch_batch_merge the replicas merged by k_merge (whatever their launch
-// group, they are all in the maps of the first), which may run beside stages
-// 1..4 once stage 0 is done.  launch_batch_sweep runs them all in order on one
-// stream.
+// Stage 0 is the tile kernel of a launch group's replicas; stages 1..4 the
+// global merge; launch_batch_merge the replicas merged by k_merge.
+// launch_batch_sweep runs them all: the groups' tile kernels beside each
+// other, then k_merge beside the global merge.
 hipError_t launch_batch_stage(const BatchDev &b, int stage, hipStream_t s);
 hipError_t launch_batch_merge(const BatchDev &b, hipStream_t s);
-hipError_t launch_batch_sweep(const BatchDev *b, int ngroups, hipStream_t s);
+// Streams (default priority) beside the main one for kernels of a sweep that do
+// not depend on each other.
+struct Forks {
+    static constexpr int kSides = 3;
+    hipStream_t side[kSides];
+    hipEvent_t fork, join[kSides];
+    int n;  // side streams there are; 0: everything runs on the main stream
+};
+hipError_t forks_create(Forks &f, int n);  // n <= kSides
+int forks_wanted(const BatchDev *b, int ngroups);
+void forks_destroy(Forks &f);  // waits for the side streams
+hipError_t launch_batch_sweep(const BatchDev *b, int ngroups, hipStream_t s, const Forks &f);
 hipError_t launch_batch_resolve(const BatchDev &b, hipStream_t s);
 
 }  // namespace swmi

@@ -3,6 +3,8 @@
 // row of 64 sites is one 64-bit mask, so row runs of horizontal bonds come
 // from bit arithmetic on ballot-sized masks, and only vertical bonds go
 // through the LDS union-find.
+#include <algorithm>
+
 #include "sw_device.h"
 #include "sw_internal.h"
 #include "sw_philox.h"
@@ -2392,10 +2394,9 @@ hipError_t launch_batch_merge(const BatchDev &b, hipStream_t s) {
 }
 
 hipError_t launch_batch_stage(const BatchDev &b, int stage, hipStream_t s) {
-    if (b.nall == 0) return hipSuccess;
-    if (b.n == 0 && stage != 0) return hipSuccess;  // stages 1..4: replicas of the global merge
     switch (stage) {
     case 0:
+        if (b.nall == 0) break;
         // b.n replicas of the global merge, the others of k_merge
         if (b.n == 0)
             launch_tile_b<1>(b, s);
@@ -2405,6 +2406,7 @@ hipError_t launch_batch_stage(const BatchDev &b, int stage, hipStream_t s) {
             launch_tile_b<2>(b, s);
         break;
     case 1:
+        if (b.nugroups == 0) break;
         if (b.tw == 64) {
             k_ulocal_b<64><<<b.nugroups, 256, 0, s>>>(b.devs, b.umap);
             k_union_b<64><<<b.nwmap / 4, 256, 0, s>>>(b.devs, b.wmap, b.nwE);
@@ -2414,10 +2416,10 @@ hipError_t launch_batch_stage(const BatchDev &b, int stage, hipStream_t s) {
         }
         break;
     case 2:
-        k_flatten_b<<<b.ngroups, 256, 0, s>>>(b.devs, b.gmap);
+        if (b.ngroups != 0) k_flatten_b<<<b.ngroups, 256, 0, s>>>(b.devs, b.gmap);
         break;
     case 3:  // and the records
-        k_roots_b<<<b.ngroups, 256, 0, s>>>(b.devs, b.gmap);
+        if (b.ngroups != 0) k_roots_b<<<b.ngroups, 256, 0, s>>>(b.devs, b.gmap);
         break;
     case 4:  // (folded by k_roots_b)
         break;
@@ -2427,12 +2429,80 @@ hipError_t launch_batch_stage(const BatchDev &b, int stage, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_batch_sweep(const BatchDev *b, int ngroups, hipStream_t s) {
+int forks_wanted(const BatchDev *b, int ngroups) {
+    int tiles = 0;
+    bool small = false, large = false;
+    for (int g = 0; g < ngroups; ++g) {
+        tiles += b[g].nall != 0;
+        small = small || b[g].nsmall > 0;
+        large = large || b[g].ngroups > 0;
+    }
+    return tiles > 1 ? std::min(tiles - 1, Forks::kSides) : small && large ? 1 : 0;
+}
+
+hipError_t forks_create(Forks &f, int n) {
+    f = Forks{};
+    if (n == 0) return hipSuccess;
+    hipError_t e = hipEventCreateWithFlags(&f.fork, hipEventDisableTiming);
+    for (int i = 0; i < n && e == hipSuccess; ++i) {
+        e = hipStreamCreateWithFlags(&f.side[i], hipStreamNonBlocking);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&f.join[i], hipEventDisableTiming);
+    }
+    f.n = n;
+    if (e != hipSuccess) forks_destroy(f);
+    return e;
+}
+
+void forks_destroy(Forks &f) {
+    for (int i = 0; i < Forks::kSides; ++i) {
+        if (f.side[i]) {
+            (void)hipStreamSynchronize(f.side[i]);
+            (void)hipStreamDestroy(f.side[i]);
+        }
+        if (f.join[i]) (void)hipEventDestroy(f.join[i]);
+    }
+    if (f.fork) (void)hipEventDestroy(f.fork);
+    f = Forks{};
+}
+
+hipError_t launch_batch_sweep(const BatchDev *b, int ngroups, hipStream_t s, const Forks &f) {
+    // the groups' tile kernels: the first on the main stream, the others beside it
     hipError_t e = hipSuccess;
-    for (int g = 0; g < ngroups && e == hipSuccess; ++g) e = launch_batch_stage(b[g], 0, s);
-    for (int g = 0; g < ngroups && e == hipSuccess; ++g) e = launch_batch_merge(b[g], s);
-    for (int stage = 1; stage < kStages; ++stage)
+    int first = -1, sides = 0;
+    for (int g = 0; g < ngroups; ++g) {
+        if (b[g].nall == 0) continue;
+        if (first < 0)
+            first = g;
+        else
+            ++sides;
+    }
+    const bool split = sides > 0 && sides <= f.n;
+    if (split) e = hipEventRecord(f.fork, s);
+    int k = 0;
+    for (int g = 0; g < ngroups && e == hipSuccess; ++g) {
+        if (b[g].nall == 0 || (split && g == first)) continue;
+        hipStream_t on = split ? f.side[k] : s;
+        if (split) e = hipStreamWaitEvent(on, f.fork, 0);
+        if (e == hipSuccess) e = launch_batch_stage(b[g], 0, on);
+        if (e == hipSuccess && split) e = hipEventRecord(f.join[k++], on);
+    }
+    if (e == hipSuccess && split) e = launch_batch_stage(b[first], 0, s);
+    for (int i = 0; i < k && e == hipSuccess; ++i) e = hipStreamWaitEvent(s, f.join[i], 0);
+    // k_merge beside the global merge when both kinds are present
+    bool small = false, large = false;
+    for (int g = 0; g < ngroups; ++g) {
+        small = small || b[g].nsmall > 0;
+        large = large || b[g].ngroups > 0;
+    }
+    const bool both = f.n > 0 && small && large;
+    hipStream_t on = both ? f.side[0] : s;
+    if (e == hipSuccess && both) e = hipEventRecord(f.fork, s);
+    if (e == hipSuccess && both) e = hipStreamWaitEvent(on, f.fork, 0);
+    for (int g = 0; g < ngroups && e == hipSuccess; ++g) e = launch_batch_merge(b[g], on);
+    for (int stage = 1; stage < kStages && e == hipSuccess; ++stage)
         for (int g = 0; g < ngroups && e == hipSuccess; ++g) e = launch_batch_stage(b[g], stage, s);
+    if (e == hipSuccess && both) e = hipEventRecord(f.join[0], on);
+    if (e == hipSuccess && both) e = hipStreamWaitEvent(s, f.join[0], 0);
     return e;
 }
 

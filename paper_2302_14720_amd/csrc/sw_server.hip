@@ -78,16 +78,7 @@ struct Pool {
     }
 };
 
-// Launch groups: Ising and Potts jobs, each with 64-wide or 32-wide tiles,
-// run different instantiations of the tile and resolve kernels.
-constexpr int kGroups = 4;
-int group_of(const Dev &d) { return (d.q ? 2 : 0) + (d.tw == 64 ? 0 : 1); }
-void set_groups(swmi::BatchDev *bd) {
-    for (int g = 0; g < kGroups; ++g) {
-        bd[g].tw = (g & 1) ? 32u : 64u;
-        bd[g].potts = g >= 2 ? 1u : 0u;
-    }
-}
+constexpr int kGroups = swmi::kBatchGroups;
 
 }  // namespace
 
@@ -108,8 +99,9 @@ struct sw_server {
     std::vector<Job *> active;
     int64_t next_id = 1;
     bool dirty = true;
-    swmi::BatchDev bd[kGroups]{};  // active jobs by launch group (see group_of)
+    swmi::BatchDev bd[kGroups]{};  // active jobs by launch group (swmi::batch_group)
     uint64_t site_updates = 0;
+    swmi::Forks forks{};
     swmi::StageUser stage_user;
 };
 
@@ -152,8 +144,8 @@ int upload_maps(sw_server *s, swmi::BatchMaps *m, swmi::BatchDev *bd, int ngroup
 int rebuild_active(sw_server *s) {
     HIP_TRY(hipStreamSynchronize(s->stream));
     swmi::BatchMaps m[kGroups];
-    for (Job *j : s->active) m[group_of(j->dev)].add((uint32_t)j->slot, j->dev, m[0]);
-    set_groups(s->bd);
+    for (Job *j : s->active) swmi::BatchMaps::add((uint32_t)j->slot, j->dev, m);
+    swmi::set_groups(s->bd);
     const int rc = upload_maps(s, m, s->bd, kGroups);
     if (rc == SW_OK) s->dirty = false;
     return rc;
@@ -275,6 +267,8 @@ int sw_server_create(void *pool, size_t pool_bytes, int32_t max_jobs, void *hip_
             s->own_stream = e == hipSuccess;
         }
     }
+    // (the legacy null stream runs everything in order on itself)
+    if (e == hipSuccess && s->stream != nullptr) e = swmi::forks_create(s->forks, swmi::Forks::kSides);
     if (e != hipSuccess) {
         const int rc = swmi::hip_fail(e, "creating the server");
         sw_server_destroy(s);
@@ -318,7 +312,7 @@ int sw_server_step(sw_server *s, int64_t n, int64_t *done_ids, int32_t cap, int3
         int64_t k = left;
         for (const Job *j : s->active) k = std::min(k, j->target - j->done);
         for (int64_t i = 0; i < k; ++i)
-            HIP_TRY(swmi::launch_batch_sweep(s->bd, kGroups, s->stream));
+            HIP_TRY(swmi::launch_batch_sweep(s->bd, kGroups, s->stream, s->forks));
         uint64_t sites = 0;
         for (Job *j : s->active) {
             j->done += k;
@@ -334,8 +328,8 @@ int sw_server_step(sw_server *s, int64_t n, int64_t *done_ids, int32_t cap, int3
         HIP_TRY(hipStreamSynchronize(s->stream));
         swmi::BatchMaps m[kGroups];
         swmi::BatchDev rb[kGroups]{};
-        for (Job *j : fin) m[group_of(j->dev)].add((uint32_t)j->slot, j->dev, m[0]);
-        set_groups(rb);
+        for (Job *j : fin) swmi::BatchMaps::add((uint32_t)j->slot, j->dev, m);
+        swmi::set_groups(rb);
         rc = upload_maps(s, m, rb, kGroups);
         if (rc != SW_OK) return rc;
         for (int g = 0; g < kGroups; ++g) HIP_TRY(swmi::launch_batch_resolve(rb[g], s->stream));
@@ -438,6 +432,7 @@ void sw_server_destroy(sw_server *s) {
     (void)srv_device(s);
     (void)hipStreamSynchronize(s->stream);
     for (auto &kv : s->jobs) delete kv.second;
+    swmi::forks_destroy(s->forks);
     if (s->d_maps) (void)hipFree(s->d_maps);
     if (s->d_devs) (void)hipFree(s->d_devs);
     if (s->own_pool && s->pool_mem) (void)hipFree(s->pool_mem);
