@@ -3,6 +3,8 @@
 // row of 64 sites is one 64-bit mask, so row runs of horizontal bonds come
 // from bit arithmetic on ballot-sized masks, and only vertical bonds go
 // through the LDS union-find.
+#include <math.h>
+
 #include <algorithm>
 
 #include "sw_device.h"
@@ -884,7 +886,7 @@ __global__ __launch_bounds__(TW *TW / SPT, TW == 64 && SPT == 16 ? kTileWavesPer
 // The global union-find links nodes by index (sw_uf.h); the cluster's
 // smallest site is gathered separately (k_flatten takes the minimum of the
 // nodes' keys into the root's key), so finds never read keys.
-template <int TW>
+template <int TW, class Order>
 __device__ __forceinline__ void union_body(const Dev &d, const uint32_t tile, const uint32_t dir) {
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t ntx = d.ntx, tx = tile % ntx, ty = tile / ntx;
@@ -922,7 +924,7 @@ __device__ __forceinline__ void union_body(const Dev &d, const uint32_t tile, co
     const int prev = below ? 63 - __clzll((long long)below) : (int)lane;
     const uint32_t pra = (uint32_t)__shfl((int)ra, prev, 64), prb = (uint32_t)__shfl((int)rb, prev, 64);
     const bool dup = below != 0ull && pra == ra && prb == rb;
-    if (has && !dup) g_union(par, ra, rb);
+    if (has && !dup) g_union<Order>(par, ra, rb);
 }
 
 // =====================================================================
@@ -1010,16 +1012,16 @@ __global__ __launch_bounds__(256) void k_ulocal_b(const Dev *devs, const uint32_
 // Plain lattices launch only the edges between kUG x kUG groups: wave w <
 // ngx * ntx takes the E edge of the last tile column of a group in tile row
 // w / ngx; the next ngx * ntx waves the N edges of the groups' last tile rows.
-template <int TW>
+template <int TW, class Order>
 __global__ __launch_bounds__(256) void k_union(Dev d) {
     const uint32_t ntx = d.ntx, ngx = (ntx + kUG - 1u) / kUG, nE = ngx * ntx;
     uint32_t w = blockIdx.x * 4u + (threadIdx.x >> 6);
     if (w < nE) {
         const uint32_t ty = w / ngx, tx = min((w % ngx) * kUG + kUG - 1u, ntx - 1u);
-        union_body<TW>(d, ty * ntx + tx, 0u);
+        union_body<TW, Order>(d, ty * ntx + tx, 0u);
     } else if ((w -= nE) < nE) {
         const uint32_t tx = w % ntx, ty = min((w / ntx) * kUG + kUG - 1u, ntx - 1u);
-        union_body<TW>(d, ty * ntx + tx, 1u);
+        union_body<TW, Order>(d, ty * ntx + tx, 1u);
     }
 }
 
@@ -1030,7 +1032,7 @@ template <int TW>
 __global__ __launch_bounds__(256) void k_union_b(const Dev *devs, const uint32_t *map, uint32_t nE) {
     const uint32_t w = blockIdx.x * 4u + (threadIdx.x >> 6);
     const uint32_t e = map[w];
-    if (e != kMapNone) union_body<TW>(devs[e >> kMapShift], e & kMapMask, w < nE ? 0u : 1u);
+    if (e != kMapNone) union_body<TW, ByIndex>(devs[e >> kMapShift], e & kMapMask, w < nE ? 0u : 1u);
 }
 
 // =====================================================================
@@ -2231,6 +2233,21 @@ void launch_tile(const Dev &d, hipStream_t s) {
         k_tile<32, false, DENSE, TWO, SPT><<<d.ntiles, 1024 / SPT, 0, s>>>(d);
 }
 
+// The order in which k_union links.  Above the critical coupling (bond
+// probability above sqrt(q) / (1 + sqrt(q))) one cluster spans the lattice, and
+// index order links its part in every group under the next group's: chains as
+// long as the lattice is wide, which bit-reversed order breaks up.  Elsewhere
+// index order is better: it makes the node with the smallest site the root
+// nearly always, and spares k_flatten an atomic per workgroup and root.  Sweeps
+// index / bits: beta = 0.5, 4064^2 208 / 189, 8192^2 389 / 368, 16384^2 1298 /
+// 1232 us; beta_c, 168 / 171, 339 / 344, 1158 / 1169; on fewer than 16 groups
+// a side there is nothing between them (1344^2, beta = 0.5, 68.9 / 69.7).
+constexpr uint32_t kBitsGroups = 16;
+bool ordered(const Dev &d) {
+    const double q = sqrt((double)(d.q ? d.q : 2u));
+    return (double)d.T > q / (1.0 + q) * 4294967296.0;
+}
+
 // Whether the tile kernels of a launch take 4 sites per thread (else 16): while
 // the GPU would not be filled with 16.  Sweeps with 4 / 16 sites at beta_c:
 // 64-wide tiles, 1024^2 53 / 64, 1280^2 (400 tiles) 72 / 76, 1536^2 82 / 79,
@@ -2330,10 +2347,16 @@ hipError_t launch_stage(const Dev &d, int stage, hipStream_t s) {
             k_merge<<<ngx * ngx, kMergeThreads, 0, s>>>(d);
         } else if (d.tw == 64) {
             k_ulocal<64><<<ngx * ngx, 256, 0, s>>>(d);
-            k_union<64><<<(nwaves + 3u) / 4u, 256, 0, s>>>(d);
+            if (ngx >= kBitsGroups && ordered(d))
+                k_union<64, ByBits><<<(nwaves + 3u) / 4u, 256, 0, s>>>(d);
+            else
+                k_union<64, ByIndex><<<(nwaves + 3u) / 4u, 256, 0, s>>>(d);
         } else {
             k_ulocal<32><<<ngx * ngx, 256, 0, s>>>(d);
-            k_union<32><<<(nwaves + 3u) / 4u, 256, 0, s>>>(d);
+            if (ngx >= kBitsGroups && ordered(d))
+                k_union<32, ByBits><<<(nwaves + 3u) / 4u, 256, 0, s>>>(d);
+            else
+                k_union<32, ByIndex><<<(nwaves + 3u) / 4u, 256, 0, s>>>(d);
         }
         break;
     }

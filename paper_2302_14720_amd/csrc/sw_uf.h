@@ -2,12 +2,7 @@
 // and in global memory (device scope).  Roots are the smallest index of
 // their set: a root is linked under the root with the smaller index, so
 // every parent is smaller than its child and the structure stays a forest
-// whatever order concurrent unions run in.  (Linking in the order of the
-// bit-reversed indices makes shallower trees -- k_union 66 -> 53 us at
-// 16384^2, beta_c -- but roots whose smallest site lies elsewhere in the
-// cluster: the minimum of the sites then takes one more atomic per workgroup
-// and root, and k_flatten went from 80 to 101 us, the cubic k_bflat3 from 175
-// to 234.)
+// whatever order concurrent unions run in (g_union can link in another order).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -116,7 +111,17 @@ __device__ __forceinline__ uint32_t g_load(uint32_t *p) {
 __device__ __forceinline__ void g_store(uint32_t *p, uint32_t v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+// Orders in which g_union links: ByIndex, the smallest index of a set is its
+// root; ByBits, the smallest bit-reversed one (for sets whose smallest site is
+// gathered separately).
+struct ByIndex {
+    static __device__ __forceinline__ bool before(uint32_t a, uint32_t b) { return a < b; }
+};
+struct ByBits {
+    static __device__ __forceinline__ bool before(uint32_t a, uint32_t b) { return __brev(a) < __brev(b); }
+};
 // Union in global memory, as lds_union.
+template <class Order = ByIndex>
 __device__ __forceinline__ void g_union(uint32_t *par, uint32_t a, uint32_t b) {
     while (true) {
         uint32_t pa = g_load(&par[a]), pb = g_load(&par[b]);
@@ -131,7 +136,7 @@ __device__ __forceinline__ void g_union(uint32_t *par, uint32_t a, uint32_t b) {
             pb = gb;
         }
         if (a == b) return;
-        if (a > b) { const uint32_t tmp = a; a = b; b = tmp; }
+        if (Order::before(b, a)) { const uint32_t tmp = a; a = b; b = tmp; }
         uint32_t expected = b;
         if (__hip_atomic_compare_exchange_strong(&par[b], &expected, a, __ATOMIC_RELAXED,
                                                  __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
