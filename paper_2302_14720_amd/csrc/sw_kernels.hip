@@ -2040,10 +2040,7 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge_b(const Dev *devs, cons
 // k_resolve: replace node codes by final spins in place and measure the
 // configuration (runs once at the end of every sw_sweep call).
 // =====================================================================
-// FOLD: the last workgroup of the lattice to finish adds up the tiles' partials
-// and completes the record (one launch less at the end of every call; where
-// there are few tiles).
-template <int TW, bool POTTS, int TWO, bool FOLD>
+template <int TW, bool POTTS, int TWO>
 __device__ __forceinline__ void resolve_body(const Dev &d, const uint32_t tile) {
     constexpr int NT = TW * TW / 16;
     constexpr uint32_t RPT = TW / 16;
@@ -2174,60 +2171,27 @@ __device__ __forceinline__ void resolve_body(const Dev &d, const uint32_t tile) 
             m += s_red[w][1];
         }
         int32_t *tp = d.tpart + (size_t)tile * kTilePart;
-        auto put = [&](int f, int32_t v) {
-            if (FOLD)
-                ag_store(&tp[f], v);
-            else
-                tp[f] = v;
-        };
-        put(TP_E, e);
-        put(TP_M, m);
+        tp[TP_E] = e;
+        tp[TP_M] = m;
         if constexpr (POTTS) {
             for (int k = 0; k < 8; ++k) {
                 int32_t c = 0;
                 for (int w = 0; w < NWAVE; ++w) c += (int32_t)(((uint32_t)s_red[w][2 + k / 2] >> (16 * (k & 1))) & 0xFFFFu);
-                put(TP_CNT + k, c);
+                tp[TP_CNT + k] = c;
             }
         }
     }
-    if constexpr (FOLD) {
-        __shared__ unsigned long long s_acc[GP_END];
-        __shared__ int s_last;
-        __builtin_amdgcn_s_waitcnt(0);
-        __syncthreads();
-        unsigned long long *acc = reinterpret_cast<unsigned long long *>(d.acc);
-        if (tid == 0u) s_last = atomicAdd(&acc[ACC_COUNT], 1ull) == (unsigned long long)d.ntiles - 1ull;
-        for (uint32_t i = tid; i < (uint32_t)GP_END; i += NT) s_acc[i] = 0ull;
-        __syncthreads();
-        if (!s_last) return;
-        if (tid == 0u) ag_store(&d.acc[ACC_COUNT], (uint64_t)0);
-        constexpr int NF = POTTS ? 2 + kMaxQ : 2;
-        int64_t v[NF] = {};
-        for (uint32_t i = tid; i < d.ntiles; i += NT) {
-            const int32_t *tp = d.tpart + (size_t)i * kTilePart;
-#pragma unroll
-            for (int f = 0; f < NF; ++f) v[f] += ag_load(&tp[f == 0 ? TP_E : f == 1 ? TP_M : TP_CNT + f - 2]);
-        }
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-#pragma unroll
-            for (int o = 32; o > 0; o >>= 1) v[f] += __shfl_xor(v[f], o, 64);
-            if ((tid & 63u) == 0u) atomicAdd(&s_acc[f == 0 ? GP_E : f == 1 ? GP_M : GP_CNT + f - 2], (unsigned long long)v[f]);
-        }
-        __syncthreads();
-        record_write(d, reinterpret_cast<const uint64_t *>(s_acc), 1);
-    }
 }
 
-template <int TW, bool POTTS, int TWO, bool FOLD>
+template <int TW, bool POTTS, int TWO>
 __global__ __launch_bounds__(TW *TW / 16) void k_resolve(Dev d) {
-    resolve_body<TW, POTTS, TWO, FOLD>(d, tile_of_block(blockIdx.x, d.ntiles));
+    resolve_body<TW, POTTS, TWO>(d, tile_of_block(blockIdx.x, d.ntiles));
 }
 
 template <int TW, bool POTTS, int TWO>
 __global__ __launch_bounds__(TW *TW / 16) void k_resolve_b(const Dev *devs, const uint32_t *map) {
     const uint32_t e = map[tile_of_block(blockIdx.x, gridDim.x)];
-    resolve_body<TW, POTTS, TWO, false>(devs[e >> kMapShift], e & kMapMask);
+    resolve_body<TW, POTTS, TWO>(devs[e >> kMapShift], e & kMapMask);
 }
 
 // Initial spins (Fig. 1): hot = bit 0 of word 0 of Philox({s, 0, 2, 0}),
@@ -2278,10 +2242,6 @@ void launch_tile(const Dev &d, hipStream_t s) {
         k_tile<32, false, DENSE, TWO, SPT><<<d.ntiles, 1024 / SPT, 0, s>>>(d);
 }
 
-// Lattices of at most this many tiles have their closing record written by
-// k_resolve itself (128^2, a sweep with record and spins: 66 -> FOLD_US us).
-constexpr uint32_t kResolveFold = 256;
-
 // The order in which k_union links.  Above the critical coupling (bond
 // probability above sqrt(q) / (1 + sqrt(q))) one cluster spans the lattice, and
 // index order links its part in every group under the next group's: chains as
@@ -2315,16 +2275,16 @@ void launch_tile(const Dev &d, hipStream_t s) {
         launch_tile<DENSE, TWO, 16>(d, s);
 }
 
-template <int TWO, bool FOLD>
+template <int TWO>
 void resolve_tiles(const Dev &d, hipStream_t s) {
     if (d.q && d.tw == 64)
-        k_resolve<64, true, TWO, FOLD><<<d.ntiles, 256, 0, s>>>(d);
+        k_resolve<64, true, TWO><<<d.ntiles, 256, 0, s>>>(d);
     else if (d.q)
-        k_resolve<32, true, TWO, FOLD><<<d.ntiles, 64, 0, s>>>(d);
+        k_resolve<32, true, TWO><<<d.ntiles, 64, 0, s>>>(d);
     else if (d.tw == 64)
-        k_resolve<64, false, TWO, FOLD><<<d.ntiles, 256, 0, s>>>(d);
+        k_resolve<64, false, TWO><<<d.ntiles, 256, 0, s>>>(d);
     else
-        k_resolve<32, false, TWO, FOLD><<<d.ntiles, 64, 0, s>>>(d);
+        k_resolve<32, false, TWO><<<d.ntiles, 64, 0, s>>>(d);
 }
 
 template <int TWO, int SPT>
@@ -2451,17 +2411,10 @@ hipError_t launch_resolve(const Dev &d, hipStream_t s) {
         k_record<<<(d.ntiles + kRecordTiles - 1) / kRecordTiles, 256, 0, s>>>(d, d.ntiles, 1);
         return hipGetLastError();
     }
-    if (d.ntiles <= kResolveFold) {  // and the record
-        if (d.two)
-            resolve_tiles<1, true>(d, s);
-        else
-            resolve_tiles<0, true>(d, s);
-        return hipGetLastError();
-    }
     if (d.two)
-        resolve_tiles<1, false>(d, s);
+        resolve_tiles<1>(d, s);
     else
-        resolve_tiles<0, false>(d, s);
+        resolve_tiles<0>(d, s);
     k_record<<<(d.ntiles + kRecordTiles - 1) / kRecordTiles, 256, 0, s>>>(d, d.ntiles, 1);
     return hipGetLastError();
 }
