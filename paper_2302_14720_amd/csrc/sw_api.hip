@@ -100,10 +100,13 @@ int validate(const sw_config *c) {
 // 78, 1536^2 91 / 82 us; 32-wide tiles: 512^2 55 / 64, 1056^2 93 / 72 us.
 // Labels and the exact histogram need the node tables that the global merge
 // leaves.
+uint32_t merge_groups(const sw_config &c) {  // 0: too many
+    const uint32_t tw = (uint32_t)resolve_tile(c), ntx = (uint32_t)c.L / tw, ngx = (ntx + kUG - 1u) / kUG;
+    return ngx * ngx <= kMergeGroups ? ngx * ngx : 0u;
+}
 bool merge_in_one(const sw_config &c) {
     if (c.dims == 3 || (c.flags & (SW_FLAG_LABEL_EQUIV | SW_FLAG_LABELS | SW_FLAG_DENSE_HIST)) != 0u) return false;
-    const uint32_t tw = (uint32_t)resolve_tile(c), ntx = (uint32_t)c.L / tw, ngx = (ntx + kUG - 1u) / kUG;
-    return ngx * ngx <= kMergeGroups;
+    return merge_groups(c) != 0u;
 }
 
 Layout layout_of(const sw_config &c) {
@@ -137,7 +140,9 @@ Layout layout_of(const sw_config &c) {
     o.rspin = brick ? 0 : take(nodes);
     o.edge = brick ? 0 : take(ntiles * 4 * tw);
     o.xb = brick ? 0 : take(ntiles * 16);
-    const size_t mg = merge_in_one(c) ? ((L / tw + kUG - 1) / kUG) * ((L / tw + kUG - 1) / kUG) : 0;
+    // (room for k_merge also where labels or the histogram rule it out, so that
+    // a flag's workspace is the plain one's and its own arrays)
+    const size_t mg = le || brick ? 0 : merge_groups(c);
     o.nref = take(mg ? nodes * 2 : 0);
     o.gnode = take(mg * kRefSlots * 8);
     o.gedge = take(mg * kRefSlots * 2);
