@@ -631,7 +631,6 @@ struct sw_batch {
     swmi::BatchDev bd[kBatchGroups];
     hipStream_t stream;
     bool own_stream;
-    swmi::Forks forks;
     void *ws;
     size_t ws_bytes;
     bool own_ws;
@@ -737,7 +736,7 @@ void batch_drop_graph(sw_batch *b) {
 }
 
 hipError_t batch_launch_sweep(const sw_batch *b) {
-    return swmi::launch_batch_sweep(b->bd, kBatchGroups, b->stream, b->forks);
+    return swmi::launch_batch_sweep(b->bd, kBatchGroups, b->stream);
 }
 
 // One batched sweep captured as a graph; on any capture failure the kernels
@@ -846,20 +845,8 @@ int batch_create(int32_t n, const int32_t *L, const double *beta, const double *
     const uint32_t *dmaps = (const uint32_t *)(base + p.maps);
     for (int g = 0; g < kBatchGroups; ++g) b->bd[g] = swmi::BatchDev{};
     swmi::set_groups(b->bd);
-    for (int g = 0; g < kBatchGroups; ++g) {
-        swmi::BatchDev &bd = b->bd[g];
-        bd.devs = (const Dev *)(base + p.devs);
-        m[g].emit(host, dmaps, bd);
-    }
-
-    if (b->stream != nullptr) {  // (the legacy null stream runs everything in order on itself)
-        e = swmi::forks_create(b->forks, swmi::forks_wanted(b->bd, kBatchGroups));
-        if (e != hipSuccess) {
-            rc = hip_fail(e, "creating the batch's side streams");
-            sw_batch_destroy(b);
-            return rc;
-        }
-    }
+    for (int g = 0; g < kBatchGroups; ++g) b->bd[g].devs = (const Dev *)(base + p.devs);
+    swmi::BatchMaps::emit(m, host, dmaps, b->bd);
 
     e = hipMemsetAsync(b->ws, 0, p.total, b->stream);
     if (e == hipSuccess)
@@ -1052,7 +1039,6 @@ void sw_batch_destroy(sw_batch *b) {
     (void)batch_device(b);
     (void)hipStreamSynchronize(b->stream);
     batch_drop_graph(b);
-    swmi::forks_destroy(b->forks);
     if (b->own_ws && b->ws) (void)hipFree(b->ws);
     if (b->own_stream && b->stream) (void)hipStreamDestroy(b->stream);
     delete b;

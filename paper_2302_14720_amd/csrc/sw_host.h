@@ -60,15 +60,14 @@ inline void set_groups(BatchDev *bd) {
 // `slot` of the Dev table, whose launch group is one of the kBatchGroups `all`,
 // under k_merge (d.two) or under the global merge; emit() appends the maps to
 // `host` (which will be copied to dev_base) and points the BatchDev at them.
-// Only the tile kernels differ by group: k_merge, k_flatten and k_roots take
-// replicas of every kind and have all their units in the first group's maps,
-// the unions depend on the tile width and have theirs in the Ising group's of
-// that width -- four kernels of a few us each, once a sweep instead of once
-// per group.
+// Only the tile kernels differ by group: those of the merges take replicas of
+// every kind and have all their units in the first group's maps -- kernels of a
+// few us each, once a sweep instead of once per group.
 struct BatchMaps {
-    std::vector<uint32_t> t, w, wn, g, u, r, s, a;  // w / wn: tiles with an E / N group edge
-    static void add(uint32_t slot, const Dev &d, BatchMaps *all) { all[batch_group(d)].add_to(slot, d, all[0], all[batch_group(d) & 1]); }
-    void add_to(uint32_t slot, const Dev &d, BatchMaps &merge, BatchMaps &edges) {
+    std::vector<uint32_t> t, w, wn, g, u, s, a;  // w / wn: tiles with an E / N group edge
+    uint32_t n = 0;                              // replicas of the global merge
+    static void add(uint32_t slot, const Dev &d, BatchMaps *all) { all[batch_group(d)].add_to(slot, d, all[0]); }
+    void add_to(uint32_t slot, const Dev &d, BatchMaps &merge) {
         const uint32_t tag = slot << kMapShift;
         a.push_back(slot);
         for (uint32_t i = 0; i < d.ntiles; ++i) t.push_back(tag | i);
@@ -77,47 +76,48 @@ struct BatchMaps {
             for (uint32_t i = 0; i < ngx * ngx; ++i) merge.s.push_back(tag | i);
             return;
         }
-        r.push_back(slot);
+        ++n;
         // edges between kUG x kUG groups of tiles (those inside a group are
         // joined by k_ulocal): the last tile column / row of every group
         for (uint32_t i = 0; i < d.ntiles; ++i) {
             const uint32_t tx = i % d.ntx, ty = i / d.ntx;
-            if (tx % kUG == kUG - 1u || tx + 1u == d.ntx) edges.w.push_back(tag | i);
-            if (ty % kUG == kUG - 1u || ty + 1u == d.ntx) edges.wn.push_back(tag | i);
+            if (tx % kUG == kUG - 1u || tx + 1u == d.ntx) merge.w.push_back(tag | i);
+            if (ty % kUG == kUG - 1u || ty + 1u == d.ntx) merge.wn.push_back(tag | i);
         }
         for (uint32_t i = 0; i < d.ngroups; ++i) merge.g.push_back(tag | i);
-        for (uint32_t i = 0; i < ngx * ngx; ++i) edges.u.push_back(tag | i);
+        for (uint32_t i = 0; i < ngx * ngx; ++i) merge.u.push_back(tag | i);
     }
     size_t words() const {
-        return t.size() + ((w.size() + wn.size() + 3u) & ~size_t(3)) + g.size() + u.size() + r.size() + s.size() +
-               a.size();
+        return t.size() + w.size() + wn.size() + g.size() + u.size() + s.size() + a.size();
+    }
+    // the tile maps of all launch groups first, so that they are one map
+    static void emit(const BatchMaps *all, std::vector<uint32_t> &host, const uint32_t *dev_base, BatchDev *b) {
+        for (int g = 0; g < kBatchGroups; ++g) {
+            b[g].ntiles = (uint32_t)all[g].t.size();
+            b[g].tmap = dev_base + host.size();
+            host.insert(host.end(), all[g].t.begin(), all[g].t.end());
+        }
+        for (int g = 0; g < kBatchGroups; ++g) all[g].emit(host, dev_base, b[g]);
     }
     void emit(std::vector<uint32_t> &host, const uint32_t *dev_base, BatchDev &b) const {
-        const size_t at = host.size();
-        b.ntiles = (uint32_t)t.size();
-        b.nwmap = (uint32_t)((w.size() + wn.size() + 3u) & ~size_t(3));
+        const uint32_t *p = dev_base + host.size();
+        b.nwmap = (uint32_t)(w.size() + wn.size());
         b.nwE = (uint32_t)w.size();
         b.ngroups = (uint32_t)g.size();
         b.nugroups = (uint32_t)u.size();
-        b.n = (uint32_t)r.size();
+        b.n = n;
         b.nsmall = (uint32_t)s.size();
         b.nall = (uint32_t)a.size();
-        host.insert(host.end(), t.begin(), t.end());
         host.insert(host.end(), w.begin(), w.end());
         host.insert(host.end(), wn.begin(), wn.end());
-        host.resize(at + b.ntiles + b.nwmap, kMapNone);
         host.insert(host.end(), g.begin(), g.end());
         host.insert(host.end(), u.begin(), u.end());
-        host.insert(host.end(), r.begin(), r.end());
         host.insert(host.end(), s.begin(), s.end());
         host.insert(host.end(), a.begin(), a.end());
-        const uint32_t *p = dev_base + at;
-        b.tmap = p;
-        b.wmap = p + b.ntiles;
+        b.wmap = p;
         b.gmap = b.wmap + b.nwmap;
         b.umap = b.gmap + b.ngroups;
-        b.rmap = b.umap + b.nugroups;
-        b.smap = b.rmap + b.n;
+        b.smap = b.umap + b.nugroups;
         b.amap = b.smap + b.nsmall;
     }
 };

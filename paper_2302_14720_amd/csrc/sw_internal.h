@@ -120,10 +120,8 @@ hipError_t launch_resolve(const Dev &d, hipStream_t s);
 // of every replica: entry = replica << kMapShift | unit.
 constexpr uint32_t kMapShift = 20;
 constexpr uint32_t kMapMask = (1u << kMapShift) - 1u;
-constexpr uint32_t kMapNone = 0xFFFFFFFFu;
-// 4095 so that no entry (replica <= 4094) can equal kMapNone, whatever the unit
 constexpr int32_t kMaxReplicas = 4095;
-static_assert(((uint32_t)(kMaxReplicas - 1) << kMapShift | kMapMask) != kMapNone, "map entry collides with kMapNone");
+static_assert(kMaxReplicas <= 1 << (32 - kMapShift), "a replica's index must fit its map entries");
 
 // The LDS merge a caller can ask for in a batch takes at most kSmallTiles tiles.
 constexpr uint32_t kSmallTiles = 16;
@@ -131,13 +129,13 @@ constexpr uint32_t kSmallTiles = 16;
 struct BatchDev {
     const Dev *devs;       // the replicas' Dev, in device memory
     const uint32_t *tmap;  // [ntiles] one entry per tile of every replica (k_tile, k_resolve)
-    const uint32_t *wmap;  // [nwmap] tiles with an E (first nwE) or N group edge (k_union), kMapNone-padded to 4
+    const uint32_t *wmap;  // [nwmap] tiles with an E (first nwE) or N group edge (k_union)
     const uint32_t *gmap;  // [ngroups] one per group of kGroupTiles tiles (k_flatten, k_roots)
     const uint32_t *umap;  // [nugroups] one per kUG x kUG group of tiles (k_ulocal)
-    const uint32_t *rmap;  // [n] the replicas (indices into devs) of the global merge
     const uint32_t *smap;  // [nsmall] one per kUG x kUG group of tiles of the replicas merged by k_merge
     const uint32_t *amap;  // [nall] every replica of the launch (records after k_resolve)
-    uint32_t n, ntiles, nwmap, ngroups, nugroups, tw;
+    uint32_t n;            // replicas of the global merge
+    uint32_t ntiles, nwmap, ngroups, nugroups, tw;
     uint32_t nwE, nsmall, nall;
     uint32_t potts;        // 1: every replica is a Potts model (q in its Dev)
 };
@@ -158,24 +156,9 @@ hipError_t launch_brick_stage(const Dev &d, int stage, hipStream_t s);
 hipError_t launch_brick_measure(const Dev &d, hipStream_t s);
 hipError_t launch_brick_labels(const Dev &d, hipStream_t s);
 
-// Stage 0 is the tile kernel of a launch group's replicas; stages 1..4 the
-// global merge; launch_batch_merge the replicas merged by k_merge.
-// launch_batch_sweep runs them all: the groups' tile kernels beside each
-// other, then k_merge beside the global merge.
-hipError_t launch_batch_stage(const BatchDev &b, int stage, hipStream_t s);
-hipError_t launch_batch_merge(const BatchDev &b, hipStream_t s);
-// Streams (default priority) beside the main one for kernels of a sweep that do
-// not depend on each other.
-struct Forks {
-    static constexpr int kSides = 3;
-    hipStream_t side[kSides];
-    hipEvent_t fork, join[kSides];
-    int n;  // side streams there are; 0: everything runs on the main stream
-};
-hipError_t forks_create(Forks &f, int n);  // n <= kSides
-int forks_wanted(const BatchDev *b, int ngroups);
-void forks_destroy(Forks &f);  // waits for the side streams
-hipError_t launch_batch_sweep(const BatchDev *b, int ngroups, hipStream_t s, const Forks &f);
+// One sweep of all launch groups: the tiles (of every group in one launch where
+// they are few), then k_merge and the global merge of the replicas of each.
+hipError_t launch_batch_sweep(const BatchDev *b, int ngroups, hipStream_t s);
 hipError_t launch_batch_resolve(const BatchDev &b, hipStream_t s);
 
 }  // namespace swmi

@@ -257,13 +257,39 @@ __device__ __forceinline__ uint32_t spread8(uint32_t v) {
 // DENSE: interior clusters also go to the exact size histogram -- those
 // below kDenseBins sites through LDS counts that leave with the tile
 // (tdense) and are added up per group in k_roots.
+// LDS of a tile workgroup.
+template <int TW, bool POTTS, bool DENSE, int SPT> struct TileShared {
+    using Row = typename RowOf<TW>::T;
+    static constexpr int NPL = POTTS ? 3 : 1, NWAVE = (TW * TW / SPT + 63) / 64;
+    // One word per site, rows padded to TW + 1 words so that the sites the
+    // lanes gather at equal offsets fall in distinct banks.  Low 16 bits:
+    // parent, as the byte offset of its word.  High 16 bits: the union work
+    // list while the unions run, then the cluster size (roots), then the
+    // root's output byte.
+    alignas(16) uint32_t par[TW * (TW + 1)];
+    Row up[POTTS && TW != 64 ? NPL * (TW + 1) : 1];  // bit planes (Potts)
+    Row ebnb[2 * TW];  // bond masks to E of every row (rows 0..TW-1)
+    Row fb[TW];        // new spins of every site as a root (Ising)
+    Row xn;            // bonds out to N
+    Row pw;            // permitted incoming bonds by row (from the W tile's last column)
+    uint32_t ps[2];    // and by column, even and odd (from the S tile's last row)
+    uint32_t eup[NPL * ((TW + 31) / 32)];
+    uint32_t xe[(TW + 31) / 32];
+    uint32_t bf[TW * TW / 32];
+    uint32_t hist[kTileBins];
+    uint32_t dense[DENSE ? kDenseBins : 1];
+    uint32_t node[TW == 64 ? 1 : 4 * TW];
+    int32_t red[NWAVE][POTTS ? 8 : 4];
+    uint8_t tab[256];
+};
+
 // SPT: sites per thread, 16 or 4.  With 16 the row masks cost least per site
 // and the tiles of a large lattice fill the GPU; a lattice of few tiles leaves
 // a wavefront or less per SIMD, which waits through every chain of its 16
 // sites alone, so there four times as many threads take 4 each (512^2,
 // beta_c: 22 -> 14 us).
 template <int TW, bool POTTS, bool DENSE, int TWO, int SPT>
-__device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
+__device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile, TileShared<TW, POTTS, DENSE, SPT> &sh) {
     using Row = typename RowOf<TW>::T;
     constexpr int NT = TW * TW / SPT;
     constexpr uint32_t RPT = TW / SPT;  // lanes per row
@@ -275,36 +301,28 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile) {
     constexpr uint32_t EW = (TW + 31) / 32;
     constexpr uint32_t CB = POTTS ? potts_code<TW>() : 2u;  // output byte of node 0
 
-    // One word per site, rows padded to PS = TW + 1 words so that the 16
-    // sites a lane gathers at equal offsets fall in distinct banks.  Low 16
-    // bits: parent, as the byte offset of its word.  High 16 bits: the union
-    // work list while the unions run, then the cluster size (roots), then
-    // the root's output byte.
     constexpr uint32_t PS = TW + 1;
-    __shared__ __align__(16) uint32_t s_par[TW * PS];
-    // spin masks (Potts: bit planes); they are dead before s_par is first
-    // written, so the 64-wide Potts tile keeps its three planes in s_par
+    auto &s_par = sh.par;
+    // the 64-wide Potts tile keeps its three planes in par, which is not in use
+    // yet while they live
     constexpr bool UP_IN_PAR = POTTS && TW == 64;
-    static_assert(!UP_IN_PAR || 3 * (TW + 1) * sizeof(Row) <= TW * PS * 4, "planes must fit in s_par");
-    __shared__ Row s_up_own[POTTS && !UP_IN_PAR ? NPL * (TW + 1) : 1];
-    Row *const s_up = UP_IN_PAR ? reinterpret_cast<Row *>(s_par) : s_up_own;
-    __shared__ Row s_ebnb[2 * TW];  // bond masks to E of every row (rows 0..TW-1)
-    Row *const s_eb = s_ebnb;
-    __shared__ Row s_fb[TW];
-    __shared__ Row s_xn;
-    __shared__ Row s_pw;          // permitted incoming bonds by row (from the W tile's last column)
-    __shared__ uint32_t s_ps[2];  // and by column, even and odd (from the S tile's last row)
-    __shared__ uint32_t s_eup[NPL * EW];
-    __shared__ uint32_t s_xe[EW];
-    __shared__ uint32_t s_bf[NW];
-    __shared__ uint8_t s_tab[256];
-    __shared__ uint32_t s_hist[kTileBins];
-    __shared__ uint32_t s_dense[DENSE ? kDenseBins : 1];
+    static_assert(!UP_IN_PAR || 3 * (TW + 1) * sizeof(Row) <= TW * PS * 4, "planes must fit in par");
+    Row *const s_up = UP_IN_PAR ? reinterpret_cast<Row *>(sh.par) : sh.up;
+    Row *const s_eb = sh.ebnb;
+    auto &s_fb = sh.fb;
+    auto &s_xn = sh.xn;
+    auto &s_pw = sh.pw;
+    auto &s_ps = sh.ps;
+    auto &s_eup = sh.eup;
+    auto &s_xe = sh.xe;
+    auto &s_bf = sh.bf;
+    auto &s_tab = sh.tab;
+    auto &s_hist = sh.hist;
+    auto &s_dense = sh.dense;
     // root | size << 16 of each node; for 64-wide tiles it reuses the bond
     // masks, which are dead once the unions are done
-    __shared__ uint32_t s_node_own[TW == 64 ? 1 : 4 * TW];
-    uint32_t *const s_node = TW == 64 ? reinterpret_cast<uint32_t *>(s_ebnb) : s_node_own;
-    __shared__ int32_t s_red[NWAVE][POTTS ? 8 : 4];
+    uint32_t *const s_node = TW == 64 ? reinterpret_cast<uint32_t *>(sh.ebnb) : sh.node;
+    auto &s_red = sh.red;
 
     const uint32_t tid = threadIdx.x;
     const uint32_t L = d.L, ntx = d.ntx;
@@ -875,7 +893,8 @@ constexpr int kTileWavesPerEU = 8;
 
 template <int TW, bool POTTS, bool DENSE, int TWO, int SPT>
 __global__ __launch_bounds__(TW *TW / SPT, TW == 64 && SPT == 16 && !DENSE ? kTileWavesPerEU : 1) void k_tile(Dev d) {
-    tile_body<TW, POTTS, DENSE, TWO, SPT>(d, tile_of_block(blockIdx.x, d.ntiles));
+    __shared__ TileShared<TW, POTTS, DENSE, SPT> sh;
+    tile_body<TW, POTTS, DENSE, TWO, SPT>(d, tile_of_block(blockIdx.x, d.ntiles), sh);
 }
 
 // Batched launches run the same bodies over a table of replicas (map
@@ -883,8 +902,42 @@ __global__ __launch_bounds__(TW *TW / SPT, TW == 64 && SPT == 16 && !DENSE ? kTi
 // those of its own plain sweep.
 template <int TW, bool POTTS, int TWO, int SPT>
 __global__ __launch_bounds__(TW *TW / SPT, TW == 64 && SPT == 16 ? kTileWavesPerEU : 1) void k_tile_b(const Dev *devs, const uint32_t *map) {
+    __shared__ TileShared<TW, POTTS, false, SPT> sh;
     const uint32_t e = map[tile_of_block(blockIdx.x, gridDim.x)];
-    tile_body<TW, POTTS, false, TWO, SPT>(devs[e >> kMapShift], e & kMapMask);
+    tile_body<TW, POTTS, false, TWO, SPT>(devs[e >> kMapShift], e & kMapMask, sh);
+}
+
+// Tiles of every kind in one launch, for batches of several launch groups whose
+// tiles do not fill the GPU group by group (kMixTiles).  256 threads suit a
+// 64-wide tile with 16 sites per thread and a 32-wide one with 4.  The bodies
+// take turns in one block of LDS; 80 VGPRs (at the 64 of the kernels of one
+// kind the four bodies together spill 54 words, here 26).  map: the groups'
+// tile maps one after another, blocks in map order, so that the slower tiles
+// spread over the XCDs.
+union MixShared {
+    TileShared<64, false, false, 16> i64;
+    TileShared<64, true, false, 16> p64;
+    TileShared<32, false, false, 4> i32;
+    TileShared<32, true, false, 4> p32;
+    __device__ MixShared() {}
+};
+
+__global__ __launch_bounds__(256, 6) void k_tile_mix(const Dev *devs, const uint32_t *map) {
+    __shared__ __align__(16) unsigned char mem[sizeof(MixShared)];
+    MixShared &sh = *reinterpret_cast<MixShared *>(mem);
+    const uint32_t e = map[blockIdx.x], tile = e & kMapMask;
+    const Dev &d = devs[e >> kMapShift];
+    if (d.tw == 64u) {
+        if (d.q)
+            tile_body<64, true, false, 2, 16>(d, tile, sh.p64);
+        else
+            tile_body<64, false, false, 2, 16>(d, tile, sh.i64);
+    } else {
+        if (d.q)
+            tile_body<32, true, false, 2, 4>(d, tile, sh.p32);
+        else
+            tile_body<32, false, false, 2, 4>(d, tile, sh.i32);
+    }
 }
 
 // =====================================================================
@@ -943,9 +996,8 @@ __device__ __forceinline__ void union_body(const Dev &d, const uint32_t tile, co
 // and k_union only has the edges between groups left.
 // =====================================================================
 template <int TW>
-__device__ __forceinline__ void ulocal_body(const Dev &d, const uint32_t ugroup) {
+__device__ __forceinline__ void ulocal_body(const Dev &d, const uint32_t ugroup, uint32_t *s_p) {
     constexpr uint32_t NG = kUG * kUG;
-    __shared__ uint32_t s_p[NG * kNodeSlots];
     const uint32_t tid = threadIdx.x, lane = tid & 63u;
     const uint32_t pc = (uint32_t)(*d.tdev & 1u);
     const uint32_t ntx = d.ntx, ngx = (ntx + kUG - 1u) / kUG;
@@ -1006,13 +1058,18 @@ __device__ __forceinline__ void ulocal_body(const Dev &d, const uint32_t ugroup)
 
 template <int TW>
 __global__ __launch_bounds__(256) void k_ulocal(Dev d) {
-    ulocal_body<TW>(d, blockIdx.x);
+    __shared__ uint32_t s_p[kUG * kUG * kNodeSlots];
+    ulocal_body<TW>(d, blockIdx.x, s_p);
 }
 
-template <int TW>
 __global__ __launch_bounds__(256) void k_ulocal_b(const Dev *devs, const uint32_t *map) {
+    __shared__ uint32_t s_p[kUG * kUG * kNodeSlots];
     const uint32_t e = map[blockIdx.x];
-    ulocal_body<TW>(devs[e >> kMapShift], e & kMapMask);
+    const Dev &d = devs[e >> kMapShift];
+    if (d.tw == 64u)
+        ulocal_body<64>(d, e & kMapMask, s_p);
+    else
+        ulocal_body<32>(d, e & kMapMask, s_p);
 }
 
 // One wavefront per (tile, direction): wave w of the launch takes tile w / 2
@@ -1033,14 +1090,20 @@ __global__ __launch_bounds__(256) void k_union(Dev d) {
     }
 }
 
-// One wavefront per map entry: the first nE entries are tiles whose E edge
-// is a group edge, the rest tiles whose N edge is (kMapNone pads the map to
-// whole workgroups).
-template <int TW>
-__global__ __launch_bounds__(256) void k_union_b(const Dev *devs, const uint32_t *map, uint32_t nE) {
-    const uint32_t w = blockIdx.x * 4u + (threadIdx.x >> 6);
-    const uint32_t e = map[w];
-    if (e != kMapNone) union_body<TW, ByIndex>(devs[e >> kMapShift], e & kMapMask, w < nE ? 0u : 1u);
+// One wavefront per map entry: the first nE of the n entries are tiles whose E
+// edge is a group edge, the rest tiles whose N edge is.
+__device__ __forceinline__ void union_b_body(const Dev *devs, const uint32_t *map, uint32_t n, uint32_t nE, uint32_t w) {
+    if (w >= n) return;
+    const uint32_t e = map[w], dir = w < nE ? 0u : 1u;
+    const Dev &d = devs[e >> kMapShift];
+    if (d.tw == 64u)
+        union_body<64, ByIndex>(d, e & kMapMask, dir);
+    else
+        union_body<32, ByIndex>(d, e & kMapMask, dir);
+}
+
+__global__ __launch_bounds__(256) void k_union_b(const Dev *devs, const uint32_t *map, uint32_t n, uint32_t nE) {
+    union_b_body(devs, map, n, nE, blockIdx.x * 4u + (threadIdx.x >> 6));
 }
 
 // =====================================================================
@@ -2036,6 +2099,24 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge_b(const Dev *devs, cons
     merge_body(devs[e >> kMapShift], e & kMapMask);
 }
 
+// k_merge of the small replicas (the first ns workgroups) beside the unions of
+// the large ones (16 wavefronts, of k_union_b, per workgroup): both are chains
+// of dependent accesses that leave the GPU nearly idle.  us per sweep, two
+// launches / one: a 64^2 and k 1088^2 lattices, k = 1 81.1 / 75.5, 16 160.6 /
+// 153.3, 96 560.8 / 563.4; 16 512^2 and k 1088^2, k = 1 118.4 / 109.4, 96 597.2
+// / 584.5.  A second stream for k_merge is 10 % better on a server where it has
+// a hardware queue of its own and 10 % worse where it has none (24 jobs, whole
+// run: 67.4 or 83.7 ms; so 69.1 in either case).
+__global__ __launch_bounds__(kMergeThreads) void k_join_b(const Dev *devs, const uint32_t *smap, uint32_t ns,
+                                                          const uint32_t *wmap, uint32_t nw, uint32_t nE) {
+    if (blockIdx.x < ns) {
+        const uint32_t e = smap[blockIdx.x];
+        merge_body(devs[e >> kMapShift], e & kMapMask);
+    } else {
+        union_b_body(devs, wmap, nw, nE, (blockIdx.x - ns) * kMergeWaves + (threadIdx.x >> 6));
+    }
+}
+
 // =====================================================================
 // k_resolve: replace node codes by final spins in place and measure the
 // configuration (runs once at the end of every sw_sweep call).
@@ -2419,123 +2500,53 @@ hipError_t launch_resolve(const Dev &d, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_batch_merge(const BatchDev &b, hipStream_t s) {
-    if (b.nsmall == 0) return hipSuccess;
-    k_merge_b<<<b.nsmall, kMergeThreads, 0, s>>>(b.devs, b.smap);
-    return hipGetLastError();
-}
+// Batches and servers whose replicas are of several launch groups take
+// k_tile_mix up to kMixTiles tiles per group: below, each group's own launch
+// leaves most of the GPU idle for the length of one tile; above, the groups'
+// own kernels gain from their occupancy and from 16 sites per thread in 32-wide
+// tiles.  us per sweep of a batch of k 512^2 and k 544^2 lattices, one launch
+// per group / k_tile_mix: k = 1 (353 tiles) 94.8 / 93.3, 8 (2824) 126.0 /
+// 118.4, 16 (5648) 143.8 / 158.3; 3-state 98.4 / 93.1, 131.1 / 119.3, 151.9 /
+// 159.8; 1024^2 and 1056^2, k = 2 (2690) 123.0 / 116.4, 4 (5380) 142.0 / 154.3.
+// A server of 24 Ising and Potts jobs of 128^2 to 2048^2 (four groups), whole
+// run: never 83.3 ms, up to 4096 tiles 75.0, up to 8192 68.4, always 67.6 to
+// 70.3.
+constexpr uint32_t kMixTiles = 2048;
 
-hipError_t launch_batch_stage(const BatchDev &b, int stage, hipStream_t s) {
-    switch (stage) {
-    case 0:
-        if (b.nall == 0) break;
-        // b.n replicas of the global merge, the others of k_merge
-        if (b.n == 0)
-            launch_tile_b<1>(b, s);
-        else if (b.n == b.nall)
-            launch_tile_b<0>(b, s);
-        else
-            launch_tile_b<2>(b, s);
-        break;
-    case 1:
-        if (b.nugroups == 0) break;
-        if (b.tw == 64) {
-            k_ulocal_b<64><<<b.nugroups, 256, 0, s>>>(b.devs, b.umap);
-            k_union_b<64><<<b.nwmap / 4, 256, 0, s>>>(b.devs, b.wmap, b.nwE);
-        } else {
-            k_ulocal_b<32><<<b.nugroups, 256, 0, s>>>(b.devs, b.umap);
-            k_union_b<32><<<b.nwmap / 4, 256, 0, s>>>(b.devs, b.wmap, b.nwE);
+hipError_t launch_batch_sweep(const BatchDev *b, int ngroups, hipStream_t s) {
+    uint32_t kinds = 0, ntiles = 0;
+    for (int g = 0; g < ngroups; ++g) {
+        kinds += b[g].nall != 0;
+        ntiles += b[g].ntiles;
+    }
+    const BatchDev &a = b[0];  // the units of every launch group but for the tiles
+    if (kinds > 1 && ntiles <= kMixTiles * kinds) {
+        k_tile_mix<<<ntiles, 256, 0, s>>>(a.devs, a.tmap);
+    } else {
+        for (int g = 0; g < ngroups; ++g) {
+            if (b[g].nall == 0) continue;
+            // n replicas of the global merge, the others of k_merge
+            if (b[g].n == 0)
+                launch_tile_b<1>(b[g], s);
+            else if (b[g].n == b[g].nall)
+                launch_tile_b<0>(b[g], s);
+            else
+                launch_tile_b<2>(b[g], s);
         }
-        break;
-    case 2:
-        if (b.ngroups != 0) k_flatten_b<<<b.ngroups, 256, 0, s>>>(b.devs, b.gmap);
-        break;
-    case 3:  // and the records
-        if (b.ngroups != 0) k_roots_b<<<b.ngroups, 256, 0, s>>>(b.devs, b.gmap);
-        break;
-    case 4:  // (folded by k_roots_b)
-        break;
-    default:
-        return hipErrorInvalidValue;
+    }
+    if (a.nugroups != 0) k_ulocal_b<<<a.nugroups, 256, 0, s>>>(a.devs, a.umap);
+    if (a.nsmall != 0 && a.nwmap != 0) {
+        k_join_b<<<a.nsmall + (a.nwmap + kMergeWaves - 1u) / kMergeWaves, kMergeThreads, 0, s>>>(
+            a.devs, a.smap, a.nsmall, a.wmap, a.nwmap, a.nwE);
+    } else {
+        if (a.nsmall != 0) k_merge_b<<<a.nsmall, kMergeThreads, 0, s>>>(a.devs, a.smap);
+        if (a.nwmap != 0) k_union_b<<<(a.nwmap + 3u) / 4u, 256, 0, s>>>(a.devs, a.wmap, a.nwmap, a.nwE);
+    }
+    if (a.ngroups != 0) {
+        k_flatten_b<<<a.ngroups, 256, 0, s>>>(a.devs, a.gmap);
+        k_roots_b<<<a.ngroups, 256, 0, s>>>(a.devs, a.gmap);  // and the records
     }
     return hipGetLastError();
-}
-
-int forks_wanted(const BatchDev *b, int ngroups) {
-    int tiles = 0;
-    bool small = false, large = false;
-    for (int g = 0; g < ngroups; ++g) {
-        tiles += b[g].nall != 0;
-        small = small || b[g].nsmall > 0;
-        large = large || b[g].ngroups > 0;
-    }
-    return tiles > 1 ? std::min(tiles - 1, Forks::kSides) : small && large ? 1 : 0;
-}
-
-hipError_t forks_create(Forks &f, int n) {
-    f = Forks{};
-    if (n == 0) return hipSuccess;
-    hipError_t e = hipEventCreateWithFlags(&f.fork, hipEventDisableTiming);
-    for (int i = 0; i < n && e == hipSuccess; ++i) {
-        e = hipStreamCreateWithFlags(&f.side[i], hipStreamNonBlocking);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&f.join[i], hipEventDisableTiming);
-    }
-    f.n = n;
-    if (e != hipSuccess) forks_destroy(f);
-    return e;
-}
-
-void forks_destroy(Forks &f) {
-    for (int i = 0; i < Forks::kSides; ++i) {
-        if (f.side[i]) {
-            (void)hipStreamSynchronize(f.side[i]);
-            (void)hipStreamDestroy(f.side[i]);
-        }
-        if (f.join[i]) (void)hipEventDestroy(f.join[i]);
-    }
-    if (f.fork) (void)hipEventDestroy(f.fork);
-    f = Forks{};
-}
-
-hipError_t launch_batch_sweep(const BatchDev *b, int ngroups, hipStream_t s, const Forks &f) {
-    // the groups' tile kernels: the first on the main stream, the others beside it
-    hipError_t e = hipSuccess;
-    int first = -1, sides = 0;
-    for (int g = 0; g < ngroups; ++g) {
-        if (b[g].nall == 0) continue;
-        if (first < 0)
-            first = g;
-        else
-            ++sides;
-    }
-    const bool split = sides > 0 && sides <= f.n;
-    if (split) e = hipEventRecord(f.fork, s);
-    int k = 0;
-    for (int g = 0; g < ngroups && e == hipSuccess; ++g) {
-        if (b[g].nall == 0 || (split && g == first)) continue;
-        hipStream_t on = split ? f.side[k] : s;
-        if (split) e = hipStreamWaitEvent(on, f.fork, 0);
-        if (e == hipSuccess) e = launch_batch_stage(b[g], 0, on);
-        if (e == hipSuccess && split) e = hipEventRecord(f.join[k++], on);
-    }
-    if (e == hipSuccess && split) e = launch_batch_stage(b[first], 0, s);
-    for (int i = 0; i < k && e == hipSuccess; ++i) e = hipStreamWaitEvent(s, f.join[i], 0);
-    // k_merge beside the global merge when both kinds are present
-    bool small = false, large = false;
-    for (int g = 0; g < ngroups; ++g) {
-        small = small || b[g].nsmall > 0;
-        large = large || b[g].ngroups > 0;
-    }
-    const bool both = f.n > 0 && small && large;
-    hipStream_t on = both ? f.side[0] : s;
-    if (e == hipSuccess && both) e = hipEventRecord(f.fork, s);
-    if (e == hipSuccess && both) e = hipStreamWaitEvent(on, f.fork, 0);
-    for (int g = 0; g < ngroups && e == hipSuccess; ++g) e = launch_batch_merge(b[g], on);
-    for (int stage = 1; stage < kStages && e == hipSuccess; ++stage)
-        for (int g = 0; g < ngroups && e == hipSuccess; ++g) e = launch_batch_stage(b[g], stage, s);
-    if (e == hipSuccess && both) e = hipEventRecord(f.join[0], on);
-    if (e == hipSuccess && both) e = hipStreamWaitEvent(s, f.join[0], 0);
-    return e;
 }
 
 hipError_t launch_batch_resolve(const BatchDev &b, hipStream_t s) {

@@ -101,7 +101,6 @@ struct sw_server {
     bool dirty = true;
     swmi::BatchDev bd[kGroups]{};  // active jobs by launch group (swmi::batch_group)
     uint64_t site_updates = 0;
-    swmi::Forks forks{};
     swmi::StageUser stage_user;
 };
 
@@ -133,10 +132,8 @@ int upload_maps(sw_server *s, swmi::BatchMaps *m, swmi::BatchDev *bd, int ngroup
     }
     std::vector<uint32_t> host;
     host.reserve(need);
-    for (int i = 0; i < ngroups; ++i) {
-        bd[i].devs = s->d_devs;
-        m[i].emit(host, s->d_maps, bd[i]);
-    }
+    for (int i = 0; i < ngroups; ++i) bd[i].devs = s->d_devs;
+    swmi::BatchMaps::emit(m, host, s->d_maps, bd);
     if (!host.empty()) HIP_TRY(hipMemcpy(s->d_maps, host.data(), host.size() * 4, hipMemcpyHostToDevice));
     return SW_OK;
 }
@@ -267,8 +264,6 @@ int sw_server_create(void *pool, size_t pool_bytes, int32_t max_jobs, void *hip_
             s->own_stream = e == hipSuccess;
         }
     }
-    // (the legacy null stream runs everything in order on itself)
-    if (e == hipSuccess && s->stream != nullptr) e = swmi::forks_create(s->forks, swmi::Forks::kSides);
     if (e != hipSuccess) {
         const int rc = swmi::hip_fail(e, "creating the server");
         sw_server_destroy(s);
@@ -312,7 +307,7 @@ int sw_server_step(sw_server *s, int64_t n, int64_t *done_ids, int32_t cap, int3
         int64_t k = left;
         for (const Job *j : s->active) k = std::min(k, j->target - j->done);
         for (int64_t i = 0; i < k; ++i)
-            HIP_TRY(swmi::launch_batch_sweep(s->bd, kGroups, s->stream, s->forks));
+            HIP_TRY(swmi::launch_batch_sweep(s->bd, kGroups, s->stream));
         uint64_t sites = 0;
         for (Job *j : s->active) {
             j->done += k;
@@ -432,7 +427,6 @@ void sw_server_destroy(sw_server *s) {
     (void)srv_device(s);
     (void)hipStreamSynchronize(s->stream);
     for (auto &kv : s->jobs) delete kv.second;
-    swmi::forks_destroy(s->forks);
     if (s->d_maps) (void)hipFree(s->d_maps);
     if (s->d_devs) (void)hipFree(s->d_devs);
     if (s->own_pool && s->pool_mem) (void)hipFree(s->pool_mem);
