@@ -647,11 +647,22 @@ namespace {
 
 constexpr int64_t kDefaultBatchRing = 1024;
 
-// A replica's device view.  k_merge takes every replica it can; one of at most
-// 16 tiles whose caller asked for the global merge gets that.
-Dev replica_dev(const sw_config &c, char *base, const Layout &lo, bool lds) {
+// A batch whose replicas of more than 16 tiles make more k_merge workgroups than
+// this merges them globally: one of those workgroups fills a CU (75 KB of LDS, 16
+// wavefronts), so from two rounds of them on the global merge's small
+// workgroups are faster.  us per sweep, global / k_merge: 512^2, 32 replicas
+// (128 groups) 99.8 / 77.3, 128 (512) 201.8 / 199.5, 256 (1024) 334.3 / 376.3;
+// 1024^2, 16 (256) 139.1 / 121.2, 32 (512) 204.8 / 207.4, 64 (1024) 337.4 /
+// 385.8; sides 64 to 1024, 128 replicas (500) 221.6 / 215.6, 160 (640) 258.9 /
+// 267.0, 256 (1020) 369.6 / 407.4.
+constexpr uint32_t kWideGroups = 512;
+
+// A replica's device view.  k_merge takes those of at most 16 tiles whose
+// caller did not ask for the global merge (lds), and larger ones as it would
+// alone while the batch's are few (wide).
+Dev replica_dev(const sw_config &c, char *base, const Layout &lo, bool lds, bool wide) {
     Dev d = make_dev(c, base, lo);
-    if (!lds && d.ntiles <= swmi::kSmallTiles) d.two = 0u;
+    if (!lds && (d.ntiles <= swmi::kSmallTiles || !wide)) d.two = 0u;
     return d;
 }
 
@@ -659,6 +670,7 @@ struct BatchPlan {
     std::vector<sw_config> cfg;
     std::vector<size_t> base;   // workspace offset of every replica
     std::vector<uint8_t> lds;   // merge in LDS
+    bool wide;                  // k_merge also for replicas of more than 16 tiles
     size_t devs, maps, total;
     size_t map_words;
 };
@@ -681,7 +693,7 @@ int plan_batch(int32_t n, const int32_t *L, const double *beta, const double *J,
     p->base.assign((size_t)n, 0);
     p->lds.assign((size_t)n, 0);
     size_t off = 0;
-    swmi::BatchMaps m[kBatchGroups];
+    uint32_t groups = 0;  // k_merge workgroups of the replicas of more than 16 tiles
     for (int32_t r = 0; r < n; ++r) {
         const std::string who = "replica " + std::to_string(r) + ": ";
         sw_config &c = p->cfg[(size_t)r];
@@ -702,11 +714,14 @@ int plan_batch(int32_t n, const int32_t *L, const double *beta, const double *J,
         if (mg == SW_MERGE_LDS && nt > swmi::kSmallTiles)
             return fail(SW_EINVAL, who + "the LDS merge takes at most " + std::to_string(swmi::kSmallTiles) + " tiles");
         p->lds[(size_t)r] = (mg != SW_MERGE_GLOBAL && nt <= swmi::kSmallTiles) ? 1u : 0u;
-        const Layout lo = layout_of(c);
+        if (nt > swmi::kSmallTiles && swmi::merge_in_one(c)) groups += swmi::merge_groups(c);
         p->base[(size_t)r] = off;
-        off = align_up(off + lo.total);
-        swmi::BatchMaps::add((uint32_t)r, replica_dev(c, nullptr, lo, p->lds[(size_t)r] != 0), m);
+        off = align_up(off + layout_of(c).total);
     }
+    p->wide = groups <= kWideGroups;
+    swmi::BatchMaps m[kBatchGroups];
+    for (size_t r = 0; r < p->cfg.size(); ++r)
+        swmi::BatchMaps::add((uint32_t)r, replica_dev(p->cfg[r], nullptr, Layout{}, p->lds[r] != 0, p->wide), m);
     p->map_words = 0;
     for (const swmi::BatchMaps &g : m) p->map_words += g.words();
     auto take = [&](size_t bytes) {
@@ -837,7 +852,7 @@ int batch_create(int32_t n, const int32_t *L, const double *beta, const double *
     b->dev.resize(p.cfg.size());
     swmi::BatchMaps m[kBatchGroups];
     for (size_t r = 0; r < p.cfg.size(); ++r) {
-        b->dev[r] = replica_dev(p.cfg[r], base + p.base[r], layout_of(p.cfg[r]), p.lds[r] != 0);
+        b->dev[r] = replica_dev(p.cfg[r], base + p.base[r], layout_of(p.cfg[r]), p.lds[r] != 0, p.wide);
         swmi::BatchMaps::add((uint32_t)r, b->dev[r], m);
     }
     std::vector<uint32_t> host;

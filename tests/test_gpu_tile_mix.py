@@ -54,3 +54,15 @@ def test_server_of_four_kinds():
         rec, spins = _expected(L, beta, seed, n, q)
         assert np.asarray(srv.series(i, 0, n)).tobytes() == rec, (L, q)
         assert np.array_equal(srv.spins(i), spins), (L, q)
+
+
+def test_batch_of_many_large_replicas():
+    """528 merge workgroups: the large replicas take the global merge, the small ones still one launch."""
+    sides, n, beta = [1024] * 33 + [256, 64], 2, 0.44
+    seeds = [31 + i for i in range(len(sides))]
+    b = sw.Batch(sides, beta, 1.0, seeds)
+    b.sweep(n)
+    for r in (0, 32, 33, 34):
+        rec, spins = _expected(sides[r], beta, seeds[r], n, 0)
+        assert np.asarray(b.series(r, 0, n)).tobytes() == rec, sides[r]
+        assert np.array_equal(b.spins(r), spins), sides[r]
