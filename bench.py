@@ -47,15 +47,14 @@ TILE_BYTES_PER_SITE = 2.0
 # out), flip 5 (label in, spin out).
 MODEL_BYTES_PER_SITE = 12.0
 PHILOX_OPS = 60.0
-# Paths with 32-bit labels in HBM, algorithmic bytes per site and sweep.
+# Paths with labels or codes in HBM, algorithmic bytes per site and sweep.
 # Label equivalence: bonds 2 (spins in, mask out), label init 4, every pass
 # 9 (scan: mask 1 + label 4; analysis: label 4), roots 4, flip 6 (labels 4,
 # new spin 1 gathered, spin 1 out), statistics 5 (spin 1, label 4).
-# Cubic bricks: bricks 6 (spin 1 in, mask 1 and label 4 out), face unions
-# 27/16 (3/16 of the sites on a +face: mask 1, two labels 8), flatten 1
-# (mask), relabel 10 (mask 1, label 4 in and out, spin 1 out), statistics 5.
+# Cubic bricks: spin in, 16-bit code out and in, spin out, and the codes of the
+# six faces out and in (3/8 of the sites, 2 bytes each); node tables are small.
 LE_BYTES_FIXED, LE_BYTES_PER_PASS = 21.0, 9.0
-BRICK_BYTES_PER_SITE = 6.0 + 27.0 / 16.0 + 1.0 + 10.0 + 5.0
+BRICK_BYTES_PER_SITE = 1.0 + 2.0 + 2.0 + 1.0 + 0.75 + 0.75
 
 
 def hbm_fields(rate: float, bytes_per_site: float) -> dict:
@@ -342,11 +341,10 @@ def serving(args):
 # Context only: other hardware, other code.
 PAPER_PHI4_GPU_MINUTES = {16: 0.186, 20: 0.305, 24: 0.619, 28: 1.188}
 PHI4_KAPPA = 0.304
-# Algorithmic bytes per site and update of the five phi^4 kernels: fields
-# 32 B in and projection 8 B, parent and size out (projections); five
-# projections in (bonds); root in and out (flatten); fields in and out,
-# root and projection in (reflection); five fields, root and size in (record).
-PHI4_BYTES_PER_SITE = (32 + 8 + 4 + 4) + 40 + 8 + (32 + 32 + 4 + 8) + (5 * 32 + 8)
+# Algorithmic bytes per site and update of the phi^4 kernels: own and four
+# neighbour fields in, parent and size out (bonds); root in and out, fields in
+# and out (flatten and reflection); five fields, root and size in (record).
+PHI4_BYTES_PER_SITE = (5 * 32 + 4 + 4) + 8 + (32 + 32) + (5 * 32 + 8)
 
 
 def phi4(args):

@@ -259,13 +259,14 @@ const char *sw_last_error(void);
 
 /* ------------------------------------------------------------- batches
  * A batch advances n independent lattices (replicas) together: every kernel
- * of a sweep (Sec. 2) runs once over all replicas of a launch group (the
- * replicas with one tile width and model), so a sweep of the whole batch
+ * of a sweep (Sec. 2) runs once over all its replicas (the tile kernels of a
+ * large batch once per tile width and model), so a sweep of the whole batch
  * costs a handful of kernel launches (replayed from one captured graph)
- * instead of five or six per replica.  The cross-tile merge of Sec. 2.3 runs
+ * instead of two to six per replica.  The cross-tile merge of Sec. 2.3 runs
  * either globally (four launches over all such replicas, the record folded
  * into the last) or, for a replica of at most 16 groups of 4 x 4 tiles, by
- * one workgroup per group in LDS (one launch for all such replicas); a
+ * one workgroup per group in LDS (one launch for all such replicas, while
+ * those of more than 16 tiles make at most 512 groups together); a
  * replica of at most 16 tiles is one group (SW_MERGE_LDS) unless its caller
  * asks for the global merge.  Replica r has its own L[r], beta[r], J[r],
  * seed[r] and its own records; its spins, clusters and records are bit for
@@ -315,7 +316,7 @@ int sw_batch_create_potts(int32_t n, const int32_t *L, const double *beta, const
  * (0 automatic, 32, 64; as sw_config.tile); merge (NULL: automatic) every
  * replica's merge (SW_MERGE_AUTO, SW_MERGE_LDS -- SW_EINVAL for a replica
  * of more than 16 tiles -- or SW_MERGE_GLOBAL).  Replicas of different tile
- * widths or models run in separate launch groups of the same sweep.  These
+ * widths and models run in the same sweep.  These
  * choices change no result, only speed; the binding's autotuner picks them
  * per lattice side. */
 size_t sw_batch_workspace_bytes_ex(int32_t n, const int32_t *L, const int32_t *q, const int32_t *tiles,

@@ -11,13 +11,17 @@
 //   k_union   union of nodes joined by bonds that cross tile edges: first
 //             (k_ulocal) inside each 4x4 group of tiles in LDS, then, for
 //             the edges between groups, by lock-free union-find in global
-//             memory (the root is the node with the smaller index).
+//             memory (the root is the node with the smaller index, or,
+//             in the ordered phase of a large lattice, with the smaller
+//             bit-reversed index).
 //   k_flatten point every node at its root; add node sizes into the roots
 //             and reduce node keys to the cluster's smallest site.
 //   k_roots   new spin of each cross-tile cluster, cluster statistics.
 //   k_record  fold partial statistics into the per-sweep record ring (on
 //             lattices of at most 64 groups the last k_roots workgroup
 //             folds them, and the sweep is four launches).
+// On lattices of at most 16 groups of 4x4 tiles, k_merge does all after k_tile
+// in one launch.  Batches and servers run the same bodies over work maps (k_*_b).
 // Spins are double-buffered by sweep parity.  A written spin byte is either
 // the final spin (0x01 = +1, 0xFF = -1) or 2 + k, a reference to node k of
 // the tile, resolved through the node tables of that sweep when the byte is

@@ -45,7 +45,7 @@ namespace {
 
 constexpr int kPhiBlock = 256;
 // Sites per workgroup (one per thread) whose bonds are joined in LDS.  A sweep
-// is bound by its chains of dependent loads and atomics, not by its 330 B per
+// is bound by its chains of dependent loads and atomics, not by its 400 B per
 // site: joining every bond in global memory, counting sizes with an atomic
 // per wavefront and root, and summing the record with 42 atomics and two
 // cache fences per 256 sites took 28 + 20 + 42 us at 20^4, kappa = 0.304;
