@@ -150,7 +150,9 @@ hipError_t copy_staged(Stage &st, void *dst, const void *src, size_t n, hipStrea
         return e;
     }
     hipError_t e = hipSuccess;
-    if (n < kCopySplit) {
+    // hipStreamPerThread names another stream in every thread: only in this one
+    // does a copy come after the caller's work
+    if (n < kCopySplit || s == hipStreamPerThread) {
         e = copy_chunks(st, (char *)dst, (const char *)src, n, 0, 1, 0, kCopySlots, s);
     } else {
         std::atomic<int> err{(int)hipSuccess};

@@ -1,0 +1,118 @@
+// Host build of sw_copy.hip against a stand-in for the HIP runtime, to look at
+// what copy_to_host asks of it: which thread copies on which stream, and what
+// it allocates.  Usage: copy_host SCENARIO; exit status 0 if it holds.
+#include <stdio.h>
+#include <stdlib.h>
+
+#include <map>
+#include <set>
+
+#include "sw_copy.hip"
+
+namespace {
+
+std::mutex mu;
+thread_local int cur_device = 0;
+
+// One device buffer: `fresh` is what the work enqueued on `stream` by the
+// thread `owner` leaves in it; a copy that does not come after that work in
+// stream order sees `stale`.
+struct Buffer {
+    std::vector<char> stale, fresh;
+    hipStream_t stream;
+    std::thread::id owner;
+
+    Buffer(size_t n, hipStream_t s) : stale(n, 0), fresh(n), stream(s), owner(std::this_thread::get_id()) {
+        for (size_t i = 0; i < n; ++i) fresh[i] = (char)(1 + i % 251 + (i >> 20));
+        std::lock_guard<std::mutex> hold(mu);
+        all.insert(this);
+    }
+    ~Buffer() {
+        std::lock_guard<std::mutex> hold(mu);
+        all.erase(this);
+    }
+    static std::set<Buffer *> all;
+};
+std::set<Buffer *> Buffer::all;
+
+bool check(bool ok, const char *what) {
+    if (!ok) printf("failed: %s\n", what);
+    return ok;
+}
+
+}  // namespace
+
+extern "C" {
+hipError_t hipGetDevice(int *d) {
+    *d = cur_device;
+    return hipSuccess;
+}
+hipError_t hipSetDevice(int d) {
+    cur_device = d;
+    return hipSuccess;
+}
+hipError_t hipGetLastError(void) { return hipSuccess; }
+hipError_t hipHostMalloc(void **p, size_t n, unsigned int) {
+    *p = malloc(n);
+    return hipSuccess;
+}
+hipError_t hipHostFree(void *p) {
+    free(p);
+    return hipSuccess;
+}
+hipError_t hipEventCreateWithFlags(hipEvent_t *e, unsigned) {
+    *e = (hipEvent_t)malloc(1);
+    return hipSuccess;
+}
+hipError_t hipEventDestroy(hipEvent_t e) {
+    free(e);
+    return hipSuccess;
+}
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind, hipStream_t s) {
+    const Buffer *b = nullptr;
+    {
+        std::lock_guard<std::mutex> hold(mu);
+        for (const Buffer *x : Buffer::all)
+            if (src >= x->stale.data() && src < x->stale.data() + x->stale.size()) b = x;
+    }
+    if (!b) return hipErrorInvalidValue;
+    const size_t at = (const char *)src - b->stale.data();
+    const bool ordered = s == b->stream && (s != hipStreamPerThread || std::this_thread::get_id() == b->owner);
+    memcpy(dst, (ordered ? b->fresh.data() : b->stale.data()) + at, n);
+    return hipSuccess;
+}
+}
+
+namespace {
+
+bool copies(size_t n, hipStream_t s) {
+    Buffer b(n, s);
+    std::vector<char> out(n, 0);
+    if (swmi::copy_to_host(out.data(), b.stale.data(), n, s) != hipSuccess) return false;
+    return out == b.fresh;
+}
+
+// Sizes below and above every limit, each with a remainder.
+const size_t kSizes[] = {1, 320, (size_t)64 << 10, ((size_t)64 << 10) + 1, (size_t)1 << 20, ((size_t)3 << 20) + 7,
+                         (size_t)8 << 20, ((size_t)33 << 20) + 11};
+
+bool every_size(hipStream_t s) {
+    swmi::StageUser user;
+    bool ok = true;
+    for (size_t n : kSizes) ok = check(copies(n, s), "copy") && ok;
+    return ok;
+}
+
+}  // namespace
+
+int main(int argc, char **argv) {
+    const std::string what = argc > 1 ? argv[1] : "";
+    bool ok = false;
+    if (what == "stream") ok = every_size((hipStream_t)0x1000);
+    if (what == "null_stream") ok = every_size(nullptr);
+    if (what == "per_thread_stream") ok = every_size(hipStreamPerThread);
+    return ok ? 0 : 1;
+}
