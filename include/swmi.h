@@ -548,6 +548,8 @@ void sw_phi4_destroy(sw_phi4 *sim);
  * same bits, same record.  spins: device pointer to N = L*L int8 spins
  * (+1 / -1, site order s = y*L + x, 16-byte aligned), read as the incoming
  * configuration and overwritten with the configuration sweep t leaves.
+ * (The host cannot check bytes in device memory: one that is neither +1 nor
+ * -1 is taken as +1.)
  * rec: device pointer to one sw_obs (8-byte aligned), which receives record t.  hip_stream:
  * the stream all work is enqueued on (NULL: the null stream); the call
  * returns without waiting.  Nothing is allocated: every other buffer of the

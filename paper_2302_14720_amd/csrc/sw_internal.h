@@ -110,6 +110,12 @@ struct Dev {
     double J;
 };
 
+// Four Ising spin bytes: 0xFF stays -1, every other byte becomes +1.
+__host__ __device__ inline uint32_t spin_bytes(uint32_t w) {
+    const uint32_t m = (((w & 0x7F7F7F7Fu) + 0x01010101u) & w & 0x80808080u) >> 7;  // 1 in every byte that is 0xFF
+    return 0x01010101u | m * 0xFFu;
+}
+
 constexpr int kStages = 5;  // kernels of one sweep, in stream order
 
 hipError_t launch_init(const Dev &d, int cold, hipStream_t s);

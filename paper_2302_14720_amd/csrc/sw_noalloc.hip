@@ -45,13 +45,24 @@ int scratch_of(int device, void **out) {
 
 // Sets the sweep index and clears what a sweep expects to start at zero:
 // the record accumulator, and the node counts of the previous parity (the
-// caller's spins are final values, never node codes).
-__global__ __launch_bounds__(256) void k_na_prepare(swmi::Dev d, uint64_t t) {
+// caller's spins are final values, never node codes).  The host cannot look at
+// the caller's spins, so bytes that are no spin become +1 here: the two tiles
+// beside an edge decide its bond each for itself and take a byte such as 0 or a
+// node code differently, and a bond that only one of them sees has no node on
+// the other's side.
+__global__ __launch_bounds__(256) void k_na_prepare(swmi::Dev d, uint64_t t, int8_t *spins) {
     const uint32_t i = blockIdx.x * 256u + threadIdx.x;
     const uint32_t pp = (uint32_t)(t & 1u) ^ 1u;
     if (i == 0u) *d.tdev = t;
     if (i < (uint32_t)swmi::kAccWords) d.acc[i] = 0u;
     for (uint32_t k = i; k < d.ntiles; k += gridDim.x * 256u) d.nk[pp][k] = 0u;
+    uint4 *sp = reinterpret_cast<uint4 *>(spins);
+    for (size_t k = i; k < d.nsite / 16u; k += (size_t)gridDim.x * 256u) {
+        const uint4 v = sp[k];
+        const uint4 f = make_uint4(swmi::spin_bytes(v.x), swmi::spin_bytes(v.y), swmi::spin_bytes(v.z),
+                                   swmi::spin_bytes(v.w));
+        if (f.x != v.x || f.y != v.y || f.z != v.z || f.w != v.w) sp[k] = f;
+    }
 }
 
 // Final spins and the record back to the caller's buffers.
@@ -94,13 +105,12 @@ extern "C" int sw_sweep_noalloc(int32_t L, double beta, double J, uint64_t seed,
     d.spins[(t + 1u) & 1u] = (int8_t *)((char *)base + lo.spins[0]);
     d.spins[t & 1u] = spins;
     hipStream_t s = (hipStream_t)hip_stream;
-    const uint32_t g = (d.ntiles + 255u) / 256u;
-    k_na_prepare<<<g > 0u ? g : 1u, 256, 0, s>>>(d, t);
+    const size_t n16 = d.nsite / 16u;
+    const uint32_t gf = (uint32_t)std::min<size_t>((n16 + 255u) / 256u, 4096u);
+    k_na_prepare<<<gf, 256, 0, s>>>(d, t, spins);
     HIP_TRY(hipGetLastError());
     HIP_TRY(launch_sweep(d, s));
     HIP_TRY(launch_resolve(d, s));
-    const size_t n16 = d.nsite / 16u;
-    const uint32_t gf = (uint32_t)std::min<size_t>((n16 + 255u) / 256u, 4096u);
     k_na_finish<<<gf, 256, 0, s>>>(d, t, spins, rec);
     HIP_TRY(hipGetLastError());
     return SW_OK;
