@@ -1,4 +1,4 @@
-// sw_copy.hip -- results to the caller's (pageable) memory through pinned
+// sw_copy.hip -- results to the caller's memory, pageable memory through pinned
 // staging buffers.
 //
 // A pageable hipMemcpy waits for its own staging: 20 us for a record, 34 us for
@@ -179,7 +179,21 @@ hipError_t copy_staged(Stage &st, void *dst, const void *src, size_t n, hipStrea
 
 }  // namespace
 
+// Memory the device reaches by itself (pinned, managed or its own) needs no
+// staging: 1 MiB into pinned memory takes 27 us straight and 60 through a slot,
+// 268 MB 4.7 and 8.4 ms.  The question costs 0.2 us.
+static bool device_writes(const void *dst) {
+    hipPointerAttribute_t at{};
+    if (hipPointerGetAttributes(&at, dst) == hipSuccess) return at.type != hipMemoryTypeUnregistered;
+    (void)hipGetLastError();
+    return false;
+}
+
 hipError_t copy_to_host(void *dst, const void *src, size_t n, hipStream_t s) {
+    if (device_writes(dst)) {
+        const hipError_t e = hipMemcpyAsync(dst, src, n, hipMemcpyDeviceToHost, s);
+        return e != hipSuccess ? e : hipStreamSynchronize(s);
+    }
     int device = 0;
     hipError_t e = hipGetDevice(&device);
     if (e != hipSuccess) return e;

@@ -22,7 +22,8 @@ int hip_fail(hipError_t e, const char *what);
 const std::string &last_error();
 
 // Copies n device bytes to host memory after everything enqueued on s, and
-// waits (through pinned staging; without any to be had, a pageable copy).
+// waits (into pageable memory through pinned staging; without any to be had, a
+// pageable copy).
 hipError_t copy_to_host(void *dst, const void *src, size_t n, hipStream_t s);
 // Held by every object that copies; the last one gives the staging back.
 struct StageUser {

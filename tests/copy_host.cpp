@@ -1,6 +1,6 @@
 // Host build of sw_copy.hip against a stand-in for the HIP runtime, to look at
-// what copy_to_host asks of it: which thread copies on which stream, and what
-// it allocates.  Usage: copy_host SCENARIO; exit status 0 if it holds.
+// what copy_to_host asks of it: which thread copies on which stream, where to,
+// and what it allocates.  Usage: copy_host SCENARIO; exit status 0 if it holds.
 #include <stdio.h>
 #include <stdlib.h>
 
@@ -34,6 +34,12 @@ struct Buffer {
     static std::set<Buffer *> all;
 };
 std::set<Buffer *> Buffer::all;
+
+// Memory the device reaches by itself, and what copies wrote there.
+const char *mapped = nullptr;
+size_t mapped_bytes = 0, straight = 0;
+
+bool is_mapped(const void *p) { return mapped && p >= mapped && p < mapped + mapped_bytes; }
 
 bool check(bool ok, const char *what) {
     if (!ok) printf("failed: %s\n", what);
@@ -71,6 +77,10 @@ hipError_t hipEventDestroy(hipEvent_t e) {
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t *at, const void *p) {
+    at->type = is_mapped(p) ? hipMemoryTypeHost : hipMemoryTypeUnregistered;
+    return hipSuccess;
+}
 hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind, hipStream_t s) {
     const Buffer *b = nullptr;
     {
@@ -80,6 +90,7 @@ hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind, h
     }
     if (!b) return hipErrorInvalidValue;
     const size_t at = (const char *)src - b->stale.data();
+    if (is_mapped(dst)) straight += n;
     const bool ordered = s == b->stream && (s != hipStreamPerThread || std::this_thread::get_id() == b->owner);
     memcpy(dst, (ordered ? b->fresh.data() : b->stale.data()) + at, n);
     return hipSuccess;
@@ -106,6 +117,23 @@ bool every_size(hipStream_t s) {
     return ok;
 }
 
+// Into memory that the device reaches by itself: one copy, straight there.
+bool into_mapped() {
+    swmi::StageUser user;
+    bool ok = true;
+    for (size_t n : kSizes) {
+        Buffer b(n, (hipStream_t)0x1000);
+        std::vector<char> out(n, 0);
+        mapped = out.data();
+        mapped_bytes = n;
+        straight = 0;
+        ok = check(swmi::copy_to_host(out.data(), b.stale.data(), n, b.stream) == hipSuccess, "copy") && ok;
+        ok = check(out == b.fresh, "bytes") && check(straight == n, "not straight") && ok;
+        mapped = nullptr;
+    }
+    return ok;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -114,5 +142,6 @@ int main(int argc, char **argv) {
     if (what == "stream") ok = every_size((hipStream_t)0x1000);
     if (what == "null_stream") ok = every_size(nullptr);
     if (what == "per_thread_stream") ok = every_size(hipStreamPerThread);
+    if (what == "into_mapped") ok = into_mapped();
     return ok ? 0 : 1;
 }
