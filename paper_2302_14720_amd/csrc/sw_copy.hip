@@ -34,17 +34,23 @@ struct Stage {
     bool events;
 };
 
-// Stages wait here between copies, at most kIdle of them (16 MiB of pinned
-// memory); a copy owns its stage while it runs, so any number of threads and
-// streams may copy at once.  When the last sim, batch, server or phi^4 sim of
-// the process is destroyed they are given back but for one (4 MiB): freeing
+// Every device has up to kPerDevice stages of its own; a copy owns one while it
+// runs and parks it afterwards, so that eight threads can read at once without
+// an allocation in the steady state (making and freeing pinned memory takes
+// hundreds of us).  With all of a device's stages taken a copy is a pageable
+// one.  When the last sim, batch, server or phi^4 sim of the process is
+// destroyed all are given back but for one (at most 4 MiB): freeing
 // pinned memory makes the next create 270 us slower (205 -> 475 us at 512^2)
 // and its first read 170 us (30 -> 200), which a program that makes one sim
 // after another would pay each time.
-constexpr int kIdle = 4;
+constexpr int kPerDevice = 8;
+constexpr int kMaxDevices = 64;
+struct DeviceStages {
+    Stage parked[kPerDevice];
+    int nparked, live;  // live: parked or owned by a copy
+};
 std::mutex g_lock;
-Stage g_idle[kIdle];
-int g_nidle = 0;
+DeviceStages g_dev[kMaxDevices];
 int64_t g_users = 0;
 
 void stage_free(Stage &st) {
@@ -54,28 +60,26 @@ void stage_free(Stage &st) {
     st = Stage{};
 }
 
-Stage stage_take(int device) {
+// false: none free.
+bool stage_take(int device, Stage &st) {
+    if (device < 0 || device >= kMaxDevices) return false;
     std::lock_guard<std::mutex> hold(g_lock);
-    for (int i = g_nidle - 1; i >= 0; --i) {
-        if (g_idle[i].device != device) continue;
-        const Stage st = g_idle[i];
-        g_idle[i] = g_idle[--g_nidle];
-        return st;
+    DeviceStages &d = g_dev[device];
+    if (d.nparked > 0) {
+        st = d.parked[--d.nparked];
+        return true;
     }
-    Stage st{};
+    if (d.live == kPerDevice) return false;
+    ++d.live;
+    st = Stage{};
     st.device = device;
-    return st;
+    return true;
 }
 
-void stage_give(Stage &st) {
-    {
-        std::lock_guard<std::mutex> hold(g_lock);
-        if (g_nidle < (g_users > 0 ? kIdle : 1)) {
-            g_idle[g_nidle++] = st;
-            return;
-        }
-    }
-    stage_free(st);
+void stage_give(const Stage &st) {
+    std::lock_guard<std::mutex> hold(g_lock);
+    DeviceStages &d = g_dev[st.device];
+    d.parked[d.nparked++] = st;
 }
 
 // Pinned memory for a copy of n bytes; false: none to be had.
@@ -134,15 +138,23 @@ hipError_t copy_chunks(const Stage &st, char *dst, const char *src, size_t n, si
     return hipSuccess;
 }
 
-}  // namespace
+hipError_t copy_straight(void *dst, const void *src, size_t n, hipStream_t s) {
+    const hipError_t e = hipMemcpyAsync(dst, src, n, hipMemcpyDeviceToHost, s);
+    return e != hipSuccess ? e : hipStreamSynchronize(s);
+}
 
-namespace {
+// Memory the device reaches by itself (pinned, managed or its own) needs no
+// staging: 1 MiB into pinned memory takes 27 us straight and 60 through a slot,
+// 268 MB 4.7 and 8.4 ms.  The question costs 0.2 us.
+bool device_writes(const void *dst) {
+    hipPointerAttribute_t at{};
+    if (hipPointerGetAttributes(&at, dst) == hipSuccess) return at.type != hipMemoryTypeUnregistered;
+    (void)hipGetLastError();
+    return false;
+}
 
 hipError_t copy_staged(Stage &st, void *dst, const void *src, size_t n, hipStream_t s) {
-    if (!stage_reserve(st, n)) {
-        const hipError_t e = hipMemcpyAsync(dst, src, n, hipMemcpyDeviceToHost, s);
-        return e != hipSuccess ? e : hipStreamSynchronize(s);
-    }
+    if (!stage_reserve(st, n)) return copy_straight(dst, src, n, s);
     if (n <= st.cap && n <= kCopyChunk) {
         hipError_t e = hipMemcpyAsync(st.pin, src, n, hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -179,25 +191,12 @@ hipError_t copy_staged(Stage &st, void *dst, const void *src, size_t n, hipStrea
 
 }  // namespace
 
-// Memory the device reaches by itself (pinned, managed or its own) needs no
-// staging: 1 MiB into pinned memory takes 27 us straight and 60 through a slot,
-// 268 MB 4.7 and 8.4 ms.  The question costs 0.2 us.
-static bool device_writes(const void *dst) {
-    hipPointerAttribute_t at{};
-    if (hipPointerGetAttributes(&at, dst) == hipSuccess) return at.type != hipMemoryTypeUnregistered;
-    (void)hipGetLastError();
-    return false;
-}
-
 hipError_t copy_to_host(void *dst, const void *src, size_t n, hipStream_t s) {
-    if (device_writes(dst)) {
-        const hipError_t e = hipMemcpyAsync(dst, src, n, hipMemcpyDeviceToHost, s);
-        return e != hipSuccess ? e : hipStreamSynchronize(s);
-    }
     int device = 0;
     hipError_t e = hipGetDevice(&device);
     if (e != hipSuccess) return e;
-    Stage st = stage_take(device);
+    Stage st;
+    if (device_writes(dst) || !stage_take(device, st)) return copy_straight(dst, src, n, s);
     e = copy_staged(st, dst, src, n, s);
     stage_give(st);
     return e;
@@ -211,7 +210,14 @@ StageUser::StageUser() {
 StageUser::~StageUser() {
     std::lock_guard<std::mutex> hold(g_lock);
     if (--g_users > 0) return;
-    while (g_nidle > 1) stage_free(g_idle[--g_nidle]);
+    bool kept = false;
+    for (DeviceStages &d : g_dev) {
+        while (d.nparked > (kept ? 0 : 1)) {
+            stage_free(d.parked[--d.nparked]);
+            --d.live;
+        }
+        kept = kept || d.nparked > 0;
+    }
 }
 
 }  // namespace swmi

@@ -25,7 +25,8 @@ const std::string &last_error();
 // waits (into pageable memory through pinned staging; without any to be had, a
 // pageable copy).
 hipError_t copy_to_host(void *dst, const void *src, size_t n, hipStream_t s);
-// Held by every object that copies; the last one gives the staging back.
+// Held by every object that copies; the last one gives the staging back, but
+// for one buffer.
 struct StageUser {
     StageUser();
     ~StageUser();

@@ -4,6 +4,7 @@
 #include <stdio.h>
 #include <stdlib.h>
 
+#include <condition_variable>
 #include <map>
 #include <set>
 
@@ -35,6 +36,15 @@ struct Buffer {
 };
 std::set<Buffer *> Buffer::all;
 
+// Pinned memory held and made.
+std::map<void *, size_t> pinned;
+size_t pinned_bytes = 0, pinned_most = 0, pinned_made = 0;
+
+// Holds every thread's next copy until `gather` threads are in one.
+std::condition_variable gathered;
+int gather = 0, waiting = 0;
+thread_local bool held = false;
+
 // Memory the device reaches by itself, and what copies wrote there.
 const char *mapped = nullptr;
 size_t mapped_bytes = 0, straight = 0;
@@ -60,9 +70,17 @@ hipError_t hipSetDevice(int d) {
 hipError_t hipGetLastError(void) { return hipSuccess; }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned int) {
     *p = malloc(n);
+    std::lock_guard<std::mutex> hold(mu);
+    pinned[*p] = n;
+    pinned_bytes += n;
+    pinned_most = std::max(pinned_most, pinned_bytes);
+    ++pinned_made;
     return hipSuccess;
 }
 hipError_t hipHostFree(void *p) {
+    std::lock_guard<std::mutex> hold(mu);
+    pinned_bytes -= pinned[p];
+    pinned.erase(p);
     free(p);
     return hipSuccess;
 }
@@ -84,7 +102,12 @@ hipError_t hipPointerGetAttributes(hipPointerAttribute_t *at, const void *p) {
 hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind, hipStream_t s) {
     const Buffer *b = nullptr;
     {
-        std::lock_guard<std::mutex> hold(mu);
+        std::unique_lock<std::mutex> hold(mu);
+        if (gather && held) {
+            held = false;
+            if (++waiting == gather) gathered.notify_all();
+            gathered.wait(hold, [] { return waiting >= gather; });
+        }
         for (const Buffer *x : Buffer::all)
             if (src >= x->stale.data() && src < x->stale.data() + x->stale.size()) b = x;
     }
@@ -134,6 +157,43 @@ bool into_mapped() {
     return ok;
 }
 
+// `threads` threads on each of `devices` devices, all in a copy at once.
+bool at_once(int devices, int threads, size_t n) {
+    {
+        std::lock_guard<std::mutex> hold(mu);
+        gather = devices * threads;
+        waiting = 0;
+    }
+    std::atomic<int> good{0};
+    std::vector<std::thread> th;
+    for (int i = 0; i < devices * threads; ++i)
+        th.emplace_back([=, &good] {
+            cur_device = i % devices;
+            held = true;
+            good += copies(n, (hipStream_t)(uintptr_t)(0x1000 + 16 * i));
+        });
+    for (std::thread &t : th) t.join();
+    gather = 0;
+    return check(good == devices * threads, "copies at once");
+}
+
+// Reading again makes no pinned memory, however many threads and devices read,
+// and what is held stays below 32 MiB a device; the last object leaves 4 MiB.
+bool steady(int devices, int threads) {
+    bool ok = true;
+    {
+        swmi::StageUser user;
+        for (size_t n : {(size_t)320, ((size_t)2 << 20) + 5, ((size_t)9 << 20) + 5}) {
+            ok = at_once(devices, threads, n) && ok;
+            const size_t made = pinned_made;
+            for (int k = 0; k < 3; ++k) ok = at_once(devices, threads, n) && ok;
+            ok = check(pinned_made == made, "pinned memory made in the steady state") && ok;
+        }
+        ok = check(pinned_most <= (size_t)devices * (33u << 20), "pinned memory held") && ok;
+    }
+    return check(pinned_bytes <= (size_t)4 << 20, "pinned memory left") && ok;
+}
+
 }  // namespace
 
 int main(int argc, char **argv) {
@@ -143,5 +203,8 @@ int main(int argc, char **argv) {
     if (what == "null_stream") ok = every_size(nullptr);
     if (what == "per_thread_stream") ok = every_size(hipStreamPerThread);
     if (what == "into_mapped") ok = into_mapped();
+    if (what == "eight_threads") ok = steady(1, 8);
+    if (what == "more_threads") ok = steady(1, 19);
+    if (what == "six_devices") ok = steady(6, 2);
     return ok ? 0 : 1;
 }

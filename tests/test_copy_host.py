@@ -1,7 +1,8 @@
 """The read-back of csrc/sw_copy.hip on the CPU, against a stand-in for the HIP
 runtime (tests/copy_host.cpp): every copy has to come after the caller's work
 in stream order, whatever stream the caller uses, and goes straight to memory
-that the device reaches by itself."""
+that the device reaches by itself; reading again makes no pinned memory, from
+however many threads and devices."""
 import os
 import subprocess
 
@@ -19,7 +20,8 @@ def program(tmp_path_factory):
     return str(exe)
 
 
-@pytest.mark.parametrize("scenario", ["stream", "null_stream", "per_thread_stream", "into_mapped"])
+@pytest.mark.parametrize("scenario", ["stream", "null_stream", "per_thread_stream", "into_mapped",
+                                      "eight_threads", "more_threads", "six_devices"])
 def test_read_back(program, scenario):
     res = subprocess.run([program, scenario], capture_output=True, text=True, timeout=60)
     assert res.returncode == 0, res.stdout + res.stderr

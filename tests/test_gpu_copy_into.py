@@ -22,3 +22,34 @@ def test_spins_into_any_memory(L):
             assert sw.lib().sw_get_spins(s.handle, out.data_ptr(), L * L) == sw.SW_OK
             torch.cuda.synchronize()
             assert np.array_equal(out.cpu().numpy(), want), out.device
+
+
+@pytest.mark.parametrize("threads", [8, 11])  # as many as have pinned memory of their own, and more
+def test_threads_read_at_once(threads):
+    import threading
+
+    L, n = 2912, 3
+    print(f"\n[case] copy from {threads} threads", flush=True)
+    sims = [sw.Sim(L, 0.4, 1.0, 20 + i) for i in range(threads)]
+    for s in sims:
+        s.sweep(n)
+    want = [(s.spins(), s.series(0, n)) for s in sims]
+    sp = oracle.init(L, 20)
+    ref = oracle.run(L, 1.0, oracle.threshold(0.4), 20, 0, n, sp)
+    assert np.array_equal(want[0][0], sp) and want[0][1].tobytes() == ref.tobytes()
+    bad, start = [], threading.Barrier(threads)
+
+    def read(i):
+        start.wait()
+        for _ in range(4):
+            if not np.array_equal(sims[i].spins(), want[i][0]) or sims[i].series(0, n).tobytes() != want[i][1].tobytes():
+                bad.append(i)
+
+    th = [threading.Thread(target=read, args=(i,)) for i in range(threads)]
+    for t in th:
+        t.start()
+    for t in th:
+        t.join()
+    for s in sims:
+        s.close()
+    assert not bad
