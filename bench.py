@@ -138,7 +138,7 @@ def batched_vs_plain(args):
     tiles, merges, tune = autotune.tune_batch_table(L, beta, 1.0, seed, sweeps=10, use_cache=False)
     tune_ms = tune["per_side"]
     choice = {int(side): {"tile": int(tiles[L == side][0]),
-                          "merge": "lds" if int(merges[L == side][0]) == sw.SW_MERGE_LDS else "global"}
+                          "merge": ("auto", "lds", "global")[int(merges[L == side][0])]}
               for side in sorted(set(L.tolist()))}
     print(f"[bench] batched: {len(L)} replicas, {sites} sites; autotuned {tune['choice']}: {choice} "
           f"(whole-table candidates, ms per sweep: {tune['batch']})", file=sys.stderr, flush=True)

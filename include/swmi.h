@@ -267,8 +267,8 @@ const char *sw_last_error(void);
  * into the last) or, for a replica of at most 16 groups of 4 x 4 tiles, by
  * one workgroup per group in LDS (one launch for all such replicas, while
  * those of more than 16 tiles make at most 512 groups together); a
- * replica of at most 16 tiles is one group (SW_MERGE_LDS) unless its caller
- * asks for the global merge.  Replica r has its own L[r], beta[r], J[r],
+ * replica of at most 16 tiles is one group (SW_MERGE_LDS).  A caller that asks
+ * for the global merge gets it.  Replica r has its own L[r], beta[r], J[r],
  * seed[r] and its own records; its spins, clusters and records are bit for
  * bit those of a plain sim created with the same parameters and swept the
  * same number of times, whatever its tile width and merge.  All replicas
@@ -276,9 +276,11 @@ const char *sw_last_error(void);
  * sw_create; no labels or dense histogram. */
 typedef struct sw_batch sw_batch;
 
-#define SW_MERGE_AUTO 0   /* LDS merge when the replica has at most 16 tiles */
+#define SW_MERGE_AUTO 0   /* in LDS where the replica has at most 16 groups of
+                             4 x 4 tiles (those of more than 16 tiles only while
+                             they make at most 512 groups together), else global */
 #define SW_MERGE_LDS 1    /* the whole merge in one workgroup (<= 16 tiles)  */
-#define SW_MERGE_GLOBAL 2 /* the global merge                                */
+#define SW_MERGE_GLOBAL 2 /* the global merge, whatever the replica's size   */
 
 /* Device bytes of a batch with these lattice sides, `ring` records per
  * replica (0 = 1024) and tile side (0 = automatic, 32, 64); 0 when the
@@ -345,8 +347,9 @@ int sw_batch_series(sw_batch *batch, int32_t r, int64_t first, int64_t count, sw
 int sw_batch_get_spins(sw_batch *batch, int32_t r, int8_t *host, int64_t n);
 
 /* Number of replicas; index of the next sweep; side, bond threshold, tile
- * width and merge (SW_MERGE_LDS / SW_MERGE_GLOBAL) of replica r (0 for a bad
- * index); the tile width every replica uses (0 if they differ). */
+ * width and merge of replica r (SW_MERGE_LDS where one workgroup does it all,
+ * else SW_MERGE_GLOBAL, also where it was left automatic and is done by one
+ * workgroup per group; 0 for a bad index); the tile width every replica uses (0 if they differ). */
 int32_t sw_batch_size(const sw_batch *batch);
 int64_t sw_batch_next_sweep(const sw_batch *batch);
 int32_t sw_batch_lattice(const sw_batch *batch, int32_t r);

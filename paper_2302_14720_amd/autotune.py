@@ -18,7 +18,7 @@ import time
 
 import numpy as np
 
-from . import SW_INIT_HOT, SW_MERGE_GLOBAL, SW_MERGE_LDS, Batch, Sim
+from . import SW_INIT_HOT, SW_MERGE_AUTO, SW_MERGE_GLOBAL, SW_MERGE_LDS, Batch, Sim
 
 
 def cache_path() -> str:
@@ -153,7 +153,7 @@ def tune_batch_table(L, beta, J=1.0, seed=0, q=None, *, sweeps: int = 10, warmup
                      use_cache: bool = True):
     """Tile side and merge for every replica of a table: the per-side choices
     of tune_batch_per_side, then a check on the whole table against the same
-    tiles with every merge global and against the widest allowed tile with
+    tiles with the larger sides' merge automatic or every merge global and against the widest allowed tile with
     either merge rule (a side that is fastest alone may cost the mixed batch
     an extra launch group or a longer merge).  Returns (tiles, merges,
     {"per_side": ..., "batch": {name: ms per sweep}, "choice": name})."""
@@ -166,14 +166,18 @@ def tune_batch_table(L, beta, J=1.0, seed=0, q=None, *, sweeps: int = 10, warmup
     tiles, merges, per_side = tune_batch_per_side(La, ba, Ja, sa, q=qa, sweeps=sweeps, warmup=warmup,
                                                   use_cache=use_cache)
     wide = np.where((La % 64 == 0) & (qa <= 4), 64, 32).astype(np.int32)
+    # (a side of more than 16 tiles is tuned under the global merge; left
+    # automatic it may merge group by group in LDS)
+    large = (La // tiles) ** 2 > SMALL_TILES
     cands = {
         "per_side": (tiles, merges),
+        "per_side_auto_merge": (tiles, np.where(large, SW_MERGE_AUTO, merges).astype(np.int32)),
         "per_side_tiles_global_merge": (tiles, np.full(n, SW_MERGE_GLOBAL, dtype=np.int32)),
         "widest_tiles_auto_merge": (wide, np.zeros(n, dtype=np.int32)),
         "widest_tiles_global_merge": (wide, np.full(n, SW_MERGE_GLOBAL, dtype=np.int32)),
     }
     digest = hashlib.sha1(La.tobytes() + qa.tobytes()).hexdigest()[:16]
-    key = f"{_device()}|batch-table|n={n}|{digest}"
+    key = f"{_device()}|batch-table-5|n={n}|{digest}"
     hit = _load().get(key) if use_cache else None
     if hit and hit.get("choice") in cands:
         ms, choice = hit["ms"], hit["choice"]

@@ -627,7 +627,7 @@ using swmi::kBatchGroups;
 struct sw_batch {
     std::vector<sw_config> cfg;
     std::vector<Dev> dev;      // host copies of the replicas' device views
-    std::vector<uint8_t> lds;  // 1 where the replica's merge runs in LDS
+    std::vector<uint8_t> lds;  // 1 where the replica's whole merge is one workgroup's
     swmi::BatchDev bd[kBatchGroups];
     hipStream_t stream;
     bool own_stream;
@@ -657,19 +657,20 @@ constexpr int64_t kDefaultBatchRing = 1024;
 // 267.0, 256 (1020) 369.6 / 407.4.
 constexpr uint32_t kWideGroups = 512;
 
-// A replica's device view.  k_merge takes those of at most 16 tiles whose
-// caller did not ask for the global merge (lds), and larger ones as it would
-// alone while the batch's are few (wide).
-Dev replica_dev(const sw_config &c, char *base, const Layout &lo, bool lds, bool wide) {
+// A replica's device view.  k_merge takes, unless the caller asked for the
+// global merge, those of at most 16 tiles, and larger ones as it would alone
+// while the batch's are few (wide).
+Dev replica_dev(const sw_config &c, char *base, const Layout &lo, bool global, bool wide) {
     Dev d = make_dev(c, base, lo);
-    if (!lds && (d.ntiles <= swmi::kSmallTiles || !wide)) d.two = 0u;
+    if (global || (d.ntiles > swmi::kSmallTiles && !wide)) d.two = 0u;
     return d;
 }
 
 struct BatchPlan {
     std::vector<sw_config> cfg;
     std::vector<size_t> base;   // workspace offset of every replica
-    std::vector<uint8_t> lds;   // merge in LDS
+    std::vector<uint8_t> global;  // 1: the caller asked for the global merge
+    std::vector<uint8_t> lds;   // 1: the whole merge in one workgroup
     bool wide;                  // k_merge also for replicas of more than 16 tiles
     size_t devs, maps, total;
     size_t map_words;
@@ -691,6 +692,7 @@ int plan_batch(int32_t n, const int32_t *L, const double *beta, const double *J,
     if (tile != 0 && tile != 32 && tile != 64) return fail(SW_EINVAL, "tile must be 0, 32 or 64");
     p->cfg.assign((size_t)n, sw_config{});
     p->base.assign((size_t)n, 0);
+    p->global.assign((size_t)n, 0);
     p->lds.assign((size_t)n, 0);
     size_t off = 0;
     uint32_t groups = 0;  // k_merge workgroups of the replicas of more than 16 tiles
@@ -713,15 +715,16 @@ int plan_batch(int32_t n, const int32_t *L, const double *beta, const double *J,
         const uint32_t nt = (uint32_t)((c.L / c.tile) * (c.L / c.tile));
         if (mg == SW_MERGE_LDS && nt > swmi::kSmallTiles)
             return fail(SW_EINVAL, who + "the LDS merge takes at most " + std::to_string(swmi::kSmallTiles) + " tiles");
+        p->global[(size_t)r] = mg == SW_MERGE_GLOBAL ? 1u : 0u;
         p->lds[(size_t)r] = (mg != SW_MERGE_GLOBAL && nt <= swmi::kSmallTiles) ? 1u : 0u;
-        if (nt > swmi::kSmallTiles && swmi::merge_in_one(c)) groups += swmi::merge_groups(c);
+        if (nt > swmi::kSmallTiles && mg != SW_MERGE_GLOBAL && swmi::merge_in_one(c)) groups += swmi::merge_groups(c);
         p->base[(size_t)r] = off;
         off = align_up(off + layout_of(c).total);
     }
     p->wide = groups <= kWideGroups;
     swmi::BatchMaps m[kBatchGroups];
     for (size_t r = 0; r < p->cfg.size(); ++r)
-        swmi::BatchMaps::add((uint32_t)r, replica_dev(p->cfg[r], nullptr, Layout{}, p->lds[r] != 0, p->wide), m);
+        swmi::BatchMaps::add((uint32_t)r, replica_dev(p->cfg[r], nullptr, Layout{}, p->global[r] != 0, p->wide), m);
     p->map_words = 0;
     for (const swmi::BatchMaps &g : m) p->map_words += g.words();
     auto take = [&](size_t bytes) {
@@ -852,7 +855,7 @@ int batch_create(int32_t n, const int32_t *L, const double *beta, const double *
     b->dev.resize(p.cfg.size());
     swmi::BatchMaps m[kBatchGroups];
     for (size_t r = 0; r < p.cfg.size(); ++r) {
-        b->dev[r] = replica_dev(p.cfg[r], base + p.base[r], layout_of(p.cfg[r]), p.lds[r] != 0, p.wide);
+        b->dev[r] = replica_dev(p.cfg[r], base + p.base[r], layout_of(p.cfg[r]), p.global[r] != 0, p.wide);
         swmi::BatchMaps::add((uint32_t)r, b->dev[r], m);
     }
     std::vector<uint32_t> host;
