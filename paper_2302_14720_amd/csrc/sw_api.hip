@@ -109,6 +109,11 @@ bool merge_in_one(const sw_config &c) {
     return merge_groups(c) != 0u;
 }
 
+uint32_t wide_groups(const sw_config &c) {
+    const uint32_t ntx = (uint32_t)c.L / (uint32_t)resolve_tile(c);
+    return ntx * ntx > kSmallTiles && merge_in_one(c) ? merge_groups(c) : 0u;
+}
+
 Layout layout_of(const sw_config &c) {
     const size_t L = (size_t)c.L, N = sites_of(c);
     // the label-equivalence path keeps labels in global memory and no tile
@@ -647,16 +652,6 @@ namespace {
 
 constexpr int64_t kDefaultBatchRing = 1024;
 
-// A batch whose replicas of more than 16 tiles make more k_merge workgroups than
-// this merges them globally: one of those workgroups fills a CU (75 KB of LDS, 16
-// wavefronts), so from two rounds of them on the global merge's small
-// workgroups are faster.  us per sweep, global / k_merge: 512^2, 32 replicas
-// (128 groups) 99.8 / 77.3, 128 (512) 201.8 / 199.5, 256 (1024) 334.3 / 376.3;
-// 1024^2, 16 (256) 139.1 / 121.2, 32 (512) 204.8 / 207.4, 64 (1024) 337.4 /
-// 385.8; sides 64 to 1024, 128 replicas (500) 221.6 / 215.6, 160 (640) 258.9 /
-// 267.0, 256 (1020) 369.6 / 407.4.
-constexpr uint32_t kWideGroups = 512;
-
 // A replica's device view.  k_merge takes, unless the caller asked for the
 // global merge, those of at most 16 tiles, and larger ones as it would alone
 // while the batch's are few (wide).
@@ -717,11 +712,11 @@ int plan_batch(int32_t n, const int32_t *L, const double *beta, const double *J,
             return fail(SW_EINVAL, who + "the LDS merge takes at most " + std::to_string(swmi::kSmallTiles) + " tiles");
         p->global[(size_t)r] = mg == SW_MERGE_GLOBAL ? 1u : 0u;
         p->lds[(size_t)r] = (mg != SW_MERGE_GLOBAL && nt <= swmi::kSmallTiles) ? 1u : 0u;
-        if (nt > swmi::kSmallTiles && mg != SW_MERGE_GLOBAL && swmi::merge_in_one(c)) groups += swmi::merge_groups(c);
+        if (mg != SW_MERGE_GLOBAL) groups += swmi::wide_groups(c);
         p->base[(size_t)r] = off;
         off = align_up(off + layout_of(c).total);
     }
-    p->wide = groups <= kWideGroups;
+    p->wide = groups <= swmi::kWideGroups;
     swmi::BatchMaps m[kBatchGroups];
     for (size_t r = 0; r < p->cfg.size(); ++r)
         swmi::BatchMaps::add((uint32_t)r, replica_dev(p->cfg[r], nullptr, Layout{}, p->global[r] != 0, p->wide), m);

@@ -35,6 +35,7 @@ struct Job {
     int64_t target = 0, done = 0;
     int32_t state = SW_JOB_QUEUED;
     int32_t slot = -1;
+    uint32_t wide = 0;  // k_merge workgroups that count towards kWideGroups
 };
 
 // First-fit allocator over [0, size) with coalescing of freed ranges.
@@ -138,12 +139,53 @@ int upload_maps(sw_server *s, swmi::BatchMaps *m, swmi::BatchDev *bd, int ngroup
     return SW_OK;
 }
 
+// Final spins (and the last record's energy and magnetisation) of these jobs.
+int resolve_jobs(sw_server *s, const std::vector<Job *> &jobs) {
+    HIP_TRY(hipStreamSynchronize(s->stream));
+    swmi::BatchMaps m[kGroups];
+    swmi::BatchDev rb[kGroups]{};
+    for (Job *j : jobs) swmi::BatchMaps::add((uint32_t)j->slot, j->dev, m);
+    swmi::set_groups(rb);
+    const int rc = upload_maps(s, m, rb, kGroups);
+    if (rc != SW_OK) return rc;
+    for (int g = 0; g < kGroups; ++g) HIP_TRY(swmi::launch_batch_resolve(rb[g], s->stream));
+    HIP_TRY(hipStreamSynchronize(s->stream));
+    return SW_OK;
+}
+
+// The merge of the active jobs of more than 16 tiles: k_merge while they are few
+// (kWideGroups), else the global one.  A job changes merge with final spins
+// and no nodes: both its spin codes and its node counts refer to the
+// tables of the merge that left them.
+int choose_merges(sw_server *s) {
+    uint32_t groups = 0;
+    for (const Job *j : s->active) groups += j->wide;
+    const uint32_t two = groups <= swmi::kWideGroups ? 1u : 0u;
+    std::vector<Job *> change;
+    for (Job *j : s->active)
+        if (j->wide != 0 && j->dev.two != two) change.push_back(j);
+    if (change.empty()) return SW_OK;
+    const int rc = resolve_jobs(s, change);
+    if (rc != SW_OK) return rc;
+    for (Job *j : change) {
+        Dev dev = j->dev;
+        dev.two = two;
+        for (uint32_t *nk : dev.nk) HIP_TRY(hipMemsetAsync(nk, 0, (size_t)dev.ntiles * 4, s->stream));
+        HIP_TRY(hipStreamSynchronize(s->stream));
+        HIP_TRY(hipMemcpy(s->d_devs + j->slot, &dev, sizeof(Dev), hipMemcpyHostToDevice));
+        j->dev = dev;
+    }
+    return SW_OK;
+}
+
 int rebuild_active(sw_server *s) {
     HIP_TRY(hipStreamSynchronize(s->stream));
+    int rc = choose_merges(s);
+    if (rc != SW_OK) return rc;
     swmi::BatchMaps m[kGroups];
     for (Job *j : s->active) swmi::BatchMaps::add((uint32_t)j->slot, j->dev, m);
     swmi::set_groups(s->bd);
-    const int rc = upload_maps(s, m, s->bd, kGroups);
+    rc = upload_maps(s, m, s->bd, kGroups);
     if (rc == SW_OK) s->dirty = false;
     return rc;
 }
@@ -207,6 +249,7 @@ int submit(sw_server *s, const sw_config &c, int64_t sweeps, int64_t *job_id) {
     j->id = s->next_id++;
     j->cfg = c;
     j->bytes = bytes;
+    j->wide = swmi::wide_groups(c);
     j->target = sweeps;
     s->jobs[j->id] = j;
     s->queue.push_back(j);
@@ -320,15 +363,8 @@ int sw_server_step(sw_server *s, int64_t n, int64_t *done_ids, int32_t cap, int3
         std::vector<Job *> fin, keep;
         for (Job *j : s->active) (j->done == j->target ? fin : keep).push_back(j);
         if (fin.empty()) continue;
-        HIP_TRY(hipStreamSynchronize(s->stream));
-        swmi::BatchMaps m[kGroups];
-        swmi::BatchDev rb[kGroups]{};
-        for (Job *j : fin) swmi::BatchMaps::add((uint32_t)j->slot, j->dev, m);
-        swmi::set_groups(rb);
-        rc = upload_maps(s, m, rb, kGroups);
+        rc = resolve_jobs(s, fin);
         if (rc != SW_OK) return rc;
-        for (int g = 0; g < kGroups; ++g) HIP_TRY(swmi::launch_batch_resolve(rb[g], s->stream));
-        HIP_TRY(hipStreamSynchronize(s->stream));
         for (Job *j : fin) {
             j->state = SW_JOB_DONE;
             s->free_slots.push_back(j->slot);
