@@ -4,8 +4,9 @@
 //   k_tile    bond formation (Sec. 2.1) and cluster formation (Sec. 2.3)
 //             inside one 64x64 (or 32x32) tile per workgroup, in LDS; new
 //             spins (Sec. 2.4) of clusters that stay inside the tile; the
-//             tile's clusters with a bond out of the tile become "nodes" of a
-//             global graph;
+//             tile's clusters with a bond out of the tile (of 32-wide tiles
+//             with 16 sites per thread, all that touch its edge) become
+//             "nodes" of a global graph;
 //             the spins of the previous sweep are resolved on the fly and
 //             measured (Sec. 2.5).
 //   k_union   union of nodes joined by bonds that cross tile edges: first

@@ -300,6 +300,14 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile, Til
     constexpr int NPL = POTTS ? 3 : 1;  // bit planes of a spin
     constexpr uint32_t EW = (TW + 31) / 32;
     constexpr uint32_t CB = POTTS ? potts_code<TW>() : 2u;  // output byte of node 0
+    // Which clusters become nodes: those with a bond out of the tile, for which
+    // the bonds that come in are drawn again, or all that touch the tile's edge.
+    // A 32-wide tile of one wavefront pays a ninth Philox call beside its eight
+    // and gains less than that: us per sweep all / bonded, 4064^2 at beta_c
+    // 165.7 / 170.0, beta = 0.6 170.3 / 175.3, 8160^2 at beta_c 464 / 473 (only
+    // in the disordered phase of few tiles it loses: 2080^2, beta = 0.3, 70.9 /
+    // 67.6).
+    constexpr bool INCOMING = TW == 64 || SPT == 4;
 
     constexpr uint32_t PS = TW + 1;
     auto &s_par = sh.par;
@@ -367,8 +375,8 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile, Til
     Seg<SPT> vs{};
     const uint32_t xw = txw * TW + TW - 1u, ys = tys * TW + TW - 1u;
     uint32_t vw = 0u;
-    if (ly == 0u) vs = load_seg<SPT>(sin + (size_t)ys * L + gx0);
-    if (seg == 0u) vw = (uint8_t)sin[(size_t)gy * L + xw];
+    if (INCOMING && ly == 0u) vs = load_seg<SPT>(sin + (size_t)ys * L + gx0);
+    if (INCOMING && seg == 0u) vw = (uint8_t)sin[(size_t)gy * L + xw];
     // the bond words of this lane's sites (Sec. 2.1), drawn while the
     // loads are in flight: bit 2j (2j+1) of rE / rN is the E / N edge of
     // site 2j (2j+1) past the lane's first site, set iff its word is below T
@@ -419,7 +427,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile, Til
     // one per two columns, 1.5 calls per 64 of a tile side beside its 8 per 16
     // sites.  With them only clusters that do go on outside become nodes: 48
     // of the 80 that touch the edge of a 64-wide tile at beta_c.
-    {
+    if constexpr (INCOMING) {
         constexpr uint32_t W0 = NT > 64 ? 64u : 0u;  // a wavefront other than the one above, if there is one
         const uint32_t r = tid - W0, c = TW == 64 ? tid - 128u : tid - W0 - 32u;
         const bool isw = r < (uint32_t)TW, iss = c < (uint32_t)TW / 2u;
@@ -480,12 +488,12 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile, Til
                 if ((ev >> b) & 1u) atomicOr(&s_eup[b * EW + (ly >> 5)], 1u << (ly & 31u));
         }
         // bit 0: the W neighbour's value equals this row's first site's
-        if (ly == 0u) {
+        if (INCOMING && ly == 0u) {
             uint32_t pn[3];
             decode_potts_remote<TW, TWO>(d, vs, tys * ntx + tx, ref_base(d, tx, tys), pn);
             inS = ~((pl[0] ^ pn[0]) | (pl[1] ^ pn[1]) | (pl[2] ^ pn[2])) & M;
         }
-        if (seg == 0u) {
+        if (INCOMING && seg == 0u) {
             uint32_t wv;
             remote_values<TW, true, TWO, 1>(d, &vw, ty * ntx + txw, ref_base(d, txw, ty), &wv);
             inW = wv == ((pl[0] & 1u) | ((pl[1] & 1u) << 1) | ((pl[2] & 1u) << 2)) ? 1u : 0u;
@@ -493,8 +501,8 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile, Til
         __syncthreads();
     } else {
         up = decode(v, s_tab);
-        if (ly == 0u) inS = ~(up ^ decode_remote<TWO>(d, vs, tys * ntx + tx, ref_base(d, tx, tys))) & M;
-        if (seg == 0u) {
+        if (INCOMING && ly == 0u) inS = ~(up ^ decode_remote<TWO>(d, vs, tys * ntx + tx, ref_base(d, tx, tys))) & M;
+        if (INCOMING && seg == 0u) {
             uint32_t wv;
             remote_values<TW, false, TWO, 1>(d, &vw, ty * ntx + txw, ref_base(d, txw, ty), &wv);
             inW = ~(up ^ wv) & 1u;
@@ -516,7 +524,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile, Til
     int32_t e_part, m_part;
     uint32_t cpk[4] = {0u, 0u, 0u, 0u};
     uint32_t bE, bN;
-    uint32_t linked = 0u;  // this lane's sites with a bond out of the tile, either way
+    uint32_t linked = 0u;  // this lane's sites whose clusters become nodes
     {
         uint32_t eqE, eqN;
         if constexpr (POTTS) {
@@ -547,16 +555,20 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile, Til
         bN = eqN & rN;
         if (seg == RPT - 1) {
             if (bE & TOP) atomicOr(&s_xe[ly >> 5], 1u << (ly & 31u));
-            linked = bE & TOP;
+            if (INCOMING) linked = bE & TOP;
             bE &= TOP - 1u;
         }
         if (ly == TW - 1) {
             put_piece(&s_xn, bN);
-            linked |= bN;
+            if (INCOMING) linked |= bN;
             bN = 0u;
         }
-        if (ly == 0u) linked |= M & inS & (spread8(s_ps[0] >> (x0 / 2u)) | (spread8(s_ps[1] >> (x0 / 2u)) << 1));
-        if (seg == 0u) linked |= inW & (uint32_t)(s_pw >> ly);
+        if constexpr (INCOMING) {
+            if (ly == 0u) linked |= M & inS & (spread8(s_ps[0] >> (x0 / 2u)) | (spread8(s_ps[1] >> (x0 / 2u)) << 1));
+            if (seg == 0u) linked |= inW & (uint32_t)(s_pw >> ly);
+        } else {
+            linked = ly == 0u || ly == (uint32_t)TW - 1u ? M : (seg == 0u ? 1u : 0u) | (seg == RPT - 1u ? TOP : 0u);
+        }
         if constexpr (SPT == 16) put_piece(&s_eb[ly], bE);
     }
     const Row E0 = row_gather<TW, SPT>(bE, seg);  // this row's E bonds inside the tile
@@ -629,7 +641,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile, Til
     // ---- cluster sizes.  Every run start in this lane's sites is pointed
     // at its root and adds the whole run's length (read off the row's
     // run-start mask; the run may go on into the next lanes' sites).  Runs
-    // with a bond out of the tile mark their root.
+    // with linked sites mark their root.
     uint32_t rootmask = 0u;
     {
         // where the run holding the lane's last site ends: the first run
@@ -678,7 +690,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile, Til
     }
     __syncthreads();
 
-    // ---- number the clusters that go on outside (nodes) in site order: every
+    // ---- number the marked clusters (nodes) in site order: every
     // wavefront scans the marks itself, lane l holding the prefix of mark
     // words (NW / 64) l .. (NW / 64) (l + 1) - 1
     uint32_t pf_a, pf_b, n_nodes;
