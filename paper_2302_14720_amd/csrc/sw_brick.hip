@@ -5,8 +5,8 @@
 //              incoming configuration (Sec. 2.5).  A component with a bond
 //              through the brick's surface becomes a node of a global graph.
 //   k_blocal3  node unions across the faces inside each 2x2x2 group of
-//              bricks, in LDS
-//   k_bunion3  node unions across the faces between groups (lock-free
+//              bricks, in LDS (not on lattices of few bricks)
+//   k_bunion3  node unions across the faces between groups, or all (lock-free
 //              union-find in global memory, the smaller node index is root)
 //   k_bflat3   every node to its root; sizes and smallest sites into the roots
 //   k_bspin3   new spins (Sec. 2.4): a brick's interior components and its
@@ -191,7 +191,8 @@ __device__ __forceinline__ void join_listed(uint32_t *s_par, uint32_t R, uint32_
 // order the sites of a brick as their global indices do, so a root is its
 // component's smallest site.
 // =====================================================================
-template <bool POTTS, bool DENSE>
+// LOCAL: k_blocal3 comes next and sets up the nodes; else they are set up here.
+template <bool POTTS, bool DENSE, bool LOCAL>
 __global__ __launch_bounds__(256, kBrickWavesPerEU) void k_brick3(Dev d) {
     constexpr uint32_t NPL = POTTS ? 3u : 1u;
     __shared__ uint32_t s_par[kRows * kPS];
@@ -361,7 +362,13 @@ __global__ __launch_bounds__(256, kBrickWavesPerEU) void k_brick3(Dev d) {
             uint32_t k = kNoNode;
             if ((bmask >> i) & 1u) {
                 k = min(kbase + __popc(bmask & ((1u << i) - 1u)), kBrickNodes - 1u);
-                d.node[B.b * kBrickNodes + k] = (sbase + i) | (S << 16);
+                const uint32_t node = B.b * kBrickNodes + k;
+                d.node[node] = (sbase + i) | (S << 16);
+                if constexpr (!LOCAL) {
+                    d.parent[0][node] = node;
+                    d.nsize[node] = S;
+                    d.key[node] = s0 + i;
+                }
             } else {
                 max_int = max(max_int, S);
                 sq_int += S * S;
@@ -525,18 +532,18 @@ __global__ __launch_bounds__(kGroupThreads) void k_blocal3(Dev d) {
 
 // =====================================================================
 // k_bunion3: the faces between groups, one workgroup per face: direction
-// blockIdx.y, the low side in brick layer min(2 j + 1, nb - 1).  Unions start
+// blockIdx.y, the low side in brick layer min(2 j + 1, nb - 1); with layers = nb
+// all faces, the low side in layer j.  Unions start
 // from the nodes' parents; a bond that joins the same two as the bond of the
 // lane below is skipped.
 // =====================================================================
-__global__ __launch_bounds__(256) void k_bunion3(Dev d) {
-    const uint32_t nb = d.L / kBrick, ng = (nb + 1u) / 2u, f = blockIdx.y, i = threadIdx.x;
+__global__ __launch_bounds__(256) void k_bunion3(Dev d, uint32_t layers) {
+    const uint32_t nb = d.L / kBrick, f = blockIdx.y, i = threadIdx.x;
     uint32_t p = tile_of_block(blockIdx.x, gridDim.x);
     // the layer is the slowest coordinate but one, so that consecutive
     // workgroups take neighbouring bricks
     const uint32_t u = p % nb, q = p / nb, v = q % nb, j = q / nb;
-    const uint32_t c = min(2u * j + 1u, nb - 1u), c1 = c + 1u == nb ? 0u : c + 1u;
-    (void)ng;
+    const uint32_t c = layers == nb ? j : min(2u * j + 1u, nb - 1u), c1 = c + 1u == nb ? 0u : c + 1u;
     uint32_t A, Bn;
     if (f == 0u) {
         A = (v * nb + u) * nb + c;
@@ -560,11 +567,13 @@ __global__ __launch_bounds__(256) void k_bunion3(Dev d) {
 
 // =====================================================================
 // k_bflat3: every node points at its root; sizes and keys into the roots,
-// gathered per workgroup (a group of eight bricks, one per wavefront) in an
-// LDS hash, then one global atomic of each kind per (workgroup, root).
+// gathered per workgroup (a group of eight bricks, one per wavefront, or one
+// brick) in an LDS hash, then one global atomic of each kind per (workgroup,
+// root).
 // =====================================================================
 constexpr uint32_t kHash = 2048;
 
+template <bool GROUP>
 __global__ __launch_bounds__(kGroupThreads) void k_bflat3(Dev d) {
     __shared__ uint32_t hk[kHash], hv[kHash], hm[kHash];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wv = tid >> 6;
@@ -575,18 +584,18 @@ __global__ __launch_bounds__(kGroupThreads) void k_bflat3(Dev d) {
     }
     __syncthreads();
     uint32_t *par = d.parent[0];
-    uint32_t b;
-    const bool ok = group_brick(tile_of_block(blockIdx.x, gridDim.x), wv, d.L / kBrick, b);
+    uint32_t b = blockIdx.x;
+    const bool ok = !GROUP || group_brick(tile_of_block(blockIdx.x, gridDim.x), wv, d.L / kBrick, b);
     const uint32_t nk = ok ? min(d.nk[0][b], kBrickNodes) : 0u;
     const uint32_t node0 = b * kBrickNodes;
     const Brick B = brick_of(b, d.L / kBrick);
-    constexpr uint32_t kChase = 4;
-    for (uint32_t k0 = 0; k0 < nk; k0 += 64u * kChase) {
+    constexpr uint32_t kChase = 4, STEP = GROUP ? 64u : kGroupThreads;
+    for (uint32_t k0 = GROUP ? 0u : 64u * wv; k0 < nk; k0 += STEP * kChase) {
         // up to four nodes per lane, their chains followed together
         uint32_t p0[kChase], r[kChase], en[kChase];
 #pragma unroll
         for (uint32_t j = 0; j < kChase; ++j) {
-            const uint32_t k = k0 + 64u * j + lane;
+            const uint32_t k = k0 + STEP * j + lane;
             p0[j] = k < nk ? g_load(&par[node0 + k]) : kEmpty;
             en[j] = k < nk ? d.node[node0 + k] : 0u;
         }
@@ -606,7 +615,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_bflat3(Dev d) {
         }
 #pragma unroll
         for (uint32_t j = 0; j < kChase; ++j) {
-            const uint32_t node = node0 + k0 + 64u * j + lane, root = r[j];
+            const uint32_t node = node0 + k0 + STEP * j + lane, root = r[j];
             if (root == kEmpty || root == node) continue;
             if (root != p0[j]) g_store(&par[node], root);
             const uint32_t e = en[j], size = e >> 16, key = site_at(B, d.L, e & 0xFFFFu);
@@ -794,29 +803,50 @@ __global__ __launch_bounds__(256) void k_blabels3(Dev d) {
     for (uint32_t j = 0; j < 16u; ++j) d.labels[s0 + j] = s_lab[cp[j] & (kVol - 1u)];
 }
 
+// Lattices of at most this many bricks a side leave out k_blocal3 and flatten with
+// a workgroup per brick: all faces' unions go to k_bunion3, where so few nodes
+// are in nobody's way, and a launch of one workgroup per eight bricks is a chain
+// of loads on an idle GPU (k_blocal3 9 us and k_bflat3 10 of the 53 us of 64^3 at
+// beta = 0.1).  us per sweep with k_blocal3 / without: 32^3, beta = 0.1, 47.3 /
+// 37.7, 64^3 53.1 / 40.1, 80^3 51.7 / 41.2; 64^3, 3-state at 0.5505, 72.0 / 53.5;
+// 80^3 at beta = 0.3 81.8 / 75.6, but 96^3 85.8 / 91.6 and 144^3 130 / 158 (the
+// group-local unions keep a giant cluster's links and atomics apart).
+constexpr uint32_t kFewBricks = 5;
+
+template <bool LOCAL> void launch_brick3(const Dev &d, uint32_t n, hipStream_t s) {
+    if (d.dense) {
+        if (d.q)
+            k_brick3<true, true, LOCAL><<<n, 256, 0, s>>>(d);
+        else
+            k_brick3<false, true, LOCAL><<<n, 256, 0, s>>>(d);
+    } else if (d.q) {
+        k_brick3<true, false, LOCAL><<<n, 256, 0, s>>>(d);
+    } else {
+        k_brick3<false, false, LOCAL><<<n, 256, 0, s>>>(d);
+    }
+}
+
 }  // namespace
 
 hipError_t launch_brick_stage(const Dev &d, int stage, hipStream_t s) {
     const uint32_t nb = d.L / kBrick, n = nb * nb * nb, ng = (nb + 1u) / 2u;
+    const bool few = nb <= kFewBricks;
     switch (stage) {
     case 0:
-        if (d.dense) {
-            if (d.q)
-                k_brick3<true, true><<<n, 256, 0, s>>>(d);
-            else
-                k_brick3<false, true><<<n, 256, 0, s>>>(d);
-        } else if (d.q) {
-            k_brick3<true, false><<<n, 256, 0, s>>>(d);
-        } else {
-            k_brick3<false, false><<<n, 256, 0, s>>>(d);
-        }
+        if (few)
+            launch_brick3<false>(d, n, s);
+        else
+            launch_brick3<true>(d, n, s);
         break;
     case 1:
-        k_blocal3<<<ng * ng * ng, kGroupThreads, 0, s>>>(d);
-        k_bunion3<<<dim3(ng * nb * nb, 3), 256, 0, s>>>(d);
+        if (!few) k_blocal3<<<ng * ng * ng, kGroupThreads, 0, s>>>(d);
+        k_bunion3<<<dim3((few ? nb : ng) * nb * nb, 3), 256, 0, s>>>(d, few ? nb : ng);
         break;
     case 2:
-        k_bflat3<<<ng * ng * ng, kGroupThreads, 0, s>>>(d);
+        if (few)
+            k_bflat3<false><<<n, kGroupThreads, 0, s>>>(d);
+        else
+            k_bflat3<true><<<ng * ng * ng, kGroupThreads, 0, s>>>(d);
         break;
     case 3:
         if (d.dense) {
