@@ -21,6 +21,8 @@
 // reach, a quarter of them Philox); k_bflat3 0.17, k_bunion3 0.17, k_blocal3
 // 0.10 and k_bspin3 0.13 ms, bound by their dependent loads and device-scope
 // atomics over 228 nodes a brick.  32-bit labels in global memory took 2.9 ms.
+#include <math.h>
+
 #include "sw_device.h"
 #include "sw_internal.h"
 #include "sw_philox.h"
@@ -803,15 +805,21 @@ __global__ __launch_bounds__(256) void k_blabels3(Dev d) {
     for (uint32_t j = 0; j < 16u; ++j) d.labels[s0 + j] = s_lab[cp[j] & (kVol - 1u)];
 }
 
-// Lattices of at most this many bricks a side leave out k_blocal3 and flatten with
-// a workgroup per brick: all faces' unions go to k_bunion3, where so few nodes
+// Whether a lattice of nb bricks a side leaves out k_blocal3 and flattens with a
+// workgroup per brick: all faces' unions go to k_bunion3, where so few nodes
 // are in nobody's way, and a launch of one workgroup per eight bricks is a chain
 // of loads on an idle GPU (k_blocal3 9 us and k_bflat3 10 of the 53 us of 64^3 at
 // beta = 0.1).  us per sweep with k_blocal3 / without: 32^3, beta = 0.1, 47.3 /
-// 37.7, 64^3 53.1 / 40.1, 80^3 51.7 / 41.2; 64^3, 3-state at 0.5505, 72.0 / 53.5;
-// 80^3 at beta = 0.3 81.8 / 75.6, but 96^3 85.8 / 91.6 and 144^3 130 / 158 (the
-// group-local unions keep a giant cluster's links and atomics apart).
-constexpr uint32_t kFewBricks = 5;
+// 37.7, 64^3 53.1 / 40.1, 80^3 51.7 / 41.2; 64^3, 3-state at 0.5505, 72.0 / 53.5.
+// In the ordered phase (bond probabilities from about the one below, which is
+// 0.366 for Ising, 0.430, 0.473, 0.533 and 0.572 for q = 3, 4, 6 and 8) the
+// group-local unions keep a giant cluster's links and atomics apart, and the line
+// lies lower: beta = 0.3, 80^3 81.8 / 75.6, 96^3 86.1 / 93.8, 144^3 130 / 158;
+// beta = 0.2, 96^3 72.0 / 53.6; 96^3 with q = 6 at 0.75, 68.1 / 51.7.
+bool few_bricks(const Dev &d, uint32_t nb) {
+    const double q = d.q ? d.q : 2u, p = sqrt(q) / (sqrt(q) + 2.0 + 0.9 / q);
+    return nb <= ((double)d.T > p * 4294967296.0 ? 5u : 6u);
+}
 
 template <bool LOCAL> void launch_brick3(const Dev &d, uint32_t n, hipStream_t s) {
     if (d.dense) {
@@ -830,7 +838,7 @@ template <bool LOCAL> void launch_brick3(const Dev &d, uint32_t n, hipStream_t s
 
 hipError_t launch_brick_stage(const Dev &d, int stage, hipStream_t s) {
     const uint32_t nb = d.L / kBrick, n = nb * nb * nb, ng = (nb + 1u) / 2u;
-    const bool few = nb <= kFewBricks;
+    const bool few = few_bricks(d, nb);
     switch (stage) {
     case 0:
         if (few)

@@ -1,5 +1,5 @@
 """The cubic lattice on both sides of the line up to which node unions go straight
-to global memory (five bricks a side), one sweep after another and together:
+to global memory (five bricks a side in the ordered phase, else six), one sweep after another and together:
 spins, records, labels and histogram against the oracle."""
 import numpy as np
 import pytest
@@ -10,7 +10,7 @@ import paper_2302_14720_amd as sw
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("L", [16, 48, 80, 96])
+@pytest.mark.parametrize("L", [16, 48, 80, 96, 112])
 @pytest.mark.parametrize("q,beta,cold", [(0, 0.0, False), (0, 0.2216544, False), (0, 0.4, True), (3, 0.5505, False)])
 def test_both_sides(L, q, beta, cold):
     print(f"\n[case] few bricks L={L} q={q} beta={beta} cold={cold}", flush=True)
