@@ -557,7 +557,8 @@ void sw_phi4_destroy(sw_phi4 *sim);
  * the stream all work is enqueued on (NULL: the null stream); the call
  * returns without waiting.  Nothing is allocated: every other buffer of the
  * sweep lives in one static device array of 16 MiB per GPU, held until the
- * process ends, so L is at most 2048 (SW_ERANGE above).  All calls on one
+ * process ends, so L is at most 2048, or 1696 where it is no multiple of 64
+ * (SW_ERANGE above).  All calls on one
  * GPU share that array: calls that overlap on one GPU (other streams or
  * threads) race; calls on one stream are ordered.  SW_EINVAL for NULL or
  * misaligned pointers and for L, beta or J outside their domain (as for

@@ -136,30 +136,29 @@ Layout layout_of(const sw_config &c) {
     };
     o.spins[0] = take(N);
     o.spins[1] = le || brick ? o.spins[0] : take(N);  // final spins in place
-    o.parent[0] = take(nodes * 4);
-    o.parent[1] = brick ? o.parent[0] : take(nodes * 4);
+    o.parent = take(nodes * 4);
     o.nk[0] = take(ntiles * 4);
     o.nk[1] = brick ? o.nk[0] : take(ntiles * 4);
     o.key = take(nodes * 4);
-    o.nsize = take(nodes * 4);
-    o.rspin = brick ? 0 : take(nodes);
+    o.nsize = brick ? 0 : take(nodes * 4);
+    const size_t mg = le || brick ? 0 : merge_groups(c);
+    // new values by node: the spin, or k_merge's reference (nref)
+    o.rspin = brick ? 0 : take(mg ? nodes * 2 : nodes);
     o.edge = brick ? 0 : take(ntiles * 4 * tw);
     o.xb = brick ? 0 : take(ntiles * 16);
-    // (room for k_merge also where labels or the histogram rule it out, so that
-    // a flag's workspace is the plain one's and its own arrays)
-    const size_t mg = le || brick ? 0 : merge_groups(c);
-    o.nref = take(mg ? nodes * 2 : 0);
-    o.gnode = take(mg * kRefSlots * 8);
-    o.gedge = take(mg * kRefSlots * 2);
-    o.gspin = take(mg * kRefSlots);
-    o.gcount = take(mg * 4);
-    o.mpart = take(mg * swmi::kGroupPart * 8);
+    // (a lattice of one group is merged by one workgroup alone; several have
+    // room here also where labels or the histogram rule k_merge out, so that a
+    // flag's workspace is the plain one's and its own arrays)
+    const size_t mt = mg > 1 ? mg : 0;
+    o.gspin = take(mt * swmi::ref_slots((uint32_t)tw));
+    o.gcount = take(mt * 4);
+    o.mpart = take(mt * swmi::kGroupPart * 8);
     o.tpart = take(ntiles * swmi::kTilePart * 4);
     o.gpart = take(ngroups * swmi::kGroupPart * 8);
     o.acc = take(swmi::kAccWords * 8);
     o.tdev = take(8);
     o.ring = take(ring * sizeof(sw_obs));
-    o.labels = (le || brick || (c.flags & SW_FLAG_LABELS)) ? take(N * 4) : 0;
+    o.labels = (le || (c.flags & SW_FLAG_LABELS)) && !brick ? take(N * 4) : 0;
     o.dense = (c.flags & SW_FLAG_DENSE_HIST) ? take((N + 1) * 8) : 0;
     o.tdense = (c.flags & SW_FLAG_DENSE_HIST) && !brick ? take(ntiles * swmi::kDenseBins * 2) : 0;
     o.le_mask = le ? take(N) : 0;
@@ -167,8 +166,14 @@ Layout layout_of(const sw_config &c) {
     o.le_rsp = le ? take(N) : 0;
     o.le_ctl = le ? take(64) : 0;
     o.codes = brick ? take(N * 2) : 0;
-    o.faces = brick ? take(ntiles * 6 * 256 * 2) : 0;
     o.node = brick ? take(nodes * 4) : 0;
+    if (brick) {
+        // labels are made on request from the codes, nodes and keys of the last
+        // sweep: over its faces and sizes, which are done with by then
+        o.faces = o.labels = take(ntiles * 6 * 256 * 2);
+        o.nsize = take(nodes * 4);
+        off = std::max(off, align_up(o.labels + N * 4));
+    }
     o.total = off;
     return o;
 }
@@ -194,9 +199,9 @@ Dev make_dev(const sw_config &c, char *base, const Layout &lo) {
     d.J = c.J;
     for (int i = 0; i < 2; ++i) {
         d.spins[i] = (int8_t *)(base + lo.spins[i]);
-        d.parent[i] = (uint32_t *)(base + lo.parent[i]);
         d.nk[i] = (uint32_t *)(base + lo.nk[i]);
     }
+    d.parent = (uint32_t *)(base + lo.parent);
     d.key = (uint32_t *)(base + lo.key);
     d.nsize = (uint32_t *)(base + lo.nsize);
     d.rspin = (int8_t *)(base + lo.rspin);
@@ -204,9 +209,7 @@ Dev make_dev(const sw_config &c, char *base, const Layout &lo) {
     d.xb = (uint64_t *)(base + lo.xb);
     if (merge_in_one(c)) {
         d.two = 1u;
-        d.nref = (uint16_t *)(base + lo.nref);
-        d.gnode = (uint64_t *)(base + lo.gnode);
-        d.gedge = (uint16_t *)(base + lo.gedge);
+        d.nref = (uint16_t *)(base + lo.rspin);
         d.gspin = (uint8_t *)(base + lo.gspin);
         d.gcount = (uint32_t *)(base + lo.gcount);
         d.mpart = (uint64_t *)(base + lo.mpart);

@@ -367,7 +367,7 @@ __global__ __launch_bounds__(256, kBrickWavesPerEU) void k_brick3(Dev d) {
                 const uint32_t node = B.b * kBrickNodes + k;
                 d.node[node] = (sbase + i) | (S << 16);
                 if constexpr (!LOCAL) {
-                    d.parent[0][node] = node;
+                    d.parent[node] = node;
                     d.nsize[node] = S;
                     d.key[node] = s0 + i;
                 }
@@ -520,7 +520,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_blocal3(Dev d) {
         const uint32_t r = lds_find(s_p, li), tr = r / kBrickNodes;
         uint32_t br;
         group_brick(g, tr, nb, br);
-        d.parent[0][node] = br * kBrickNodes + (r - tr * kBrickNodes);
+        d.parent[node] = br * kBrickNodes + (r - tr * kBrickNodes);
         if (r == li) {  // only a group root can be a cluster's root
             d.nsize[node] = e >> 16;
             d.key[node] = site_at(B, d.L, e & 0xFFFFu);
@@ -559,7 +559,7 @@ __global__ __launch_bounds__(256) void k_bunion3(Dev d, uint32_t layers) {
     }
     const uint32_t na = d.faces[((size_t)A * 6u + f) * kRows + i], nn = d.faces[((size_t)Bn * 6u + 3u + f) * kRows + i];
     const bool has = na != kNoNode;
-    uint32_t *par = d.parent[0];
+    uint32_t *par = d.parent;
     const uint32_t ra = has ? g_load(&par[A * kBrickNodes + na]) : kEmpty;
     const uint32_t rb = has ? g_load(&par[Bn * kBrickNodes + nn]) : 0u;
     const uint32_t pa = __shfl_up(ra, 1, 64), pb = __shfl_up(rb, 1, 64);
@@ -585,7 +585,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_bflat3(Dev d) {
         hm[i] = kEmpty;
     }
     __syncthreads();
-    uint32_t *par = d.parent[0];
+    uint32_t *par = d.parent;
     uint32_t b = blockIdx.x;
     const bool ok = !GROUP || group_brick(tile_of_block(blockIdx.x, gridDim.x), wv, d.L / kBrick, b);
     const uint32_t nk = ok ? min(d.nk[0][b], kBrickNodes) : 0u;
@@ -682,7 +682,7 @@ __global__ __launch_bounds__(256) void k_bspin3(Dev d) {
     const uint4 c0 = cp[0], c1 = cp[1];
     const uint32_t nk = min(d.nk[0][B.b], kBrickNodes);
     // the first round's node entries (a brick rarely has more than 256 nodes)
-    const uint32_t *par = d.parent[0];
+    const uint32_t *par = d.parent;
     const uint32_t mine = B.b * kBrickNodes + tid;
     const uint32_t root0 = tid < nk ? par[mine] : 0u, site0 = tid < nk ? d.node[mine] : 0u;
     const uint32_t key0 = tid < nk ? d.key[root0] : 0u;
@@ -798,7 +798,7 @@ __global__ __launch_bounds__(256) void k_blabels3(Dev d) {
     const uint32_t nk = min(d.nk[0][B.b], kBrickNodes);
     for (uint32_t k = tid; k < nk; k += kRows) {
         const uint32_t node = B.b * kBrickNodes + k;
-        s_lab[d.node[node] & (kVol - 1u)] = d.key[d.parent[0][node]];
+        s_lab[d.node[node] & (kVol - 1u)] = d.key[d.parent[node]];
     }
     __syncthreads();
     const uint16_t *cp = d.codes + (size_t)B.b * kVol + tid * kBrick;

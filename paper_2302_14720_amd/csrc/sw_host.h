@@ -38,7 +38,7 @@ struct StageUser {
 uint32_t bond_threshold(double beta, double J);
 
 struct Layout {
-    size_t spins[2], parent[2], nk[2], key, nsize, rspin, edge, xb, nref, gnode, gedge, gspin, gcount, mpart, tpart, gpart, acc, tdev, ring, labels,
+    size_t spins[2], parent, nk[2], key, nsize, rspin, edge, xb, gspin, gcount, mpart, tpart, gpart, acc, tdev, ring, labels,
         dense, tdense, le_mask, le_cnt, le_rsp, le_ctl, codes, faces, node, total;
 };
 

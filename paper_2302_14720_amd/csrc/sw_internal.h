@@ -52,8 +52,15 @@ constexpr int kGroupTiles = 16;       // tiles per workgroup in k_flatten / k_ro
 constexpr uint32_t kDenseBins = 256;  // sizes below this are counted per tile and group (dense histogram)
 constexpr uint32_t kUG = 4;           // side, in tiles, of a k_ulocal or k_merge group
 constexpr uint32_t kRef = 8;          // nref: below, a final value
-constexpr uint32_t kRefSlots = 1024;  // clusters of a k_merge group that go on outside it (its perimeter)
 constexpr uint32_t kMergeGroups = 16; // most groups of a lattice merged by k_merge
+// Slots of a k_merge group for its clusters that go on outside it: the sites of its perimeter.
+__host__ __device__ constexpr uint32_t ref_slots(uint32_t tw) { return 4u * kUG * tw; }
+// What the groups hand to the lattice's last workgroup (10 bytes a slot) lies in
+// the spin buffer that the sweep has read by then; 5, 9 and 13 tiles a side are
+// the smallest lattices of 4, 9 and 16 groups.
+static_assert(4u * ref_slots(32) * 10u <= 25u * 32u * 32u && 9u * ref_slots(32) * 10u <= 81u * 32u * 32u &&
+                  16u * ref_slots(32) * 10u <= 169u * 32u * 32u,
+              "the group tables must fit in a lattice's spins (64-wide tiles: half of this share)");
 
 // tile partial (int32 words)
 // hist: kTileBins bins (sizes up to 64 * 64 or 16^3); TP_CNT..: population of each Potts value
@@ -66,26 +73,24 @@ enum { ACC_COUNT = 48 };
 
 struct Dev {
     int8_t *spins[2];     // [N] by sweep parity
-    uint32_t *parent[2];  // [ntiles * kNodeSlots] by sweep parity
+    uint32_t *parent;     // [ntiles * kNodeSlots] of the sweep that runs
     uint32_t *nk[2];      // [ntiles] number of nodes per tile, by parity
     uint32_t *key;        // [ntiles * kNodeSlots] smallest site of the node
     uint32_t *nsize;      // [ntiles * kNodeSlots] node size; cluster size at roots
-    int8_t *rspin;        // [ntiles * kNodeSlots] new spin of each node's cluster
+    int8_t *rspin;        // [ntiles * kNodeSlots] new spin of each node's cluster (in the place of nref)
     uint8_t *edge;        // [ntiles][4][tw] node index of W, E, S, N edge sites
     uint64_t *xb;         // [ntiles][2] bonds leaving the tile: E (bit y), N (bit x)
     int32_t *tpart;       // [ntiles][kTilePart]
     uint64_t *gpart;      // [ngroups][kGroupPart]
     uint64_t *acc;        // [kAccWords]
     uint64_t *tdev;       // [0] = index of the next sweep
-    // lattices merged by k_merge (two = 1)
+    // lattices merged by k_merge (two = 1); the last three with several groups
     uint16_t *nref;       // [ntiles * kNodeSlots] value of the node's cluster, or kRef + its number in the group
-    uint64_t *gnode;      // [groups][kRefSlots] key | size << 32 of the clusters that go on outside the group
-    uint16_t *gedge;      // [groups][4][256] their numbers at the bonds on the group's E, N, W, S sides (0xFFFF: none)
-    uint8_t *gspin;       // [groups][kRefSlots] their new values
+    uint8_t *gspin;       // [groups][ref_slots] new values of the clusters that go on outside the group
     uint32_t *gcount;     // [groups] how many
     uint64_t *mpart;      // [groups][kGroupPart] partial statistics
     sw_obs *ring;         // [ring_cap]
-    uint32_t *labels;     // [N] or nullptr
+    uint32_t *labels;     // [N] or nullptr (bricks: in the place of faces, nsize and on)
     uint64_t *dense;      // [N + 1] or nullptr
     uint16_t *tdense;     // [ntiles][kDenseBins] interior clusters by size (with dense, tile path)
     // label-equivalence path (SW_FLAG_LABEL_EQUIV); nullptr otherwise
@@ -93,7 +98,7 @@ struct Dev {
     uint32_t *le_cnt;     // [N] cluster size at each root
     int8_t *le_rsp;       // [N] new spin, valid at roots
     uint32_t *le_ctl;     // [8] pass flags (3), passes of the last sweep, status
-    // simple cubic lattice on bricks (sw_brick.hip); parent[0], nk[0], key, nsize
+    // simple cubic lattice on bricks (sw_brick.hip); parent, nk[0], key, nsize
     // and tpart by brick, kBrickNodes node slots each; gpart one per brick
     uint16_t *codes;      // [nbricks][4096] brick-local index of the site's component's smallest site
     uint16_t *faces;      // [nbricks][6][256] nodes of the sites of the +x, +y, +z faces (0xFFFF unless

@@ -104,7 +104,7 @@ __device__ __forceinline__ typename RowOf<TW>::T row_gather(uint32_t piece, uint
 // New value of a node's cluster in the previous sweep: the Potts value, or 1
 // for spin +1 and 0 for -1 (Ising).  Lattices merged by k_merge keep a
 // reference per node: the value itself, or kRef + j for cluster j of the
-// tile's group, whose table starts at gb (kRefSlots per group); the others
+// tile's group, whose table starts at gb (ref_slots per group); the others
 // keep the spin.  Both steps are loads without a compare behind them, so that
 // the loads of several nodes overlap (a compare between them makes the tile
 // kernel wait for each: 0.93 -> 0.97 ms at 16384^2).
@@ -124,7 +124,7 @@ template <bool POTTS, int TWO> __device__ __forceinline__ uint32_t value_of(cons
 }
 // Start of the cluster table of the group that holds tile (tx, ty).
 __device__ __forceinline__ uint32_t ref_base(const Dev &d, uint32_t tx, uint32_t ty) {
-    return ((ty / kUG) * ((d.ntx + kUG - 1u) / kUG) + tx / kUG) * kRefSlots;
+    return ((ty / kUG) * ((d.ntx + kUG - 1u) / kUG) + tx / kUG) * ref_slots(d.tw);
 }
 
 // Shared front end of k_tile and k_resolve: the table that maps every byte
@@ -340,7 +340,7 @@ __device__ __forceinline__ void tile_body(const Dev &d, const uint32_t tile, Til
     const uint32_t pc = (uint32_t)(tsw & 1u), pp = pc ^ 1u;
     const int8_t *__restrict__ sin = d.spins[pc];
     int8_t *__restrict__ sout = d.spins[pp];
-    uint32_t *__restrict__ par_cur = d.parent[pc];
+    uint32_t *__restrict__ par_cur = d.parent;
 
     const uint32_t ly = tid / RPT, seg = tid % RPT, x0 = seg * (uint32_t)SPT;
     const uint32_t gy = ty * TW + ly, gx0 = tx * TW + x0;
@@ -972,16 +972,14 @@ __device__ __forceinline__ void union_body(const Dev &d, const uint32_t tile, co
                                   : (ty + 1u == ntx ? 0u : ty + 1u) * ntx + tx;
     const uint8_t *eg = d.edge + (size_t)tile * 4u * TW;
     const uint8_t *egb = d.edge + (size_t)nb * 4u * TW;
-    // one lane per edge position; the bond bits, both sides' node bytes and
-    // the sweep parity are all loaded before any of them is waited on
+    // one lane per edge position; the bond bits and both sides' node bytes are
+    // all loaded before any of them is waited on
     const bool in = lane < (uint32_t)TW;
     const uint32_t i = in ? lane : 0u;
     const uint32_t an = dir == 0u ? eg[1 * TW + i] : eg[3 * TW + i];
     const uint32_t bn = dir == 0u ? egb[0 * TW + i] : egb[2 * TW + i];
     const uint64_t bits = d.xb[2u * tile + dir];
-    // (volatile: keeps the compiler from sinking the load to its first use)
-    const uint32_t pc = (uint32_t)(*(volatile const uint64_t *)d.tdev & 1u);
-    uint32_t *par = pc ? d.parent[1] : d.parent[0];
+    uint32_t *par = d.parent;
     const bool has = in && ((bits >> i) & 1u);
     const uint32_t a = tile * kNodeSlots + an, b = nb * kNodeSlots + bn;
     // every union starts from the two nodes' parents (their group roots, or
@@ -1059,7 +1057,7 @@ __device__ __forceinline__ void ulocal_body(const Dev &d, const uint32_t ugroup,
     }
     __syncthreads();
 
-    uint32_t *par = d.parent[pc];
+    uint32_t *par = d.parent;
     const uint32_t gt = tile_of(mt);
     for (uint32_t k = mk; k < nkt; k += 16u) {
         const uint32_t li = mt * kNodeSlots + k;
@@ -1172,7 +1170,7 @@ __device__ __forceinline__ void flatten_body(const Dev &d, const uint32_t group)
     }
     __syncthreads();
     const uint32_t pc = (uint32_t)(*d.tdev & 1u);
-    uint32_t *par = d.parent[pc];
+    uint32_t *par = d.parent;
     const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6;
     const uint32_t g0 = group * FT;
     static_assert(FT % 16u == 0u, "four tiles per wavefront and quad");
@@ -1254,8 +1252,7 @@ __global__ __launch_bounds__(256) void k_flatten_b(const Dev *devs, const uint32
 // Canonical labels of sites of cross-tile clusters (only with SW_FLAG_LABELS).
 __global__ __launch_bounds__(256) void k_relabel(Dev d) {
     const size_t n = (size_t)d.L * d.L;
-    const uint32_t pc = (uint32_t)(*d.tdev & 1u);
-    const uint32_t *par = d.parent[pc];
+    const uint32_t *par = d.parent;
     const uint32_t nnodes = d.ntiles * kNodeSlots;
     for (size_t i = blockIdx.x * (size_t)256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
         const uint32_t l = d.labels[i];
@@ -1294,7 +1291,7 @@ __device__ __forceinline__ void roots_body(const Dev &d, const uint32_t group) {
     if (threadIdx.x < (uint32_t)kMaxQ) s_cnt[threadIdx.x] = 0u;
     const uint64_t tsw = *d.tdev;
     const uint32_t t = (uint32_t)tsw, pc = (uint32_t)(tsw & 1u);
-    const uint32_t *par = d.parent[pc];
+    const uint32_t *par = d.parent;
     const uint32_t lane = threadIdx.x & 63u, wv = threadIdx.x >> 6;
     const uint32_t g0 = group * (uint32_t)kGroupTiles;
     uint64_t n = 0, mx = 0, sq = 0;
@@ -1644,7 +1641,7 @@ __global__ __launch_bounds__(256) void k_roots_b(const Dev *devs, const uint32_t
 //   level 1  unions across the tile edges inside the group; sizes and smallest
 //            sites at the roots; a cluster with no bond out of the group is
 //            complete and draws its spin
-//   level 2  the other clusters, numbered per group (kRefSlots slots; each
+//   level 2  the other clusters, numbered per group (ref_slots slots; each
 //            holds a bond on the group's perimeter, of at most 1024 sites): the
 //            last workgroup of the lattice to count itself in unites them
 //            across the group edges, draws their spins and writes the record
@@ -1750,12 +1747,15 @@ struct TopLoads {
     static constexpr uint32_t kEnt = 5, kPos = 8;
     uint64_t e[kEnt];
     uint32_t a[kPos], b[kPos];  // clusters on both sides (kNoRef: no bond)
+    const uint64_t *gnode;      // key | size << 32 of a group's clusters
+    const uint16_t *gedge;      // numbers of the clusters at the bonds on its E, N, W, S sides (kNoRef: none)
+    uint32_t slots;             // of each, per group
 
-    __device__ __forceinline__ void clusters(const Dev &d, uint32_t g, uint32_t ng, uint32_t j0) {
+    __device__ __forceinline__ void clusters(uint32_t g, uint32_t ng, uint32_t j0) {
 #pragma unroll
         for (uint32_t u = 0; u < kEnt; ++u) {
             const uint32_t j = j0 + 64u * u + (threadIdx.x & 63u);
-            e[u] = g < ng && j < kRefSlots ? ag_load(&d.gnode[(size_t)g * kRefSlots + j]) : 0u;
+            e[u] = g < ng && j < slots ? ag_load(&gnode[(size_t)g * slots + j]) : 0u;
         }
     }
     // Group g, its neighbour nb, the direction and the place p of position f,
@@ -1779,8 +1779,8 @@ struct TopLoads {
         for (uint32_t u = 0; u < kPos; ++u) {
             uint32_t g, nb, dir, p;
             const bool ok = place(d, f0 + kMergeThreads * u + (threadIdx.x & ~63u), ngx, g, nb, dir, p);
-            a[u] = ok ? ag_load(&d.gedge[(size_t)g * kRefSlots + dir * 256u + p]) : kNoRef;
-            b[u] = ok ? ag_load(&d.gedge[(size_t)nb * kRefSlots + (2u + dir) * 256u + p]) : kNoRef;
+            a[u] = ok ? ag_load(&gedge[(size_t)g * slots + dir * (slots / 4u) + p]) : kNoRef;
+            b[u] = ok ? ag_load(&gedge[(size_t)nb * slots + (2u + dir) * (slots / 4u) + p]) : kNoRef;
         }
     }
 };
@@ -1835,7 +1835,7 @@ __device__ __forceinline__ void merge_top(const Dev &d, uint32_t ng, uint32_t ng
     for (uint32_t g = wv; g < ng; g += kMergeWaves) {
         const uint32_t off = s_off[g], n = s_off[g + 1u] - off;
         for (uint32_t j0 = 0; j0 < n; j0 += 64u * TopLoads::kEnt) {
-            if (g != wv || j0 != 0u) ld1.clusters(d, g, ng, j0);
+            if (g != wv || j0 != 0u) ld1.clusters(g, ng, j0);
 #pragma unroll
             for (uint32_t u = 0; u < TopLoads::kEnt; ++u) {
                 const uint32_t j = j0 + 64u * u + lane, i = off + j;
@@ -1862,7 +1862,7 @@ __device__ __forceinline__ void merge_top(const Dev &d, uint32_t ng, uint32_t ng
     for (uint32_t g = wv; g < ng; g += kMergeWaves)
         for (uint32_t j = lane; j < s_off[g + 1u] - s_off[g]; j += 64u) {
             const uint32_t i = s_off[g] + j, r = ld(&par[i]);
-            d.gspin[(size_t)g * kRefSlots + j] = (uint8_t)new_value(d, ld(&key[r]), t);
+            d.gspin[(size_t)g * ld1.slots + j] = (uint8_t)new_value(d, ld(&key[r]), t);
             if (r == i) cs.add(ld(&sz[i]), s_acc);
         }
     cs.flush(s_acc);
@@ -1891,6 +1891,11 @@ __device__ __forceinline__ void merge_body(const Dev &d, const uint32_t ug) {
     const uint32_t ntx = d.ntx, tw = d.tw, lw = tw == 64u ? 6u : 5u;
     const uint32_t ngx = (ntx + kUG - 1u) / kUG, ng = ngx * ngx, gy = ug / ngx, gx = ug - gy * ngx;
     const bool whole = ng == 1u;
+    // the groups' results for the last workgroup lie in the spins that k_tile has
+    // read and replaced by then, of no more use until the next sweep writes them
+    const uint32_t slots = 16u << lw, side = 4u << lw;  // (ref_slots; positions of a side)
+    uint64_t *const gnode = reinterpret_cast<uint64_t *>(d.spins[pc]);
+    uint16_t *const gedge = reinterpret_cast<uint16_t *>(gnode + ng * slots);
     uint32_t *const s_par = s_buf, *const s_sz = s_buf + kTopLds, *const s_key = s_buf + 2u * kTopLds;
 
     // edge positions: E and N of every tile (two per thread, one with 32-wide
@@ -1915,7 +1920,7 @@ __device__ __forceinline__ void merge_body(const Dev &d, const uint32_t ug) {
         const bool has = ok && ((bits >> i) & 1u);
         ua[u] = has ? T * kNodeSlots + an : kEmpty;
         ub[u] = inside ? TB * kNodeSlots + bn : kEmpty;
-        uo[u] = ok && !inside ? dir * 256u + (dir == 0u ? ly : lx) * tw + i : kEmpty;
+        uo[u] = ok && !inside ? dir * side + (dir == 0u ? ly : lx) * tw + i : kEmpty;
     }
     uint32_t va = kEmpty, vo = kEmpty;  // incoming: node, place
     if (!whole) {
@@ -1928,7 +1933,7 @@ __device__ __forceinline__ void merge_body(const Dev &d, const uint32_t ug) {
         const uint64_t bits = d.xb[2u * P + dir];
         const uint32_t an = d.edge[((size_t)A * 4u + (dir == 0u ? 0u : 2u)) * tw + i];
         if (ok && ((bits >> i) & 1u)) va = (dir == 0u ? l * kUG : l) * kNodeSlots + an;
-        if (ok) vo = (2u + dir) * 256u + l * tw + i;
+        if (ok) vo = (2u + dir) * side + l * tw + i;
     }
     // nodes: wavefront wv has tile wv of the group, its node slots lane + 64 j
     const uint32_t mx = gx * kUG + wv % kUG, my = gy * kUG + wv / kUG;
@@ -1998,12 +2003,12 @@ __device__ __forceinline__ void merge_body(const Dev &d, const uint32_t ug) {
             }
             s_pre[2u * lane] = incl - c;
             s_pre[2u * lane + 1u] = incl - c + ca;
-            open = min((uint32_t)__shfl((int)incl, 63, 64), kRefSlots);
+            open = min((uint32_t)__shfl((int)incl, 63, 64), slots);
         }
         __syncthreads();
     }
     auto number = [&](uint32_t r) {
-        return min(s_pre[r >> 5] + __popc(s_link[r >> 5] & ((1u << (r & 31u)) - 1u)), kRefSlots - 1u);
+        return min(s_pre[r >> 5] + __popc(s_link[r >> 5] & ((1u << (r & 31u)) - 1u)), slots - 1u);
     };
     Stats cs;
 #pragma unroll
@@ -2014,7 +2019,7 @@ __device__ __forceinline__ void merge_body(const Dev &d, const uint32_t ug) {
         if ((s_link[r >> 5] >> (r & 31u)) & 1u) {
             const uint32_t n = number(r);
             ref = kRef + n;
-            if (r == li) ag_store(&d.gnode[(size_t)ug * kRefSlots + n], (uint64_t)s_key[r] | ((uint64_t)s_sz[r] << 32));
+            if (r == li) ag_store(&gnode[(size_t)ug * slots + n], (uint64_t)s_key[r] | ((uint64_t)s_sz[r] << 32));
         } else {
             ref = new_value(d, s_key[r], t);
             if (r == li) cs.add(s_sz[r], s_acc);
@@ -2022,7 +2027,7 @@ __device__ __forceinline__ void merge_body(const Dev &d, const uint32_t ug) {
         d.nref[mtile * kNodeSlots + k] = (uint16_t)ref;
     }
     if (!whole) {
-        uint16_t *ge = d.gedge + (size_t)ug * kRefSlots;
+        uint16_t *ge = gedge + (size_t)ug * slots;
 #pragma unroll
         for (uint32_t u = 0; u < 2u; ++u)
             if (uo[u] != kEmpty) ag_store(&ge[uo[u]], (uint16_t)(ur[u] == kEmpty ? kNoRef : number(ur[u])));
@@ -2067,7 +2072,10 @@ __device__ __forceinline__ void merge_body(const Dev &d, const uint32_t ug) {
         if (!s_last) return;
         if (tid == 0u) ag_store(&d.acc[ACC_COUNT], (uint64_t)0);
         TopLoads top;
-        top.clusters(d, wv, ng, 0u);
+        top.gnode = gnode;
+        top.gedge = gedge;
+        top.slots = slots;
+        top.clusters(wv, ng, 0u);
         top.bonds(d, 0u, ngx);
         // the groups' partials, and in wavefront 0 the first cluster of every group
         uint64_t v = 0u;
@@ -2078,7 +2086,7 @@ __device__ __forceinline__ void merge_body(const Dev &d, const uint32_t ug) {
         if (wv == 0u) {
             uint32_t c[2];
 #pragma unroll
-            for (uint32_t h = 0; h < 2u; ++h) c[h] = 2u * lane + h < ng ? min(ag_load(&d.gcount[2u * lane + h]), kRefSlots) : 0u;
+            for (uint32_t h = 0; h < 2u; ++h) c[h] = 2u * lane + h < ng ? min(ag_load(&d.gcount[2u * lane + h]), slots) : 0u;
             uint32_t incl = c[0] + c[1];
             const uint32_t own = incl;
 #pragma unroll
@@ -2098,7 +2106,7 @@ __device__ __forceinline__ void merge_body(const Dev &d, const uint32_t ug) {
         if (s_off[ng] <= kTopLds)
             merge_top<true>(d, ng, ngx, t, s_off, top, s_par, s_sz, s_key, s_acc);
         else
-            merge_top<false>(d, ng, ngx, t, s_off, top, d.parent[pc], d.nsize, d.key, s_acc);
+            merge_top<false>(d, ng, ngx, t, s_off, top, d.parent, d.nsize, d.key, s_acc);
     }
     __syncthreads();
     record_write(d, reinterpret_cast<const uint64_t *>(s_acc), 0);

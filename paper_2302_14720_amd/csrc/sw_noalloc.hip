@@ -18,7 +18,7 @@
 
 namespace {
 
-constexpr size_t kScratchBytes = (size_t)16 << 20;  // L = 2048 needs 12.7 MiB
+constexpr size_t kScratchBytes = (size_t)16 << 20;  // L = 2048 needs 11.7 MiB
 constexpr int32_t kNoallocMaxL = 2048;
 constexpr int kMaxDevices = 64;
 

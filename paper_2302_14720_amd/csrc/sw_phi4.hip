@@ -459,8 +459,8 @@ PhiLayout phi_layout(int32_t L, int64_t ring) {
     lo.cross = take(N);
     lo.dir = take(8 * sizeof(double));
     lo.part = take(std::min<size_t>((N + kPhiChunk - 1) / kPhiChunk, kPhiRecGroups) * kPhiPart * sizeof(uint64_t));
-    lo.acc = take(sizeof(uint64_t));
-    lo.tdev = take(sizeof(uint64_t));
+    lo.acc = take(2 * sizeof(uint64_t));
+    lo.tdev = lo.acc + sizeof(uint64_t);
     lo.ring = take((size_t)ring * sizeof(sw_phi4_obs));
     lo.total = off;
     return lo;

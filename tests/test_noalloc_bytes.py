@@ -36,7 +36,7 @@ def test_every_byte_becomes_a_spin(tmp_path):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("L", [64, 96, 512, 1024, 1088])  # one-launch merges and the global one
+@pytest.mark.parametrize("L", [64, 96, 512, 1024, 1088, 1696])  # one-launch merges and the global one
 @pytest.mark.parametrize("coding", ["0/1", "any"])
 def test_bytes_that_are_no_spins(L, coding):
     import torch
