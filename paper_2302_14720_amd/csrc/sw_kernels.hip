@@ -1718,7 +1718,8 @@ __device__ __forceinline__ void join_pairs(uint32_t *par, uint32_t *list, const 
     __builtin_amdgcn_wave_barrier();
 }
 
-// A first step for join_pairs: every pair hooks its larger index under the
+// A first step for join_pairs, while every entry of par is a root (an entry that
+// is not would lose its link): every pair hooks its larger index under the
 // smallest it meets, compress() points all entries at their roots, and pairs
 // that share a root are done.  Level 2 of 1024^2 (beta = 0.44, 3264 clusters):
 // unions 9.6 -> 6.8 us; of 512^2 (758) 4.4 -> 4.7.
@@ -1742,7 +1743,7 @@ __device__ __forceinline__ void hook_pairs(uint32_t *par, uint32_t *a, uint32_t 
 // the first batch is loaded while the clusters are being counted.  Clusters:
 // a wavefront takes a group at a time, kEnt rounds of 64 (about 200 are
 // open).  Bonds: position f of the groups' E and N sides, one per thread and
-// round.
+// round, all in the one batch.
 struct TopLoads {
     static constexpr uint32_t kEnt = 5, kPos = 8;
     uint64_t e[kEnt];
@@ -1774,11 +1775,11 @@ struct TopLoads {
         nb = dir == 0u ? gy * ngx + (gx + 1u == ngx ? 0u : gx + 1u) : (gy + 1u == ngx ? 0u : gy + 1u) * ngx + gx;
         return in && (dir == 0u ? gy : gx) * kUG + (p >> lw) < d.ntx;
     }
-    __device__ __forceinline__ void bonds(const Dev &d, uint32_t f0, uint32_t ngx) {
+    __device__ __forceinline__ void bonds(const Dev &d, uint32_t ngx) {
 #pragma unroll
         for (uint32_t u = 0; u < kPos; ++u) {
             uint32_t g, nb, dir, p;
-            const bool ok = place(d, f0 + kMergeThreads * u + (threadIdx.x & ~63u), ngx, g, nb, dir, p);
+            const bool ok = place(d, kMergeThreads * u + (threadIdx.x & ~63u), ngx, g, nb, dir, p);
             a[u] = ok ? ag_load(&gedge[(size_t)g * slots + dir * (slots / 4u) + p]) : kNoRef;
             b[u] = ok ? ag_load(&gedge[(size_t)nb * slots + (2u + dir) * (slots / 4u) + p]) : kNoRef;
         }
@@ -1808,28 +1809,26 @@ __device__ __forceinline__ void merge_top(const Dev &d, uint32_t ng, uint32_t ng
     const uint32_t m = s_off[ng];
     for (uint32_t i = tid; i < m; i += kMergeThreads) st(&par[i], i);
     barrier();
-    // bonds across the E and N edges of every group
-    const uint32_t np = ng * 8u * d.tw;
-    for (uint32_t f0 = 0; f0 < np; f0 += kMergeThreads * TopLoads::kPos) {
-        if (f0 != 0u) ld1.bonds(d, f0, ngx);
+    // bonds across the E and N edges of every group: all of them at once, since
+    // hook_pairs is right only while every entry is a root
+    static_assert(kMergeGroups * 8u * 64u <= kMergeThreads * TopLoads::kPos, "one position per thread and round");
 #pragma unroll
-        for (uint32_t u = 0; u < TopLoads::kPos; ++u) {
-            uint32_t g, nb, dir, p;
-            TopLoads::place(d, f0 + kMergeThreads * u + (tid & ~63u), ngx, g, nb, dir, p);
-            const bool has = ld1.a[u] != kNoRef && ld1.b[u] != kNoRef;
-            ld1.a[u] = has ? s_off[g] + ld1.a[u] : kEmpty;
-            ld1.b[u] = has ? s_off[nb] + ld1.b[u] : kEmpty;
-        }
-        if (LDS) {  // the lists lie where sizes and keys go afterwards
-            hook_pairs<TopLoads::kPos>(par, ld1.a, ld1.b, [&] {
-                for (uint32_t i = tid; i < m; i += kMergeThreads) lds_store(&par[i], lds_find(par, i));
-            });
-            join_pairs<TopLoads::kPos>(par, sz + wv * 64u * TopLoads::kPos, ld1.a, ld1.b);
-        } else {
+    for (uint32_t u = 0; u < TopLoads::kPos; ++u) {
+        uint32_t g, nb, dir, p;
+        TopLoads::place(d, kMergeThreads * u + (tid & ~63u), ngx, g, nb, dir, p);
+        const bool has = ld1.a[u] != kNoRef && ld1.b[u] != kNoRef;
+        ld1.a[u] = has ? s_off[g] + ld1.a[u] : kEmpty;
+        ld1.b[u] = has ? s_off[nb] + ld1.b[u] : kEmpty;
+    }
+    if (LDS) {  // the lists lie where sizes and keys go afterwards
+        hook_pairs<TopLoads::kPos>(par, ld1.a, ld1.b, [&] {
+            for (uint32_t i = tid; i < m; i += kMergeThreads) lds_store(&par[i], lds_find(par, i));
+        });
+        join_pairs<TopLoads::kPos>(par, sz + wv * 64u * TopLoads::kPos, ld1.a, ld1.b);
+    } else {
 #pragma unroll
-            for (uint32_t u = 0; u < TopLoads::kPos; ++u)
-                if (ld1.a[u] != kEmpty) g_union(par, ld1.a[u], ld1.b[u]);
-        }
+        for (uint32_t u = 0; u < TopLoads::kPos; ++u)
+            if (ld1.a[u] != kEmpty) g_union(par, ld1.a[u], ld1.b[u]);
     }
     if (LDS) __syncthreads();
     for (uint32_t g = wv; g < ng; g += kMergeWaves) {
@@ -2076,7 +2075,7 @@ __device__ __forceinline__ void merge_body(const Dev &d, const uint32_t ug) {
         top.gedge = gedge;
         top.slots = slots;
         top.clusters(wv, ng, 0u);
-        top.bonds(d, 0u, ngx);
+        top.bonds(d, ngx);
         // the groups' partials, and in wavefront 0 the first cluster of every group
         uint64_t v = 0u;
         for (uint32_t g = wv; g < ng; g += kMergeWaves) {
