@@ -265,11 +265,12 @@ const char *sw_last_error(void);
  * instead of two to six per replica.  The cross-tile merge of Sec. 2.3 runs
  * either globally (four launches over all such replicas, the record folded
  * into the last) or, for a replica of at most 16 groups of 4 x 4 tiles, by
- * one workgroup per group in LDS (one launch for all such replicas, while
- * those of more than 16 tiles make at most 512 groups together); a
- * replica of at most 16 tiles is one group (SW_MERGE_LDS).  A caller that asks
- * for the global merge gets it.  Replica r has its own L[r], beta[r], J[r],
- * seed[r] and its own records; its spins, clusters and records are bit for
+ * one workgroup per group in LDS (one launch for all such replicas; those of
+ * more than 16 tiles only while they make at most 512 groups together and no
+ * replica is merged globally); a replica of at most 16 tiles is one group
+ * (SW_MERGE_LDS).  A caller that asks for the global merge gets it.  Replica r
+ * has its own L[r], beta[r], J[r], seed[r] and its own records; its spins,
+ * clusters and records are bit for
  * bit those of a plain sim created with the same parameters and swept the
  * same number of times, whatever its tile width and merge.  All replicas
  * share the sweep counter t.  Limits: 1 <= n <= 4095; every L[r] as for
@@ -278,7 +279,8 @@ typedef struct sw_batch sw_batch;
 
 #define SW_MERGE_AUTO 0   /* in LDS where the replica has at most 16 groups of
                              4 x 4 tiles (those of more than 16 tiles only while
-                             they make at most 512 groups together), else global */
+                             they make at most 512 groups together and no replica
+                             is merged globally), else global */
 #define SW_MERGE_LDS 1    /* the whole merge in one workgroup (<= 16 tiles)  */
 #define SW_MERGE_GLOBAL 2 /* the global merge, whatever the replica's size   */
 

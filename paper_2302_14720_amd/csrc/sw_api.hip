@@ -657,7 +657,7 @@ constexpr int64_t kDefaultBatchRing = 1024;
 
 // A replica's device view.  k_merge takes, unless the caller asked for the
 // global merge, those of at most 16 tiles, and larger ones as it would alone
-// while the batch's are few (wide).
+// if the batch has few of them and no others (wide).
 Dev replica_dev(const sw_config &c, char *base, const Layout &lo, bool global, bool wide) {
     Dev d = make_dev(c, base, lo);
     if (global || (d.ntiles > swmi::kSmallTiles && !wide)) d.two = 0u;
@@ -694,6 +694,7 @@ int plan_batch(int32_t n, const int32_t *L, const double *beta, const double *J,
     p->lds.assign((size_t)n, 0);
     size_t off = 0;
     uint32_t groups = 0;  // k_merge workgroups of the replicas of more than 16 tiles
+    bool global = false;  // some replica is merged globally in any case
     for (int32_t r = 0; r < n; ++r) {
         const std::string who = "replica " + std::to_string(r) + ": ";
         sw_config &c = p->cfg[(size_t)r];
@@ -715,11 +716,12 @@ int plan_batch(int32_t n, const int32_t *L, const double *beta, const double *J,
             return fail(SW_EINVAL, who + "the LDS merge takes at most " + std::to_string(swmi::kSmallTiles) + " tiles");
         p->global[(size_t)r] = mg == SW_MERGE_GLOBAL ? 1u : 0u;
         p->lds[(size_t)r] = (mg != SW_MERGE_GLOBAL && nt <= swmi::kSmallTiles) ? 1u : 0u;
-        if (mg != SW_MERGE_GLOBAL) groups += swmi::wide_groups(c);
+        groups += swmi::wide_groups(c);
+        global = global || mg == SW_MERGE_GLOBAL || !swmi::merge_in_one(c);
         p->base[(size_t)r] = off;
         off = align_up(off + layout_of(c).total);
     }
-    p->wide = groups <= swmi::kWideGroups;
+    p->wide = swmi::take_wide(groups, global);
     swmi::BatchMaps m[kBatchGroups];
     for (size_t r = 0; r < p->cfg.size(); ++r)
         swmi::BatchMaps::add((uint32_t)r, replica_dev(p->cfg[r], nullptr, Layout{}, p->global[r] != 0, p->wide), m);

@@ -47,18 +47,26 @@ int validate(const sw_config *c);
 Layout layout_of(const sw_config &c);
 Dev make_dev(const sw_config &c, char *base, const Layout &lo);
 
-// A batch or server whose lattices of more than 16 tiles make more k_merge
-// workgroups than this merges them globally: one of those workgroups fills a CU
-// (75 KB of LDS, 16 wavefronts), so from two rounds of them on the global
-// merge's small workgroups are faster.  us per sweep, global / k_merge: 512^2,
-// 32 replicas (128 groups) 99.8 / 77.3, 128 (512) 201.8 / 199.5, 256 (1024)
-// 334.3 / 376.3; 1024^2, 16 (256) 139.1 / 121.2, 32 (512) 204.8 / 207.4, 64
-// (1024) 337.4 / 385.8; sides 64 to 1024, 128 replicas (500) 221.6 / 215.6, 160
-// (640) 258.9 / 267.0, 256 (1020) 369.6 / 407.4.  Servers: 64 jobs of 1024^2
-// 333.0 / 371.4, 256 of 512^2 331.2 / 371.9, 400 of 320^2 (1600) 240.2 / 343.0.
-constexpr uint32_t kWideGroups = 512;
-// k_merge workgroups of a lattice that counts towards the limit (0: none).
+// Whether k_merge takes a lattice that it can (at most 16 groups).
+bool merge_in_one(const sw_config &c);
+// Its workgroups for such a lattice of more than 16 tiles (0 for any other).
 uint32_t wide_groups(const sw_config &c);
+
+// Whether k_merge takes those larger lattices of a batch or server too: while
+// they make at most kWideGroups of its workgroups, and nothing is merged globally
+// in any case.  One of those workgroups fills a CU (16 wavefronts of 76 to 86
+// VGPRs), so from two rounds of them on the global merge's small workgroups are
+// faster.  us per sweep, global / k_merge: 512^2, 32 replicas (128 groups) 99.8 /
+// 77.3, 128 (512) 201.8 / 199.5, 256 (1024) 334.3 / 376.3; 1024^2, 16 (256)
+// 139.1 / 121.2, 32 (512) 204.8 / 207.4, 64 (1024) 337.4 / 385.8; sides 64 to
+// 1024, 128 replicas (500) 221.6 / 215.6, 160 (640) 258.9 / 267.0, 256 (1020)
+// 369.6 / 407.4.  Servers: 64 jobs of 1024^2 333.0 / 371.4, 256 of 512^2 331.2 /
+// 371.9, 400 of 320^2 (1600) 240.2 / 343.0.  Beside a lattice of the global merge,
+// whose launches are there anyway, k_merge only adds its own time: 512^2 and
+// 1088^2 75.5 / 91.7, 16 of 512^2 and four of 2048^2 156.2 / 175.2, 128 of 320^2
+// and one of 1088^2 130.8 / 175.9, 32 of 1024^2 and 20 of 2048^2 551 / 598.
+constexpr uint32_t kWideGroups = 512;
+inline bool take_wide(uint32_t groups, bool global) { return groups <= kWideGroups && !global; }
 
 // Launch groups of a batch: Ising and Potts replicas, each with 64-wide or
 // 32-wide tiles, run different instantiations of the tile kernels.

@@ -1867,7 +1867,8 @@ __device__ __forceinline__ void merge_top(const Dev &d, uint32_t ng, uint32_t ng
     cs.flush(s_acc);
 }
 
-// Open clusters that level 2 holds in LDS (two workgroups share a CU); a group
+// Open clusters that level 2 holds in LDS (75 KB with the rest; a workgroup's
+// registers leave no room for a second one on its CU); a group
 // of 64-wide tiles has at most about 270 (beta = 0.4), so that 16 groups fit;
 // more goes through the node tables.
 constexpr uint32_t kTopLds = 6144;
@@ -2122,10 +2123,9 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge_b(const Dev *devs, cons
 // the large ones (16 wavefronts, of k_union_b, per workgroup): both are chains
 // of dependent accesses that leave the GPU nearly idle.  us per sweep, two
 // launches / one: a 64^2 and k 1088^2 lattices, k = 1 81.1 / 75.5, 16 160.6 /
-// 153.3, 96 560.8 / 563.4; 16 512^2 and k 1088^2, k = 1 118.4 / 109.4, 96 597.2
-// / 584.5.  A second stream for k_merge is 10 % better on a server where it has
-// a hardware queue of its own and 10 % worse where it has none (24 jobs, whole
-// run: 67.4 or 83.7 ms; so 69.1 in either case).
+// 153.3, 96 560.8 / 563.4.  A second stream for k_merge is 10 % better on a server
+// where it has a hardware queue of its own and 10 % worse where it has none (24
+// jobs, whole run: 67.4 or 83.7 ms; 69.1 so in either case).
 __global__ __launch_bounds__(kMergeThreads) void k_join_b(const Dev *devs, const uint32_t *smap, uint32_t ns,
                                                           const uint32_t *wmap, uint32_t nw, uint32_t nE) {
     if (blockIdx.x < ns) {

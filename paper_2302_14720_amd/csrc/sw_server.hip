@@ -35,7 +35,8 @@ struct Job {
     int64_t target = 0, done = 0;
     int32_t state = SW_JOB_QUEUED;
     int32_t slot = -1;
-    uint32_t wide = 0;  // k_merge workgroups that count towards kWideGroups
+    uint32_t wide = 0;    // its k_merge workgroups if it has more than 16 tiles
+    bool global = false;  // too large for k_merge
 };
 
 // First-fit allocator over [0, size) with coalescing of freed ranges.
@@ -153,14 +154,18 @@ int resolve_jobs(sw_server *s, const std::vector<Job *> &jobs) {
     return SW_OK;
 }
 
-// The merge of the active jobs of more than 16 tiles: k_merge while they are few
-// (kWideGroups), else the global one.  A job changes merge with final spins
+// The merge of the active jobs of more than 16 tiles that k_merge can take: its
+// or the global one (take_wide).  A job changes merge with final spins
 // and no nodes: both its spin codes and its node counts refer to the
 // tables of the merge that left them.
 int choose_merges(sw_server *s) {
     uint32_t groups = 0;
-    for (const Job *j : s->active) groups += j->wide;
-    const uint32_t two = groups <= swmi::kWideGroups ? 1u : 0u;
+    bool global = false;
+    for (const Job *j : s->active) {
+        groups += j->wide;
+        global = global || j->global;
+    }
+    const uint32_t two = swmi::take_wide(groups, global) ? 1u : 0u;
     std::vector<Job *> change;
     for (Job *j : s->active)
         if (j->wide != 0 && j->dev.two != two) change.push_back(j);
@@ -250,6 +255,7 @@ int submit(sw_server *s, const sw_config &c, int64_t sweeps, int64_t *job_id) {
     j->cfg = c;
     j->bytes = bytes;
     j->wide = swmi::wide_groups(c);
+    j->global = !swmi::merge_in_one(c);
     j->target = sweeps;
     s->jobs[j->id] = j;
     s->queue.push_back(j);

@@ -1,6 +1,7 @@
 """A server whose active jobs go past the number of merge workgroups up to which
-k_merge is taken, and back: jobs change merge in the middle of their chains,
-and every one of them still runs the oracle's."""
+k_merge is taken, or are joined by one that it cannot take, and back: jobs change
+merge in the middle of their chains, and every one of them still runs the
+oracle's."""
 import math
 
 import numpy as np
@@ -12,10 +13,10 @@ import paper_2302_14720_amd as sw
 pytestmark = pytest.mark.gpu
 
 
-def test_jobs_change_merge_and_back():
+@pytest.mark.parametrize("late", [[(1024, 0, 3)] * 33, [(1088, 0, 3)]], ids=["528 groups more", "one of 25"])
+def test_jobs_change_merge_and_back(late):
     # (L, q, sweeps): 16 groups each, 4 of 32-wide tiles, 1 that never changes
-    early = [(1024, 0, 9), (1024, 3, 8), (320, 0, 12), (160, 5, 11), (128, 0, 10), (1088, 0, 7)]
-    late = [(1024, 0, 3)] * 33  # 528 groups
+    early = [(1024, 0, 9), (1024, 3, 8), (320, 0, 12), (160, 5, 11), (128, 0, 10)]
     beta = lambda q: math.log(1.0 + math.sqrt(q)) if q else 0.44
     print("\n[case] server merge change", flush=True)
     srv = sw.Server(256 << 20, 64)

@@ -19,14 +19,16 @@ def test_global_merge_is_planned(L):
     assert asked - auto >= 4 * words - 256
 
 
-def test_global_replicas_do_not_count_as_merge_groups():
-    """33 replicas of 1024^2 make 528 groups, too many for k_merge; with one of
-    them global the other 32 are few enough."""
-    sides = np.full(33, 1024, dtype=np.int32)
-    merge = np.zeros(33, dtype=np.int32)
-    all_auto = sw.sw_batch_workspace_bytes(sides, ring=1, merge=merge)
-    merge[5] = sw.SW_MERGE_GLOBAL
-    assert all_auto - sw.sw_batch_workspace_bytes(sides, ring=1, merge=merge) >= 4 * 32 * (2 * 4 * 16 + 16) - 256
+@pytest.mark.parametrize("other,merge", [(1088, sw.SW_MERGE_AUTO), (64, sw.SW_MERGE_GLOBAL)])
+def test_beside_a_global_replica_all_large_ones_are(other, merge):
+    """Replicas of more than 16 tiles take k_merge only where nothing needs the
+    global merge's launches."""
+    sides = np.array([1024] * 8 + [other], dtype=np.int32)
+    auto = sw.sw_batch_workspace_bytes(sides, ring=1, merge=[sw.SW_MERGE_AUTO] * 8 + [merge])
+    asked = sw.sw_batch_workspace_bytes(sides, ring=1, merge=[sw.SW_MERGE_GLOBAL] * 8 + [merge])
+    assert auto == asked
+    alone = sw.sw_batch_workspace_bytes(sides[:8], ring=1, merge=sw.SW_MERGE_AUTO)
+    assert alone < sw.sw_batch_workspace_bytes(sides[:8], ring=1, merge=sw.SW_MERGE_GLOBAL)
 
 
 @pytest.mark.gpu
