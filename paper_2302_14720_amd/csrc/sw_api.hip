@@ -96,8 +96,10 @@ int validate(const sw_config *c) {
 // 4 tiles (L <= 1024 with 64-wide tiles, 512 with 32-wide ones), where that
 // beats the four launches of the global merge -- the last workgroup's share
 // grows with the lattice while the launches cost the same.  Sweeps at beta_c,
-// one launch / four: 128^2 36 / 51, 512^2 52 / 71, 1024^2 64 / 75, 1280^2 76 /
-// 78, 1536^2 91 / 82 us; 32-wide tiles: 512^2 55 / 64, 1056^2 93 / 72 us.
+// one launch / four: 128^2 26 / 41, 512^2 43 / 57, 1024^2 52 / 62 us; 32-wide
+// tiles: 512^2 42 / 50; with room for more groups, and both sides 10 to 20 us
+// slower than now, 1280^2 took 76 / 78, 1536^2 91 / 82, 1056^2 in 32-wide tiles
+// 93 / 72.
 // Labels and the exact histogram need the node tables that the global merge
 // leaves.
 uint32_t merge_groups(const sw_config &c) {  // 0: too many

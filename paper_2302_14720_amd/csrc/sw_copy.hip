@@ -1,14 +1,13 @@
 // sw_copy.hip -- results to the caller's memory, pageable memory through pinned
 // staging buffers.
 //
-// A pageable hipMemcpy waits for its own staging: 20 us for a record, 34 us for
-// 64 KB, 111 us for 256 KB, and 9-18 GB/s for whole configurations, whose
+// A pageable hipMemcpy waits for its own staging: 24 us for a record, 36 us for
+// 64 KB, 112 us for 256 KB, and 10-17 GB/s for whole configurations, whose
 // pages in the caller's memory one thread touches for the first time.  Here
 // the device writes pinned slots in stream order (no wait in between) and the
 // host moves them on; from kCopySplit bytes on kCopySlots threads of this
-// call take a slot each.  Measured: 11 us for a record, 12 us and the host's
-// copy for 256 KB; 128^2: a sweep with its record and spins 120 -> 91 us;
-// the 268 MB of 16384^2: 28 -> 12 ms.
+// call take a slot each.  Measured, pageable / here: a record 24 / 14 us, 256 KB
+// 112 / 21 us, 4 MiB 243 / 178 us, 16 MiB 0.96 / 0.59 ms, 256 MiB 25.6 / 9.4 ms.
 #include <string.h>
 
 #include <algorithm>
@@ -21,10 +20,18 @@
 namespace swmi {
 namespace {
 
-constexpr size_t kCopySmall = (size_t)64 << 10;  // a stage that has copied no more than this at once
-constexpr size_t kCopyChunk = (size_t)1 << 20;   // bytes of a slot
+// A stage that has copied no more than this at once is that small: a program that
+// reads records and small lattices holds 64 KB, not 4 MiB.
+constexpr size_t kCopySmall = (size_t)64 << 10;
+constexpr size_t kCopyChunk = (size_t)1 << 20;  // bytes of a slot
+// With 2 / 4 / 8 slots (and as many threads): 16 MiB 668 / 593 / 624 us, 64 MiB
+// 4.7 / 2.6 / 2.3 ms, 256 MiB 18.4 / 9.4 / 8.8 ms, 5.5 MiB (one thread) 258 /
+// 244 / 243 us.
 constexpr int kCopySlots = 4;
-constexpr size_t kCopySplit = (size_t)8 << 20;   // below, starting threads costs more than they save
+// Below, starting threads costs more than they save; one thread / four: 1.9 MiB
+// 97 / 124 us, 4 MiB 187 / 197, 7.6 MiB 316 / 310, 9.8 MiB 405 / 385, 16 MiB
+// 661 / 593.
+constexpr size_t kCopySplit = (size_t)8 << 20;
 
 struct Stage {
     int device;

@@ -23,7 +23,8 @@
 //             folds them, and the sweep is four launches).
 // On lattices of at most 16 groups of 4x4 tiles, k_merge does all after k_tile
 // in one launch.  Batches and servers run the same bodies over work maps (k_*_b).
-// Spins are double-buffered by sweep parity.  A written spin byte is either
+// Spins are double-buffered by sweep parity (the buffer that a sweep has read
+// then holds k_merge's results of the groups).  A written spin byte is either
 // the final spin (0x01 = +1, 0xFF = -1) or 2 + k, a reference to node k of
 // the tile, resolved through the node tables of that sweep when the byte is
 // read next (by the next sweep's k_tile, or by k_resolve at the end of

@@ -127,10 +127,6 @@ __device__ __forceinline__ uint32_t ref_base(const Dev &d, uint32_t tx, uint32_t
     return ((ty / kUG) * ((d.ntx + kUG - 1u) / kUG) + tx / kUG) * ref_slots(d.tw);
 }
 
-// Shared front end of k_tile and k_resolve: the table that maps every byte
-// of this tile's previous output to its spin as an up bit (1 for +1): final
-// spins 0x01 / 0xFF map to themselves, node code 2 + k to the spin of node
-// k's root.
 // Output bytes of the Potts model on the tile path: a byte below
 // potts_code<TW>() is a final value, potts_code<TW>() + k refers to node k of
 // its tile.  A 32-wide tile has at most 124 nodes, so all values 0..7 fit
@@ -138,6 +134,10 @@ __device__ __forceinline__ uint32_t ref_base(const Dev &d, uint32_t tx, uint32_t
 // the values of q <= 4.
 template <int TW> constexpr uint32_t potts_code() { return TW == 64 ? 4u : 8u; }
 
+// Shared front end of k_tile and k_resolve: the table that maps every byte
+// of this tile's previous output to its value (Ising: an up bit, 1 for +1):
+// final spins map to themselves, node code 2 + k (Potts: potts_code<TW>() + k)
+// to the new value of node k's cluster.
 // The node spins are loaded whether or not the node exists (every slot is
 // in bounds), so that this load does not wait for the node count.
 template <int TW, bool POTTS, int TWO, int NT>
@@ -241,9 +241,9 @@ __device__ __forceinline__ uint32_t spread8(uint32_t v) {
 // =====================================================================
 // k_tile: bonds (Sec. 2.1), tile-local clusters (Sec. 2.3), new spins of
 // tile-interior clusters (Sec. 2.4), measurement of the incoming
-// configuration (Sec. 2.5).  One workgroup per TW x TW tile, 16 sites per
-// thread (one 16-site segment of a row), so per-row bond and run data are
-// bit masks and most per-site work is one bit operation per 16 sites.
+// configuration (Sec. 2.5).  One workgroup per TW x TW tile, SPT = 16 or 4
+// sites of a row per thread, so per-row bond and run data are bit masks and
+// most per-site work is one bit operation per SPT sites.
 // Cluster formation: every site's LDS word first points at the start of its
 // row run; vertical bonds (one per group that joins the same two runs) are
 // unions of run starts; each run start is then pointed at its root, which
@@ -923,7 +923,7 @@ __global__ __launch_bounds__(TW *TW / SPT, TW == 64 && SPT == 16 ? kTileWavesPer
 // tiles do not fill the GPU group by group (kMixTiles).  256 threads suit a
 // 64-wide tile with 16 sites per thread and a 32-wide one with 4.  The bodies
 // take turns in one block of LDS; 80 VGPRs (at the 64 of the kernels of one
-// kind the four bodies together spill 54 words, here 26).  map: the groups'
+// kind the four bodies together spill 54 words, here 24).  map: the groups'
 // tile maps one after another, blocks in map order, so that the slower tiles
 // spread over the XCDs.
 union MixShared {
@@ -2122,10 +2122,10 @@ __global__ __launch_bounds__(kMergeThreads) void k_merge_b(const Dev *devs, cons
 // k_merge of the small replicas (the first ns workgroups) beside the unions of
 // the large ones (16 wavefronts, of k_union_b, per workgroup): both are chains
 // of dependent accesses that leave the GPU nearly idle.  us per sweep, two
-// launches / one: a 64^2 and k 1088^2 lattices, k = 1 81.1 / 75.5, 16 160.6 /
-// 153.3, 96 560.8 / 563.4.  A second stream for k_merge is 10 % better on a server
-// where it has a hardware queue of its own and 10 % worse where it has none (24
-// jobs, whole run: 67.4 or 83.7 ms; 69.1 so in either case).
+// launches / one: a 64^2 and k 1088^2 lattices, k = 1 81.5 / 76.9, 16 162.0 /
+// 154.7, 96 563 / 567; 100 of 256^2 and k of 1088^2, k = 1 111.9 / 103.1, 16
+// 190.6 / 185.1.  (A second stream for k_merge was 10 % better on a server where
+// it had a hardware queue of its own and 10 % worse where it had none.)
 __global__ __launch_bounds__(kMergeThreads) void k_join_b(const Dev *devs, const uint32_t *smap, uint32_t ns,
                                                           const uint32_t *wmap, uint32_t nw, uint32_t nE) {
     if (blockIdx.x < ns) {
@@ -2348,9 +2348,9 @@ void launch_tile(const Dev &d, hipStream_t s) {
 // long as the lattice is wide, which bit-reversed order breaks up.  Elsewhere
 // index order is better: it makes the node with the smallest site the root
 // nearly always, and spares k_flatten an atomic per workgroup and root.  Sweeps
-// index / bits: beta = 0.5, 4064^2 208 / 189, 8192^2 389 / 368, 16384^2 1298 /
-// 1232 us; beta_c, 168 / 171, 339 / 344, 1158 / 1169; on fewer than 16 groups
-// a side there is nothing between them (1344^2, beta = 0.5, 68.9 / 69.7).
+// index / bits: beta = 0.5, 4064^2 202 / 186, 8192^2 386 / 370, 16384^2 1300 /
+// 1238 us; beta_c, 161 / 164, 341 / 344, 1168 / 1184; on fewer than 16 groups
+// a side there is nothing between them (1344^2, beta = 0.5, 65.8 / 65.9).
 constexpr uint32_t kBitsGroups = 16;
 bool ordered(const Dev &d) {
     const double q = sqrt((double)(d.q ? d.q : 2u));
@@ -2360,8 +2360,8 @@ bool ordered(const Dev &d) {
 // Whether the tile kernels of a launch take 4 sites per thread (else 16): while
 // the GPU would not be filled with 16.  Sweeps with 4 / 16 sites at beta_c:
 // 64-wide tiles, 1024^2 53 / 64, 1280^2 (400 tiles) 72 / 76, 1536^2 82 / 79,
-// 2048^2 91 / 84 us; 32-wide, 512^2 43 / 57, 1056^2 63 / 73, 1536^2 (2304
-// tiles) 74 / 77, 2080^2 89 / 88 us.  64-wide Potts tiles take more registers:
+// 2048^2 91 / 84 us; 32-wide, 512^2 42 / 53, 1056^2 59 / 69, 1536^2 (2304
+// tiles) 70 / 74, 1824^2 77 / 79, 2080^2 88 / 86 us.  64-wide Potts tiles take more registers:
 // q = 3, 1024^2 (256 tiles) 55 / 68, 1280^2 86 / 78 us.
 bool few_tiles(uint32_t ntiles, uint32_t tw, bool potts) {
     return ntiles <= (tw == 32u ? 2304u : potts ? 256u : 400u);
@@ -2524,12 +2524,11 @@ hipError_t launch_resolve(const Dev &d, hipStream_t s) {
 // leaves most of the GPU idle for the length of one tile; above, the groups'
 // own kernels gain from their occupancy and from 16 sites per thread in 32-wide
 // tiles.  us per sweep of a batch of k 512^2 and k 544^2 lattices, one launch
-// per group / k_tile_mix: k = 1 (353 tiles) 94.8 / 93.3, 8 (2824) 126.0 /
-// 118.4, 16 (5648) 143.8 / 158.3; 3-state 98.4 / 93.1, 131.1 / 119.3, 151.9 /
-// 159.8; 1024^2 and 1056^2, k = 2 (2690) 123.0 / 116.4, 4 (5380) 142.0 / 154.3.
-// A server of 24 Ising and Potts jobs of 128^2 to 2048^2 (four groups), whole
-// run: never 83.3 ms, up to 4096 tiles 75.0, up to 8192 68.4, always 67.6 to
-// 70.3.
+// per group / k_tile_mix: k = 1 (353 tiles) 79.0 / 76.5, 8 (2824) 108.1 /
+// 101.8, 16 (5648) 125.0 / 138.5; 3-state 82.3 / 76.4, 111.4 / 102.9, 132.2 /
+// 141.9; 1024^2 and 1056^2, k = 2 (2690) 106.6 / 102.2, 4 (5380) 126.3 / 138.0.
+// A server of 24 Ising and Potts jobs of 128^2 to 2048^2 (three groups), whole
+// run: never 73.5 ms, up to this limit 62.5, always 62.5.
 constexpr uint32_t kMixTiles = 2048;
 
 hipError_t launch_batch_sweep(const BatchDev *b, int ngroups, hipStream_t s) {

@@ -53,3 +53,21 @@ def test_threads_read_at_once(threads):
     for s in sims:
         s.close()
     assert not bad
+
+
+def test_spins_on_the_per_thread_stream():
+    """A handle that names another stream in every thread (16 MB, read by four)."""
+    import torch
+
+    L, n = 4096, 20
+    print("\n[case] copy per-thread stream", flush=True)
+    sp = oracle.init(L, 3)
+    ref = oracle.run(L, 1.0, oracle.threshold(0.44), 3, 0, n, sp)
+    cfg = sw.sw_config_init(L, 0.44, 1.0, 3, ring=n)
+    ws = torch.empty(sw.sw_workspace_bytes_ex(cfg), dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    h = sw.sw_create_ex(cfg, ws.data_ptr(), ws.numel(), 2)
+    sw.sw_sweep(h, n)
+    assert np.array_equal(sw.sw_get_spins(h, L * L), sp)
+    assert sw.sw_series(h, 0, n).tobytes() == ref.tobytes()
+    sw.sw_destroy(h)
