@@ -36,6 +36,8 @@ struct Buffer {
 };
 std::set<Buffer *> Buffer::all;
 
+bool waited = false;  // for the stream, since the last copy
+
 // Pinned memory held and made.
 std::map<void *, size_t> pinned;
 size_t pinned_bytes = 0, pinned_most = 0, pinned_made = 0;
@@ -94,7 +96,11 @@ hipError_t hipEventDestroy(hipEvent_t e) {
 }
 hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
 hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
-hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) {
+    std::lock_guard<std::mutex> hold(mu);
+    waited = true;
+    return hipSuccess;
+}
 hipError_t hipPointerGetAttributes(hipPointerAttribute_t *at, const void *p) {
     at->type = is_mapped(p) ? hipMemoryTypeHost : hipMemoryTypeUnregistered;
     return hipSuccess;
@@ -114,6 +120,10 @@ hipError_t hipMemcpyAsync(void *dst, const void *src, size_t n, hipMemcpyKind, h
     if (!b) return hipErrorInvalidValue;
     const size_t at = (const char *)src - b->stale.data();
     if (is_mapped(dst)) straight += n;
+    {
+        std::lock_guard<std::mutex> hold(mu);
+        waited = false;
+    }
     const bool ordered = s == b->stream && (s != hipStreamPerThread || std::this_thread::get_id() == b->owner);
     memcpy(dst, (ordered ? b->fresh.data() : b->stale.data()) + at, n);
     return hipSuccess;
@@ -136,7 +146,10 @@ const size_t kSizes[] = {1, 320, (size_t)64 << 10, ((size_t)64 << 10) + 1, (size
 bool every_size(hipStream_t s) {
     swmi::StageUser user;
     bool ok = true;
-    for (size_t n : kSizes) ok = check(copies(n, s), "copy") && ok;
+    for (size_t n : kSizes) {
+        ok = check(copies(n, s), "copy") && ok;
+        ok = check(waited, "stream not waited for") && ok;
+    }
     return ok;
 }
 
