@@ -2138,7 +2138,9 @@ __global__ __launch_bounds__(kMergeThreads) void k_join_b(const Dev *devs, const
 
 // =====================================================================
 // k_resolve: replace node codes by final spins in place and measure the
-// configuration (runs once at the end of every sw_sweep call).
+// configuration (runs once at the end of every sw_sweep call).  No byte refers
+// to a node then, and the tiles have none left for the next sweep's tables (a
+// server may give the lattice another merge with other tables).
 // =====================================================================
 template <int TW, bool POTTS, int TWO>
 __device__ __forceinline__ void resolve_body(const Dev &d, const uint32_t tile) {
@@ -2265,6 +2267,7 @@ __device__ __forceinline__ void resolve_body(const Dev &d, const uint32_t tile) 
     }
     __syncthreads();
     if (tid == 0u) {
+        d.nk[pp][tile] = 0u;  // (its readers are this workgroup's, before the barriers)
         int32_t e = 0, m = 0;
         for (int w = 0; w < NWAVE; ++w) {
             e += s_red[w][0];

@@ -93,6 +93,7 @@ struct sw_server {
     int device = 0;
     int32_t max_jobs = 0;
     Dev *d_devs = nullptr;      // [max_jobs] Dev of the job in each slot
+    std::vector<Dev> devs;      // the same in host memory
     uint32_t *d_maps = nullptr;  // map entries of the current launch groups
     size_t maps_cap = 0;
     std::vector<int32_t> free_slots;
@@ -155,9 +156,8 @@ int resolve_jobs(sw_server *s, const std::vector<Job *> &jobs) {
 }
 
 // The merge of the active jobs of more than 16 tiles that k_merge can take: its
-// or the global one (take_wide).  A job changes merge with final spins
-// and no nodes: both its spin codes and its node counts refer to the
-// tables of the merge that left them.
+// or the global one (take_wide).  A job that has swept is resolved first: its
+// spin codes and node counts refer to the tables of the merge that left them.
 int choose_merges(sw_server *s) {
     uint32_t groups = 0;
     bool global = false;
@@ -166,20 +166,26 @@ int choose_merges(sw_server *s) {
         global = global || j->global;
     }
     const uint32_t two = swmi::take_wide(groups, global) ? 1u : 0u;
-    std::vector<Job *> change;
-    for (Job *j : s->active)
-        if (j->wide != 0 && j->dev.two != two) change.push_back(j);
-    if (change.empty()) return SW_OK;
-    const int rc = resolve_jobs(s, change);
-    if (rc != SW_OK) return rc;
-    for (Job *j : change) {
-        Dev dev = j->dev;
-        dev.two = two;
-        for (uint32_t *nk : dev.nk) HIP_TRY(hipMemsetAsync(nk, 0, (size_t)dev.ntiles * 4, s->stream));
-        HIP_TRY(hipStreamSynchronize(s->stream));
-        HIP_TRY(hipMemcpy(s->d_devs + j->slot, &dev, sizeof(Dev), hipMemcpyHostToDevice));
-        j->dev = dev;
+    std::vector<Job *> change, swept;
+    for (Job *j : s->active) {
+        if (j->wide == 0 || j->dev.two == two) continue;
+        change.push_back(j);
+        if (j->done > 0) swept.push_back(j);
     }
+    if (change.empty()) return SW_OK;
+    if (!swept.empty()) {
+        const int rc = resolve_jobs(s, swept);
+        if (rc != SW_OK) return rc;
+    }
+    int32_t lo = change[0]->slot, hi = lo;
+    for (Job *j : change) {
+        s->devs[(size_t)j->slot] = j->dev;
+        s->devs[(size_t)j->slot].two = two;
+        lo = std::min(lo, j->slot);
+        hi = std::max(hi, j->slot);
+    }
+    HIP_TRY(hipMemcpy(s->d_devs + lo, &s->devs[(size_t)lo], (size_t)(hi - lo + 1) * sizeof(Dev), hipMemcpyHostToDevice));
+    for (Job *j : change) j->dev.two = two;
     return SW_OK;
 }
 
@@ -216,6 +222,7 @@ int admit(sw_server *s) {
         }
         s->queue.pop_front();
         s->free_slots.pop_back();
+        s->devs[(size_t)slot] = dev;
         j->off = off;
         j->slot = slot;
         j->dev = dev;
@@ -318,6 +325,7 @@ int sw_server_create(void *pool, size_t pool_bytes, int32_t max_jobs, void *hip_
         sw_server_destroy(s);
         return rc;
     }
+    s->devs.resize((size_t)max_jobs);
     for (int32_t i = max_jobs - 1; i >= 0; --i) s->free_slots.push_back(i);
     *out = s;
     return SW_OK;
