@@ -16,8 +16,8 @@
 // (2 bytes, not 4) is written once and read once; 32-bit labels are made
 // from the codes only when they are asked for (k_blabels3).
 //
-// At 512^3, q = 3 at 0.5505 (times per sweep): k_brick3 0.59 ms, bound by VALU
-// issue (410 M wavefront instructions, 84 % of what independent integer chains
+// At 512^3, q = 3 at 0.5505 (times per sweep): k_brick3 0.58 ms, bound by VALU
+// issue (399 M wavefront instructions, 83 % of what independent integer chains
 // reach, a quarter of them Philox); k_bflat3 0.17, k_bunion3 0.17, k_blocal3
 // 0.10 and k_bspin3 0.13 ms, bound by their dependent loads and device-scope
 // atomics over 228 nodes a brick.  32-bit labels in global memory took 2.9 ms.

@@ -7,7 +7,7 @@
 // the device writes pinned slots in stream order (no wait in between) and the
 // host moves them on; from kCopySplit bytes on kCopySlots threads of this
 // call take a slot each.  Measured, pageable / here: a record 24 / 14 us, 256 KB
-// 112 / 21 us, 4 MiB 242 / 204 us, 16 MiB 0.95 / 0.62 ms, 256 MiB 25.6 / 9.5 ms.
+// 112 / 21 us, 4 MiB 242 / 204 us, 16 MiB 0.95 / 0.62 ms, 256 MiB 25.4 / 9.5 ms.
 #include <string.h>
 
 #include <algorithm>
@@ -24,13 +24,12 @@ namespace {
 // reads records and small lattices holds 64 KB, not 4 MiB.
 constexpr size_t kCopySmall = (size_t)64 << 10;
 constexpr size_t kCopyChunk = (size_t)1 << 20;  // bytes of a slot
-// With 2 / 4 / 8 slots (and as many threads): 16 MiB 668 / 593 / 624 us, 64 MiB
-// 4.7 / 2.6 / 2.3 ms, 256 MiB 18.4 / 9.4 / 8.8 ms, 5.5 MiB (one thread) 258 /
-// 244 / 243 us.
+// With 2 / 4 / 8 slots (and as many threads): 9.8 MiB 423 / 411 / 445 us, 16 MiB
+// 664 / 622 / 653 us, 64 MiB 4.5 / 2.6 / 2.4 ms, 256 MiB 17.8 / 9.9 / 8.9 ms.
 constexpr int kCopySlots = 4;
 // Below, starting threads costs more than they save; one thread / four: 1.9 MiB
-// 97 / 124 us, 4 MiB 187 / 197, 7.6 MiB 316 / 310, 9.8 MiB 405 / 385, 16 MiB
-// 661 / 593.
+// 97 / 123 us, 4 MiB 214 / 228, 7.6 MiB 347 / 345, 9.8 MiB 440 / 411, 16 MiB
+// 683 / 622.
 constexpr size_t kCopySplit = (size_t)8 << 20;
 
 struct Stage {
